@@ -1,4 +1,9 @@
-"""ctypes binding of libtvg.so.  Names and argument order follow include/tvg.h."""
+"""Binding of libtvg.so.  Names and argument order follow include/tvg.h.
+
+The operator calls are native functions of the extension module ``_native`` (``csrc/native_calls.cpp``),
+loaded with the library when one of them is first looked up; queries, tuning and set-up calls, which
+no inner loop makes, go through ctypes.
+"""
 from __future__ import annotations
 
 import ctypes
@@ -129,6 +134,35 @@ def load() -> ctypes.CDLL:
     return lib
 
 
+# What lives in the extension module; looked up through __getattr__ below (and the package's), so that
+# importing the package needs neither the library nor torch.
+NATIVE_NAMES = ("tvg_conv2d_fused", "tvg_conv2d_fused_static", "tvg_conv2d_fused_dual",
+                "tvg_conv2d_fused_prepacked", "tvg_dwconv2d_fused", "tvg_dwpw_fused", "tvg_maxpool2d_3x3s2",
+                "conv2d_fused", "dwconv2d_fused", "dwpw_fused")
+_native = None
+
+
+def native():
+    """The extension module with the operator calls (built in-tree like the library)."""
+    global _native
+    if _native is None:
+        load()
+        import torch  # noqa: F401  (the extension links against the libraries torch has loaded)
+        from importlib import import_module
+        module = import_module("._native", __package__)
+        module.setup(ConvDesc, TvgError, {"conv2d_fused": _conv2d_fused, "dwconv2d_fused": _dwconv2d_fused,
+                                          "dwpw_fused": _dwpw_fused})
+        _native = module
+    return _native
+
+
+def __getattr__(name):
+    if name in NATIVE_NAMES:
+        globals()[name] = fn = getattr(native(), name)
+        return fn
+    raise AttributeError(f"module {__name__!r} has no attribute {name!r}")
+
+
 def status_string(status: int) -> str:
     return load().tvg_status_string(int(status)).decode()
 
@@ -210,27 +244,6 @@ def tvg_dwconv2d_workspace_size(desc: ConvDesc) -> int:
     return int(out.value)
 
 
-def tvg_conv2d_fused(desc, x, w, scale, shift, bias, residual, y, workspace=None,
-                     workspace_bytes=0, stream=None) -> int:
-    return int(load().tvg_conv2d_fused(ctypes.byref(desc), _addr(x), _addr(w), _addr(scale),
-                                       _addr(shift), _addr(bias), _addr(residual), _addr(y),
-                                       _addr(workspace), workspace_bytes, _stream(stream)))
-
-
-def tvg_conv2d_fused_dual(desc, k1, flags2, x, w, scale, shift, bias, residual1, y1, y2, stream=None) -> int:
-    """Two fused 3x3 convolutions of the same input in one launch (see include/tvg.h)."""
-    return int(load().tvg_conv2d_fused_dual(ctypes.byref(desc), int(k1), int(flags2), _addr(x), _addr(w),
-                                            _addr(scale), _addr(shift), _addr(bias), _addr(residual1),
-                                            _addr(y1), _addr(y2), _stream(stream)))
-
-
-def tvg_conv2d_fused_static(desc, x, w, scale, shift, bias, residual, y, stream=None) -> int:
-    """tvg_conv2d_fused with the library's own static scratch instead of a workspace."""
-    return int(load().tvg_conv2d_fused_static(ctypes.byref(desc), _addr(x), _addr(w), _addr(scale),
-                                              _addr(shift), _addr(bias), _addr(residual), _addr(y),
-                                              _stream(stream)))
-
-
 def tvg_conv2d_prepack_size(desc):
     """Returns (packed_bytes, workspace_bytes) of the pre-transformed-weights path; raises on error."""
     pb, wb = ctypes.c_size_t(0), ctypes.c_size_t(0)
@@ -243,13 +256,6 @@ def tvg_conv2d_prepack_size(desc):
 def tvg_conv2d_prepack(desc, w, packed, packed_bytes, stream=None) -> int:
     return int(load().tvg_conv2d_prepack(ctypes.byref(desc), _addr(w), _addr(packed), int(packed_bytes),
                                          _stream(stream)))
-
-
-def tvg_conv2d_fused_prepacked(desc, x, packed, scale, shift, bias, residual, y, workspace,
-                               workspace_bytes, stream=None) -> int:
-    return int(load().tvg_conv2d_fused_prepacked(ctypes.byref(desc), _addr(x), _addr(packed), _addr(scale),
-                                                 _addr(shift), _addr(bias), _addr(residual), _addr(y),
-                                                 _addr(workspace), int(workspace_bytes), _stream(stream)))
 
 
 def tvg_static_scratch_bytes() -> int:
@@ -268,13 +274,6 @@ def tvg_probe_mfma(dtype, iters, workgroups, out, stream=None):
     return int(st), float(fl.value)
 
 
-def tvg_dwconv2d_fused(desc, x, w, scale, shift, bias, residual, y, workspace=None,
-                       workspace_bytes=0, stream=None) -> int:
-    return int(load().tvg_dwconv2d_fused(ctypes.byref(desc), _addr(x), _addr(w), _addr(scale),
-                                         _addr(shift), _addr(bias), _addr(residual), _addr(y),
-                                         _addr(workspace), workspace_bytes, _stream(stream)))
-
-
 def tvg_dwpw_workspace_size(dw_desc: ConvDesc, pw_k: int) -> int:
     out = ctypes.c_size_t(0)
     st = load().tvg_dwpw_workspace_size(ctypes.byref(dw_desc), int(pw_k), ctypes.byref(out))
@@ -291,15 +290,6 @@ def tvg_dwpw_one_kernel(dw_desc: ConvDesc, pw_k: int) -> bool:
     return bool(out.value)
 
 
-def tvg_dwpw_fused(dw_desc, pw_k, pw_flags, x, w_dw, scale_dw, shift_dw, w_pw, scale_pw, shift_pw,
-                   bias_pw, residual, y, workspace=None, workspace_bytes=0, stream=None) -> int:
-    return int(load().tvg_dwpw_fused(ctypes.byref(dw_desc), int(pw_k), int(pw_flags), _addr(x),
-                                     _addr(w_dw), _addr(scale_dw), _addr(shift_dw), _addr(w_pw),
-                                     _addr(scale_pw), _addr(shift_pw), _addr(bias_pw),
-                                     _addr(residual), _addr(y), _addr(workspace), workspace_bytes,
-                                     _stream(stream)))
-
-
 def tvg_plan_arena(lives):
     """lives: sequence of (bytes, first_step, last_step).  Returns (offsets, arena_bytes)."""
     n = len(lives)
@@ -312,12 +302,10 @@ def tvg_plan_arena(lives):
     return [int(o) for o in offs[:n]], int(total.value)
 
 
-def tvg_maxpool2d_3x3s2(n, c, h, w, dtype, x, y, stream=None) -> int:
-    return int(load().tvg_maxpool2d_3x3s2(n, c, h, w, dtype, _addr(x), _addr(y), _stream(stream)))
-
-
 # ---------------------------------------------------------------------------------------
-# conveniences: build the descriptor from tensors, allocate y and workspace with torch
+# conveniences: build the descriptor from tensors, allocate y and workspace with torch.
+# The native conv2d_fused, dwconv2d_fused and dwpw_fused hand calls with unusual arguments to the
+# functions below, which check them one by one and raise what fits.
 # ---------------------------------------------------------------------------------------
 
 def _dtype_code(t) -> int:
@@ -355,7 +343,7 @@ def make_desc(x, w, stride, pad, relu, depthwise=False, stream_out=False) -> Con
     return ConvDesc(n, c, h, wd, k, r, s, sh, sw, ph, pw, _dtype_code(x), flags)
 
 
-def conv2d_fused(x, w, scale, shift, bias=None, residual=None, *, stride=1, pad=0, relu=False,
+def _conv2d_fused(x, w, scale, shift, bias=None, residual=None, *, stride=1, pad=0, relu=False,
                  out=None, workspace=None, stream=None, stream_out=False):
     """y = tail(conv2d(x, w)); allocates y (and the workspace when needed) with torch."""
     import torch
@@ -369,26 +357,26 @@ def conv2d_fused(x, w, scale, shift, bias=None, residual=None, *, stride=1, pad=
     if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
         workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = tvg_conv2d_fused(desc, x, w, scale, shift, bias, residual, out, workspace, ws_bytes, stream)
+    st = native().tvg_conv2d_fused(desc, x, w, scale, shift, bias, residual, out, workspace, ws_bytes, stream)
     if st != TVG_OK:
         raise TvgError(st, "tvg_conv2d_fused")
     return out
 
 
-def dwconv2d_fused(x, w, scale, shift, bias=None, residual=None, *, stride=1, pad=1, relu=False,
+def _dwconv2d_fused(x, w, scale, shift, bias=None, residual=None, *, stride=1, pad=1, relu=False,
                    out=None, stream=None, stream_out=False):
     import torch
     _check(x, w, scale, shift, bias, residual)
     desc = make_desc(x, w, stride, pad, relu, depthwise=True, stream_out=stream_out)
     if out is None:
         out = torch.empty((desc.n, desc.k, desc.oh, desc.ow), dtype=x.dtype, device=x.device)
-    st = tvg_dwconv2d_fused(desc, x, w, scale, shift, bias, residual, out, None, 0, stream)
+    st = native().tvg_dwconv2d_fused(desc, x, w, scale, shift, bias, residual, out, None, 0, stream)
     if st != TVG_OK:
         raise TvgError(st, "tvg_dwconv2d_fused")
     return out
 
 
-def dwpw_fused(x, w_dw, scale_dw, shift_dw, w_pw, scale_pw, shift_pw, bias_pw=None, residual=None, *,
+def _dwpw_fused(x, w_dw, scale_dw, shift_dw, w_pw, scale_pw, shift_pw, bias_pw=None, residual=None, *,
                stride=1, relu_dw=True, relu_pw=True, out=None, workspace=None, stream=None,
                stream_out=False, one_kernel=False):
     """MobileNet block (depthwise 3x3 + tail, 1x1 conv + tail) through tvg_dwpw_fused;
@@ -411,7 +399,7 @@ def dwpw_fused(x, w_dw, scale_dw, shift_dw, w_pw, scale_pw, shift_pw, bias_pw=No
         if workspace is None or workspace.numel() * workspace.element_size() < need:
             workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = tvg_dwpw_fused(desc, k, flags, x, w_dw, scale_dw, shift_dw, w_pw, scale_pw, shift_pw,
+    st = native().tvg_dwpw_fused(desc, k, flags, x, w_dw, scale_dw, shift_dw, w_pw, scale_pw, shift_pw,
                         bias_pw, residual, out, workspace, ws_bytes, stream)
     if st != TVG_OK:
         raise TvgError(st, "tvg_dwpw_fused")
@@ -425,7 +413,7 @@ def maxpool2d_3x3s2(x, out=None, stream=None):
     n, c, h, w = x.shape
     if out is None:
         out = torch.empty((n, c, (h - 1) // 2 + 1, (w - 1) // 2 + 1), dtype=x.dtype, device=x.device)
-    st = tvg_maxpool2d_3x3s2(n, c, h, w, _dtype_code(x), x, out, stream)
+    st = native().tvg_maxpool2d_3x3s2(n, c, h, w, _dtype_code(x), x, out, stream)
     if st != TVG_OK:
         raise TvgError(st, "tvg_maxpool2d_3x3s2")
     return out

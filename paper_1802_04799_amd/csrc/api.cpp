@@ -8,6 +8,7 @@
 #include <initializer_list>
 #include <utility>
 #include <mutex>
+#include <unordered_map>
 #include <vector>
 #include "tvg_internal.h"
 
@@ -94,10 +95,10 @@ void tile_key(const ConvProblem &p, int (&key)[12])
 
 // Everything planning derives from a problem, computed once per distinct problem: which
 // kernel takes it and with what launch shape.  The descriptor's flags do not enter (no plan
-// depends on them).  A short list under a mutex, scanned linearly; tvg_conv2d_set_tile empties
-// it.  The launch-bound batch-1 layers spend 1-5 us per call in planning otherwise.
+// depends on them).  A hash table under a mutex; tvg_conv2d_set_tile empties it, and so does the
+// 257th distinct problem.  The launch-bound batch-1 layers spend 1-5 us per call in planning
+// otherwise.
 struct Dispatch {
-    int key[12];
     bool patch_shape, stem_shape, pw_shape, pwd_shape, f32_shape;
     tvg::Patch3x3Plan patch;
     tvg::StemPlan stem;
@@ -107,22 +108,32 @@ struct Dispatch {
     tvg::ConvPlan generic;          // the generic kernel's plan, reduction split allowed
     tvg::ConvPlan generic_single;   // the same in a single pass (no workspace)
 };
+struct ProblemKey {
+    int v[12];
+    bool operator==(const ProblemKey &o) const { return memcmp(v, o.v, sizeof(v)) == 0; }
+};
+struct ProblemHash {
+    size_t operator()(const ProblemKey &k) const
+    {
+        uint64_t h = 0x9E3779B97F4A7C15ull;
+        for (int e : k.v) h = (h ^ (uint32_t)e) * 0xFF51AFD7ED558CCDull, h ^= h >> 29;
+        return (size_t)h;
+    }
+};
 std::mutex g_dispatch_mutex;
-std::vector<Dispatch> g_dispatch;
-size_t g_dispatch_next = 0;
+std::unordered_map<ProblemKey, Dispatch, ProblemHash> g_dispatch;
 constexpr size_t kMaxDispatchEntries = 256;
 
 Dispatch dispatch_for(const ConvProblem &p)
 {
-    int key[12];
-    tile_key(p, key);
+    ProblemKey key;
+    tile_key(p, key.v);
     {
         std::lock_guard<std::mutex> lock(g_dispatch_mutex);
-        for (const Dispatch &d : g_dispatch)
-            if (memcmp(d.key, key, sizeof(key)) == 0) return d;
+        const auto it = g_dispatch.find(key);
+        if (it != g_dispatch.end()) return it->second;
     }
     Dispatch d{};
-    memcpy(d.key, key, sizeof(key));
     d.patch_shape = tvg::plan_conv3x3_patch(p, &d.patch);
     d.stem_shape = !d.patch_shape && tvg::plan_conv7x7s2_stem(p, &d.stem);
     d.pw_shape = !d.patch_shape && !d.stem_shape && tvg::plan_conv1x1(p, &d.pw);
@@ -137,8 +148,8 @@ Dispatch dispatch_for(const ConvProblem &p)
     d.generic = tvg::plan_conv(p, true);
     d.generic_single = tvg::plan_conv(p, false);
     std::lock_guard<std::mutex> lock(g_dispatch_mutex);
-    if (g_dispatch.size() < kMaxDispatchEntries) g_dispatch.push_back(d);
-    else g_dispatch[g_dispatch_next++ % kMaxDispatchEntries] = d;     // replace the oldest slot
+    if (g_dispatch.size() >= kMaxDispatchEntries) g_dispatch.clear();
+    g_dispatch.emplace(key, d);
     return d;
 }
 
