@@ -289,7 +289,7 @@ tvg_status tvg_plan_arena(const tvg_tensor_life *tensors, int32_t count, uint64_
  * (alignment of the pointers aside).  kernel, mt, nt are host pointers.
  */
 typedef enum {
-    TVG_KERNEL_GENERIC = 0,        /* implicit GEMM with gathered operands, any shape      */
+    TVG_KERNEL_GENERIC = 0,        /* implicit GEMM, any shape (bf16: weights packed first) */
     TVG_KERNEL_3X3 = 1,            /* bf16 3x3, input patch in LDS, one stage              */
     TVG_KERNEL_3X3_PIPELINED = 2,  /* bf16 3x3, two LDS stages, software-pipelined         */
     TVG_KERNEL_STEM = 3,           /* bf16 7x7 or 3x3 stride 2, few input channels (mt 64|32) */

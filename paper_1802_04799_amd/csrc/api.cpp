@@ -99,12 +99,13 @@ void tile_key(const ConvProblem &p, int (&key)[12])
 // 257th distinct problem.  The launch-bound batch-1 layers spend 1-5 us per call in planning
 // otherwise.
 struct Dispatch {
-    bool patch_shape, stem_shape, pw_shape, pwd_shape, f32_shape;
+    bool patch_shape, stem_shape, pw_shape, pwd_shape, f32_shape, any_shape;
     tvg::Patch3x3Plan patch;
     tvg::StemPlan stem;
     tvg::Pw1x1Plan pw;
     tvg::PwDeepPlan pwd;            // the deep-reduction 1x1 kernel, where its rule (or a knob) picks it
     tvg::F32SmallPlan f32;
+    tvg::ConvAnyPlan any;
     tvg::ConvPlan generic;          // the generic kernel's plan, reduction split allowed
     tvg::ConvPlan generic_single;   // the same in a single pass (no workspace)
 };
@@ -144,6 +145,7 @@ Dispatch dispatch_for(const ConvProblem &p)
         const int want = tvg::forced_knobs(p).stages;
         d.pwd_shape = d.pw_shape && want == 2 && tvg::plan_conv1x1_deep(p, &d.pwd);
     }
+    d.any_shape = !d.patch_shape && !d.stem_shape && !d.pw_shape && tvg::plan_conv_bf16_any(p, &d.any);
     d.f32_shape = tvg::plan_conv_f32_small(p, &d.f32);
     d.generic = tvg::plan_conv(p, true);
     d.generic_single = tvg::plan_conv(p, false);
@@ -157,6 +159,45 @@ void forget_dispatch()
 {
     std::lock_guard<std::mutex> lock(g_dispatch_mutex);
     g_dispatch.clear();
+}
+
+// Bytes of workspace that the dispatch's kernels want.
+size_t dense_workspace(const Dispatch &d)
+{
+    if (d.patch_shape || d.stem_shape || d.pw_shape) return 0;
+    return d.any_shape ? d.any.workspace_bytes : d.f32_shape ? d.f32.workspace_bytes : d.generic.workspace_bytes;
+}
+
+// One dense convolution through whichever kernel takes it (ptr.workspace: workspace_bytes of scratch).
+tvg_status run_dense(const ConvProblem &p, const Dispatch &d, const tvg::ConvPointers &ptr, size_t workspace_bytes,
+                     hipStream_t stream)
+{
+    if (d.patch_shape && tvg::conv3x3_patch_pointers_ok(ptr))
+        return tvg::launch_conv3x3_patch(p, d.patch, ptr, stream);
+    if (d.stem_shape && tvg::conv7x7s2_stem_pointers_ok(ptr))
+        return tvg::launch_conv7x7s2_stem(p, d.stem, ptr, stream);
+    if (d.pwd_shape && tvg::conv1x1_deep_pointers_ok(ptr)) return tvg::launch_conv1x1_deep(p, d.pwd, ptr, stream);
+    if (d.pw_shape && tvg::conv1x1_pointers_ok(ptr)) return tvg::launch_conv1x1(p, d.pw, ptr, stream);
+    const auto workspace_short = [&](size_t need) {
+        return need > 0 && (!ptr.workspace || workspace_bytes < need ||
+                            reinterpret_cast<uintptr_t>(ptr.workspace) % 256 != 0);
+    };
+    // (a caller with less memory than the query reported gets the gather kernel, if that has enough)
+    if (d.any_shape && tvg::conv_bf16_any_pointers_ok(ptr) && !workspace_short(d.any.workspace_bytes))
+        return tvg::launch_conv_bf16_any(p, d.any, ptr, stream);
+    if (d.f32_shape && tvg::conv_f32_small_pointers_ok(ptr)) {
+        if (workspace_short(d.f32.workspace_bytes)) return TVG_ERR_WORKSPACE;
+        return tvg::launch_conv_f32_small(p, d.f32, ptr, stream);
+    }
+    // A problem shaped for a specialised kernel reported a zero workspace; if its pointers
+    // rule that kernel out, the generic kernel runs it in a single pass over the reduction.
+    // (an fp32 problem whose x is not 16-byte aligned: the generic kernel, within the workspace
+    // that the query reported for the fp32 kernel if that is all the caller has)
+    const tvg::ConvPlan &plan =
+        (d.patch_shape || d.stem_shape || d.pw_shape ||
+         (d.f32_shape && workspace_short(d.generic.workspace_bytes))) ? d.generic_single : d.generic;
+    if (workspace_short(plan.workspace_bytes)) return TVG_ERR_WORKSPACE;
+    return tvg::launch_conv_igemm(p, plan, ptr, stream);
 }
 
 // Scratch memory of tvg_conv2d_fused_static: the split-reduction partials of the generic kernel
@@ -289,6 +330,11 @@ tvg_status tvg_conv2d_get_knobs(const tvg_conv_desc *desc, tvg_conv_knobs *knobs
     } else if (d.f32_shape) {
         k.stages = 1;
         k.split_k = d.f32.nw * d.f32.ksplit;     // waves of a workgroup x slices across workgroups
+    } else if (d.any_shape) {
+        k.mt = d.any.mt;
+        k.nt = d.any.nt;
+        k.stages = 2;
+        k.split_k = d.any.splits;
     } else {
         k.mt = d.generic.mt;
         k.nt = d.generic.nt;
@@ -328,8 +374,8 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
         *nt = d.f32.stem ? 64 : d.f32.tile;
     } else {
         *kernel = TVG_KERNEL_GENERIC;
-        *mt = d.generic.mt;
-        *nt = d.generic.nt;
+        *mt = d.any_shape ? d.any.mt : d.generic.mt;
+        *nt = d.any_shape ? d.any.nt : d.generic.nt;
     }
     return TVG_OK;
 }
@@ -341,9 +387,7 @@ tvg_status tvg_conv2d_workspace_size(const tvg_conv_desc *desc, size_t *bytes)
     ConvProblem p;
     tvg_status st = make_problem(desc, false, &p);
     if (st != TVG_OK) return st;
-    const Dispatch d = dispatch_for(p);
-    const bool single_pass = d.patch_shape || d.stem_shape || d.pw_shape;
-    *bytes = single_pass ? 0 : d.f32_shape ? d.f32.workspace_bytes : d.generic.workspace_bytes;
+    *bytes = dense_workspace(dispatch_for(p));
     return TVG_OK;
 }
 
@@ -366,32 +410,8 @@ tvg_status tvg_conv2d_fused(const tvg_conv_desc *desc, const void *x, const void
     tvg_status st = make_problem(desc, false, &p);
     if (st != TVG_OK) return st;
     if (!x || !w || !scale || !shift || !y) return TVG_ERR_NULL;
-    tvg::ConvPointers ptr{x, w, scale, shift, bias, residual, y, static_cast<float *>(workspace)};
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const Dispatch d = dispatch_for(p);
-    if (d.patch_shape && tvg::conv3x3_patch_pointers_ok(ptr))
-        return tvg::launch_conv3x3_patch(p, d.patch, ptr, stream);
-    if (d.stem_shape && tvg::conv7x7s2_stem_pointers_ok(ptr))
-        return tvg::launch_conv7x7s2_stem(p, d.stem, ptr, stream);
-    if (d.pwd_shape && tvg::conv1x1_deep_pointers_ok(ptr)) return tvg::launch_conv1x1_deep(p, d.pwd, ptr, stream);
-    if (d.pw_shape && tvg::conv1x1_pointers_ok(ptr)) return tvg::launch_conv1x1(p, d.pw, ptr, stream);
-    const auto workspace_short = [&](size_t need) {
-        return need > 0 && (!workspace || workspace_bytes < need ||
-                            reinterpret_cast<uintptr_t>(workspace) % 256 != 0);
-    };
-    if (d.f32_shape && tvg::conv_f32_small_pointers_ok(ptr)) {
-        if (workspace_short(d.f32.workspace_bytes)) return TVG_ERR_WORKSPACE;
-        return tvg::launch_conv_f32_small(p, d.f32, ptr, stream);
-    }
-    // A problem shaped for a specialised kernel reported a zero workspace; if its pointers
-    // rule that kernel out, the generic kernel runs it in a single pass over the reduction.
-    // (an fp32 problem whose x is not 16-byte aligned: the generic kernel, within the workspace
-    // that the query reported for the fp32 kernel if that is all the caller has)
-    const tvg::ConvPlan &plan =
-        (d.patch_shape || d.stem_shape || d.pw_shape ||
-         (d.f32_shape && workspace_short(d.generic.workspace_bytes))) ? d.generic_single : d.generic;
-    if (workspace_short(plan.workspace_bytes)) return TVG_ERR_WORKSPACE;
-    return tvg::launch_conv_igemm(p, plan, ptr, stream);
+    const tvg::ConvPointers ptr{x, w, scale, shift, bias, residual, y, static_cast<float *>(workspace)};
+    return run_dense(p, dispatch_for(p), ptr, workspace_bytes, static_cast<hipStream_t>(hip_stream));
 }
 
 tvg_status tvg_conv2d_fused_dual(const tvg_conv_desc *desc, int32_t k1, uint32_t flags2,
@@ -421,6 +441,12 @@ tvg_status tvg_conv2d_fused_static(const tvg_conv_desc *desc, const void *x, con
     size_t need = 0;
     tvg_status st = tvg_conv2d_workspace_size(desc, &need);       // validates the descriptor
     if (st != TVG_OK) return st;
+    if (need > kStaticScratchBytes) {      // packed weights that do not fit: what the gather kernel needs
+        ConvProblem p;
+        make_problem(desc, false, &p);
+        const Dispatch d = dispatch_for(p);
+        if (d.any_shape) need = d.generic.workspace_bytes;
+    }
     if (!x || !w || !scale || !shift || !y) return TVG_ERR_NULL;
     if (need > kStaticScratchBytes) return TVG_ERR_WORKSPACE;     // before any device call
     void *ws = nullptr;
@@ -511,9 +537,7 @@ static size_t dwpw_workspace(const ConvProblem &dw, const ConvProblem &pw)
 {
     const size_t elem = dw.dtype == TVG_BF16 ? 2 : 4;
     size_t bytes = ((size_t)dw.N * dw.IC * dw.OH * dw.OW * elem + 255) & ~(size_t)255;
-    tvg::Pw1x1Plan p1;
-    if (!tvg::plan_conv1x1(pw, &p1)) bytes += tvg::plan_conv(pw).workspace_bytes;   // split-K scratch
-    return bytes;
+    return bytes + dense_workspace(dispatch_for(pw));              // packed weights, split-K scratch
 }
 
 tvg_status tvg_dwpw_workspace_size(const tvg_conv_desc *dw_desc, int32_t pw_k, size_t *bytes)
@@ -575,10 +599,7 @@ tvg_status tvg_dwpw_fused(const tvg_conv_desc *dw_desc, int32_t pw_k, uint32_t p
     if (st != TVG_OK) return st;
     const tvg::ConvPointers pptr{workspace, w_pw, scale_pw, shift_pw, bias_pw, residual, y,
                                  reinterpret_cast<float *>(static_cast<char *>(workspace) + t_bytes)};
-    tvg::Pw1x1Plan p1;
-    if (tvg::plan_conv1x1(pw, &p1) && tvg::conv1x1_pointers_ok(pptr))
-        return tvg::launch_conv1x1(pw, p1, pptr, stream);
-    return tvg::launch_conv_igemm(pw, tvg::plan_conv(pw), pptr, stream);
+    return run_dense(pw, dispatch_for(pw), pptr, workspace_bytes - t_bytes, stream);
 }
 
 tvg_status tvg_plan_arena(const tvg_tensor_life *tensors, int32_t count, uint64_t *offsets,

@@ -130,6 +130,25 @@ bool conv1x1_deep_pointers_ok(const ConvPointers &ptr);
 tvg_status launch_conv1x1_deep(const ConvProblem &p, const PwDeepPlan &plan, const ConvPointers &ptr,
                                hipStream_t stream);
 
+// bf16, any filter, stride, padding and channel counts: a pack launch lays the weights out in the
+// workspace, then one launch (and a reduce launch where the reduction is split) convolves.
+struct ConvAnyPlan {
+    int mt, nt, px, pt;               // output channels x pixels per workgroup, pixels per load, load tasks per thread
+    int co, nchunks, steps;           // channel octets per chunk, chunks, MFMA steps per chunk
+    int rows, pws, cp, groups;        // patch rows, row pitch and words per column phase, loads per row
+    int vh, vsh;                      // virtual rows per image and per output row
+    int splits, chunks_per_split;
+    int tpi;                          // pixel tiles per image, 0 = tiles cross images
+    int tab_bytes, patch_bytes;
+    long ntiles, tiles;               // pixel tiles, workgroups per slice
+    size_t lds_bytes, packed_bytes, workspace_bytes;
+};
+bool plan_conv_bf16_any(const ConvProblem &p, ConvAnyPlan *plan);
+bool conv_bf16_any_pointers_ok(const ConvPointers &ptr);
+// ptr.workspace: plan.workspace_bytes, the packed weights first
+tvg_status launch_conv_bf16_any(const ConvProblem &p, const ConvAnyPlan &plan, const ConvPointers &ptr,
+                                hipStream_t stream);
+
 // bf16 MobileNet block in one kernel: depthwise 3x3 (pad 1, stride 1) computed in LDS as the
 // pixel operand of the 1x1 stage.  `dw` is the depthwise problem, OC the 1x1 stage's channels.
 struct DwPwPlan {

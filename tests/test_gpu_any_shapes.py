@@ -1,0 +1,38 @@
+"""The bf16 kernel for any filter, stride, padding and channel count (plan: generic) against the
+oracle, every output, at the edges of its tiling: rows narrower than a load and one pixel longer,
+maps that end inside a tile and tiles that cross images, one and several channel chunks, a chunk's
+surplus units, filters with more taps than the stride and fewer, reductions split over workgroups.
+Bounds as for every single operator (tests/_util.py)."""
+import pytest
+
+import oracle
+import tvg_inputs as ti
+from _util import check, dev_inputs, to_host
+
+pytestmark = pytest.mark.gpu
+
+# n, ic, h, w, oc, r, s, stride, pad
+SHAPES = [
+    (6, 83, 45, 37, 139, 3, 3, 1, 1), (1, 1, 1, 1, 1, 1, 1, 1, 0), (3, 7, 3, 3, 33, 3, 3, 1, 1),
+    (3, 9, 6, 4, 31, 3, 3, 1, 1), (2, 17, 5, 9, 65, 5, 5, 1, 2), (9, 33, 7, 7, 64, 3, 3, 1, 1),
+    (1, 40, 64, 65, 96, 3, 5, 1, 1), (2, 20, 33, 30, 97, 1, 1, 2, 0), (4, 5, 20, 18, 40, 2, 3, 3, 1),
+    (2, 3, 40, 41, 24, 7, 7, 2, 3), (1, 8, 30, 130, 20, 11, 11, 1, 5), (1, 130, 6, 6, 200, 5, 5, 1, 2),
+    (2, 300, 9, 9, 40, 7, 7, 1, 3), (1, 9, 20, 20, 16, 15, 16, 1, 7), (40, 24, 3, 5, 70, 3, 3, 2, 0),
+]
+
+
+@pytest.mark.parametrize("tail", ["plain", "bias+residual"])
+@pytest.mark.parametrize("cfg", SHAPES, ids=lambda c: "x".join(map(str, c)))
+def test_bf16_any_shape(tvg, cfg, tail):
+    n, ic, h, w, oc, r, s, stride, pad = cfg
+    sh = ti.ConvShape("any", n, ic, h, w, oc, r, s, stride, pad)
+    desc = tvg.ConvDesc(n, ic, h, w, oc, r, s, stride, stride, pad, pad, tvg.TVG_BF16, 0)
+    assert tvg.tvg_conv2d_get_plan(desc)[0] == 0 and tvg.tvg_conv2d_workspace_size(desc) > 0
+    full = tail != "plain"
+    inp = ti.make_inputs(sh, 6100 + sum(cfg), "bf16", residual=full, bias=full)
+    d = dev_inputs(inp, "bf16")
+    y = tvg.conv2d_fused(d["x"], d["w"], d["scale"], d["shift"], d["bias"], d["residual"], stride=stride,
+                         pad=pad, relu=full)
+    want = oracle.conv2d_fused(inp["x"], inp["w"], inp["scale"], inp["shift"], inp["bias"], inp["residual"],
+                               stride=(stride,) * 2, pad=(pad,) * 2, relu=full)
+    check(to_host(y), want, "bf16", cfg)
