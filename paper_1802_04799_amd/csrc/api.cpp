@@ -99,13 +99,14 @@ void tile_key(const ConvProblem &p, int (&key)[12])
 // 257th distinct problem.  The launch-bound batch-1 layers spend 1-5 us per call in planning
 // otherwise.
 struct Dispatch {
-    bool patch_shape, stem_shape, pw_shape, pwd_shape, f32_shape, any_shape;
+    bool patch_shape, stem_shape, pw_shape, pwd_shape, f32_shape, any_shape, tiled_shape;
     tvg::Patch3x3Plan patch;
     tvg::StemPlan stem;
     tvg::Pw1x1Plan pw;
     tvg::PwDeepPlan pwd;            // the deep-reduction 1x1 kernel, where its rule (or a knob) picks it
     tvg::F32SmallPlan f32;
     tvg::ConvAnyPlan any;
+    tvg::F32TiledPlan tiled;
     tvg::ConvPlan generic;          // the generic kernel's plan, reduction split allowed
     tvg::ConvPlan generic_single;   // the same in a single pass (no workspace)
 };
@@ -146,7 +147,8 @@ Dispatch dispatch_for(const ConvProblem &p)
         d.pwd_shape = d.pw_shape && want == 2 && tvg::plan_conv1x1_deep(p, &d.pwd);
     }
     d.any_shape = !d.patch_shape && !d.stem_shape && !d.pw_shape && tvg::plan_conv_bf16_any(p, &d.any);
-    d.f32_shape = tvg::plan_conv_f32_small(p, &d.f32);
+    d.tiled_shape = tvg::plan_conv_f32_tiled(p, &d.tiled);
+    d.f32_shape = !d.tiled_shape && tvg::plan_conv_f32_small(p, &d.f32);
     d.generic = tvg::plan_conv(p, true);
     d.generic_single = tvg::plan_conv(p, false);
     std::lock_guard<std::mutex> lock(g_dispatch_mutex);
@@ -164,7 +166,7 @@ void forget_dispatch()
 // Bytes of workspace that the dispatch's kernels want.
 size_t dense_workspace(const Dispatch &d)
 {
-    if (d.patch_shape || d.stem_shape || d.pw_shape) return 0;
+    if (d.patch_shape || d.stem_shape || d.pw_shape || d.tiled_shape) return 0;
     return d.any_shape ? d.any.workspace_bytes : d.f32_shape ? d.f32.workspace_bytes : d.generic.workspace_bytes;
 }
 
@@ -185,6 +187,8 @@ tvg_status run_dense(const ConvProblem &p, const Dispatch &d, const tvg::ConvPoi
     // (a caller with less memory than the query reported gets the gather kernel, if that has enough)
     if (d.any_shape && tvg::conv_bf16_any_pointers_ok(ptr) && !workspace_short(d.any.workspace_bytes))
         return tvg::launch_conv_bf16_any(p, d.any, ptr, stream);
+    if (d.tiled_shape && tvg::conv_f32_tiled_pointers_ok(ptr))
+        return tvg::launch_conv_f32_tiled(p, d.tiled, ptr, stream);
     if (d.f32_shape && tvg::conv_f32_small_pointers_ok(ptr)) {
         if (workspace_short(d.f32.workspace_bytes)) return TVG_ERR_WORKSPACE;
         return tvg::launch_conv_f32_small(p, d.f32, ptr, stream);
@@ -194,7 +198,7 @@ tvg_status run_dense(const ConvProblem &p, const Dispatch &d, const tvg::ConvPoi
     // (an fp32 problem whose x is not 16-byte aligned: the generic kernel, within the workspace
     // that the query reported for the fp32 kernel if that is all the caller has)
     const tvg::ConvPlan &plan =
-        (d.patch_shape || d.stem_shape || d.pw_shape ||
+        (d.patch_shape || d.stem_shape || d.pw_shape || d.tiled_shape ||
          (d.f32_shape && workspace_short(d.generic.workspace_bytes))) ? d.generic_single : d.generic;
     if (workspace_short(plan.workspace_bytes)) return TVG_ERR_WORKSPACE;
     return tvg::launch_conv_igemm(p, plan, ptr, stream);
@@ -327,6 +331,11 @@ tvg_status tvg_conv2d_get_knobs(const tvg_conv_desc *desc, tvg_conv_knobs *knobs
         k.mt = d.pw.mt;
         k.nt = d.pw.nt;
         k.stages = 1;
+    } else if (d.tiled_shape) {
+        k.mt = 64;
+        k.nt = d.tiled.nt;
+        k.stages = 2;
+        k.split_k = 1;
     } else if (d.f32_shape) {
         k.stages = 1;
         k.split_k = d.f32.nw * d.f32.ksplit;     // waves of a workgroup x slices across workgroups
@@ -374,8 +383,8 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
         *nt = d.f32.stem ? 64 : d.f32.tile;
     } else {
         *kernel = TVG_KERNEL_GENERIC;
-        *mt = d.any_shape ? d.any.mt : d.generic.mt;
-        *nt = d.any_shape ? d.any.nt : d.generic.nt;
+        *mt = d.tiled_shape ? 64 : d.any_shape ? d.any.mt : d.generic.mt;
+        *nt = d.tiled_shape ? d.tiled.nt : d.any_shape ? d.any.nt : d.generic.nt;
     }
     return TVG_OK;
 }

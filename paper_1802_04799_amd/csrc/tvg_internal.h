@@ -149,6 +149,19 @@ bool conv_bf16_any_pointers_ok(const ConvPointers &ptr);
 tvg_status launch_conv_bf16_any(const ConvProblem &p, const ConvAnyPlan &plan, const ConvPointers &ptr,
                                 hipStream_t stream);
 
+// fp32 1x1 / 3x3 / 5x5 / 7x7 at throughput size: input rows and weight runs staged in LDS, one launch.
+struct F32TiledPlan {
+    int nt, pt;                       // pixels per workgroup (x 64 channels), patch elements per thread
+    int pitch, plane, buf_floats;     // patch floats per row and channel, floats per LDS buffer
+    int nchunks, tpi;                 // channel chunks, pixel tiles per image
+    long tiles;
+    size_t lds_bytes;
+};
+bool plan_conv_f32_tiled(const ConvProblem &p, F32TiledPlan *plan);
+bool conv_f32_tiled_pointers_ok(const ConvPointers &ptr);
+tvg_status launch_conv_f32_tiled(const ConvProblem &p, const F32TiledPlan &plan, const ConvPointers &ptr,
+                                 hipStream_t stream);
+
 // bf16 MobileNet block in one kernel: depthwise 3x3 (pad 1, stride 1) computed in LDS as the
 // pixel operand of the 1x1 stage.  `dw` is the depthwise problem, OC the 1x1 stage's channels.
 struct DwPwPlan {
