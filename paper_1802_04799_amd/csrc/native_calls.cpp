@@ -145,13 +145,17 @@ bool descriptor(PyObject *o, tvg_conv_desc *out)
     return fits;
 }
 
+// Runs a library call without the GIL, which is held again on every way out.  Nothing of torch's
+// belongs in `f`: reading a tensor's address may raise (tensors without storage), so callers read
+// every address before.
 template <typename F>
 tvg_status without_gil(F &&f)
 {
-    PyThreadState *save = PyEval_SaveThread();
-    const tvg_status st = f();
-    PyEval_RestoreThread(save);
-    return st;
+    struct Released {
+        PyThreadState *state = PyEval_SaveThread();
+        ~Released() { PyEval_RestoreThread(state); }
+    } released;
+    return f();
 }
 
 // Runs a call's body; C++ exceptions (torch's) become RuntimeError.
@@ -476,10 +480,11 @@ PyObject *convolution(bool depthwise, const Spec &spec, PyObject *const *args, P
         void *scratch_ptr = scratch.defined() ? scratch.data_ptr() : nullptr;
         const size_t scratch_bytes = scratch.defined() ? bytes_of(&scratch) : 0;
         void *yp = y.data_ptr();
+        const void *xp = data(x), *wp = data(w), *rp = data(residual);
+        const float *sp = floats(scale), *hp = floats(shift), *bp = floats(bias);
         const tvg_status st = without_gil([&] {
-            return (depthwise ? tvg_dwconv2d_fused : tvg_conv2d_fused)(&d, data(x), data(w), floats(scale),
-                                                                      floats(shift), floats(bias), data(residual), yp,
-                                                                      scratch_ptr, scratch_bytes, stream);
+            return (depthwise ? tvg_dwconv2d_fused : tvg_conv2d_fused)(&d, xp, wp, sp, hp, bp, rp, yp, scratch_ptr,
+                                                                      scratch_bytes, stream);
         });
         if (st != TVG_OK) return raise_status(st, depthwise ? "tvg_dwconv2d_fused" : "tvg_conv2d_fused");
         if (out) {
@@ -525,9 +530,11 @@ PyObject *py_dwpw_fused(ARGS)
         const size_t scratch_bytes = scratch.defined() ? bytes_of(&scratch) : 0;
         void *yp = y.data_ptr();
         const uint32_t flags = (relu_pw ? (uint32_t)TVG_RELU : 0u) | (stream_out ? (uint32_t)TVG_STREAM_OUT : 0u);
+        const void *xp = data(x), *wdp = data(wd), *wpp = data(wp), *rp = data(residual);
+        const float *scdp = floats(scd), *shdp = floats(shd), *scpp = floats(scp), *shpp = floats(shp), *bp = floats(bias);
         const tvg_status st = without_gil([&] {
-            return tvg_dwpw_fused(&d, k, flags, data(x), data(wd), floats(scd), floats(shd), data(wp), floats(scp),
-                                  floats(shp), floats(bias), data(residual), yp, scratch_ptr, scratch_bytes, stream);
+            return tvg_dwpw_fused(&d, k, flags, xp, wdp, scdp, shdp, wpp, scpp, shpp, bp, rp, yp, scratch_ptr,
+                                  scratch_bytes, stream);
         });
         if (st != TVG_OK) return raise_status(st, "tvg_dwpw_fused");
         if (out) {
