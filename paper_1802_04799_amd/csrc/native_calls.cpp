@@ -17,6 +17,7 @@
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <exception>
@@ -158,14 +159,15 @@ tvg_status without_gil(F &&f)
     return f();
 }
 
-// Runs a call's body; C++ exceptions (torch's) become RuntimeError.
+// Runs a call's body; C++ exceptions become the Python ones that torch's own calls raise for them
+// (OutOfMemoryError where an allocation failed, else RuntimeError and the like).
 template <typename F>
 PyObject *guarded(F &&f)
 {
     try {
         return f();
-    } catch (const std::exception &e) {
-        if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what());
+    } catch (...) {
+        if (!PyErr_Occurred()) torch::translate_exception_to_python(std::current_exception());
         return nullptr;
     }
 }
