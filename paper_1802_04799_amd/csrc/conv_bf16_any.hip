@@ -29,6 +29,8 @@
 // is issued, 2.8 until the first patch is in LDS, 2.8 in the loop, 1.5 in the tail.  The gather
 // kernel with its split reduction took 62 + 8 us.  Larger problems: 9 x 24 x 99 x 99 -> 200, 5x5, 256
 // us before, 60 now (350 TFLOP/s); 27 x 168 x 10 x 76 -> 312, 3x3, 132 before, 38 now (506).
+#include <type_traits>
+
 #include "tvg_device.h"
 #include "tvg_internal.h"
 
@@ -40,6 +42,7 @@ constexpr int kWord = 16;                 // bytes: eight channels of one positi
 constexpr int kRsrcFlags = 0x00020000;
 constexpr uint32_t kOutOfRange = 0x80000000u;      // and everything above: tensors stay below 2 GiB
 constexpr size_t kMaxLds = 160 * 1024;
+constexpr int kNoTap = 1 << 24;           // patch offset of a unit without a tap: past the LDS
 
 // Exact division of 0 <= n < 2^31 by a divisor the host knows: one high multiply and a shift.
 struct Divider { uint32_t d, m, s; };
@@ -78,7 +81,7 @@ struct AnyArgs {
     int mtiles, splits, tpi;              // tpi: pixel tiles per image, 0 = tiles cross images
     int border;                           // zero columns per patch row
     uint32_t x_bytes, packed_bytes;
-    int tab_bytes, patch_bytes;
+    int tab_bytes, patch_bytes, zero_at;  // LDS: unit table, one patch, offset of the word of zeros
     Divider by_ohw, by_ow, by_vh, by_r, by_groups, by_mtiles, by_co, by_s, by_sw, by_tpi, by_border;
 };
 
@@ -249,10 +252,10 @@ __global__ __launch_bounds__(256, 2) void conv_bf16_any_kernel(const AnyArgs a)
     for (int u = tid; u < 2 * tpitch; u += 256) {
         int o, s, f;
         int t = divide(u, a.by_co, &o);
-        if (t >= a.R * a.S) t = o = 0;              // units without a tap: their weights are zeros
         const int r = divide(t, a.by_s, &s), q = divide(s, a.by_sw, &f);
-        tab[(u & 1) * tpitch + (u >> 1)] = o * plane + (r * a.pws + f * a.cp + q) * kWord;
+        tab[(u & 1) * tpitch + (u >> 1)] = t < a.R * a.S ? o * plane + (r * a.pws + f * a.cp + q) * kWord : kNoTap;
     }
+    if (tid == 0) *reinterpret_cast<uint4v *>(smem + a.zero_at) = uint4v{0u, 0u, 0u, 0u};
     // zero columns left and right of the image: no load task writes them
     for (int i = tid; i < (c_end - c_beg > 1 ? 2 : 1) * a.co * a.rows * a.border; i += 256) {
         int e, f;
@@ -293,26 +296,31 @@ __global__ __launch_bounds__(256, 2) void conv_bf16_any_kernel(const AnyArgs a)
     typedef int int4v __attribute__((ext_vector_type(4)));
     struct Offsets { int4v v[RING / 4]; };
     const Offsets *tb = reinterpret_cast<const Offsets *>(tab + lhalf * tpitch);
-    const int turns = a.steps / RING;
+    const int turns = a.steps / RING, patch_at = a.tab_bytes + 2 * MT * 4;
     int c = rot;
     for (int k = c_beg; k < c_end; ++k) {
-        const unsigned char *P = patch + ((k - c_beg) & 1) * a.patch_bytes;
+        const int P = patch_at + ((k - c_beg) & 1) * a.patch_bytes;
         const int cn = c + 1 < c_end ? c + 1 : c_beg;
         if (k + 1 < c_end) load_patch(cn);
         uint4v bf[4][NJ];
-        auto fetch = [&](int off, int slot) __attribute__((always_inline)) {
+        // A unit without a tap multiplies zeros by zeros: its weights against pixels of the image would turn an
+        // infinity there into a NaN.  Its offset is past everything and the word of zeros lies last, so that one
+        // minimum per address selects it; only a chunk's last turn has such units.  (A minimum in every turn:
+        // 0 to 2 % slower; a compare and select: 1 to 4 %; branches around the MFMAs of such steps: 2 to 18 %.)
+        auto fetch = [&](int off, int slot, bool surplus) __attribute__((always_inline)) {
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) bf[slot][j] = *reinterpret_cast<const uint4v *>(P + (pb[j] + off));
+            for (int j = 0; j < NJ; ++j)
+                bf[slot][j] = *reinterpret_cast<const uint4v *>(smem + (surplus ? min(P + pb[j] + off, a.zero_at) : P + pb[j] + off));
         };
         Offsets cur = tb[0];
-        fetch(cur.v[0][0], 0);
-        fetch(cur.v[0][1], 1);
-        for (int t = 0; t < turns; ++t) {
+        fetch(cur.v[0][0], 0, true);
+        fetch(cur.v[0][1], 1, true);
+        auto turn = [&](int t, auto last) __attribute__((always_inline)) {
             const Offsets nxt = tb[t + 1];
-            if (t + 1 == turns) wat = wtile + cn * wchunk;         // the weights read ahead are the next chunk's
+            if (last) wat = wtile + cn * wchunk;                   // the weights read ahead are the next chunk's
 #pragma unroll
             for (int d = 0; d < RING; ++d) {
-                fetch(d + 2 < RING ? cur.v[(d + 2) / 4][(d + 2) & 3] : nxt.v[0][d + 2 - RING], (d + 2) & 3);
+                fetch(d + 2 < RING ? cur.v[(d + 2) / 4][(d + 2) & 3] : nxt.v[0][d + 2 - RING], (d + 2) & 3, last || d + 2 >= RING);
 #pragma unroll
                 for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -323,7 +331,9 @@ __global__ __launch_bounds__(256, 2) void conv_bf16_any_kernel(const AnyArgs a)
                 __builtin_amdgcn_sched_barrier(0);
             }
             cur = nxt;
-        }
+        };
+        for (int t = 0; t + 1 < turns; ++t) turn(t, std::false_type{});
+        turn(turns - 1, std::true_type{});
         c = cn;
         if (k + 1 < c_end) store_patch(patch + ((k + 1 - c_beg) & 1) * a.patch_bytes);
         __syncthreads();
@@ -503,7 +513,7 @@ bool fit_tile(const ConvProblem &p, int mt, int nt, size_t lds_limit, ConvAnyPla
         if (tasks > 512 || co * 8 * T > 2040) continue;      // (the pack launch stages 16 rows of an octet in 64 KB)
         const int tab_bytes = (2 * (steps + ring) * 4 + 15) / 16 * 16;
         const size_t body = (nchunks > 1 ? 2 : 1) * plane * co;
-        const size_t lds_bytes = tab_bytes + 2 * mt * 4 + (body > stage ? body : stage);
+        const size_t lds_bytes = tab_bytes + 2 * mt * 4 + (body + kWord > stage ? body + kWord : stage);
         if (lds_bytes > lds_limit || (best >= 0 && (long)nchunks * (steps + 3) >= best)) continue;   // (a chunk change costs about 3 steps)
         best = (long)nchunks * (steps + 3);
         plan->co = co;
@@ -601,6 +611,7 @@ tvg_status launch_conv_bf16_any(const ConvProblem &p, const ConvAnyPlan &plan, c
     a.x_bytes = (uint32_t)((size_t)p.N * p.IC * p.H * p.W * 2);
     a.packed_bytes = (uint32_t)plan.packed_bytes;
     a.tab_bytes = plan.tab_bytes; a.patch_bytes = plan.patch_bytes;
+    a.zero_at = plan.tab_bytes + 2 * plan.mt * 4 + (plan.nchunks > 1 ? 2 : 1) * plan.patch_bytes;
     a.by_ohw = make_divider(p.OH * p.OW); a.by_ow = make_divider(p.OW); a.by_vh = make_divider(plan.vh);
     a.by_r = make_divider(p.R); a.by_groups = make_divider(plan.groups); a.by_mtiles = make_divider(mtiles);
     a.by_co = make_divider(plan.co); a.by_s = make_divider(p.S); a.by_sw = make_divider(p.sw);

@@ -36,3 +36,32 @@ def test_bf16_any_shape(tvg, cfg, tail):
     want = oracle.conv2d_fused(inp["x"], inp["w"], inp["scale"], inp["shift"], inp["bias"], inp["residual"],
                                stride=(stride,) * 2, pad=(pad,) * 2, relu=full)
     check(to_host(y), want, "bf16", cfg)
+
+
+# one shape per tile of the kernel, each with units that no tap fills in the last turn of a chunk
+WITH_SURPLUS_UNITS = [
+    (3, 7, 3, 3, 33, 3, 1, 1), (8, 45, 65, 63, 60, 3, 1, 1), (16, 20, 65, 63, 50, 3, 1, 1),
+    (20, 20, 65, 63, 31, 3, 1, 1), (8, 20, 65, 63, 31, 3, 1, 1), (2, 300, 13, 13, 31, 5, 1, 2),
+]
+
+
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("cfg", WITH_SURPLUS_UNITS, ids=lambda c: "x".join(map(str, c)))
+def test_an_infinity_in_x_reaches_its_outputs_and_no_others(tvg, cfg, relu):
+    """An overflowed activation: every output whose window holds it is an infinity of the right sign (or 0
+    behind the ReLU), every other one is what it is without it.  Reference: torch in 64 bits on the CPU."""
+    import torch
+    n, ic, h, w, oc, r, stride, pad = cfg
+    inp = ti.make_inputs(ti.ConvShape("inf", n, ic, h, w, oc, r, r, stride, pad), 6400 + sum(cfg), "bf16")
+    inp["x"][0, 0, 1, 1] = float("inf")
+    inp["x"][n - 1, ic - 1, h - 1, w - 1] = float("-inf")
+    d = dev_inputs(inp, "bf16")
+    got = tvg.conv2d_fused(d["x"], d["w"], d["scale"], d["shift"], stride=stride, pad=pad, relu=relu).cpu().double()
+    t = {k: torch.from_numpy(inp[k]).double() for k in ("x", "w", "scale", "shift")}
+    want = torch.nn.functional.conv2d(t["x"], t["w"], stride=stride, padding=pad)
+    want = want * t["scale"].view(1, -1, 1, 1) + t["shift"].view(1, -1, 1, 1)
+    want = want.relu() if relu else want
+    assert bool(torch.isposinf(want).any()) and not bool(torch.isnan(want).any())
+    odd = torch.isinf(want)
+    assert torch.equal(got[odd], want[odd]) and bool(torch.isfinite(got[~odd]).all())
+    check(got[~odd].numpy(), want[~odd].numpy(), "bf16", cfg)
