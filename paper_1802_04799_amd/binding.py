@@ -343,6 +343,25 @@ def make_desc(x, w, stride, pad, relu, depthwise=False, stream_out=False) -> Con
     return ConvDesc(n, c, h, wd, k, r, s, sh, sw, ph, pw, _dtype_code(x), flags)
 
 
+def _empty(shape, dtype, device, stream, result=True):
+    """torch.empty for a launch on `stream`: memory from that stream's pool, since torch's allocator
+    hands blocks out again in the order of the stream they were allocated on; a `result`, which the caller
+    goes on to use on the current stream, is marked as used there too."""
+    import torch
+    if stream is None:
+        return torch.empty(shape, dtype=dtype, device=device)
+    current = torch.cuda.current_stream(device)
+    handle = stream if isinstance(stream, int) else stream.cuda_stream
+    if handle == current.cuda_stream:
+        return torch.empty(shape, dtype=dtype, device=device)
+    other = torch.cuda.ExternalStream(handle, device=device) if handle else torch.cuda.default_stream(device)
+    with torch.cuda.stream(other):
+        t = torch.empty(shape, dtype=dtype, device=device)
+    if result:
+        t.record_stream(current)
+    return t
+
+
 def _conv2d_fused(x, w, scale, shift, bias=None, residual=None, *, stride=1, pad=0, relu=False,
                  out=None, workspace=None, stream=None, stream_out=False):
     """y = tail(conv2d(x, w)); allocates y (and the workspace when needed) with torch."""
@@ -353,9 +372,9 @@ def _conv2d_fused(x, w, scale, shift, bias=None, residual=None, *, stride=1, pad
         raise ValueError("weight input channels do not match x")
     need = tvg_conv2d_workspace_size(desc)
     if out is None:
-        out = torch.empty((desc.n, desc.k, desc.oh, desc.ow), dtype=x.dtype, device=x.device)
+        out = _empty((desc.n, desc.k, desc.oh, desc.ow), x.dtype, x.device, stream)
     if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
-        workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
+        workspace = _empty((need,), torch.uint8, x.device, stream, result=False)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     st = native().tvg_conv2d_fused(desc, x, w, scale, shift, bias, residual, out, workspace, ws_bytes, stream)
     if st != TVG_OK:
@@ -365,11 +384,10 @@ def _conv2d_fused(x, w, scale, shift, bias=None, residual=None, *, stride=1, pad
 
 def _dwconv2d_fused(x, w, scale, shift, bias=None, residual=None, *, stride=1, pad=1, relu=False,
                    out=None, stream=None, stream_out=False):
-    import torch
     _check(x, w, scale, shift, bias, residual)
     desc = make_desc(x, w, stride, pad, relu, depthwise=True, stream_out=stream_out)
     if out is None:
-        out = torch.empty((desc.n, desc.k, desc.oh, desc.ow), dtype=x.dtype, device=x.device)
+        out = _empty((desc.n, desc.k, desc.oh, desc.ow), x.dtype, x.device, stream)
     st = native().tvg_dwconv2d_fused(desc, x, w, scale, shift, bias, residual, out, None, 0, stream)
     if st != TVG_OK:
         raise TvgError(st, "tvg_dwconv2d_fused")
@@ -391,13 +409,13 @@ def _dwpw_fused(x, w_dw, scale_dw, shift_dw, w_pw, scale_pw, shift_pw, bias_pw=N
         raise ValueError("w_pw must be [k][c][1][1]")
     flags = (TVG_RELU if relu_pw else 0) | (TVG_STREAM_OUT if stream_out else 0)
     if out is None:
-        out = torch.empty((desc.n, k, desc.oh, desc.ow), dtype=x.dtype, device=x.device)
+        out = _empty((desc.n, k, desc.oh, desc.ow), x.dtype, x.device, stream)
     if one_kernel:
         workspace = None
     else:
         need = tvg_dwpw_workspace_size(desc, k)
         if workspace is None or workspace.numel() * workspace.element_size() < need:
-            workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
+            workspace = _empty((need,), torch.uint8, x.device, stream, result=False)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     st = native().tvg_dwpw_fused(desc, k, flags, x, w_dw, scale_dw, shift_dw, w_pw, scale_pw, shift_pw,
                         bias_pw, residual, out, workspace, ws_bytes, stream)
@@ -407,12 +425,11 @@ def _dwpw_fused(x, w_dw, scale_dw, shift_dw, w_pw, scale_pw, shift_pw, bias_pw=N
 
 
 def maxpool2d_3x3s2(x, out=None, stream=None):
-    import torch
     if not x.is_cuda or not x.is_contiguous():
         raise ValueError("x must be a contiguous device tensor")
     n, c, h, w = x.shape
     if out is None:
-        out = torch.empty((n, c, (h - 1) // 2 + 1, (w - 1) // 2 + 1), dtype=x.dtype, device=x.device)
+        out = _empty((n, c, (h - 1) // 2 + 1, (w - 1) // 2 + 1), x.dtype, x.device, stream)
     st = native().tvg_maxpool2d_3x3s2(n, c, h, w, _dtype_code(x), x, out, stream)
     if st != TVG_OK:
         raise TvgError(st, "tvg_maxpool2d_3x3s2")

@@ -16,6 +16,7 @@
 
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
+#include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -419,21 +420,53 @@ bool describe(const at::Tensor &x, const at::Tensor &w, PyObject *stride, PyObje
 
 int64_t out_extent(int64_t in, int32_t pad, int32_t taps, int32_t stride) { return (in + 2 * pad - taps) / stride + 1; }
 
+// Memory for a launch on a stream of the caller's choice.  torch's allocator hands a block out again in
+// the order of the stream it was allocated on: from the current stream's pool it could still be in use
+// there when the launch writes it, and a workspace released on return would be the next allocation's
+// while the launch works in it.  So it comes from the pool of the launch's stream; a result, which the
+// caller goes on to use on the current stream, is marked as used there too.
+class Allocator {
+public:
+    // `stream`: the call's argument (absent: the current stream), `handle`: what it stands for
+    Allocator(const at::Tensor &x, PyObject *stream, void *handle)
+        : device_(x.device()), chosen_(stream && stream != Py_None), handle_(handle) {}
+    at::Tensor workspace(size_t bytes) const { return make({(int64_t)bytes}, at::kByte, false); }
+    at::Tensor result(at::IntArrayRef shape, c10::ScalarType type) const { return make(shape, type, true); }
+
+private:
+    at::Tensor make(at::IntArrayRef shape, c10::ScalarType type, bool result) const
+    {
+        const at::TensorOptions options = at::TensorOptions().dtype(type).device(device_);
+        if (!chosen_) return at::empty(shape, options);
+        struct Restored {
+            c10::hip::HIPStream current;
+            ~Restored() { c10::hip::setCurrentHIPStream(current); }
+        } restored{c10::hip::getCurrentHIPStream(device_.index())};
+        if (restored.current.stream() == handle_) return at::empty(shape, options);
+        c10::hip::setCurrentHIPStream(c10::hip::getStreamFromExternal(static_cast<hipStream_t>(handle_), device_.index()));
+        at::Tensor t = at::empty(shape, options);
+        if (result) c10::hip::HIPCachingAllocator::recordStream(t.storage().data_ptr(), restored.current);
+        return t;
+    }
+    c10::Device device_;
+    bool chosen_;
+    void *handle_;
+};
+
 // The tensor that receives the result: the caller's, or a new one.
-at::Tensor result(const at::Tensor *given, const at::Tensor &x, const tvg_conv_desc &d, int64_t k)
+at::Tensor result(const at::Tensor *given, const Allocator &memory, const at::Tensor &x, const tvg_conv_desc &d, int64_t k)
 {
     if (given) return *given;
-    return at::empty({d.n, k, out_extent(d.h, d.pad_h, d.r, d.stride_h), out_extent(d.w, d.pad_w, d.s, d.stride_w)},
-                     at::TensorOptions().dtype(x.scalar_type()).device(x.device()));
+    return memory.result({d.n, k, out_extent(d.h, d.pad_h, d.r, d.stride_h), out_extent(d.w, d.pad_w, d.s, d.stride_w)},
+                         x.scalar_type());
 }
 
 size_t bytes_of(const at::Tensor *t) { return t ? (size_t)t->numel() * t->element_size() : 0; }
 
 // The workspace to pass: the caller's if it is large enough, else a new one.
-at::Tensor enough_workspace(const at::Tensor *given, size_t need, const at::Tensor &x)
+at::Tensor enough_workspace(const at::Tensor *given, size_t need, const Allocator &memory)
 {
-    if (given && bytes_of(given) >= need) return *given;
-    return at::empty({(int64_t)need}, at::TensorOptions().dtype(at::kByte).device(x.device()));
+    return given && bytes_of(given) >= need ? *given : memory.workspace(need);
 }
 
 const float *floats(const at::Tensor *t) { return t ? static_cast<const float *>(t->data_ptr()) : nullptr; }
@@ -475,9 +508,10 @@ PyObject *convolution(bool depthwise, const Spec &spec, PyObject *const *args, P
             const tvg_status st = tvg_dwconv2d_workspace_size(&d, &need);      // validates the descriptor
             if (st != TVG_OK) return fall_back(where, args, nargs, kwnames);
         }
-        at::Tensor y = result(out, *x, d, d.k);
+        const Allocator memory(*x, v[11], stream);
+        at::Tensor y = result(out, memory, *x, d, d.k);
         at::Tensor scratch;
-        if (need) scratch = enough_workspace(ws, need, *x);
+        if (need) scratch = enough_workspace(ws, need, memory);
         else if (ws) scratch = *ws;
         void *scratch_ptr = scratch.defined() ? scratch.data_ptr() : nullptr;
         const size_t scratch_bytes = scratch.defined() ? bytes_of(&scratch) : 0;
@@ -525,9 +559,10 @@ PyObject *py_dwpw_fused(ARGS)
         if (tvg_dwpw_workspace_size(&d, k, &need) != TVG_OK) return fall_back("dwpw_fused", args, nargs, kwnames);
         void *stream;
         if (!stream_handle(v[14], &stream)) return nullptr;
-        at::Tensor y = result(out, *x, d, k);
+        const Allocator memory(*x, v[14], stream);
+        at::Tensor y = result(out, memory, *x, d, k);
         at::Tensor scratch;
-        if (!one_kernel) scratch = enough_workspace(ws, need, *x);
+        if (!one_kernel) scratch = enough_workspace(ws, need, memory);
         void *scratch_ptr = scratch.defined() ? scratch.data_ptr() : nullptr;
         const size_t scratch_bytes = scratch.defined() ? bytes_of(&scratch) : 0;
         void *yp = y.data_ptr();

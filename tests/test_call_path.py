@@ -25,7 +25,7 @@ def outcome(f):
         print(type(e).__name__, str(e).splitlines()[0])
 with FakeTensorMode(allow_non_fake_inputs=True):
     x, w, s, o = dev(2, 1, 8, 5, 5), dev(8, 8, 3, 3), dev(8), dev(1, 8, 5, 5)
-    wd, wp = dev(8, 1, 3, 3), dev(8, 8, 1, 1)
+    wd, wp, ws = dev(8, 1, 3, 3), dev(8, 8, 1, 1), dev(1 << 16, dtype=torch.uint8)
 """
 
 
@@ -40,7 +40,7 @@ def outcome(body):
 @pytest.mark.parametrize("call", [
     "tvg.conv2d_fused(a, w, s, s, pad=1, out=o, stream=0)",
     "tvg.dwconv2d_fused(a, wd, s, s, pad=1, out=o, stream=0)",
-    "tvg.dwpw_fused(a, wd, s, s, wp, s, s, out=o, stream=0)",
+    "tvg.dwpw_fused(a, wd, s, s, wp, s, s, out=o, workspace=ws, stream=0)",
 ])
 @pytest.mark.parametrize("transform", ["torch.vmap(f)(x)", "torch.func.vjp(f, x[0])", "torch.func.jvp(f, (x[0],), (x[0],))"])
 def test_a_tensor_without_storage_is_a_python_exception(call, transform):
