@@ -37,7 +37,10 @@
  *   - Which kernel runs a problem, its launch shape and its workspace size depend on the
  *     descriptor (flags aside) and on what tvg_conv2d_set_tile has fixed, on nothing else: no
  *     environment variable is read.  Plans are remembered per problem; a size query and the
- *     call that follows it therefore agree unless tvg_conv2d_set_tile runs in between.
+ *     call that follows it therefore agree unless tvg_conv2d_set_tile runs in between.  Two
+ *     exceptions fall back to the generic kernel, which is slower and adds in another order (so
+ *     that results may differ in their last bit): pointers not aligned as a kernel needs them, and
+ *     a workspace below the queried size where tvg_conv2d_workspace_size says so.
  */
 #ifndef TVG_H
 #define TVG_H
@@ -54,7 +57,7 @@ typedef enum {
     TVG_ERR_NULL = 1,          /* a required pointer is NULL */
     TVG_ERR_BAD_SHAPE = 2,     /* non-positive extent, empty output, stride/pad out of range */
     TVG_ERR_UNSUPPORTED = 3,   /* unknown dtype or flag, tensor too large, kernel size not built */
-    TVG_ERR_WORKSPACE = 4,     /* workspace NULL, smaller than the query says or misaligned */
+    TVG_ERR_WORKSPACE = 4,     /* workspace NULL, too small or misaligned */
     TVG_ERR_LAUNCH = 5         /* the HIP runtime refused the launch */
 } tvg_status;
 
@@ -84,10 +87,14 @@ typedef struct {
 } tvg_conv_desc;               /* depthwise: k == c, r == s == 3                            */
 
 /*
- * Bytes of scratch that tvg_conv2d_fused needs for this problem (0 when the
- * problem is not split along the reduction axis).  Pure host computation.
+ * Bytes of scratch that tvg_conv2d_fused needs for this problem: the partial sums of a
+ * reduction that is split across workgroups, and the packed weights of bf16 problems that the
+ * 3x3, 1x1 and stem kernels do not take; 0 for all others.  Pure host computation.
  * `bytes` is a host pointer.  Returns TVG_OK or the same validation error the
  * operator itself would return.
+ * With less (or NULL, or misaligned) a call is TVG_ERR_WORKSPACE, except for the bf16 problems
+ * with packed weights: those run on the generic kernel, several times slower, if it splits no
+ * reduction or what it is given holds its partial sums.
  */
 tvg_status tvg_conv2d_workspace_size(const tvg_conv_desc *desc, size_t *bytes);
 
@@ -105,7 +112,7 @@ tvg_status tvg_dwconv2d_workspace_size(const tvg_conv_desc *desc, size_t *bytes)
  *   bias     device, fp32 [k], or NULL
  *   residual device, [n][k][oh][ow], dtype, or NULL
  *   y        device, [n][k][oh][ow], dtype, written completely
- *   workspace device, at least tvg_conv2d_workspace_size() bytes, 256-byte
+ *   workspace device, at least tvg_conv2d_workspace_size() bytes (see there for less), 256-byte
  *            aligned; may be NULL when that size is 0.  Contents are scratch.
  */
 tvg_status tvg_conv2d_fused(const tvg_conv_desc *desc, const void *x, const void *w,
@@ -174,19 +181,22 @@ tvg_status tvg_conv2d_fused_prepacked(const tvg_conv_desc *desc, const void *x, 
 /*
  * tvg_conv2d_fused for callers that cannot allocate device memory and so have no workspace to
  * pass: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
- * Same operator, same kernels, same results bit for bit; the scratch that a split reduction
- * needs comes from an array inside the library (tvg_static_scratch_bytes() = 16 MiB per GPU,
- * held from the library's load to the end of the process) instead of a workspace argument.
- *   - A problem whose tvg_conv2d_workspace_size() exceeds that is TVG_ERR_WORKSPACE (use
- *     tvg_conv2d_fused with a workspace); all other arguments and errors as tvg_conv2d_fused.
+ * Same operator; the scratch (packed weights, partial sums) comes from an array inside the
+ * library (tvg_static_scratch_bytes() = 16 MiB per GPU, held from the library's load to the end
+ * of the process) instead of a workspace argument.
+ *   - Where tvg_conv2d_workspace_size() fits the array: same kernels, same results bit for bit.
+ *   - A bf16 problem whose packed weights make it exceed the array runs on the generic kernel,
+ *     slower and adding in another order, if its partial sums fit (tvg_conv2d_fused with a
+ *     workspace is the fast way).  Every other problem that exceeds it is TVG_ERR_WORKSPACE; all
+ *     other arguments and errors as tvg_conv2d_fused.
  *   - The call allocates and frees nothing and never synchronises.  The device that owns
  *     hip_stream and the pointers must be the current device: the array's address is looked up
  *     for the current device on the first call that needs it (TVG_ERR_LAUNCH if the runtime
  *     cannot resolve it).
  *   - Every call on a GPU shares that GPU's array.  Calls on one stream are ordered and safe;
  *     calls that may overlap on one GPU (different streams, concurrent graphs) race on it and
- *     give wrong results.  Nothing in the array needs clearing between calls: every partial sum
- *     is written before it is read.
+ *     give wrong results.  Nothing in the array needs clearing between calls: every packed
+ *     weight and partial sum is written before it is read.
  */
 tvg_status tvg_conv2d_fused_static(const tvg_conv_desc *desc, const void *x, const void *w,
                                    const float *scale, const float *shift, const float *bias,
@@ -229,8 +239,10 @@ tvg_status tvg_dwconv2d_fused(const tvg_conv_desc *desc, const void *x, const vo
  *     for bf16, stride 1, c a multiple of 32 and maps whose rows are short enough
  *     (tvg_dwpw_one_kernel() says whether a problem qualifies); TVG_ERR_WORKSPACE otherwise.
  *     This form also needs w_dw 4-byte aligned (TVG_ERR_UNSUPPORTED otherwise).
- * A workspace that is too small or misaligned is TVG_ERR_WORKSPACE.  Both forms follow the
- * definition above (t rounded to dtype between the stages).
+ * A workspace that is too small or misaligned is TVG_ERR_WORKSPACE; too small is one that does
+ * not hold t (n*c*oh*ow elements, rounded up to 256 bytes) and the generic kernel's partial sums -
+ * between that and the queried size the 1x1 stage runs on the generic kernel, slower.  Both forms
+ * follow the definition above (t rounded to dtype between the stages).
  */
 tvg_status tvg_dwpw_workspace_size(const tvg_conv_desc *dw_desc, int32_t pw_k, size_t *bytes);
 /* *available = 1 if the one-kernel form exists for this problem, else 0.  Host only. */

@@ -184,8 +184,10 @@ tvg_status run_dense(const ConvProblem &p, const Dispatch &d, const tvg::ConvPoi
         return need > 0 && (!ptr.workspace || workspace_bytes < need ||
                             reinterpret_cast<uintptr_t>(ptr.workspace) % 256 != 0);
     };
-    // (a caller with less memory than the query reported gets the gather kernel, if that has enough)
-    if (d.any_shape && tvg::conv_bf16_any_pointers_ok(ptr) && !workspace_short(d.any.workspace_bytes))
+    // A caller with less memory than the query reported gets the gather kernel, if that has enough: such
+    // problems ran there, within its smaller workspace, before their weights were packed.
+    const bool any_short = d.any_shape && workspace_short(d.any.workspace_bytes);
+    if (d.any_shape && !any_short && tvg::conv_bf16_any_pointers_ok(ptr))
         return tvg::launch_conv_bf16_any(p, d.any, ptr, stream);
     if (d.tiled_shape && tvg::conv_f32_tiled_pointers_ok(ptr))
         return tvg::launch_conv_f32_tiled(p, d.tiled, ptr, stream);
@@ -195,11 +197,12 @@ tvg_status run_dense(const ConvProblem &p, const Dispatch &d, const tvg::ConvPoi
     }
     // A problem shaped for a specialised kernel reported a zero workspace; if its pointers
     // rule that kernel out, the generic kernel runs it in a single pass over the reduction.
-    // (an fp32 problem whose x is not 16-byte aligned: the generic kernel, within the workspace
-    // that the query reported for the fp32 kernel if that is all the caller has)
+    // (an fp32 problem whose x is not 16-byte aligned, a bf16 one at an odd address: the generic
+    // kernel, within the workspace that the query reported if that is all the caller has)
     const tvg::ConvPlan &plan =
         (d.patch_shape || d.stem_shape || d.pw_shape || d.tiled_shape ||
-         (d.f32_shape && workspace_short(d.generic.workspace_bytes))) ? d.generic_single : d.generic;
+         ((d.f32_shape || (d.any_shape && !any_short)) && workspace_short(d.generic.workspace_bytes)))
+            ? d.generic_single : d.generic;
     if (workspace_short(plan.workspace_bytes)) return TVG_ERR_WORKSPACE;
     return tvg::launch_conv_igemm(p, plan, ptr, stream);
 }
@@ -542,11 +545,11 @@ static tvg_status make_pw_problem(const tvg_conv_desc *dw_desc, const ConvProble
     return make_problem(&d, false, pw);
 }
 
-static size_t dwpw_workspace(const ConvProblem &dw, const ConvProblem &pw)
+// Bytes of the block's intermediate tensor t at the start of the workspace.
+static size_t dwpw_t_bytes(const ConvProblem &dw)
 {
     const size_t elem = dw.dtype == TVG_BF16 ? 2 : 4;
-    size_t bytes = ((size_t)dw.N * dw.IC * dw.OH * dw.OW * elem + 255) & ~(size_t)255;
-    return bytes + dense_workspace(dispatch_for(pw));              // packed weights, split-K scratch
+    return ((size_t)dw.N * dw.IC * dw.OH * dw.OW * elem + 255) & ~(size_t)255;
 }
 
 tvg_status tvg_dwpw_workspace_size(const tvg_conv_desc *dw_desc, int32_t pw_k, size_t *bytes)
@@ -557,7 +560,7 @@ tvg_status tvg_dwpw_workspace_size(const tvg_conv_desc *dw_desc, int32_t pw_k, s
     if (st != TVG_OK) return st;
     st = make_pw_problem(dw_desc, dw, pw_k, 0, &pw);
     if (st != TVG_OK) return st;
-    *bytes = dwpw_workspace(dw, pw);
+    *bytes = dwpw_t_bytes(dw) + dense_workspace(dispatch_for(pw));      // + packed weights, partial sums
     return TVG_OK;
 }
 
@@ -597,18 +600,22 @@ tvg_status tvg_dwpw_fused(const tvg_conv_desc *dw_desc, int32_t pw_k, uint32_t p
                                     residual, y};
         return tvg::launch_dwpw(dw, pw.OC, pw.relu, pw.stream_out, plan, ptr, stream);
     }
-    const size_t need = dwpw_workspace(dw, pw);
-    if (!workspace || workspace_bytes < need || reinterpret_cast<uintptr_t>(workspace) % 256 != 0)
+    // Less than the query reports will do where it holds t and the gather kernel's partial sums, which run
+    // the 1x1 stage then.
+    const size_t t_bytes = dwpw_t_bytes(dw);
+    const Dispatch d = dispatch_for(pw);
+    const bool whole = workspace_bytes >= t_bytes + dense_workspace(d);
+    if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 256 != 0 ||
+        (!whole && workspace_bytes < t_bytes + d.generic.workspace_bytes))
         return TVG_ERR_WORKSPACE;
-    const size_t elem = dw.dtype == TVG_BF16 ? 2 : 4;
-    const size_t t_bytes = ((size_t)dw.N * dw.IC * dw.OH * dw.OW * elem + 255) & ~(size_t)255;
     dw.stream_out = 0;                       // t is read by the next launch
     const tvg::ConvPointers dptr{x, w_dw, scale_dw, shift_dw, nullptr, nullptr, workspace, nullptr};
     st = tvg::launch_dwconv3x3(dw, dptr, stream);
     if (st != TVG_OK) return st;
     const tvg::ConvPointers pptr{workspace, w_pw, scale_pw, shift_pw, bias_pw, residual, y,
                                  reinterpret_cast<float *>(static_cast<char *>(workspace) + t_bytes)};
-    return run_dense(pw, dispatch_for(pw), pptr, workspace_bytes - t_bytes, stream);
+    return whole ? run_dense(pw, d, pptr, workspace_bytes - t_bytes, stream)
+                 : tvg::launch_conv_igemm(pw, d.generic, pptr, stream);
 }
 
 tvg_status tvg_plan_arena(const tvg_tensor_life *tensors, int32_t count, uint64_t *offsets,
