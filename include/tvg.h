@@ -301,7 +301,7 @@ tvg_status tvg_plan_arena(const tvg_tensor_life *tensors, int32_t count, uint64_
  * (alignment of the pointers aside).  kernel, mt, nt are host pointers.
  */
 typedef enum {
-    TVG_KERNEL_GENERIC = 0,        /* implicit GEMM, any shape (bf16: weights packed first) */
+    TVG_KERNEL_GENERIC = 0,        /* implicit GEMM, any shape: three kernels, see tvg_conv2d_get_knobs */
     TVG_KERNEL_3X3 = 1,            /* bf16 3x3, input patch in LDS, one stage              */
     TVG_KERNEL_3X3_PIPELINED = 2,  /* bf16 3x3, two LDS stages, software-pipelined         */
     TVG_KERNEL_STEM = 3,           /* bf16 7x7 or 3x3 stride 2, few input channels (mt 64|32) */
@@ -341,6 +341,10 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
  * not fit the LDS) makes the call fall back - to the other 3x3 kernel or to the generic kernel,
  * correct but possibly slow - so time before you fix; tvg_conv2d_get_knobs tells what a call
  * would really use now (0 where a knob does not apply to the kernel that runs).
+ * TVG_KERNEL_GENERIC stands for three kernels.  The gather kernel has the knobs mt, nt and
+ * split_k (get_knobs reports stages = 2 with them).  The bf16 kernel with packed weights and the
+ * fp32 kernel for throughput sizes have none: get_knobs reports zeros, which set_knobs takes as
+ * "leave it to the library", and fixing mt, nt or split_k selects the gather kernel.
  */
 typedef struct {
     int32_t mt, nt, stages, split_k, lds_pitch, row_loads;

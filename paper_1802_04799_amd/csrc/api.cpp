@@ -334,20 +334,10 @@ tvg_status tvg_conv2d_get_knobs(const tvg_conv_desc *desc, tvg_conv_knobs *knobs
         k.mt = d.pw.mt;
         k.nt = d.pw.nt;
         k.stages = 1;
-    } else if (d.tiled_shape) {
-        k.mt = 64;
-        k.nt = d.tiled.nt;
-        k.stages = 2;
-        k.split_k = 1;
     } else if (d.f32_shape) {
         k.stages = 1;
         k.split_k = d.f32.nw * d.f32.ksplit;     // waves of a workgroup x slices across workgroups
-    } else if (d.any_shape) {
-        k.mt = d.any.mt;
-        k.nt = d.any.nt;
-        k.stages = 2;
-        k.split_k = d.any.splits;
-    } else {
+    } else if (!d.any_shape && !d.tiled_shape) {     // (those two have no knobs: fixing one selects the gather kernel)
         k.mt = d.generic.mt;
         k.nt = d.generic.nt;
         k.stages = 2;

@@ -345,3 +345,37 @@ def test_knob_table_host_side():
     lib = tvg.load()
     assert lib.tvg_conv2d_set_knobs(None, None) == 1
     assert lib.tvg_conv2d_get_knobs(ctypes.byref(c6), None) == 1
+
+
+@pytest.mark.parametrize("kw,plan", [
+    # bf16 with packed weights: five tiles, one of them no tile of the gather kernel
+    (dict(n=6, c=83, h=45, w=37, k=139, dtype=1), (0, 64, 64)),
+    (dict(n=8, c=45, h=65, w=63, k=60, dtype=1), (0, 64, 128)),
+    (dict(n=16, c=20, h=65, w=63, k=50, dtype=1), (0, 64, 256)),
+    (dict(n=8, c=20, h=65, w=63, k=31, dtype=1), (0, 32, 128)),
+    (dict(n=20, c=20, h=65, w=63, k=31, dtype=1), (0, 32, 256)),
+    # fp32 at throughput size
+    (dict(n=32, c=128, h=28, w=28, k=128), (0, 64, 64)),
+    (dict(n=32, c=64, h=56, w=56, k=64), (0, 64, 128)),
+    # the gather kernel and the specialised ones, as before
+    (dict(n=1, c=60, h=56, w=56, k=64), (0, 64, 128)),
+    (dict(n=1, c=508, h=7, w=7, k=512), (0, 128, 128)),
+    (dict(n=64, c=128, h=28, w=28, k=128, dtype=1), (2, 64, 256)),
+    (dict(n=64, c=128, h=28, w=28, k=256, r=1, s=1, pad_h=0, pad_w=0, dtype=1), None),
+])
+def test_fixing_the_knobs_that_a_plan_reports_changes_nothing(kw, plan):
+    """tvg_conv2d_set_knobs(tvg_conv2d_get_knobs()) plans the same kernel with the same tile and workspace;
+    problems of the two kernels without knobs report zeros, the gather kernel never does."""
+    d = desc(**kw)
+    state = lambda: (tvg.tvg_conv2d_get_plan(d), tvg.tvg_conv2d_get_knobs(d), tvg.tvg_conv2d_workspace_size(d))
+    before = state()
+    assert plan is None or before[0] == plan
+    try:
+        assert tvg.tvg_conv2d_set_knobs(d, before[1]) == 0
+        assert state() == before
+        if not any(before[1]):                                          # the gather kernel, when asked for
+            assert tvg.tvg_conv2d_set_tile(d, 64, 128) == 0
+            assert tvg.tvg_conv2d_get_plan(d) == (0, 64, 128) and tvg.tvg_conv2d_get_knobs(d)[2] == 2
+    finally:
+        assert tvg.tvg_conv2d_set_knobs(d, None) == 0
+    assert state() == before
