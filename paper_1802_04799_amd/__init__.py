@@ -20,10 +20,15 @@ from .binding import (  # noqa: F401
 def __getattr__(name):
     # the operator calls (binding.NATIVE_NAMES): resolved on first use, see binding.native()
     if name in _binding.NATIVE_NAMES:
-        globals()[name] = fn = getattr(_binding, name)
+        fn = getattr(_binding, name)
+        if name in vars(_binding):           # (resolved for good)
+            globals()[name] = fn
         return fn
     raise AttributeError(f"module {__name__!r} has no attribute {name!r}")
 
 
 def __dir__():
     return sorted(set(globals()) | set(_binding.NATIVE_NAMES))
+
+
+__all__ = [_n for _n in globals() if not _n.startswith("_")] + list(_binding.NATIVE_NAMES)

@@ -7,6 +7,7 @@ no inner loop makes, go through ctypes.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional
 
@@ -134,11 +135,22 @@ def load() -> ctypes.CDLL:
     return lib
 
 
-# What lives in the extension module; looked up through __getattr__ below (and the package's), so that
-# importing the package needs neither the library nor torch.
-NATIVE_NAMES = ("tvg_conv2d_fused", "tvg_conv2d_fused_static", "tvg_conv2d_fused_dual",
-                "tvg_conv2d_fused_prepacked", "tvg_dwconv2d_fused", "tvg_dwpw_fused", "tvg_maxpool2d_3x3s2",
-                "conv2d_fused", "dwconv2d_fused", "dwpw_fused")
+# What lives in the extension module, as the kinds of its C entry points' arguments: d a descriptor, p an
+# address, i an integer that int() makes, u one that is an int already, s the stream; the last `optional`
+# may be left out.  Looked up through __getattr__ below (and the package's), so that importing the package
+# needs neither the library nor torch.
+_RAW = {
+    "tvg_conv2d_fused": ("desc x w scale shift bias residual y workspace workspace_bytes stream", "dppppppppus", 3),
+    "tvg_conv2d_fused_static": ("desc x w scale shift bias residual y stream", "dppppppps", 1),
+    "tvg_conv2d_fused_dual": ("desc k1 flags2 x w scale shift bias residual1 y1 y2 stream", "diipppppppps", 1),
+    "tvg_conv2d_fused_prepacked": ("desc x packed scale shift bias residual y workspace workspace_bytes stream",
+                                   "dppppppppis", 1),
+    "tvg_dwconv2d_fused": ("desc x w scale shift bias residual y workspace workspace_bytes stream", "dppppppppus", 3),
+    "tvg_dwpw_fused": ("dw_desc pw_k pw_flags x w_dw scale_dw shift_dw w_pw scale_pw shift_pw bias_pw residual y "
+                       "workspace workspace_bytes stream", "diipppppppppppus", 3),
+    "tvg_maxpool2d_3x3s2": ("n c h w dtype x y stream", "uuuuupps", 1),
+}
+NATIVE_NAMES = tuple(_RAW) + ("conv2d_fused", "dwconv2d_fused", "dwpw_fused")
 _native = None
 
 
@@ -150,17 +162,44 @@ def native():
         import torch  # noqa: F401  (the extension links against the libraries torch has loaded)
         from importlib import import_module
         module = import_module("._native", __package__)
-        module.setup(ConvDesc, TvgError, {"conv2d_fused": _conv2d_fused, "dwconv2d_fused": _dwconv2d_fused,
-                                          "dwpw_fused": _dwpw_fused})
+        module.setup(ConvDesc, TvgError, _CONVENIENCES)
         _native = module
     return _native
 
 
+def _raw_call(name, *args, **kwargs):
+    """A C entry point where the extension module cannot be loaded.  Without torch the addresses and the
+    stream are integers and the call goes through ctypes; with torch the module is missing, and the call
+    says so."""
+    try:
+        import torch  # noqa: F401
+    except ImportError:
+        pass
+    else:
+        return getattr(native(), name)(*args, **kwargs)
+    names, kinds, optional = _RAW[name]
+    names = names.split()
+    given = dict(zip(names, args), **{k: v for k, v in kwargs.items() if k in names[len(args):]})
+    if len(args) > len(names) or len(given) != len(args) + len(kwargs):
+        raise TypeError(f"{name}() takes {', '.join(names)}")
+    convert = {"d": ctypes.byref, "p": _addr, "s": _stream, "i": int, "u": lambda v: v}
+    values = []
+    for i, (n, kind) in enumerate(zip(names, kinds)):
+        if n not in given and i < len(names) - optional:
+            raise TypeError(f"{name}() missing a required argument: '{n}'")
+        values.append(convert[kind](given.get(n, 0 if n == "workspace_bytes" else None)))
+    return int(getattr(load(), name)(*values))
+
+
 def __getattr__(name):
-    if name in NATIVE_NAMES:
-        globals()[name] = fn = getattr(native(), name)
-        return fn
-    raise AttributeError(f"module {__name__!r} has no attribute {name!r}")
+    if name not in NATIVE_NAMES:
+        raise AttributeError(f"module {__name__!r} has no attribute {name!r}")
+    try:
+        fn = getattr(native(), name)
+    except ImportError:                # a function that raises it when it is called (or does without, see above)
+        return _CONVENIENCES.get(name) or functools.partial(_raw_call, name)
+    globals()[name] = fn
+    return fn
 
 
 def status_string(status: int) -> str:
@@ -434,3 +473,7 @@ def maxpool2d_3x3s2(x, out=None, stream=None):
     if st != TVG_OK:
         raise TvgError(st, "tvg_maxpool2d_3x3s2")
     return out
+
+
+_CONVENIENCES = {"conv2d_fused": _conv2d_fused, "dwconv2d_fused": _dwconv2d_fused, "dwpw_fused": _dwpw_fused}
+__all__ = [_n for _n in globals() if not _n.startswith("_")] + list(NATIVE_NAMES)

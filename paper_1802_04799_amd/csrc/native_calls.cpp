@@ -9,8 +9,9 @@
 // kernels), 41 us now: a call costs 3.6 us, 2.5 of them the launch itself and 1.0 the output tensor.
 //
 // Only the ordinary case is handled natively.  A convenience call whose arguments are anything
-// else (a wrong type, device, layout or dtype, objects that merely look like tensors) is handed
-// to the Python implementation in binding.py, which raises the error that fits or handles it.
+// else (a wrong type, device, layout or dtype, a subclass of Tensor, objects that merely look like
+// tensors) is handed to the Python implementation in binding.py, which raises the error that fits or
+// handles it.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -84,7 +85,7 @@ bool address(PyObject *o, void **out)
 {
     *out = nullptr;
     if (!o || o == Py_None) return true;
-    if (THPVariable_Check(o)) {
+    if (THPVariable_CheckExact(o)) {       // (a subclass is asked like any other object: its answer may differ)
         *out = THPVariable_Unpack(o).data_ptr();
         return true;
     }
@@ -119,15 +120,26 @@ bool stream_handle(PyObject *o, void **out)
     return !(PyErr_Occurred() != nullptr);
 }
 
+// An integer; values beyond the C type wrap around, as in ctypes.
 bool integer(PyObject *o, long long fallback, long long *out)
 {
     *out = fallback;
     if (!o) return true;
     PyObject *i = PyNumber_Index(o);
     if (!i) return false;
-    *out = PyLong_AsLongLong(i);
+    *out = (long long)PyLong_AsUnsignedLongLongMask(i);
     Py_DECREF(i);
     return !(*out == -1 && PyErr_Occurred());
+}
+
+// What int() makes an integer of, for the arguments that take it.
+bool as_integer(PyObject *o, long long fallback, long long *out)
+{
+    if (!o || PyLong_Check(o)) return integer(o, fallback, out);
+    PyObject *i = PyNumber_Long(o);
+    const bool ok = i && integer(i, fallback, out);
+    Py_XDECREF(i);
+    return ok;
 }
 
 bool descriptor(PyObject *o, tvg_conv_desc *out)
@@ -220,7 +232,8 @@ SPEC(tvg_maxpool2d_3x3s2, 8, 7, "n", "c", "h", "w", "dtype", "x", "y", "stream")
 typedef tvg_status (*conv_entry)(const tvg_conv_desc *, const void *, const void *, const float *, const float *,
                                  const float *, const void *, void *, void *, size_t, void *);
 
-PyObject *conv_like(conv_entry fn, const Spec &spec, PyObject *const *args, Py_ssize_t nargs, PyObject *kwnames)
+PyObject *conv_like(conv_entry fn, const Spec &spec, PyObject *const *args, Py_ssize_t nargs, PyObject *kwnames,
+                    bool prepacked = false)
 {
     return guarded([&]() -> PyObject * {
         PyObject *v[11];
@@ -230,7 +243,7 @@ PyObject *conv_like(conv_entry fn, const Spec &spec, PyObject *const *args, Py_s
         if (!parse(spec, args, nargs, kwnames, v) || !descriptor(v[0], &d)) return nullptr;
         for (int i = 0; i < 8; ++i)
             if (!address(v[1 + i], &p[i])) return nullptr;
-        if (!integer(v[9], 0, &bytes) || !stream_handle(v[10], &stream)) return nullptr;
+        if (!(prepacked ? as_integer : integer)(v[9], 0, &bytes) || !stream_handle(v[10], &stream)) return nullptr;
         const tvg_status st = without_gil([&] {
             return fn(&d, p[0], p[1], static_cast<float *>(p[2]), static_cast<float *>(p[3]),
                       static_cast<float *>(p[4]), p[5], p[6], p[7], (size_t)bytes, stream);
@@ -246,7 +259,7 @@ PyObject *py_tvg_dwconv2d_fused(ARGS)
 }
 PyObject *py_tvg_conv2d_fused_prepacked(ARGS)
 {
-    return conv_like(tvg_conv2d_fused_prepacked, tvg_conv2d_fused_prepacked_spec, args, nargs, kwnames);
+    return conv_like(tvg_conv2d_fused_prepacked, tvg_conv2d_fused_prepacked_spec, args, nargs, kwnames, true);
 }
 
 PyObject *py_tvg_conv2d_fused_static(ARGS)
@@ -275,7 +288,7 @@ PyObject *py_tvg_conv2d_fused_dual(ARGS)
         void *p[8], *stream;
         long long k1, flags2;
         if (!parse(tvg_conv2d_fused_dual_spec, args, nargs, kwnames, v) || !descriptor(v[0], &d) ||
-            !integer(v[1], 0, &k1) || !integer(v[2], 0, &flags2))
+            !as_integer(v[1], 0, &k1) || !as_integer(v[2], 0, &flags2))
             return nullptr;
         for (int i = 0; i < 8; ++i)
             if (!address(v[3 + i], &p[i])) return nullptr;
@@ -297,7 +310,7 @@ PyObject *py_tvg_dwpw_fused(ARGS)
         void *p[11], *stream;
         long long k, flags, bytes;
         if (!parse(tvg_dwpw_fused_spec, args, nargs, kwnames, v) || !descriptor(v[0], &d) ||
-            !integer(v[1], 0, &k) || !integer(v[2], 0, &flags))
+            !as_integer(v[1], 0, &k) || !as_integer(v[2], 0, &flags))
             return nullptr;
         for (int i = 0; i < 11; ++i)
             if (!address(v[3 + i], &p[i])) return nullptr;
@@ -348,7 +361,7 @@ bool plain_tensor(PyObject *o, bool optional, c10::ScalarType dtype, const at::T
 {
     *out = nullptr;
     if (absent(o)) return optional;
-    if (!THPVariable_Check(o)) return false;
+    if (!THPVariable_CheckExact(o)) return false;
     const at::Tensor &t = THPVariable_Unpack(o);
     if (!t.is_cuda() || !t.is_contiguous() || t.scalar_type() != dtype) return false;
     *out = &t;
@@ -360,7 +373,7 @@ bool plain_buffer(PyObject *o, const at::Tensor **out)
 {
     *out = nullptr;
     if (absent(o)) return true;
-    if (!THPVariable_Check(o)) return false;
+    if (!THPVariable_CheckExact(o)) return false;
     *out = &THPVariable_Unpack(o);
     return true;
 }
@@ -376,21 +389,28 @@ bool flag(PyObject *o, bool fallback, bool *out)
     return true;
 }
 
+bool extent(PyObject *o, int32_t *out)
+{
+    if (!PyLong_CheckExact(o)) return false;
+    const long v = PyLong_AsLong(o);
+    if ((v == -1 && PyErr_Occurred()) || v < INT32_MIN || v > INT32_MAX) {
+        PyErr_Clear();
+        return false;
+    }
+    *out = (int32_t)v;
+    return true;
+}
+
+// An int for both directions, or a tuple of two.
 bool extent_pair(PyObject *o, int fallback, int32_t *a, int32_t *b)
 {
     *a = *b = fallback;
     if (!o) return true;
-    if (PyLong_CheckExact(o)) {
-        const long v = PyLong_AsLong(o);
-        if ((v == -1 && PyErr_Occurred()) || v < INT32_MIN || v > INT32_MAX) {
-            PyErr_Clear();
-            return false;
-        }
-        *a = *b = (int32_t)v;
-        return true;
-    }
-    if (!PyTuple_CheckExact(o) || PyTuple_GET_SIZE(o) != 2) return false;
-    return extent_pair(PyTuple_GET_ITEM(o, 0), 0, a, a) && extent_pair(PyTuple_GET_ITEM(o, 1), 0, b, b);
+    if (PyTuple_CheckExact(o) && PyTuple_GET_SIZE(o) == 2)
+        return extent(PyTuple_GET_ITEM(o, 0), a) && extent(PyTuple_GET_ITEM(o, 1), b);
+    if (!extent(o, a)) return false;
+    *b = *a;
+    return true;
 }
 
 bool known_dtype(const at::Tensor &x, int32_t *code)
@@ -487,7 +507,7 @@ PyObject *convolution(bool depthwise, const Spec &spec, PyObject *const *args, P
         bool relu, stream_out;
         tvg_conv_desc d;
         const char *where = depthwise ? "dwconv2d_fused" : "conv2d_fused";
-        if (!THPVariable_Check(v[0])) return fall_back(where, args, nargs, kwnames);
+        if (!THPVariable_CheckExact(v[0])) return fall_back(where, args, nargs, kwnames);
         const c10::ScalarType dtype = THPVariable_Unpack(v[0]).scalar_type();
         if (!plain_tensor(v[0], false, dtype, &x) || !plain_tensor(v[1], false, dtype, &w) ||
             !plain_tensor(v[2], false, at::kFloat, &scale) || !plain_tensor(v[3], false, at::kFloat, &shift) ||
@@ -542,7 +562,7 @@ PyObject *py_dwpw_fused(ARGS)
         const at::Tensor *x, *wd, *scd, *shd, *wp, *scp, *shp, *bias, *residual, *out, *ws;
         bool relu_dw, relu_pw, stream_out, one_kernel;
         tvg_conv_desc d;
-        if (!THPVariable_Check(v[0])) return fall_back("dwpw_fused", args, nargs, kwnames);
+        if (!THPVariable_CheckExact(v[0])) return fall_back("dwpw_fused", args, nargs, kwnames);
         const c10::ScalarType dtype = THPVariable_Unpack(v[0]).scalar_type();
         if (!plain_tensor(v[0], false, dtype, &x) || !plain_tensor(v[1], false, dtype, &wd) ||
             !plain_tensor(v[2], false, at::kFloat, &scd) || !plain_tensor(v[3], false, at::kFloat, &shd) ||

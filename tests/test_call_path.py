@@ -48,3 +48,81 @@ def test_a_tensor_without_storage_is_a_python_exception(call, transform):
     for the Python implementation of these calls, and the process lives on."""
     got = outcome(f"f = lambda a: {call}\noutcome(lambda: {transform})")
     assert len(got) == 1 and got[0].startswith("RuntimeError Cannot access data pointer"), got
+
+
+def test_star_import_holds_the_operator_calls():
+    names = ["conv2d_fused", "dwconv2d_fused", "dwpw_fused", "maxpool2d_3x3s2", "tvg_conv2d_fused", "tvg_dwconv2d_fused",
+             "tvg_conv2d_fused_static", "tvg_conv2d_fused_dual", "tvg_conv2d_fused_prepacked", "tvg_dwpw_fused",
+             "tvg_maxpool2d_3x3s2", "ConvDesc", "TvgError", "TVG_BF16", "tvg_conv2d_get_plan", "binding"]
+    for module in ("paper_1802_04799_amd", "paper_1802_04799_amd.binding"):
+        scope = {}
+        exec(f"from {module} import *", scope)
+        assert [n for n in names if n not in scope and (n != "binding" or "." not in module)] == []
+
+
+def _plain(code):
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
+    return r.stdout.split()
+
+
+def test_raw_calls_with_integer_addresses_need_no_torch():
+    """NULL addresses and descriptors that fail: the library's answers, through ctypes."""
+    assert _plain("""
+import sys; sys.modules["torch"] = None
+import paper_1802_04799_amd as tvg
+d = tvg.ConvDesc(1, 8, 10, 10, 8, 3, 3, 1, 1, 1, 1, 0, 0)
+n = tvg.ConvDesc(0, 8, 10, 10, 8, 3, 3, 1, 1, 1, 1, 0, 0)
+print(tvg.tvg_conv2d_fused(d, 4096, None, 4096, 4096, None, None, 4096, None, 0, 0),
+      tvg.tvg_conv2d_fused(n, 4096, 4096, 4096, 4096, None, None, y=4096, stream=0),
+      tvg.tvg_conv2d_fused_dual(d, 4.0, 8, 0, 0, 0, 0, None, None, 0, 0, 0),
+      tvg.tvg_conv2d_fused_prepacked(d, 0, 0, 0, 0, None, None, 0, 0, 0, 0),
+      tvg.tvg_dwpw_fused(d, 8.0, 0, *[None] * 10, stream=0),
+      tvg.tvg_maxpool2d_3x3s2(1, 1, 0, 4, 0, 4096, 4096, 0))
+for wrong in (lambda: tvg.tvg_maxpool2d_3x3s2(1, 1, 4, 4, 0, 0), lambda: tvg.tvg_maxpool2d_3x3s2(1, 1, 4, 4, 0, 0, 0, 0, nope=1),
+              lambda: tvg.tvg_maxpool2d_3x3s2(1, 1, 4, 4, 0, 0, 0, 0, n=1)):
+    try:
+        wrong()
+    except TypeError:
+        print("TypeError")
+""") == ["1", "2", "3", "3", "1", "2"] + ["TypeError"] * 3
+
+
+def test_names_resolve_and_calls_fail_loudly_without_the_library():
+    assert _plain("""
+import paper_1802_04799_amd.binding as b
+b._LIB_PATH = "/nowhere/libtvg.so"
+import paper_1802_04799_amd as tvg
+from paper_1802_04799_amd import *
+for call in (lambda: conv2d_fused(*[__import__("torch").zeros(1, 1, 1, 1)] * 4), lambda: tvg.tvg_conv2d_fused(*[None] * 8)):
+    try:
+        call()
+    except (ImportError, ValueError) as e:
+        print(type(e).__name__)
+""") == ["ValueError", "ImportError"]
+
+
+def test_integers_are_taken_as_before():
+    import paper_1802_04799_amd as tvg
+    d = tvg.ConvDesc(1, 8, 10, 10, 8, 3, 3, 1, 1, 1, 1, 0, 0)
+    assert tvg.tvg_dwpw_fused(d, 8.0, 0.0, *[None] * 10, stream=0) == 1             # int() of what is given
+    assert tvg.tvg_conv2d_fused_dual(d, "4", 8.0, 0, 0, 0, 0, None, None, 0, 0, 0) == 3
+    assert tvg.tvg_conv2d_fused(d, *[None] * 7, None, 2**64 - 1, 0) == 1            # size_t
+    for call in (lambda: tvg.tvg_maxpool2d_3x3s2(1.0, 1, 4, 4, 0, None, None, 0),
+                 lambda: tvg.tvg_conv2d_fused(d, *[None] * 7, None, 1.5, 0)):
+        with pytest.raises(TypeError):
+            call()
+
+
+def test_a_tensor_subclass_is_asked_for_its_address():
+    import torch
+    import paper_1802_04799_amd as tvg
+
+    class Guarded(torch.Tensor):
+        def data_ptr(self):
+            raise LookupError("no address for you")
+
+    t = torch.zeros(1, 8, 5, 5).as_subclass(Guarded)
+    d = tvg.ConvDesc(1, 8, 5, 5, 8, 3, 3, 1, 1, 1, 1, 0, 0)
+    with pytest.raises(LookupError):
+        tvg.tvg_conv2d_fused(d, t, None, None, None, None, None, None, None, 0, 0)

@@ -109,3 +109,26 @@ def test_a_stream_of_the_callers_choice_inside_a_captured_graph(tvg):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(y, want) and torch.equal(call(None, None), want)
+
+
+def test_unusual_arguments_get_the_answers_of_the_python_implementation(tvg):
+    """A tensor without storage (inside vmap and vjp), a nested stride, a tensor subclass."""
+    import torch
+    x, w, s = torch.rand(2, 1, 8, 5, 5, device="cuda"), torch.rand(8, 8, 3, 3, device="cuda"), torch.ones(8, device="cuda")
+    want = tvg.conv2d_fused(x[0], w, s, s, pad=1)
+    o = torch.empty(1, 8, 5, 8, device="cuda")
+    for f in (lambda a: tvg.conv2d_fused(a, w, s, s, pad=1, out=o), lambda a: tvg.conv2d_fused(x[0], w, a[0, 0, 0], s, pad=1)):
+        for transform in (lambda: torch.vmap(f)(x[..., :1].expand(2, 1, 8, 5, 8).contiguous()),
+                          lambda: torch.func.vjp(f, x[0][..., :1].expand(1, 8, 5, 8).contiguous())):
+            with pytest.raises(RuntimeError, match="Cannot access data pointer"):
+                transform()
+    for stride in (((1, 2), 1), (1, (1, 1)), [1], (1, 1, 1), "1", 1.0):
+        with pytest.raises((TypeError, ValueError)):
+            tvg.conv2d_fused(x[0], w, s, s, pad=1, stride=stride)
+    for stride in (1, (1, 1), [1, 1]):
+        assert torch.equal(tvg.conv2d_fused(x[0], w, s, s, pad=1, stride=stride), want)
+
+    class Named(torch.Tensor):
+        pass
+
+    assert torch.equal(tvg.conv2d_fused(x[0].as_subclass(Named), torch.nn.Parameter(w), s, s, pad=1), want)
