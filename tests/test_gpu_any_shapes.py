@@ -65,3 +65,20 @@ def test_an_infinity_in_x_reaches_its_outputs_and_no_others(tvg, cfg, relu):
     odd = torch.isinf(want)
     assert torch.equal(got[odd], want[odd]) and bool(torch.isfinite(got[~odd]).all())
     check(got[~odd].numpy(), want[~odd].numpy(), "bf16", cfg)
+
+
+# several chunks of channels; pixel tiles within an image, tiles that cross images, a split reduction
+SEVERAL_CHUNKS = [(12, 100, 45, 37, 40, 5, 1, 2), (24, 300, 9, 9, 70, 5, 1, 2), (9, 300, 13, 13, 31, 5, 1, 2),
+                  (4, 509, 14, 14, 100, 1, 1, 0)]
+
+
+@pytest.mark.parametrize("cfg", SEVERAL_CHUNKS, ids=lambda c: "x".join(map(str, c)))
+def test_equal_images_of_a_batch_get_equal_results(tvg, cfg):
+    """Bit for bit, wherever in the batch (and so in which tile) an image lies."""
+    import torch
+    n, ic, h, w, oc, r, stride, pad = cfg
+    inp = ti.make_inputs(ti.ConvShape("same", n, ic, h, w, oc, r, r, stride, pad), 6700 + sum(cfg), "bf16")
+    inp["x"][:] = inp["x"][:1]
+    d = dev_inputs(inp, "bf16")
+    y = tvg.conv2d_fused(d["x"], d["w"], d["scale"], d["shift"], stride=stride, pad=pad)
+    assert torch.equal(y, y[:1].expand_as(y))
