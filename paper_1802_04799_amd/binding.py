@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import functools
+import math
 import os
 from typing import Optional
 
@@ -382,6 +383,37 @@ def make_desc(x, w, stride, pad, relu, depthwise=False, stream_out=False) -> Con
     return ConvDesc(n, c, h, wd, k, r, s, sh, sw, ph, pw, _dtype_code(x), flags)
 
 
+def _output(out, shape, x, stream):
+    """The tensor that receives the result: the caller's (any type and shape, if it is a dense device tensor
+    that holds the bytes), or a new one.  `shape` is called for it, on a descriptor not yet validated."""
+    import torch
+    if out is None:
+        return _empty(shape(), x.dtype, x.device, stream)
+    if isinstance(out, torch.Tensor):
+        if not out.is_cuda:
+            raise ValueError("out must be a device tensor")
+        if not out.is_contiguous():
+            raise ValueError("out must be contiguous")
+        try:
+            extents = shape()
+        except ZeroDivisionError:          # (a stride that the library refuses)
+            return out
+        if min(extents) > 0 and out.numel() * out.element_size() < math.prod(extents) * x.element_size():
+            raise ValueError(f"out is too small for {extents}")
+    return out
+
+
+def _workspace(workspace, need, x, stream):
+    """The caller's workspace if it has `need` bytes, else a new one."""
+    import torch
+    if workspace is not None and workspace.numel() * workspace.element_size() >= need:
+        if not isinstance(workspace, torch.Tensor) or (workspace.is_cuda and workspace.is_contiguous()):
+            return workspace
+        if not workspace.is_cuda:
+            raise ValueError("workspace must be a device tensor")
+    return _empty((need,), torch.uint8, x.device, stream, result=False)
+
+
 def _empty(shape, dtype, device, stream, result=True):
     """torch.empty for a launch on `stream`: memory from that stream's pool, since torch's allocator
     hands blocks out again in the order of the stream they were allocated on; a `result`, which the caller
@@ -404,16 +436,14 @@ def _empty(shape, dtype, device, stream, result=True):
 def _conv2d_fused(x, w, scale, shift, bias=None, residual=None, *, stride=1, pad=0, relu=False,
                  out=None, workspace=None, stream=None, stream_out=False):
     """y = tail(conv2d(x, w)); allocates y (and the workspace when needed) with torch."""
-    import torch
     _check(x, w, scale, shift, bias, residual)
     desc = make_desc(x, w, stride, pad, relu, stream_out=stream_out)
     if w.shape[1] != x.shape[1]:
         raise ValueError("weight input channels do not match x")
     need = tvg_conv2d_workspace_size(desc)
-    if out is None:
-        out = _empty((desc.n, desc.k, desc.oh, desc.ow), x.dtype, x.device, stream)
-    if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
-        workspace = _empty((need,), torch.uint8, x.device, stream, result=False)
+    out = _output(out, lambda: (desc.n, desc.k, desc.oh, desc.ow), x, stream)
+    if need:
+        workspace = _workspace(workspace, need, x, stream)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     st = native().tvg_conv2d_fused(desc, x, w, scale, shift, bias, residual, out, workspace, ws_bytes, stream)
     if st != TVG_OK:
@@ -425,8 +455,7 @@ def _dwconv2d_fused(x, w, scale, shift, bias=None, residual=None, *, stride=1, p
                    out=None, stream=None, stream_out=False):
     _check(x, w, scale, shift, bias, residual)
     desc = make_desc(x, w, stride, pad, relu, depthwise=True, stream_out=stream_out)
-    if out is None:
-        out = _empty((desc.n, desc.k, desc.oh, desc.ow), x.dtype, x.device, stream)
+    out = _output(out, lambda: (desc.n, desc.k, desc.oh, desc.ow), x, stream)
     st = native().tvg_dwconv2d_fused(desc, x, w, scale, shift, bias, residual, out, None, 0, stream)
     if st != TVG_OK:
         raise TvgError(st, "tvg_dwconv2d_fused")
@@ -439,7 +468,6 @@ def _dwpw_fused(x, w_dw, scale_dw, shift_dw, w_pw, scale_pw, shift_pw, bias_pw=N
     """MobileNet block (depthwise 3x3 + tail, 1x1 conv + tail) through tvg_dwpw_fused;
     allocates y with torch, and the workspace of the two-kernel form unless ``one_kernel``
     asks for the form that needs none."""
-    import torch
     _check(x, w_pw, scale_pw, shift_pw, bias_pw, residual)
     _check(x, w_dw, scale_dw, shift_dw, None, None)
     desc = make_desc(x, w_dw, stride, 1, relu_dw, depthwise=True)
@@ -447,14 +475,8 @@ def _dwpw_fused(x, w_dw, scale_dw, shift_dw, w_pw, scale_pw, shift_pw, bias_pw=N
     if w_pw.shape[1] != x.shape[1] or tuple(w_pw.shape[2:]) != (1, 1):
         raise ValueError("w_pw must be [k][c][1][1]")
     flags = (TVG_RELU if relu_pw else 0) | (TVG_STREAM_OUT if stream_out else 0)
-    if out is None:
-        out = _empty((desc.n, k, desc.oh, desc.ow), x.dtype, x.device, stream)
-    if one_kernel:
-        workspace = None
-    else:
-        need = tvg_dwpw_workspace_size(desc, k)
-        if workspace is None or workspace.numel() * workspace.element_size() < need:
-            workspace = _empty((need,), torch.uint8, x.device, stream, result=False)
+    out = _output(out, lambda: (desc.n, k, desc.oh, desc.ow), x, stream)
+    workspace = None if one_kernel else _workspace(workspace, tvg_dwpw_workspace_size(desc, k), x, stream)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     st = native().tvg_dwpw_fused(desc, k, flags, x, w_dw, scale_dw, shift_dw, w_pw, scale_pw, shift_pw,
                         bias_pw, residual, out, workspace, ws_bytes, stream)
@@ -467,8 +489,7 @@ def maxpool2d_3x3s2(x, out=None, stream=None):
     if not x.is_cuda or not x.is_contiguous():
         raise ValueError("x must be a contiguous device tensor")
     n, c, h, w = x.shape
-    if out is None:
-        out = _empty((n, c, (h - 1) // 2 + 1, (w - 1) // 2 + 1), x.dtype, x.device, stream)
+    out = _output(out, lambda: (n, c, (h - 1) // 2 + 1, (w - 1) // 2 + 1), x, stream)
     st = native().tvg_maxpool2d_3x3s2(n, c, h, w, _dtype_code(x), x, out, stream)
     if st != TVG_OK:
         raise TvgError(st, "tvg_maxpool2d_3x3s2")

@@ -368,7 +368,7 @@ bool plain_tensor(PyObject *o, bool optional, c10::ScalarType dtype, const at::T
     return true;
 }
 
-// None or a dense device tensor (an output or a workspace, of any type and shape).
+// None or a tensor (an output or a workspace: of any type and shape, the bytes are what counts).
 bool plain_buffer(PyObject *o, const at::Tensor **out)
 {
     *out = nullptr;
@@ -377,6 +377,10 @@ bool plain_buffer(PyObject *o, const at::Tensor **out)
     *out = &THPVariable_Unpack(o);
     return true;
 }
+
+size_t bytes_of(const at::Tensor *t) { return t ? (size_t)t->numel() * t->element_size() : 0; }
+
+bool dense_on_device(const at::Tensor &t) { return t.is_cuda() && t.is_contiguous(); }
 
 bool flag(PyObject *o, bool fallback, bool *out)
 {
@@ -481,7 +485,16 @@ at::Tensor result(const at::Tensor *given, const Allocator &memory, const at::Te
                          x.scalar_type());
 }
 
-size_t bytes_of(const at::Tensor *t) { return t ? (size_t)t->numel() * t->element_size() : 0; }
+// Whether an output of the caller's holds the result.
+bool holds_result(const at::Tensor *out, const at::Tensor &x, const tvg_conv_desc &d, int64_t k)
+{
+    if (!out) return true;
+    const int64_t oh = out_extent(d.h, d.pad_h, d.r, d.stride_h), ow = out_extent(d.w, d.pad_w, d.s, d.stride_w);
+    return dense_on_device(*out) && (oh < 1 || ow < 1 || bytes_of(out) >= (size_t)(d.n * k * oh * ow) * x.element_size());
+}
+
+// Whether a workspace of the caller's that is large enough to be used can be used.
+bool usable(const at::Tensor *ws, size_t need) { return bytes_of(ws) < need || !need || dense_on_device(*ws); }
 
 // The workspace to pass: the caller's if it is large enough, else a new one.
 at::Tensor enough_workspace(const at::Tensor *given, size_t need, const Allocator &memory)
@@ -516,7 +529,7 @@ PyObject *convolution(bool depthwise, const Spec &spec, PyObject *const *args, P
             !flag(v[12], false, &stream_out) ||
             !describe(*x, *w, v[6], v[7], depthwise ? 1 : 0,
                       (relu ? (uint32_t)TVG_RELU : 0u) | (stream_out ? (uint32_t)TVG_STREAM_OUT : 0u), &d) ||
-            (!depthwise && w->size(1) != x->size(1)))
+            (!depthwise && w->size(1) != x->size(1)) || !holds_result(out, *x, d, d.k))
             return fall_back(where, args, nargs, kwnames);
         void *stream;
         if (!stream_handle(v[11], &stream)) return nullptr;
@@ -524,6 +537,7 @@ PyObject *convolution(bool depthwise, const Spec &spec, PyObject *const *args, P
         if (!depthwise) {
             const tvg_status st = tvg_conv2d_workspace_size(&d, &need);
             if (st != TVG_OK) return raise_status(st, "tvg_conv2d_workspace_size");
+            if (!usable(ws, need)) return fall_back(where, args, nargs, kwnames);
         } else {
             const tvg_status st = tvg_dwconv2d_workspace_size(&d, &need);      // validates the descriptor
             if (st != TVG_OK) return fall_back(where, args, nargs, kwnames);
@@ -576,7 +590,9 @@ PyObject *py_dwpw_fused(ARGS)
             return fall_back("dwpw_fused", args, nargs, kwnames);
         const int32_t k = (int32_t)wp->size(0);
         size_t need = 0;
-        if (tvg_dwpw_workspace_size(&d, k, &need) != TVG_OK) return fall_back("dwpw_fused", args, nargs, kwnames);
+        if (tvg_dwpw_workspace_size(&d, k, &need) != TVG_OK || !holds_result(out, *x, d, k) ||
+            (!one_kernel && !usable(ws, need)))
+            return fall_back("dwpw_fused", args, nargs, kwnames);
         void *stream;
         if (!stream_handle(v[14], &stream)) return nullptr;
         const Allocator memory(*x, v[14], stream);

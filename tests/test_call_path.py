@@ -126,3 +126,32 @@ def test_a_tensor_subclass_is_asked_for_its_address():
     d = tvg.ConvDesc(1, 8, 5, 5, 8, 3, 3, 1, 1, 1, 1, 0, 0)
     with pytest.raises(LookupError):
         tvg.tvg_conv2d_fused(d, t, None, None, None, None, None, None, None, 0, 0)
+
+
+@pytest.mark.parametrize("call,k", [("tvg.conv2d_fused(x[0], w, s, s, pad=1, out=OUT, stream=0)", 8),
+                                    ("tvg.dwconv2d_fused(x[0], wd, s, s, pad=1, out=OUT, stream=0)", 8),
+                                    ("tvg.dwpw_fused(x[0], wd, s, s, wp, s, s, out=OUT, workspace=ws, stream=0)", 8),
+                                    ("tvg.maxpool2d_3x3s2(x[0], out=OUT, stream=0)", 8)])
+def test_an_output_the_kernel_must_not_write_is_refused(call, k):
+    """On the host, short, strided or overlapping: an exception before any launch; a larger one, or one of
+    another type that holds the bytes, is taken (and gets as far as the NULL address)."""
+    outs = {"torch.empty(1, 8, 5, 5)": "must be a device tensor", "dev(1, 8, 2, 4)": "too small",
+            "dev(1, 8, 5, 10)[..., ::2]": "must be contiguous", "dev(1, 8, 5, 1).expand(1, 8, 5, 5)": "must be contiguous",
+            "dev(800, dtype=torch.uint8)": "NULL", "dev(4, 8, 5, 5)": "NULL"}
+    got = outcome("\n".join(f"outcome(lambda: {call.replace('OUT', o)})" for o in outs))
+    assert len(got) == len(outs)
+    for (o, want), line in zip(outs.items(), got):
+        assert want in line and line.startswith("TvgError" if want == "NULL" else "ValueError"), (o, line)
+
+
+def test_a_workspace_on_the_host_is_refused():
+    got = outcome("""
+b = lambda *s: dev(*s, dtype=torch.bfloat16)
+xr, wr, o = b(1, 83, 45, 37), b(139, 83, 3, 3), b(1, 139, 45, 37)
+sr = dev(139)
+for ws in (torch.empty(1 << 24, dtype=torch.uint8), dev(1 << 24, dtype=torch.uint8)):
+    outcome(lambda: tvg.conv2d_fused(xr, wr, sr, sr, pad=1, out=o, workspace=ws, stream=0))
+outcome(lambda: tvg.conv2d_fused(x[0], w, s, s, pad=1, out=dev(1, 8, 5, 5), workspace=torch.empty(9), stream=0))
+outcome(lambda: tvg.dwpw_fused(x[0], wd, s, s, wp, s, s, out=dev(1, 8, 5, 5), workspace=torch.empty(1 << 16), stream=0))
+""")
+    assert [line.split()[0] for line in got] == ["ValueError", "TvgError", "TvgError", "ValueError"], got

@@ -132,3 +132,24 @@ def test_unusual_arguments_get_the_answers_of_the_python_implementation(tvg):
         pass
 
     assert torch.equal(tvg.conv2d_fused(x[0].as_subclass(Named), torch.nn.Parameter(w), s, s, pad=1), want)
+
+
+def test_outputs_and_workspaces_of_the_callers_own(tvg):
+    """Natively: an output on the host, short or strided is refused, a larger one takes the result at its
+    start; a strided workspace is not written."""
+    import torch
+    x, w, s = torch.rand(1, 83, 9, 9, device="cuda").bfloat16(), torch.rand(40, 83, 3, 3, device="cuda").bfloat16(), torch.ones(40, device="cuda")
+    want = tvg.conv2d_fused(x, w, s, s, pad=1)
+    b = lambda *shape: torch.full(shape, 7.0, dtype=torch.bfloat16, device="cuda")
+    for out in (torch.empty(1, 40, 9, 9, dtype=torch.bfloat16), b(1, 40, 9, 8), b(1, 40, 9, 18)[..., ::2], b(1, 40, 9, 1).expand(1, 40, 9, 9)):
+        with pytest.raises(ValueError):
+            tvg.conv2d_fused(x, w, s, s, pad=1, out=out)
+    out = b(2, 40, 9, 9)
+    assert tvg.conv2d_fused(x, w, s, s, pad=1, out=out) is out
+    assert torch.equal(out[:1], want) and bool((out[1] == 7.0).all())
+    ws = torch.full((2, 1 << 20), 9, dtype=torch.uint8, device="cuda").t()
+    assert torch.equal(tvg.conv2d_fused(x, w, s, s, pad=1, workspace=ws), want) and bool((ws == 9).all())
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    assert torch.equal(tvg.conv2d_fused(x, w, s, s, pad=1, workspace=ws), want)
+    with pytest.raises(ValueError):
+        tvg.conv2d_fused(x, w, s, s, pad=1, workspace=ws.cpu())
