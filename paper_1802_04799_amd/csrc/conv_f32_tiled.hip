@@ -14,14 +14,15 @@
 //     and the LDS pitch is odd, so that the 32 lanes of an operand read 32 banks.
 //   - Chunks are double-buffered: registers receive the next one while the matrix cores work, one
 //     barrier per chunk.
-//   - The MFMAs of a chunk start from zero and their sums are added to the totals in plain adds, so that
-//     no chain is longer than a chunk (32 to 196 products): the error is below that of one long chain.
+//   - MFMAs start from zero again after a filter row (5x5: 20 products, 7x7: 28), a chunk (3x3: 72) or a part of
+//     one (1x1: 8 to 32), and their sums are added to the totals in plain adds.
 //
 // What bounds it: per chunk, the wait for LDS operands at each filter row and the barrier (a lone
 // workgroup per CU takes 1.95 us for a 3x3 chunk whose MFMAs take 1), and rounds of tiles that do not fill
 // the CUs.  32 x 128 -> 128, 3x3 at 28x28: 127 us by the 32 x 32 tiles of the launch-bound kernel, 99 here
 // (75 TFLOP/s); 32 x 64 -> 64 at 56x56: 146 by the gather kernel, 101; 1x1, 32 x 512 -> 512 at 14x14: 128, 59.
-// Error against 64 bits over 60 shapes: 0.8 times that of the kernels before (geometric mean).
+// Error against 64 bits over the 54 smaller of 85 such shapes, relative to the kernels that ran them before:
+// 0.83 in the geometric mean, 0.36 to 1.00.  (With whole chunks as chains: 1.00, 0.36 to 1.59.)
 #include <algorithm>
 
 #include "tvg_device.h"
@@ -60,7 +61,8 @@ __device__ __forceinline__ float load_f32(__amdgpu_buffer_rsrc_t r, uint32_t off
     return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
 }
 
-template <int R, int CIC, int NJ, int PT>
+// CHAINS: how a 1x1 chunk's 16 MFMAs are summed - one chain, 2: two of eight, 4: four of four, added in pairs
+template <int R, int CIC, int NJ, int PT, int CHAINS>
 __global__ __launch_bounds__(256, 2) void conv_f32_tiled_kernel(const TiledArgs a)
 {
     constexpr int RS = R * R, CPH = CIC / 2, NT = 64 * NJ;
@@ -172,30 +174,71 @@ __global__ __launch_bounds__(256, 2) void conv_f32_tiled_kernel(const TiledArgs 
     for (int c = 0; c < a.nchunks; ++c) {
         const float *buf = bufs + (c & 1) * a.buf_floats;
         if (c + 1 < a.nchunks) load_chunk(c + 1);
-        float16v part[NJ];
+        // pixel operand first: the accumulator tile is D[pixel][channel]
+        if constexpr (CHAINS > 1) {
+            // Eight channels (per half-wave) of one pixel group at a time; their sums are added while the next
+            // ones are under way.
+            float16v pa, pb;
+            auto add = [&](int j) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
+                for (int v = 0; v < 16; ++v) acc[0][j][v] += CHAINS == 4 ? pa[v] + pb[v] : pb[v];
+                // (nothing is emitted here: it keeps the compiler from putting off all sums of the chunk to its
+                // end, which holds 16 registers each and costs a workgroup per CU: 13.9 us against 15.5 at
+                // 8 x 64 -> 128, 56x56)
+                asm volatile("" : "+v"(acc[0][j]));
+            };
 #pragma unroll
-            for (int v = 0; v < 16; ++v) part[j][v] = 0.0f;
+            for (int t = 0; t < CPH / 8 * NJ; ++t) {
+                const int j = t % NJ, ch = t / NJ * 8;
+                float16v qa, qb;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) qa[v] = qb[v] = 0.0f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    qa = __builtin_amdgcn_mfma_f32_32x32x2f32(buf[bbase[j] + (ch + e) * a.plane], buf[abase + ch + e], qa, 0, 0, 0);
+                if (CHAINS == 4 && t > 0) add((t - 1) % NJ);
+                if (CHAINS == 2) qb = qa;
+#pragma unroll
+                for (int e = 4; e < 8; ++e)
+                    qb = __builtin_amdgcn_mfma_f32_32x32x2f32(buf[bbase[j] + (ch + e) * a.plane], buf[abase + ch + e], qb, 0, 0, 0);
+                if (CHAINS == 2 && t > 0) add((t - 1) % NJ);       // (in mid-chain: 65.7 us against 59.9 at 32 x 512 -> 512, 14x14)
+                pa = qa;
+                pb = qb;
+            }
+            add(NJ - 1);
+        } else {
+            float16v part[NJ];
+            auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) part[j][v] = 0.0f;
+            };
+            auto add = [&]() __attribute__((always_inline)) {
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[0][j][v] += part[j][v];
+            };
+            if constexpr (R <= 3) clear();
 #pragma unroll 1                        // (3x3 rows unrolled: 104 us against 99 at 32 x 128 -> 128, 28x28)
-        for (int r = 0; r < R; ++r) {
+            for (int r = 0; r < R; ++r) {
+                if constexpr (R > 3) clear();
 #pragma unroll
-            for (int ch = 0; ch < CPH; ++ch)
+                for (int ch = 0; ch < CPH; ++ch)
 #pragma unroll
-                for (int s = 0; s < R; ++s) {
-                    const float wv = buf[abase + r * R + ch * RS + s];
+                    for (int s = 0; s < R; ++s) {
+                        const float wv = buf[abase + r * R + ch * RS + s];
 #pragma unroll
-                    for (int j = 0; j < NJ; ++j) {
-                        const float xv = buf[bbase[j] + r * a.pitch + ch * a.plane + s];
-                        // pixel operand first: the accumulator tile is D[pixel][channel]
-                        part[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xv, wv, part[j], 0, 0, 0);
+                        for (int j = 0; j < NJ; ++j) {
+                            const float xv = buf[bbase[j] + r * a.pitch + ch * a.plane + s];
+                            part[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xv, wv, part[j], 0, 0, 0);
+                        }
                     }
-                }
+                if constexpr (R > 3) add();
+            }
+            if constexpr (R <= 3) add();
         }
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[0][j][v] += part[j][v];
         if (c + 1 < a.nchunks) store_chunk((c + 1) & 1);
         __syncthreads();
     }
@@ -207,20 +250,20 @@ __global__ __launch_bounds__(256, 2) void conv_f32_tiled_kernel(const TiledArgs 
     store_acc_tiles<float, 1, NJ>(acc, stage, lane, m0 + wm * 32, img + p0 + wn * 32 * NJ, tail, a.vmode, ss, wm * 32);
 }
 
-template <int R, int CIC, int NJ, int PT>
+template <int R, int CIC, int NJ, int PT, int CHAINS>
 tvg_status launch_one(const TiledArgs &a, long tiles, size_t lds, hipStream_t stream)
 {
-    static const bool ok = hipFuncSetAttribute(reinterpret_cast<const void *>(conv_f32_tiled_kernel<R, CIC, NJ, PT>),
+    static const bool ok = hipFuncSetAttribute(reinterpret_cast<const void *>(conv_f32_tiled_kernel<R, CIC, NJ, PT, CHAINS>),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds) == hipSuccess;
     if (!ok) return TVG_ERR_LAUNCH;
-    hipLaunchKernelGGL((conv_f32_tiled_kernel<R, CIC, NJ, PT>), dim3((unsigned)tiles), dim3(256), lds, stream, a);
+    hipLaunchKernelGGL((conv_f32_tiled_kernel<R, CIC, NJ, PT, CHAINS>), dim3((unsigned)tiles), dim3(256), lds, stream, a);
     return hipGetLastError() == hipSuccess ? TVG_OK : TVG_ERR_LAUNCH;
 }
 
-template <int R, int CIC>
+template <int R, int CIC, int CHAINS = 1>
 tvg_status launch_filter(const TiledArgs &a, const F32TiledPlan &t, hipStream_t stream)
 {
-#define TVG_TILED_ONE(NJ_, PT_) launch_one<R, CIC, NJ_, PT_>(a, t.tiles, t.lds_bytes, stream)
+#define TVG_TILED_ONE(NJ_, PT_) launch_one<R, CIC, NJ_, PT_, CHAINS>(a, t.tiles, t.lds_bytes, stream)
     if (t.nt == 128) return t.pt == 8 ? TVG_TILED_ONE(2, 8) : t.pt == 16 ? TVG_TILED_ONE(2, 16) : TVG_TILED_ONE(2, 32);
     return t.pt == 8 ? TVG_TILED_ONE(1, 8) : t.pt == 16 ? TVG_TILED_ONE(1, 16) : TVG_TILED_ONE(1, 32);
 #undef TVG_TILED_ONE
@@ -325,7 +368,14 @@ tvg_status launch_conv_f32_tiled(const ConvProblem &p, const F32TiledPlan &t, co
     a.buf_floats = t.buf_floats;
     a.x_bytes = (uint32_t)((size_t)p.N * p.IC * a.HW * 4);
     a.w_bytes = (uint32_t)((size_t)p.OC * p.K * 4);
-    if (p.R == 1) return launch_filter<1, 32>(a, t, stream);
+    // 1x1: the fewest chains whose error is not above that of the kernels that ran these problems before (the
+    // launch-bound kernel's waves split the reduction).  Relative to it, by channels, with one / two / four chains:
+    // 32: 1.52 1.17 0.98, 64: 1.38 1.09 0.94, 128: 1.19 1.00 0.89, 256: 1.00 0.91 0.84.  Two chains cost 0 to 2 % of
+    // the time, four 1 to 3 % at few channels and 4 to 9 % at many; under a stride four are as fast as one.
+    if (p.R == 1) {
+        if (t.nchunks <= 2 || p.sh > 1) return launch_filter<1, 32, 4>(a, t, stream);
+        return t.nchunks < 8 ? launch_filter<1, 32, 2>(a, t, stream) : launch_filter<1, 32>(a, t, stream);
+    }
     if (p.R == 3) return launch_filter<3, 8>(a, t, stream);
     if (p.R == 5) return launch_filter<5, 4>(a, t, stream);
     return launch_filter<7, 4>(a, t, stream);

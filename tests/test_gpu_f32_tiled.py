@@ -36,3 +36,27 @@ def test_f32_tiled(tvg, cfg, tail):
     want = oracle.conv2d_fused(inp["x"], inp["w"], inp["scale"], inp["shift"], inp["bias"], inp["residual"],
                                stride=(stride,) * 2, pad=(pad,) * 2, relu=full)
     check(to_host(y), want, "f32", cfg)
+
+
+# shape and bound on the error against 64 bits (2-norm, relative).  A sum of n random terms one after the other
+# has an error of about 2.5e-8 sqrt(n / 2) (2.5e-8: the rms of one fp32 rounding); chains of the kernel's lengths, added up,
+# give 6.1e-8, 6.7e-8, 8.8e-8, 1.0e-7 and 1.06e-7 for these, a chunk's products in one chain 9.6e-8 to 2.5e-7.
+PRECISION = [((2, 32, 112, 112, 64, 1, 1, 0), 8e-8), ((6, 64, 56, 56, 128, 1, 1, 0), 8.5e-8),
+             ((8, 128, 28, 28, 256, 1, 1, 0), 1e-7), ((3, 8, 82, 82, 128, 5, 1, 2), 1.4e-7),
+             ((23, 4, 34, 19, 176, 7, 1, 3), 1.5e-7)]
+
+
+@pytest.mark.parametrize("cfg,bound", PRECISION, ids=lambda c: "x".join(map(str, c)) if isinstance(c, tuple) else None)
+def test_f32_tiled_sums_in_short_chains(tvg, cfg, bound):
+    """The error is that of the kernels which split the reduction over waves, not that of one long sum."""
+    import torch
+    n, ic, h, w, oc, r, stride, pad = cfg
+    desc = tvg.ConvDesc(n, ic, h, w, oc, r, r, stride, stride, pad, pad, tvg.TVG_F32, 0)
+    assert tvg.tvg_conv2d_get_plan(desc)[:2] == (0, 64) and not any(tvg.tvg_conv2d_get_knobs(desc))
+    inp = ti.make_inputs(ti.ConvShape("sums", n, ic, h, w, oc, r, r, stride, pad), 7400 + sum(cfg), "f32")
+    one, none = torch.ones(oc), torch.zeros(oc)
+    x, wt = torch.from_numpy(inp["x"]), torch.from_numpy(inp["w"])
+    got = tvg.conv2d_fused(x.cuda(), wt.cuda(), one.cuda(), none.cuda(), stride=stride, pad=pad).cpu().double()
+    want = torch.nn.functional.conv2d(x.double(), wt.double(), stride=stride, padding=pad)
+    err = float((got - want).norm() / want.norm())
+    assert err <= bound, (cfg, err)
