@@ -316,7 +316,8 @@ bool plan_conv_f32_tiled(const ConvProblem &p, F32TiledPlan *plan)
     const Knobs knobs = forced_knobs(p);
     if (knobs.mt || knobs.nt || knobs.split_k) return false;     // a caller who shapes the gather kernel
     // Where the gather kernel has 128 x 128 tiles for every CU and aligned weight rows, it is the better one
-    // for 1x1 filters (nothing to share between taps): 32 x 256 -> 256 at 28x28 50 us against 60.
+    // for 1x1 filters (nothing to share between taps): 32 x 256 -> 256 at 28x28 50 us against 60, this kernel
+    // 0.58 to 1.27 times as fast on 42 such shapes, 0.89 in the geometric mean.
     const long gtiles = (long)ceil_div(p.OC, 128) * ceil_div(p.npix, 128);
     if (p.R == 1 && gtiles >= kComputeUnits && p.IC % 4 == 0) return false;
     if (p.R == 7 && gtiles >= kComputeUnits) return false;       // (40 x 12 -> 128 at 40x40: 127 us against 135)
@@ -333,8 +334,11 @@ bool plan_conv_f32_tiled(const ConvProblem &p, F32TiledPlan *plan)
     // kernel do (32 x 512 -> 512, 3x3 at 7x7: 119 us against 127; 4 x 64 -> 64 at 56x56: 29 against 24).
     if (p.R > 1 && plan->tiles <= kComputeUnits && plan->nchunks > 16) return false;
     // The share of the matrix cores' turns that is not padding: channels filled up to tiles and chunks, pixels to
-    // tiles, tiles to whole rounds of the CUs.  Measured from 0.77 up: 1x1 1.6 to 3.1
-    // times as fast as the kernels below, 3x3 1.1 to 1.4; at 0.5 and less 0.3 to 1.
+    // tiles, tiles to whole rounds of the CUs.  Timed against the kernels below on 580 shapes (420 drawn at random,
+    // the ResNet-18 and MobileNet layers at ten batches): the 85 that this rule takes run 0.93 to 3.3 times as
+    // fast, one of them below 1 (1x1 2.1 times in the geometric mean, 3x3 1.34, 5x5 1.85, 7x7 1.43).  Below the line
+    // it is no longer a safe choice: 3x3 from 0.6 to 0.75 0.75 to 1.31 times, from 0.5 to 0.6 0.67 to 1.51; 1x1 from
+    // 0.5 to 0.6 0.67 to 2.12, and 0.3 to 1 where the share is small.  (5x5 would gain down to 0.25: 0.93 to 2.6 times.)
     const double rounds = (double)((plan->tiles + kComputeUnits - 1) / kComputeUnits);
     const double useful = (double)p.npix * p.OC * p.IC /
                           (rounds * kComputeUnits * kMT * plan->nt * plan->nchunks * chunk_channels(p.R));
