@@ -36,13 +36,6 @@ constexpr int kKC = 32;                  // channels per K chunk
 constexpr int kRsrcFlags = 0x00020000;   // raw buffer descriptor word 3 on gfx9-family targets
 constexpr uint32_t kOutOfRange = 0xFFFFFFF0u;
 
-__device__ __forceinline__ int xcd_remap(int bid, int nb)
-{
-    const int q = nb >> 3, rem = nb & 7;
-    const int xcd = bid & 7, local = bid >> 3;
-    return xcd < rem ? xcd * (q + 1) + local : rem * (q + 1) + (xcd - rem) * q + local;
-}
-
 // NCH > 0: the reduction is exactly NCH chunks and all of them are fetched before the first is
 // used, each into registers of its own.  These layers do 4 to 16 MFMAs per wave and chunk, so
 // with one chunk in flight at a time every chunk costs a full memory latency (measured: 8

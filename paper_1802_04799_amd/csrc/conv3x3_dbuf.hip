@@ -57,13 +57,6 @@ constexpr int kChunk = 16;                       // input channels per chunk = K
 constexpr int kAPlane = 9 * kMT * 16 + 128;      // bytes of one weight plane
 constexpr int kRsrcFlags = 0x00020000;           // raw buffer descriptor word 3 on gfx9-family targets
 
-__device__ __forceinline__ int xcd_remap(int bid, int nb)
-{
-    const int q = nb >> 3, rem = nb & 7;
-    const int xcd = bid & 7, local = bid >> 3;
-    return xcd < rem ? xcd * (q + 1) + local : rem * (q + 1) + (xcd - rem) * q + local;
-}
-
 // 16-bit half `ha` of a in the low half of the result, half `hb` of b in the high half.
 __device__ __forceinline__ uint32_t pack_halves(uint32_t a, int ha, uint32_t b, int hb)
 {

@@ -65,13 +65,6 @@ constexpr int kWordBytes = 16;
 constexpr int kChunk = 16;       // input channels per chunk = K of one 32x32x16 MFMA
 constexpr int kRsrcFlags = 0x00020000;   // raw buffer descriptor word 3 on gfx9-family targets
 
-__device__ __forceinline__ int xcd_remap(int bid, int nb)
-{
-    const int q = nb >> 3, rem = nb & 7;
-    const int xcd = bid & 7, local = bid >> 3;
-    return xcd < rem ? xcd * (q + 1) + local : rem * (q + 1) + (xcd - rem) * q + local;
-}
-
 // (half `ha` of a) | (half `hb` of b) << 16 in one byte permute (v_perm_b32 takes its selector
 // bytes 0-3 from the second source, 4-7 from the first); written as shifts and masks the same
 // pair costs two to three instructions, and the staging of a chunk was a third of the loop's

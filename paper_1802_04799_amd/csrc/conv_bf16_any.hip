@@ -85,13 +85,6 @@ struct AnyArgs {
     Divider by_ohw, by_ow, by_vh, by_r, by_groups, by_mtiles, by_co, by_s, by_sw, by_tpi, by_border;
 };
 
-__device__ __forceinline__ int xcd_remap(int bid, int nb)
-{
-    const int q = nb >> 3, rem = nb & 7;
-    const int xcd = bid & 7, local = bid >> 3;
-    return xcd < rem ? xcd * (q + 1) + local : rem * (q + 1) + (xcd - rem) * q + local;
-}
-
 __device__ __forceinline__ uint32_t pack_halves(uint32_t a, uint32_t b, int half)
 {
     return __builtin_amdgcn_perm(b, a, half ? 0x07060302u : 0x05040100u);

@@ -49,13 +49,6 @@ struct TiledArgs {
     uint32_t x_bytes, w_bytes;
 };
 
-__device__ __forceinline__ int xcd_remap(int bid, int nb)
-{
-    const int q = nb >> 3, rem = nb & 7;
-    const int xcd = bid & 7, local = bid >> 3;
-    return xcd < rem ? xcd * (q + 1) + local : rem * (q + 1) + (xcd - rem) * q + local;
-}
-
 __device__ __forceinline__ float load_f32(__amdgpu_buffer_rsrc_t r, uint32_t off)
 {
     return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));

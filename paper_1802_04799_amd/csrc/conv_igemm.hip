@@ -41,16 +41,6 @@ constexpr int kThreads = 256;
 constexpr int kNT = 128;        // pixels per workgroup tile
 constexpr int kLdsRow = 80;     // bytes per LDS row: 64 of data + 16 of padding (conflict-free b128)
 
-// Workgroups are dealt round-robin to the 8 XCDs; hand each XCD a contiguous
-// range of tiles so that neighbouring tiles (shared halos, shared weights) meet
-// in the same L2.
-__device__ __forceinline__ int xcd_remap(int bid, int nb)
-{
-    const int q = nb >> 3, rem = nb & 7;
-    const int xcd = bid & 7, local = bid >> 3;
-    return xcd < rem ? xcd * (q + 1) + local : rem * (q + 1) + (xcd - rem) * q + local;
-}
-
 template <typename T> struct Mma;
 
 template <> struct Mma<float> {

@@ -42,13 +42,6 @@ constexpr int kSets = 4;                 // register sets of loads: kSets - 1 ch
 constexpr int kGroup = 2;                // channels whose taps are fetched from LDS together
 constexpr int kSegs = 3;                 // images a 64-pixel tile can span (maps of >= 32 pixels)
 
-__device__ __forceinline__ int xcd_remap(int bid, int nb)
-{
-    const int q = nb >> 3, rem = nb & 7;
-    const int xcd = bid & 7, local = bid >> 3;
-    return xcd < rem ? xcd * (q + 1) + local : rem * (q + 1) + (xcd - rem) * q + local;
-}
-
 // The input rows of one image that a run of output pixels [lo, hi) of that image touches.
 struct Seg {
     int estart;      // first element (ih_lo * W)

@@ -17,6 +17,16 @@ typedef float float16v __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8v __attribute__((ext_vector_type(8)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 
+// Workgroups are dealt round-robin to the 8 XCDs; hand each XCD a contiguous
+// range of tiles so that neighbouring tiles (shared halos, shared weights) meet
+// in the same L2.
+__device__ __forceinline__ int xcd_remap(int bid, int nb)
+{
+    const int q = nb >> 3, rem = nb & 7;
+    const int xcd = bid & 7, local = bid >> 3;
+    return xcd < rem ? xcd * (q + 1) + local : rem * (q + 1) + (xcd - rem) * q + local;
+}
+
 __device__ __forceinline__ float bf16_to_f32(bf16_t b) { return __uint_as_float(uint32_t(b) << 16); }
 
 // fp32 -> bf16, round to nearest, ties to even: the hardware conversion of gfx950
