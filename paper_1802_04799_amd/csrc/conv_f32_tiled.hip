@@ -257,6 +257,8 @@ template <int R, int CIC, int CHAINS = 1>
 tvg_status launch_filter(const TiledArgs &a, const F32TiledPlan &t, hipStream_t stream)
 {
 #define TVG_TILED_ONE(NJ_, PT_) launch_one<R, CIC, NJ_, PT_, CHAINS>(a, t.tiles, t.lds_bytes, stream)
+    // (1x1 without a stride: a tile is one row of the map as the patch sees it)
+    if constexpr (R == 1 && CHAINS < 4) return t.nt == 128 ? TVG_TILED_ONE(2, 16) : TVG_TILED_ONE(1, 8);
     if (t.nt == 128) return t.pt == 8 ? TVG_TILED_ONE(2, 8) : t.pt == 16 ? TVG_TILED_ONE(2, 16) : TVG_TILED_ONE(2, 32);
     return t.pt == 8 ? TVG_TILED_ONE(1, 8) : t.pt == 16 ? TVG_TILED_ONE(1, 16) : TVG_TILED_ONE(1, 32);
 #undef TVG_TILED_ONE
