@@ -28,6 +28,7 @@ def test_bf16_any_shape(tvg, cfg, tail):
     sh = ti.ConvShape("any", n, ic, h, w, oc, r, s, stride, pad)
     desc = tvg.ConvDesc(n, ic, h, w, oc, r, s, stride, stride, pad, pad, tvg.TVG_BF16, 0)
     assert tvg.tvg_conv2d_get_plan(desc)[0] == 0 and tvg.tvg_conv2d_workspace_size(desc) > 0
+    assert not any(tvg.tvg_conv2d_get_knobs(desc))                  # (the gather kernel's are not zero)
     full = tail != "plain"
     inp = ti.make_inputs(sh, 6100 + sum(cfg), "bf16", residual=full, bias=full)
     d = dev_inputs(inp, "bf16")
@@ -82,3 +83,39 @@ def test_equal_images_of_a_batch_get_equal_results(tvg, cfg):
     d = dev_inputs(inp, "bf16")
     y = tvg.conv2d_fused(d["x"], d["w"], d["scale"], d["shift"], stride=stride, pad=pad)
     assert torch.equal(y, y[:1].expand_as(y))
+
+
+# (n, ic, h, w, oc, r, s, stride, pad), tile: every instance of the kernel - 1, 4 or 8 pixels per load, one or two
+# loads per thread under each tile -, tiles within an image and across images, several chunks, a split reduction
+EVERY_INSTANCE = [
+    ((1, 5, 3, 1, 1, 3, 1, 3, 0), (32, 128)), ((2, 35, 31, 3, 1, 1, 1, 3, 0), (32, 128)),
+    ((1, 9, 5, 4, 96, 1, 1, 2, 0), (32, 128)), ((40, 9, 3, 7, 1, 2, 1, 3, 0), (32, 128)),
+    ((8, 500, 5, 33, 1, 2, 2, 1, 0), (32, 128)), ((3, 5, 65, 9, 1, 5, 1, 3, 0), (32, 128)),
+    ((400, 3, 63, 2, 96, 1, 1, 1, 0), (32, 256)), ((400, 3, 65, 3, 16, 1, 1, 1, 0), (32, 256)),
+    ((200, 3, 63, 7, 1, 1, 1, 1, 0), (32, 256)), ((400, 60, 19, 5, 96, 1, 1, 1, 0), (32, 256)),
+    ((90, 3, 63, 130, 1, 1, 1, 3, 0), (32, 256)), ((90, 20, 31, 100, 1, 3, 1, 2, 0), (32, 256)),
+    ((8, 60, 90, 45, 65, 2, 1, 1, 0), (32, 256)), ((1, 3, 5, 2, 50, 1, 1, 3, 0), (64, 64)),
+    ((1, 20, 45, 3, 33, 3, 1, 3, 0), (64, 64)), ((1, 5, 1, 7, 97, 1, 1, 2, 0), (64, 64)),
+    ((1, 500, 13, 7, 130, 5, 1, 1, 0), (64, 64)), ((1, 3, 3, 13, 60, 1, 1, 3, 0), (64, 64)),
+    ((1, 17, 19, 45, 33, 3, 1, 3, 0), (64, 64)), ((200, 3, 63, 2, 120, 1, 1, 1, 0), (64, 128)),
+    ((400, 9, 90, 3, 33, 1, 1, 2, 0), (64, 128)), ((90, 5, 90, 6, 33, 1, 1, 1, 0), (64, 128)),
+    ((200, 35, 63, 4, 130, 2, 2, 2, 0), (64, 128)), ((90, 3, 7, 65, 33, 1, 1, 1, 0), (64, 128)),
+    ((20, 9, 90, 100, 130, 3, 1, 3, 0), (64, 128)), ((90, 3, 90, 2, 97, 3, 3, 1, 2), (64, 256)),
+    ((200, 9, 45, 2, 130, 2, 2, 1, 1), (64, 256)), ((90, 3, 63, 6, 97, 1, 1, 1, 0), (64, 256)),
+    ((400, 9, 90, 5, 130, 2, 1, 3, 0), (64, 256)), ((400, 3, 19, 11, 33, 1, 1, 1, 0), (64, 256)),
+    ((90, 17, 31, 100, 60, 3, 1, 2, 0), (64, 256)),
+]
+
+
+@pytest.mark.parametrize("cfg,tile", EVERY_INSTANCE, ids=lambda c: "x".join(map(str, c)))
+def test_bf16_any_shape_every_instance(tvg, cfg, tile):
+    n, ic, h, w, oc, r, s, stride, pad = cfg
+    desc = tvg.ConvDesc(n, ic, h, w, oc, r, s, stride, stride, pad, pad, tvg.TVG_BF16, 0)
+    assert tvg.tvg_conv2d_get_plan(desc) == (0, *tile) and not any(tvg.tvg_conv2d_get_knobs(desc))
+    inp = ti.make_inputs(ti.ConvShape("any", n, ic, h, w, oc, r, s, stride, pad), 6800 + sum(cfg), "bf16", residual=True, bias=True)
+    d = dev_inputs(inp, "bf16")
+    y = tvg.conv2d_fused(d["x"], d["w"], d["scale"], d["shift"], d["bias"], d["residual"], stride=stride,
+                         pad=pad, relu=True)
+    want = oracle.conv2d_fused(inp["x"], inp["w"], inp["scale"], inp["shift"], inp["bias"], inp["residual"],
+                               stride=(stride,) * 2, pad=(pad,) * 2, relu=True)
+    check(to_host(y), want, "bf16", cfg)
