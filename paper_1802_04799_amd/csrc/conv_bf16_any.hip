@@ -24,11 +24,11 @@
 //     chosen so that little of the last turn is padding, whatever R, S and IC are.
 // The patch is double-buffered (one chunk ahead, in registers), one barrier per chunk.
 //
-// What bounds it: latency.  At 6 x 83 x 45 x 37 -> 139, 3x3 (486 workgroups of 64 x 64, about two
-// per CU) the pack launch takes 3.8 us and this kernel 12.5: 2 us launch, 1.2 until the first load
-// is issued, 2.8 until the first patch is in LDS, 2.8 in the loop, 1.5 in the tail.  The gather
-// kernel with its split reduction took 62 + 8 us.  Larger problems: 9 x 24 x 99 x 99 -> 200, 5x5, 256
-// us before, 60 now (350 TFLOP/s); 27 x 168 x 10 x 76 -> 312, 3x3, 132 before, 38 now (506).
+// What bounds it: latency.  At 6 x 83 x 45 x 37 -> 139, 3x3 (486 workgroups of 64 x 64 with one chunk each, about two
+// per CU) the pack launch takes 4 us and this kernel 12, a tenth of them on the matrix pipe.  The gather kernel
+// with its split reduction took 62 + 8 us.  Larger problems: 9 x 24 x 99 x 99 -> 200, 5x5, 256 us before, 58 now
+// (366 TFLOP/s, matrix pipe 20 %); 27 x 168 x 10 x 76 -> 312, 3x3, 132 before, 33 now (583, 28 %), both beside 5 us of
+// packing.  About half of the LDS cycles are bank conflicts.
 #include <type_traits>
 
 #include "tvg_device.h"

@@ -17,10 +17,11 @@
 //   - MFMAs start from zero again after a filter row (5x5: 20 products, 7x7: 28), a chunk (3x3: 72) or a part of
 //     one (1x1: 8 to 32), and their sums are added to the totals in plain adds.
 //
-// What bounds it: per chunk, the wait for LDS operands at each filter row and the barrier (a lone
-// workgroup per CU takes 1.95 us for a 3x3 chunk whose MFMAs take 1), and rounds of tiles that do not fill
-// the CUs.  32 x 128 -> 128, 3x3 at 28x28: 127 us by the 32 x 32 tiles of the launch-bound kernel, 99 here
-// (75 TFLOP/s); 32 x 64 -> 64 at 56x56: 146 by the gather kernel, 101; 1x1, 32 x 512 -> 512 at 14x14: 128, 59.
+// What bounds it: per chunk, the wait for LDS operands at each filter row and the barrier, and rounds of tiles
+// that do not fill the CUs; the matrix pipe is busy for 47 to 48 % of the time in the first three of these.
+// 32 x 128 -> 128, 3x3 at 28x28: 127 us by the 32 x 32 tiles of the launch-bound kernel, 99 here
+// (75 TFLOP/s); 32 x 64 -> 64 at 56x56: 146 by the gather kernel, 101; 1x1, 32 x 512 -> 512 at 14x14: 128, 59;
+// 16 x 64 -> 128, 1x1 stride 2 at 56x56: 36, 12.
 // Error against 64 bits over the 54 smaller of 85 such shapes, relative to the kernels that ran them before:
 // 0.83 in the geometric mean, 0.36 to 1.00.  (With whole chunks as chains: 1.00, 0.36 to 1.59.)
 #include <algorithm>
