@@ -344,7 +344,9 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
  * TVG_KERNEL_GENERIC stands for three kernels.  The gather kernel has the knobs mt, nt and
  * split_k (get_knobs reports stages = 2 with them).  The bf16 kernel with packed weights and the
  * fp32 kernel for throughput sizes have none: get_knobs reports zeros, which set_knobs takes as
- * "leave it to the library", and fixing mt, nt or split_k selects the gather kernel.
+ * "leave it to the library", and fixing mt, nt or split_k selects the gather kernel.  The same goes for
+ * bf16 3x3 and 1x1 problems with few tiles, whose waves split the reduction: get_plan reports TVG_KERNEL_3X3
+ * or TVG_KERNEL_1X1 with mt = 16, get_knobs zeros, and fixing any knob selects the kernels above.
  */
 typedef struct {
     int32_t mt, nt, stages, split_k, lds_pitch, row_loads;

@@ -99,7 +99,8 @@ void tile_key(const ConvProblem &p, int (&key)[12])
 // 257th distinct problem.  The launch-bound batch-1 layers spend 1-5 us per call in planning
 // otherwise.
 struct Dispatch {
-    bool patch_shape, stem_shape, pw_shape, pwd_shape, f32_shape, any_shape, tiled_shape;
+    bool rows_shape, patch_shape, stem_shape, pw_shape, pwd_shape, f32_shape, any_shape, tiled_shape;
+    tvg::RowsPlan rows;             // few tiles: in front of the 3x3 and 1x1 kernels
     tvg::Patch3x3Plan patch;
     tvg::StemPlan stem;
     tvg::Pw1x1Plan pw;
@@ -139,6 +140,7 @@ Dispatch dispatch_for(const ConvProblem &p)
     d.patch_shape = tvg::plan_conv3x3_patch(p, &d.patch);
     d.stem_shape = !d.patch_shape && tvg::plan_conv7x7s2_stem(p, &d.stem);
     d.pw_shape = !d.patch_shape && !d.stem_shape && tvg::plan_conv1x1(p, &d.pw);
+    d.rows_shape = (d.patch_shape || d.pw_shape) && tvg::plan_conv_rows(p, &d.rows);
     {
         // stages knob of a 1x1 problem: 2 = the deep-reduction kernel.  No rule picks it: measured at
         // batch 32 / 64 over thirteen MobileNet and ResNet-50 pointwise shapes it takes 1.15-1.5 times
@@ -174,6 +176,7 @@ size_t dense_workspace(const Dispatch &d)
 tvg_status run_dense(const ConvProblem &p, const Dispatch &d, const tvg::ConvPointers &ptr, size_t workspace_bytes,
                      hipStream_t stream)
 {
+    if (d.rows_shape && tvg::conv_rows_pointers_ok(ptr)) return tvg::launch_conv_rows(p, d.rows, ptr, stream);
     if (d.patch_shape && tvg::conv3x3_patch_pointers_ok(ptr))
         return tvg::launch_conv3x3_patch(p, d.patch, ptr, stream);
     if (d.stem_shape && tvg::conv7x7s2_stem_pointers_ok(ptr))
@@ -313,7 +316,9 @@ tvg_status tvg_conv2d_get_knobs(const tvg_conv_desc *desc, tvg_conv_knobs *knobs
     if (st != TVG_OK) return st;
     const Dispatch d = dispatch_for(p);
     tvg_conv_knobs k = {0, 0, 0, 0, 0, 0};
-    if (d.patch_shape) {
+    if (d.rows_shape) {
+        // no knobs: fixing one selects the 3x3 or 1x1 kernel behind it
+    } else if (d.patch_shape) {
         k.mt = d.patch.mt;
         k.nt = d.patch.nt;
         k.stages = d.patch.dbuf ? 2 : 1;
@@ -354,7 +359,11 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
     tvg_status st = make_problem(desc, false, &p);
     if (st != TVG_OK) return st;
     const Dispatch d = dispatch_for(p);
-    if (d.patch_shape) {
+    if (d.rows_shape) {
+        *kernel = d.patch_shape ? TVG_KERNEL_3X3 : TVG_KERNEL_1X1;
+        *mt = 16;
+        *nt = 16 * d.rows.nj;
+    } else if (d.patch_shape) {
         *kernel = d.patch.dbuf ? TVG_KERNEL_3X3_PIPELINED : TVG_KERNEL_3X3;
         *mt = d.patch.mt;
         *nt = d.patch.nt;
@@ -433,6 +442,10 @@ tvg_status tvg_conv2d_fused_dual(const tvg_conv_desc *desc, int32_t k1, uint32_t
     if (!tvg::conv3x3_patch_pointers_ok(ptr)) return TVG_ERR_UNSUPPORTED;
     const tvg::DualHead dual{k1, (int)((flags2 & TVG_RELU ? 1 : 0) | (flags2 & TVG_STREAM_OUT ? 2 : 0)),
                              (flags2 & TVG_CENTRE_TAP_ONLY) ? 1 : 0, y2};
+    tvg::RowsPlan rows;
+    if (tvg::plan_conv_rows_dual(p, k1, dual.centre2 != 0, &rows) && tvg::conv_rows_pointers_ok(ptr) &&
+        reinterpret_cast<uintptr_t>(y2) % 2 == 0)
+        return tvg::launch_conv_rows(p, rows, ptr, static_cast<hipStream_t>(hip_stream), &dual);
     return tvg::launch_conv3x3_patch(p, plan, ptr, static_cast<hipStream_t>(hip_stream), &dual);
 }
 

@@ -71,6 +71,28 @@ __device__ __forceinline__ int fast_div(int a, int b, float inv_b, int *rem)
     return q;
 }
 
+// Exact division of 0 <= n < 2^31 by a divisor the host knows: one high multiply and a shift.
+struct Divider { uint32_t d, m, s; };
+
+inline Divider make_divider(int d)
+{
+    Divider v{(uint32_t)d, 0, 0};
+    if (d > 1) {
+        int l = 1;
+        while (((int64_t)1 << l) < d) ++l;                 // ceil(log2 d)
+        v.m = (uint32_t)(((uint64_t)1 << (31 + l)) / (uint64_t)d + 1);
+        v.s = (uint32_t)(l - 1);
+    }
+    return v;
+}
+
+__device__ __forceinline__ int divide(int n, const Divider &v, int *rem)
+{
+    const int q = v.d == 1 ? n : (int)(__umulhi((uint32_t)n, v.m) >> v.s);
+    *rem = n - q * (int)v.d;
+    return q;
+}
+
 template <typename T> struct Elem;
 template <> struct Elem<float> {
     static __device__ __forceinline__ float load(const float *p, int i) { return p[i]; }

@@ -97,6 +97,24 @@ bool plan_conv3x3_dbuf(const ConvProblem &p, Patch3x3Plan *plan);
 tvg_status launch_conv3x3_dbuf(const ConvProblem &p, const Patch3x3Plan &plan,
                                const ConvPointers &ptr, hipStream_t stream);
 
+// bf16 3x3 and 1x1, stride 1 or 2, of problems with few tiles: the waves of a workgroup split the reduction.
+struct RowsPlan {
+    int nj, pt, nw;                   // 16-pixel blocks per tile, load tasks per lane, waves
+    int rs;                           // 1 = a wave takes one filter row of a chunk
+    int flat;                         // an image is one row (1x1 without a stride)
+    int tr, groups, cblocks, t8;      // rows per tile, 4-pixel groups per row, tiles across a row, loads per staged row
+    int vh, rows, images;             // staged rows per image and per tile, images a tile may touch
+    int plane, region;                // LDS bytes per channel and per wave
+    long ptiles, tiles;
+    size_t lds_bytes;
+};
+bool plan_conv_rows(const ConvProblem &p, RowsPlan *plan);
+// p: both heads together, k1 channels in the first (centre: the second is a 1x1 convolution)
+bool plan_conv_rows_dual(const ConvProblem &p, int k1, bool centre, RowsPlan *plan);
+bool conv_rows_pointers_ok(const ConvPointers &ptr);
+tvg_status launch_conv_rows(const ConvProblem &p, const RowsPlan &plan, const ConvPointers &ptr, hipStream_t stream,
+                            const DualHead *dual = nullptr);
+
 // bf16 7x7 stride-2 pad-3 kernel for IC <= 4 (the ResNet stem).
 struct StemPlan {
     int rows;           // virtual input rows staged per tile
