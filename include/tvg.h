@@ -306,7 +306,7 @@ typedef enum {
     TVG_KERNEL_3X3_PIPELINED = 2,  /* bf16 3x3, two LDS stages, software-pipelined         */
     TVG_KERNEL_STEM = 3,           /* bf16 7x7 or 3x3 stride 2, few input channels (mt 64|32) */
     TVG_KERNEL_1X1 = 4,            /* bf16 1x1                                             */
-    TVG_KERNEL_F32_SMALL = 5,      /* fp32 1x1 / 3x3 / 7x7 stem of launch-bound problems (mt = nt = 32 or 16; stem 32 x 64) */
+    TVG_KERNEL_F32_SMALL = 5,      /* fp32 1x1 / 3x3 / 7x7 stem of launch-bound problems (mt = nt = 32 or 16; stem 32 x 64; 1x1 also 32 x 64 and 32 x 128) */
     TVG_KERNEL_1X1_DEEP = 6        /* bf16 1x1 stride 1, reductions of 128 n channels       */
 } tvg_kernel;
 tvg_status tvg_conv2d_set_tile(const tvg_conv_desc *desc, int32_t mt, int32_t nt);
@@ -346,7 +346,8 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
  * fp32 kernel for throughput sizes have none: get_knobs reports zeros, which set_knobs takes as
  * "leave it to the library", and fixing mt, nt or split_k selects the gather kernel.  The same goes for
  * bf16 3x3 and 1x1 problems with few tiles, whose waves split the reduction: get_plan reports TVG_KERNEL_3X3
- * or TVG_KERNEL_1X1 with mt = 16, get_knobs zeros, and fixing any knob selects the kernels above.
+ * or TVG_KERNEL_1X1 with mt = 16, get_knobs zeros, and fixing any knob selects the kernels above.  And for fp32
+ * 1x1 problems with 8 n channels (TVG_KERNEL_F32_SMALL or TVG_KERNEL_GENERIC, zeros).
  */
 typedef struct {
     int32_t mt, nt, stages, split_k, lds_pitch, row_loads;

@@ -99,7 +99,7 @@ void tile_key(const ConvProblem &p, int (&key)[12])
 // 257th distinct problem.  The launch-bound batch-1 layers spend 1-5 us per call in planning
 // otherwise.
 struct Dispatch {
-    bool rows_shape, patch_shape, stem_shape, pw_shape, pwd_shape, f32_shape, any_shape, tiled_shape;
+    bool rows_shape, patch_shape, stem_shape, pw_shape, pwd_shape, f32_shape, any_shape, tiled_shape, pw32_shape;
     tvg::RowsPlan rows;             // few tiles: in front of the 3x3 and 1x1 kernels
     tvg::Patch3x3Plan patch;
     tvg::StemPlan stem;
@@ -108,6 +108,7 @@ struct Dispatch {
     tvg::F32SmallPlan f32;
     tvg::ConvAnyPlan any;
     tvg::F32TiledPlan tiled;
+    tvg::F32PwPlan pw32;            // fp32 1x1: in front of the three kernels that follow
     tvg::ConvPlan generic;          // the generic kernel's plan, reduction split allowed
     tvg::ConvPlan generic_single;   // the same in a single pass (no workspace)
 };
@@ -151,6 +152,9 @@ Dispatch dispatch_for(const ConvProblem &p)
     d.any_shape = !d.patch_shape && !d.stem_shape && !d.pw_shape && tvg::plan_conv_bf16_any(p, &d.any);
     d.tiled_shape = tvg::plan_conv_f32_tiled(p, &d.tiled);
     d.f32_shape = !d.tiled_shape && tvg::plan_conv_f32_small(p, &d.f32);
+    // fp32 1x1 by what it takes the place of: tiles as the throughput kernel cuts them, narrow ones where the
+    // launch-bound kernel would run, its own where the gather kernel would have 128 x 128 tiles for every CU
+    d.pw32_shape = tvg::plan_conv_f32_pw(p, d.f32_shape, d.tiled_shape ? d.tiled.nt : 0, &d.pw32);
     d.generic = tvg::plan_conv(p, true);
     d.generic_single = tvg::plan_conv(p, false);
     std::lock_guard<std::mutex> lock(g_dispatch_mutex);
@@ -168,7 +172,7 @@ void forget_dispatch()
 // Bytes of workspace that the dispatch's kernels want.
 size_t dense_workspace(const Dispatch &d)
 {
-    if (d.patch_shape || d.stem_shape || d.pw_shape || d.tiled_shape) return 0;
+    if (d.patch_shape || d.stem_shape || d.pw_shape || d.tiled_shape || d.pw32_shape) return 0;
     return d.any_shape ? d.any.workspace_bytes : d.f32_shape ? d.f32.workspace_bytes : d.generic.workspace_bytes;
 }
 
@@ -192,9 +196,10 @@ tvg_status run_dense(const ConvProblem &p, const Dispatch &d, const tvg::ConvPoi
     const bool any_short = d.any_shape && workspace_short(d.any.workspace_bytes);
     if (d.any_shape && !any_short && tvg::conv_bf16_any_pointers_ok(ptr))
         return tvg::launch_conv_bf16_any(p, d.any, ptr, stream);
+    if (d.pw32_shape && tvg::conv_f32_pw_pointers_ok(ptr)) return tvg::launch_conv_f32_pw(p, d.pw32, ptr, stream);
     if (d.tiled_shape && tvg::conv_f32_tiled_pointers_ok(ptr))
         return tvg::launch_conv_f32_tiled(p, d.tiled, ptr, stream);
-    if (d.f32_shape && tvg::conv_f32_small_pointers_ok(ptr)) {
+    if (d.f32_shape && tvg::conv_f32_small_pointers_ok(ptr) && !(d.pw32_shape && workspace_short(d.f32.workspace_bytes))) {
         if (workspace_short(d.f32.workspace_bytes)) return TVG_ERR_WORKSPACE;
         return tvg::launch_conv_f32_small(p, d.f32, ptr, stream);
     }
@@ -203,7 +208,7 @@ tvg_status run_dense(const ConvProblem &p, const Dispatch &d, const tvg::ConvPoi
     // (an fp32 problem whose x is not 16-byte aligned, a bf16 one at an odd address: the generic
     // kernel, within the workspace that the query reported if that is all the caller has)
     const tvg::ConvPlan &plan =
-        (d.patch_shape || d.stem_shape || d.pw_shape || d.tiled_shape ||
+        (d.patch_shape || d.stem_shape || d.pw_shape || d.tiled_shape || d.pw32_shape ||
          ((d.f32_shape || (d.any_shape && !any_short)) && workspace_short(d.generic.workspace_bytes)))
             ? d.generic_single : d.generic;
     if (workspace_short(plan.workspace_bytes)) return TVG_ERR_WORKSPACE;
@@ -339,6 +344,8 @@ tvg_status tvg_conv2d_get_knobs(const tvg_conv_desc *desc, tvg_conv_knobs *knobs
         k.mt = d.pw.mt;
         k.nt = d.pw.nt;
         k.stages = 1;
+    } else if (d.pw32_shape) {
+        // none either
     } else if (d.f32_shape) {
         k.stages = 1;
         k.split_k = d.f32.nw * d.f32.ksplit;     // waves of a workgroup x slices across workgroups
@@ -379,6 +386,10 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
         *kernel = TVG_KERNEL_1X1;
         *mt = d.pw.mt;
         *nt = d.pw.nt;
+    } else if (d.pw32_shape) {
+        *kernel = d.f32_shape ? TVG_KERNEL_F32_SMALL : TVG_KERNEL_GENERIC;
+        *mt = d.pw32.mt;
+        *nt = d.pw32.nt;
     } else if (d.f32_shape) {
         *kernel = TVG_KERNEL_F32_SMALL;
         *mt = d.f32.stem ? 32 : d.f32.tile;

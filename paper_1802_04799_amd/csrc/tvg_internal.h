@@ -180,6 +180,17 @@ bool conv_f32_tiled_pointers_ok(const ConvPointers &ptr);
 tvg_status launch_conv_f32_tiled(const ConvProblem &p, const F32TiledPlan &plan, const ConvPointers &ptr,
                                  hipStream_t stream);
 
+// fp32 1x1: operands straight from memory, the waves of a workgroup split the reduction.
+struct F32PwPlan {
+    int ks, nb, pxl;                  // waves per reduction, 32-lane pixel blocks, adjacent pixels per lane
+    int mt, nt;
+    long tiles;
+};
+// few_tiles: one round of narrow tiles; else tiles of nt pixels (0: the kernel's own choice)
+bool plan_conv_f32_pw(const ConvProblem &p, bool few_tiles, int nt, F32PwPlan *plan);
+bool conv_f32_pw_pointers_ok(const ConvPointers &ptr);
+tvg_status launch_conv_f32_pw(const ConvProblem &p, const F32PwPlan &plan, const ConvPointers &ptr, hipStream_t stream);
+
 // bf16 MobileNet block in one kernel: depthwise 3x3 (pad 1, stride 1) computed in LDS as the
 // pixel operand of the 1x1 stage.  `dw` is the depthwise problem, OC the 1x1 stage's channels.
 struct DwPwPlan {

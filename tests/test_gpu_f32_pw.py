@@ -1,0 +1,76 @@
+"""The fp32 1x1 kernel (plan: fp32-small or generic, no knobs) against the oracle, every output: each instance
+(pixels per lane, blocks, waves per reduction, chain length), channels and pixels that end inside a tile, maps of
+odd size, strides, reductions shorter than the waves.  Bounds as for every single operator, and the
+error of the sums against 64 bits."""
+import numpy as np
+import pytest
+
+import oracle
+import tvg_inputs as ti
+from _util import check, dev_inputs, to_host
+
+pytestmark = pytest.mark.gpu
+
+# (n, ic, h, w, oc, stride), plan
+EVERY_INSTANCE = [
+    ((1, 32, 5, 5, 33, 1), (5, 32, 32)), ((2, 40, 7, 6, 40, 1), (5, 32, 32)), ((3, 56, 6, 6, 31, 2), (5, 32, 32)),
+    ((40, 32, 10, 11, 70, 1), (5, 32, 64)), ((40, 64, 11, 9, 70, 1), (5, 32, 64)), ((80, 48, 9, 9, 96, 1), (5, 32, 128)),
+    ((80, 40, 10, 9, 96, 1), (5, 32, 128)), ((20, 264, 14, 12, 96, 1), (5, 32, 64)), ((50, 72, 12, 12, 97, 1), (5, 32, 128)),
+    ((8, 72, 31, 28, 121, 1), (0, 64, 64)), ((64, 72, 31, 14, 121, 1), (0, 64, 128)), ((8, 64, 55, 57, 126, 1), (0, 64, 64)),
+    ((8, 128, 28, 28, 256, 1), (0, 64, 64)), ((40, 256, 5, 63, 50, 1), (0, 64, 64)), ((128, 256, 1, 77, 256, 1), (0, 64, 128)),
+    ((16, 64, 57, 57, 128, 2), (0, 64, 64)), ((17, 256, 29, 30, 128, 2), (5, 32, 64)), ((33, 136, 33, 31, 128, 1), (0, 64, 64)),
+    ((22, 264, 42, 33, 192, 1), (0, 64, 128)), ((22, 264, 41, 33, 192, 1), (0, 64, 128)), ((22, 264, 44, 33, 192, 1), (0, 64, 128)),
+]
+
+
+@pytest.mark.parametrize("tail", ["plain", "bias+residual"])
+@pytest.mark.parametrize("cfg,plan", EVERY_INSTANCE, ids=lambda c: "x".join(map(str, c)))
+def test_f32_1x1_every_instance(tvg, cfg, plan, tail):
+    n, ic, h, w, oc, stride = cfg
+    desc = tvg.ConvDesc(n, ic, h, w, oc, 1, 1, stride, stride, 0, 0, tvg.TVG_F32, 0)
+    assert tvg.tvg_conv2d_get_plan(desc) == plan and not any(tvg.tvg_conv2d_get_knobs(desc))
+    assert tvg.tvg_conv2d_workspace_size(desc) == 0
+    full = tail != "plain"
+    inp = ti.make_inputs(ti.ConvShape("pw", n, ic, h, w, oc, 1, 1, stride, 0), 8700 + sum(cfg), "f32", residual=full, bias=full)
+    d = dev_inputs(inp, "f32")
+    y = tvg.conv2d_fused(d["x"], d["w"], d["scale"], d["shift"], d["bias"], d["residual"], stride=stride, relu=full)
+    want = oracle.conv2d_fused(inp["x"], inp["w"], inp["scale"], inp["shift"], inp["bias"], inp["residual"],
+                               stride=(stride,) * 2, pad=(0, 0), relu=full)
+    check(to_host(y), want, "f32", cfg)
+
+
+# One rounding of a partial sum is 2.5e-8 rms of it, and a chain of m products errs by about 2.5e-8 sqrt(m / 2) of its
+# sum; chains of 8 (16, 32) channels added up one after the other give below 1.1e-7 for these, one chain of all 1.8e-7
+# to 5.7e-7.
+@pytest.mark.parametrize("cfg", [(1, 512, 14, 14, 512, 1), (4, 256, 14, 14, 512, 1), (8, 256, 28, 28, 256, 1), (3, 1000, 26, 26, 228, 1)],
+                         ids=lambda c: "x".join(map(str, c)))
+def test_f32_1x1_sums_in_short_chains(tvg, cfg):
+    import torch
+    n, ic, h, w, oc, _ = cfg
+    inp = ti.make_inputs(ti.ConvShape("sums", n, ic, h, w, oc, 1, 1, 1, 0), 8800 + sum(cfg), "f32")
+    one, none = torch.ones(oc), torch.zeros(oc)
+    got = tvg.conv2d_fused(torch.from_numpy(inp["x"]).cuda(), torch.from_numpy(inp["w"]).cuda(), one.cuda(), none.cuda(), relu=False)
+    want = np.matmul(inp["w"].astype(np.float64).reshape(oc, ic), inp["x"].astype(np.float64).reshape(n, ic, h * w))
+    err = np.linalg.norm(got.cpu().numpy().astype(np.float64).reshape(n, oc, h * w) - want) / np.linalg.norm(want)
+    assert err <= 1.3e-7, (cfg, err)
+
+
+@pytest.mark.parametrize("shape", [(2, 64, 8, 8, 40), (1, 512, 14, 14, 512)])
+def test_f32_1x1_unaligned_pointers(tvg, shape):
+    """y and the residual at any element; x at any element runs elsewhere, within the workspace that was queried."""
+    import torch
+    n, ic, h, w, oc = shape
+    inp = ti.make_inputs(ti.ConvShape("pwa", n, ic, h, w, oc, 1, 1, 1, 0), 8900, "f32", residual=True)
+    d = dev_inputs(inp, "f32")
+    want = oracle.conv2d_fused(inp["x"], inp["w"], inp["scale"], inp["shift"], None, inp["residual"], stride=(1, 1), pad=(0, 0), relu=True)
+    def at(t, off):
+        store = torch.zeros(t.numel() + 8, device="cuda")
+        v = store[off:off + t.numel()].view(t.shape)
+        v.copy_(t)
+        return v
+    desc = tvg.ConvDesc(n, ic, h, w, oc, 1, 1, 1, 1, 0, 0, tvg.TVG_F32, tvg.TVG_RELU)
+    for ox, oy in ((0, 1), (1, 0)):
+        y = at(torch.zeros_like(d["residual"]), oy)
+        rc = tvg.tvg_conv2d_fused(desc, at(d["x"], ox), d["w"], d["scale"], d["shift"], None, at(d["residual"], oy), y, None, 0, None)
+        assert rc == 0, tvg.status_string(rc)
+        check(to_host(y), want, "f32", (shape, ox, oy))
