@@ -335,6 +335,8 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
  *               (operand reads free of bank conflicts across row ends, more LDS)
  *   row_loads   pipelined 3x3, odd rows of at most 7 pixels: 1 = element loads, 2 = one 16-byte
  *               load per row and channel from the aligned address below the row, shifted into place
+ *               bf16 1x1, stride 1, c a multiple of 32: 2 = 16-byte loads of pixels as they lie in
+ *               memory (tiles 64x64, 64x128, 128x128), 1 or a tile alone = element loads
  * tvg_conv2d_set_knobs: fix the knobs of this exact problem (every descriptor field but flags);
  * knobs == NULL or all zero forgets the problem.  Values outside the ranges above are
  * TVG_ERR_UNSUPPORTED.  A combination the problem's kernel cannot use (say, two stages that do

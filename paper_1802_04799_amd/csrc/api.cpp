@@ -99,11 +99,11 @@ void tile_key(const ConvProblem &p, int (&key)[12])
 // 257th distinct problem.  The launch-bound batch-1 layers spend 1-5 us per call in planning
 // otherwise.
 struct Dispatch {
-    bool rows_shape, patch_shape, stem_shape, pw_shape, pwd_shape, f32_shape, any_shape, tiled_shape, pw32_shape;
+    bool rows_shape, patch_shape, stem_shape, pw_shape, pwr_shape, pwd_shape, f32_shape, any_shape, tiled_shape, pw32_shape;
     tvg::RowsPlan rows;             // few tiles: in front of the 3x3 and 1x1 kernels
     tvg::Patch3x3Plan patch;
     tvg::StemPlan stem;
-    tvg::Pw1x1Plan pw;
+    tvg::Pw1x1Plan pw, pwr;         // pwr: in front of pw
     tvg::PwDeepPlan pwd;            // the deep-reduction 1x1 kernel, where its rule (or a knob) picks it
     tvg::F32SmallPlan f32;
     tvg::ConvAnyPlan any;
@@ -141,6 +141,7 @@ Dispatch dispatch_for(const ConvProblem &p)
     d.patch_shape = tvg::plan_conv3x3_patch(p, &d.patch);
     d.stem_shape = !d.patch_shape && tvg::plan_conv7x7s2_stem(p, &d.stem);
     d.pw_shape = !d.patch_shape && !d.stem_shape && tvg::plan_conv1x1(p, &d.pw);
+    d.pwr_shape = d.pw_shape && tvg::plan_conv1x1_rows(p, &d.pwr);
     d.rows_shape = (d.patch_shape || d.pw_shape) && tvg::plan_conv_rows(p, &d.rows);
     {
         // stages knob of a 1x1 problem: 2 = the deep-reduction kernel.  No rule picks it: measured at
@@ -186,6 +187,7 @@ tvg_status run_dense(const ConvProblem &p, const Dispatch &d, const tvg::ConvPoi
     if (d.stem_shape && tvg::conv7x7s2_stem_pointers_ok(ptr))
         return tvg::launch_conv7x7s2_stem(p, d.stem, ptr, stream);
     if (d.pwd_shape && tvg::conv1x1_deep_pointers_ok(ptr)) return tvg::launch_conv1x1_deep(p, d.pwd, ptr, stream);
+    if (d.pwr_shape && tvg::conv1x1_rows_pointers_ok(ptr)) return tvg::launch_conv1x1_rows(p, d.pwr, ptr, stream);
     if (d.pw_shape && tvg::conv1x1_pointers_ok(ptr)) return tvg::launch_conv1x1(p, d.pw, ptr, stream);
     const auto workspace_short = [&](size_t need) {
         return need > 0 && (!ptr.workspace || workspace_bytes < need ||
@@ -340,6 +342,11 @@ tvg_status tvg_conv2d_get_knobs(const tvg_conv_desc *desc, tvg_conv_knobs *knobs
         k.mt = 64;
         k.nt = 128;
         k.stages = 2;
+    } else if (d.pwr_shape) {
+        k.mt = d.pwr.mt;
+        k.nt = d.pwr.nt;
+        k.stages = 1;
+        k.row_loads = 2;
     } else if (d.pw_shape) {
         k.mt = d.pw.mt;
         k.nt = d.pw.nt;
@@ -382,6 +389,10 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
         *kernel = TVG_KERNEL_1X1_DEEP;
         *mt = 64;
         *nt = 128;
+    } else if (d.pwr_shape) {
+        *kernel = TVG_KERNEL_1X1;
+        *mt = d.pwr.mt;
+        *nt = d.pwr.nt;
     } else if (d.pw_shape) {
         *kernel = TVG_KERNEL_1X1;
         *mt = d.pw.mt;

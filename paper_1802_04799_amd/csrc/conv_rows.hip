@@ -476,9 +476,12 @@ bool plan_conv_rows(const ConvProblem &p, RowsPlan *plan)
     // 1x1 without a stride: reductions of 1, 2 and 4 chunks are whole in flight in the other kernel (64 -> 128 56x56 at
     // batch 1 3.1 us against 3.6); strided ones are even (3.4 and 3.5; 4 chunks 4.1 and 3.5).
     // Two chunks, 3x3, without a stride: beyond the split into filter rows the other kernel is as fast (7.3, 7.4).
-    const int most = p.R == 1 ? (nch >= 16 || (nch >= 8 && p.sh == 2) ? 4096 : 2048) : nch >= 16 || (nch >= 8 && p.sh == 2) ? 3584 : 2048;
+    int most_first = 2048;
+    int most = p.R == 1 ? (nch >= 16 || (nch >= 8 && p.sh == 2) ? 4096 : 2048) : nch >= 16 || (nch >= 8 && p.sh == 2) ? 3584 : 2048;
     if (p.R == 1 && p.sh == 1 && (nch == 1 || nch == 2 || nch == 4)) return false;
-    for (int limit : {2048, most})
+    // (maps of an odd number of pixels are tiled by rows: 96 -> 160, 5 images 19x19, 4.7 us there against 5.7)
+    if (p.R == 1 && p.sh == 1 && nch < 16 && p.H * p.W % 4 != 0) most_first = most = 512;
+    for (int limit : {most_first, most})
         for (int rs = p.R == 3 && nch <= 2 ? 1 : 0; rs >= 0; --rs) {
             if (p.R == 3 && p.sh == 1 && nch <= 2 && !rs) break;
             for (int nj : {1, 2, 4})

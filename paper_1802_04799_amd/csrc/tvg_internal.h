@@ -137,6 +137,11 @@ bool conv1x1_pointers_ok(const ConvPointers &ptr);
 tvg_status launch_conv1x1(const ConvProblem &p, const Pw1x1Plan &plan, const ConvPointers &ptr,
                           hipStream_t stream);
 
+// bf16 1x1 without a stride, IC a multiple of 32: pixels staged as they lie in memory, transposed by the LDS reads.
+bool plan_conv1x1_rows(const ConvProblem &p, Pw1x1Plan *plan);
+bool conv1x1_rows_pointers_ok(const ConvPointers &ptr);
+tvg_status launch_conv1x1_rows(const ConvProblem &p, const Pw1x1Plan &plan, const ConvPointers &ptr, hipStream_t stream);
+
 // bf16 1x1 stride-1 kernel for deep reductions (IC a multiple of 128, maps of 4n pixels): wide
 // pixel loads transposed in registers, two steps of 64 channels in flight.
 struct PwDeepPlan {

@@ -69,8 +69,9 @@ def space_for(desc, kernel: int) -> Dict[str, list]:
                 "lds_pitch": [1, 2] if s1 else [0], "row_loads": [1, 2] if odd_small else [0]}
     if kernel in (4, 6):                         # bf16 1x1: its tiles, or the deep-reduction kernel
         deep = desc.stride_w == 1 and desc.c % 128 == 0 and (desc.h * desc.w) % 4 == 0
+        rows = desc.stride_w == 1 and desc.c % 32 == 0
         return {"tile": TILES[1:], "stages": [1, 2] if deep else [1], "split_k": [0], "lds_pitch": [0],
-                "row_loads": [0]}
+                "row_loads": [0, 2] if rows else [0]}
     if kernel == 0:                              # generic kernel: tile rows and the reduction split
         return {"tile": [(64, 0), (128, 0)], "stages": [0],
                 "split_k": [1, 2, 3, 4, 6, 8, 12, 16, 24, 32], "lds_pitch": [0], "row_loads": [0]}
@@ -82,11 +83,14 @@ def _point(tile, stages, split_k, lds_pitch, row_loads) -> Tuple[int, ...]:
 
 
 def _normalise(p: Tuple[int, ...]) -> Tuple[int, ...]:
-    """Knobs that only the pipelined kernel has are dropped from a single-stage point, so that
+    """Knobs that only the pipelined 3x3 kernel has (it always names its split) are dropped from a
+    single-stage point, and the wide loads of the 1x1 kernel from a deep-reduction point, so that
     equivalent points share one measurement."""
     mt, nt, stages, split_k, pitch, rows = p
     if stages == 1:
-        return (mt, nt, 1, 0, 0, 0)
+        return (mt, nt, 1, 0, 0, 0 if split_k else rows)
+    if not split_k and not pitch:
+        return (mt, nt, stages, 0, 0, 0)
     return p
 
 

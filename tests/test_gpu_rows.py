@@ -14,8 +14,8 @@ pytestmark = pytest.mark.gpu
 # (n, ic, h, w, oc, stride, filter), pixels per tile
 EVERY_INSTANCE = [
     ((4, 96, 13, 2, 17, 1, 1), 16), ((3, 96, 1, 22, 33, 1, 1), 32), ((1, 96, 1, 34, 40, 1, 1), 64),
-    ((16, 160, 31, 10, 17, 1, 1), 64), ((2, 96, 5, 5, 33, 1, 1), 16), ((1, 96, 1, 27, 33, 1, 1), 32),
-    ((1, 96, 1, 43, 17, 1, 1), 64), ((16, 256, 17, 17, 1, 1, 1), 64), ((2, 96, 6, 6, 17, 2, 1), 16),
+    ((14, 512, 31, 10, 17, 1, 1), 64), ((2, 96, 5, 5, 33, 1, 1), 16), ((1, 96, 1, 27, 33, 1, 1), 32),
+    ((1, 96, 1, 43, 17, 1, 1), 64), ((16, 512, 17, 17, 1, 1, 1), 64), ((2, 96, 6, 6, 17, 2, 1), 16),
     ((1, 96, 1, 46, 33, 2, 1), 32), ((16, 256, 34, 34, 1, 2, 1), 64), ((2, 96, 5, 5, 17, 2, 1), 16),
     ((1, 96, 1, 45, 33, 2, 1), 32), ((16, 256, 33, 33, 1, 2, 1), 64), ((2, 96, 15, 2, 17, 1, 3), 16),
     ((4, 32, 6, 4, 17, 1, 3), 16), ((7, 96, 1, 2, 33, 1, 3), 16), ((4, 64, 1, 4, 17, 1, 3), 16),
