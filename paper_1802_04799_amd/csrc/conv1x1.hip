@@ -29,6 +29,7 @@ struct PwArgs {
     int N, IC, H, W, OC, OH, OW, stride, npix, relu, mtiles, vmode;
     uint32_t x_bytes, w_bytes;
     int ntiles, m_major;
+    Divider by_tiles, by_ohw, by_ow;      // by_tiles: the tile-order divisor
 };
 
 constexpr int kRow = 80;                 // bytes per LDS row: 32 channels (64 B) + 16 B padding
@@ -63,8 +64,9 @@ __global__ __launch_bounds__(256) void conv1x1_kernel(const PwArgs a)
     // Consecutive tiles (which share an XCD's L2) share the larger operand: the same pixel
     // tile under all channel tiles, or - when the weights outweigh the input - the same
     // channel tile over consecutive pixel tiles.
-    const int m0 = (a.m_major ? tile / a.ntiles : tile % a.mtiles) * MT;
-    const int n0 = (a.m_major ? tile % a.ntiles : tile / a.mtiles) * NT;
+    int r;
+    const int q = divide(tile, a.by_tiles, &r);
+    const int m0 = (a.m_major ? q : r) * MT, n0 = (a.m_major ? r : q) * NT;
     const int HW = a.H * a.W, OHW = a.OH * a.OW;
 
     stage_scale_shift(ss_lds, m0, MT, a.scale, a.shift, a.bias, a.OC, tid, 256);
@@ -81,8 +83,8 @@ __global__ __launch_bounds__(256) void conv1x1_kernel(const PwArgs a)
         bdst[j] = pl * kRow + octet * 16;
         boff[j] = 0;       // pixels past the end read pixel 0; their columns are never stored
         if (p < a.npix) {
-            const int n = p / OHW, rem = p - n * OHW;
-            const int oh = rem / a.OW, ow = rem - oh * a.OW;
+            int rem, ow;
+            const int n = divide(p, a.by_ohw, &rem), oh = divide(rem, a.by_ow, &ow);
             boff[j] = 2u * (uint32_t)((n * a.IC + octet * 8) * HW + oh * a.stride * a.W +
                                       ow * a.stride);
         }
@@ -307,6 +309,9 @@ tvg_status launch_conv1x1(const ConvProblem &p, const Pw1x1Plan &plan, const Con
     a.mtiles = (p.OC + plan.mt - 1) / plan.mt;
     a.ntiles = (p.npix + plan.nt - 1) / plan.nt;
     a.m_major = (size_t)p.OC * p.IC > (size_t)p.N * p.IC * p.H * p.W;
+    a.by_tiles = make_divider(a.m_major ? a.ntiles : a.mtiles);
+    a.by_ohw = make_divider(p.OH * p.OW);
+    a.by_ow = make_divider(p.OW);
     a.vmode = pick_store_vmode(p.dtype, p.OH * p.OW, ptr.y, ptr.residual);
     a.x_bytes = (uint32_t)((size_t)p.N * p.IC * p.H * p.W * 2);
     a.w_bytes = (uint32_t)((size_t)p.OC * p.IC * 2);

@@ -47,9 +47,7 @@ struct DbufArgs {
     int stage_bytes;  // weight planes + patch planes + dump area
     int ss_offset;    // byte offset in LDS of the staged (scale, offset) pairs
     int ntiles, m_major;
-    // reciprocals for fast_div (host-computed 1.0f / x): of the tile-order divisor, OH*OW, OW,
-    // H + 2 and W / PX
-    float inv_tdiv, inv_ohw, inv_ow, inv_vh, inv_wpx;
+    Divider by_tiles, by_ohw, by_ow, by_vh, by_wpx;      // tile-order divisor, OH*OW, OW, H + 2 and W / PX
 };
 
 constexpr int kMT = 64;
@@ -150,13 +148,11 @@ __global__ __launch_bounds__(256 * (MG ? 2 : KG), 2) void conv3x3_dbuf_kernel(co
     const int PWS = a.pws, PWH = PWS >> 1;
     const int stage_bytes = a.stage_bytes;
 
-    // All index arithmetic divides through host-computed float reciprocals; the host admits
-    // this kernel when every dividend stays below 2^22, where fast_div is exact.
     int m0, n0;
     {
         const int tile = xcd_remap(blockIdx.x, gridDim.x);
         int r;
-        const int q = fast_div(tile, a.m_major ? a.ntiles : a.mtiles, a.inv_tdiv, &r);
+        const int q = divide(tile, a.by_tiles, &r);
         m0 = (a.m_major ? q : r) * (MG ? 2 * MT : MT) + (MG ? group * MT : 0);
         n0 = (a.m_major ? r : q) * NT;
     }
@@ -315,9 +311,9 @@ __global__ __launch_bounds__(256 * (MG ? 2 : KG), 2) void conv3x3_dbuf_kernel(co
     {
         const int p_last = min(n0 + NT, a.npix) - 1;
         int ra, rb, t;
-        na = fast_div(n0, OHW, a.inv_ohw, &ra);
-        const int oha = fast_div(ra, a.OW, a.inv_ow, &t);
-        const int nb = fast_div(p_last, OHW, a.inv_ohw, &rb), ohb = fast_div(rb, a.OW, a.inv_ow, &t);
+        na = divide(n0, a.by_ohw, &ra);
+        const int oha = divide(ra, a.by_ow, &t);
+        const int nb = divide(p_last, a.by_ohw, &rb), ohb = divide(rb, a.by_ow, &t);
         vr_lo = na * VH + oha * STRIDE;
         nrows = nb * VH + ohb * STRIDE + 2 - vr_lo + 1;
     }
@@ -337,9 +333,9 @@ __global__ __launch_bounds__(256 * (MG ? 2 : KG), 2) void conv3x3_dbuf_kernel(co
             const int octet = t >= per_octet;
             const int rem = t - (octet ? per_octet : 0);
             int iw, vi;
-            const int vrow = fast_div(rem, WPX, a.inv_wpx, &iw);
+            const int vrow = divide(rem, a.by_wpx, &iw);
             iw *= PX;
-            const int n = fast_div(vr_lo + vrow, VH, a.inv_vh, &vi);
+            const int n = divide(vr_lo + vrow, a.by_vh, &vi);
             const int ih = vi - 1;
             const bool live = t < 2 * per_octet && ih >= 0 && ih < H && n < a.N;
             const int col = iw + 1;
@@ -404,8 +400,8 @@ __global__ __launch_bounds__(256 * (MG ? 2 : KG), 2) void conv3x3_dbuf_kernel(co
         if (j < 4) second_chunk_loads(j, NJ < 4 ? NJ + 2 : 6);
         const int p = n0 + wn * WTN + j * 32 + lrow;
         int rem, ow;
-        const int n = fast_div(p, OHW, a.inv_ohw, &rem);
-        const int oh = fast_div(rem, a.OW, a.inv_ow, &ow);
+        const int n = divide(p, a.by_ohw, &rem);
+        const int oh = divide(rem, a.by_ow, &ow);
         bpix[j] = gbase + kWAll + lhalf * a.pplane +
                   (p < a.npix ? ((n * VH + oh * STRIDE - vr_lo) * PWS + ow) * 16 + (n - na) * a.xp16 : 0);
     }
@@ -825,7 +821,7 @@ bool plan_conv3x3_dbuf(const ConvProblem &p, Patch3x3Plan *plan)
     }
     // two workgroups per CU, or one per CU when the whole grid is resident at once anyway
     if (kg == 1 && lds > 80 * 1024 && !(lds <= 160 * 1024 && plan->tiles <= kComputeUnits)) return false;
-    if (plan->tiles >= (1 << 22)) return false;      // fast_div range of the tile index
+    if (plan->tiles >= (1 << 22)) return false;      // tile numbers
     if (mg) kg = 3;                                   // (the launch's name for the channel split)
     plan->kg = kg;
     plan->dbuf = 1;
@@ -859,11 +855,11 @@ tvg_status launch_conv3x3_dbuf(const ConvProblem &p, const Patch3x3Plan &plan,
     a.w_bytes = (uint32_t)((size_t)p.OC * p.IC * 9 * 2);
     a.ntiles = (p.npix + plan.nt - 1) / plan.nt;
     a.m_major = (size_t)p.OC * p.IC * 9 > (size_t)p.N * p.IC * p.H * p.W;
-    a.inv_tdiv = 1.0f / (float)(a.m_major ? a.ntiles : a.mtiles);
-    a.inv_ohw = 1.0f / (float)(p.OH * p.OW);
-    a.inv_ow = 1.0f / (float)p.OW;
-    a.inv_vh = 1.0f / (float)(p.H + 2);
-    a.inv_wpx = 1.0f / (float)((p.W + plan.px - 1) / plan.px);
+    a.by_tiles = make_divider(a.m_major ? a.ntiles : a.mtiles);
+    a.by_ohw = make_divider(p.OH * p.OW);
+    a.by_ow = make_divider(p.OW);
+    a.by_vh = make_divider(p.H + 2);
+    a.by_wpx = make_divider((p.W + plan.px - 1) / plan.px);
     switch (plan.nt) {
     case 256: return launch_pt<1, 2>(a, plan.lds_bytes, p.sh, plan.pt, plan.px, plan.kg, stream);
     case 128:

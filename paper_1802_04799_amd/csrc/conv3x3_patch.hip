@@ -49,6 +49,7 @@ struct PatchArgs {
     uint32_t x_bytes, w_bytes;
     int ss_offset;    // byte offset in LDS of the staged (scale, offset) pairs
     int ntiles, m_major;
+    Divider by_tiles, by_ohw, by_ow, by_vh, by_wpx;      // tile-order divisor, OH*OW, OW, H + 2 and W / PX
     // Two heads (tvg_conv2d_fused_dual): output channels [0, oc1) go to y with `relu` and the
     // residual, channels [oc1, OC) to y2 with relu2; oc1 = 0: one head.  centre2: the filters of
     // head 2 are zero outside their centre tap (a 1x1 convolution of the same input), its tiles
@@ -108,8 +109,9 @@ __global__ __launch_bounds__(256, 2) void conv3x3_patch_kernel(const PatchArgs a
     // Consecutive tiles (which share an XCD's L2) share the larger operand: the same pixel
     // tile under all channel tiles, or - when the weights outweigh the input - the same
     // channel tile over consecutive pixel tiles.
-    const int m0 = (a.m_major ? tile / a.ntiles : tile % a.mtiles) * MT;
-    const int n0 = (a.m_major ? tile % a.ntiles : tile / a.mtiles) * NT;
+    int tr;
+    const int tq = divide(tile, a.by_tiles, &tr);
+    const int m0 = (a.m_major ? tq : tr) * MT, n0 = (a.m_major ? tr : tq) * NT;
 
     const int H = a.H, W = a.W, HW = H * W, OHW = a.OH * a.OW;
     const int VH = H + 2, PW = W + 2;
@@ -119,15 +121,11 @@ __global__ __launch_bounds__(256, 2) void conv3x3_patch_kernel(const PatchArgs a
     // would be 96 bytes apart and collide in pairs.
     const int HALF = (PW + 1) / 2;
 
-    // Index arithmetic below divides by OH*OW, OW, W and H+2 only; the host admits this
-    // kernel when every dividend stays below 2^22, where fast_div is exact.
-    const float inv_ohw = 1.0f / (float)OHW, inv_ow = 1.0f / (float)a.OW;
-    const float inv_vh = 1.0f / (float)VH;
-
     // ---- tile geometry (uniform) ---------------------------------------------------------
     const int p_last = min(n0 + NT, a.npix) - 1;
-    const int na = n0 / OHW, oha = (n0 - na * OHW) / a.OW;
-    const int nb = p_last / OHW, ohb = (p_last - nb * OHW) / a.OW;
+    int rem0, ow0;
+    const int na = divide(n0, a.by_ohw, &rem0), oha = divide(rem0, a.by_ow, &ow0);
+    const int nb = divide(p_last, a.by_ohw, &rem0), ohb = divide(rem0, a.by_ow, &ow0);
     const int vr_lo = na * VH + oha * STRIDE;
     const int nrows = nb * VH + ohb * STRIDE + 2 - vr_lo + 1;
     const int npos = nrows * PW;
@@ -143,7 +141,6 @@ __global__ __launch_bounds__(256, 2) void conv3x3_patch_kernel(const PatchArgs a
         // a row that is not a multiple of PX ends in a task with fewer pixels; its load reads on
         // into the next row (or, at the very end of x, past the buffer: zeros), 4-byte aligned
         const int WPX = (W + PX - 1) / PX;
-        const float inv_wpx = 1.0f / (float)WPX;
         const int per_octet = nrows * WPX;
 #pragma unroll
         for (int j = 0; j < PT; ++j) {
@@ -155,9 +152,9 @@ __global__ __launch_bounds__(256, 2) void conv3x3_patch_kernel(const PatchArgs a
                 const int octet = t >= per_octet;
                 const int rem = t - octet * per_octet;
                 int iw, vi;
-                const int vrow = fast_div(rem, WPX, inv_wpx, &iw);
+                const int vrow = divide(rem, a.by_wpx, &iw);
                 iw *= PX;
-                const int n = fast_div(vr_lo + vrow, VH, inv_vh, &vi);
+                const int n = divide(vr_lo + vrow, a.by_vh, &vi);
                 const int ih = vi - 1;
                 if (ih >= 0 && ih < H && n < a.N) {
                     goff[j] = 2u * (uint32_t)((n * a.IC + octet * 8) * HW + ih * W + iw);
@@ -178,8 +175,8 @@ __global__ __launch_bounds__(256, 2) void conv3x3_patch_kernel(const PatchArgs a
         pb[j] = lhalf * pplane;
         if (p < a.npix) {
             int rem, ow;
-            const int n = fast_div(p, OHW, inv_ohw, &rem);
-            const int oh = fast_div(rem, a.OW, inv_ow, &ow);
+            const int n = divide(p, a.by_ohw, &rem);
+            const int oh = divide(rem, a.by_ow, &ow);
             // (stride 2: column 2*ow is even, at position ow of its row)
             pb[j] += ((n * VH + oh * STRIDE - vr_lo) * PW + ow) * kWordBytes;
         }
@@ -465,7 +462,7 @@ bool plan_conv3x3_patch(const ConvProblem &p, Patch3x3Plan *plan, int single_sta
     if (p.dtype != TVG_BF16 || p.R != 3 || p.S != 3 || p.ph != 1 || p.pw != 1) return false;
     if (p.sh != p.sw || (p.sh != 1 && p.sh != 2)) return false;
     if (p.IC % kChunk != 0) return false;
-    if (p.npix >= (1 << 22) || (long)p.N * (p.H + 2) >= (1 << 22)) return false;   // fast_div range
+    if (p.npix >= (1 << 22) || (long)p.N * (p.H + 2) >= (1 << 22)) return false;   // tile and pixel numbers
     // (two-head launches: the single-stage kernel only, channel tiles that divide head 1)
     const bool dual = single_stage_mt_divides > 0;
     const Knobs knobs = dual ? Knobs{0, 0, 1, 0, 0, 0} : forced_knobs(p);
@@ -560,6 +557,11 @@ tvg_status launch_conv3x3_patch(const ConvProblem &p, const Patch3x3Plan &plan,
     const int ntiles = (p.npix + plan.nt - 1) / plan.nt;
     a.ntiles = ntiles;
     a.m_major = (size_t)p.OC * p.IC * 9 > (size_t)p.N * p.IC * p.H * p.W;
+    a.by_tiles = make_divider(a.m_major ? a.ntiles : a.mtiles);
+    a.by_ohw = make_divider(p.OH * p.OW);
+    a.by_ow = make_divider(p.OW);
+    a.by_vh = make_divider(p.H + 2);
+    a.by_wpx = make_divider((p.W + plan.px - 1) / plan.px);
     if (plan.nt == 512) {
         if (p.sh == 1 && plan.px == 8 && plan.pt <= 1 && !dual)
             return launch_instance_d<64, 512, 1, 1, 8, false>(a, ntiles, plan.lds_bytes, stream);

@@ -42,6 +42,7 @@ struct StemArgs {
     int nrows;          // staged virtual rows per tile (maximum over tiles)
     int ntiles, mtiles, wg_per_mtile;
     uint32_t x_bytes, w_bytes;
+    Divider by_ohw, by_ow, by_vh;
 };
 
 constexpr int kNT = 256;                 // pixels per tile
@@ -138,18 +139,16 @@ __global__ __launch_bounds__(256, 2) void conv_stem_s2_kernel(const StemArgs a)
     const TailArgs tail{a.scale, a.shift, a.bias, a.residual, a.y, a.OC, OHW, a.npix, a.relu};
 
     uint4v lreg[LT];
-    // index arithmetic through the float reciprocal (exact below 2^22, checked on the host)
-    const float inv_ohw = 1.0f / (float)OHW, inv_ow = 1.0f / (float)a.OW, inv_vh = 1.0f / (float)VH;
     auto first_vrow = [&](int tile) {
         int rem, ow;
-        const int n = fast_div(tile * kNT, OHW, inv_ohw, &rem);
-        const int oh = fast_div(rem, a.OW, inv_ow, &ow);
+        const int n = divide(tile * kNT, a.by_ohw, &rem);
+        const int oh = divide(rem, a.by_ow, &ow);
         return n * VH + oh * 2;
     };
     auto load_tile = [&](int tile) {
         const int vr_lo = first_vrow(tile);
         int vi_lo;
-        const int n_lo = fast_div(vr_lo, VH, inv_vh, &vi_lo);
+        const int n_lo = divide(vr_lo, a.by_vh, &vi_lo);
 #pragma unroll
         for (int j = 0; j < LT; ++j) {
             int vi = vi_lo + rslot[j], n = n_lo;
@@ -191,8 +190,8 @@ __global__ __launch_bounds__(256, 2) void conv_stem_s2_kernel(const StemArgs a)
             pb[j] = 0;
             if (p < a.npix) {
                 int rem, ow;
-                const int n = fast_div(p, OHW, inv_ohw, &rem);
-                const int oh = fast_div(rem, a.OW, inv_ow, &ow);
+                const int n = divide(p, a.by_ohw, &rem);
+                const int oh = divide(rem, a.by_ow, &ow);
                 pb[j] = (n * VH + oh * 2 - vr_lo) * pitch + ow * 4;
             }
         }
@@ -279,7 +278,7 @@ bool plan_conv7x7s2_stem(const ConvProblem &p, StemPlan *plan)
         p.ph != p.R / 2 || p.pw != p.R / 2)
         return false;
     if (p.IC > 4 || p.W % 8 != 0) return false;
-    if (p.npix >= (1 << 22) || (long)p.N * (p.H + 2 * p.ph) >= (1 << 22)) return false;   // fast_div range
+    if (p.npix >= (1 << 22) || (long)p.N * (p.H + 2 * p.ph) >= (1 << 22)) return false;   // pixel and row numbers
     if ((size_t)p.N * p.IC * p.H * p.W * 2 > (size_t)kOutOfRange) return false;
     const int rows = max_stem_rows(p);
     if (rows > p.H + 2 * p.ph) return false;            // a tile may wrap into the next image once
@@ -314,6 +313,9 @@ tvg_status launch_conv7x7s2_stem(const ConvProblem &p, const StemPlan &plan, con
     a.npix = p.npix; a.relu = p.relu | (p.stream_out << 1);
     a.vmode = pick_store_vmode(p.dtype, p.OH * p.OW, ptr.y, ptr.residual);
     a.nrows = plan.rows;
+    a.by_ohw = make_divider(p.OH * p.OW);
+    a.by_ow = make_divider(p.OW);
+    a.by_vh = make_divider(p.H + 2 * p.ph);
     a.ntiles = (p.npix + kNT - 1) / kNT;
     a.mtiles = (p.OC + plan.mt - 1) / plan.mt;
     // persistent workgroups: two per CU, shared between the output-channel tiles

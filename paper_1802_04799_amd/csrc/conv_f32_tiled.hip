@@ -48,6 +48,7 @@ struct TiledArgs {
     int pitch, plane;                     // patch floats per row and per channel
     int mtiles, tpi, nchunks, relu, vmode, buf_floats;
     uint32_t x_bytes, w_bytes;
+    Divider by_mtiles, by_tpi, by_ow, by_plane, by_pitch;
 };
 
 __device__ __forceinline__ float load_f32(__amdgpu_buffer_rsrc_t r, uint32_t off)
@@ -70,14 +71,12 @@ __global__ __launch_bounds__(256, 2) void conv_f32_tiled_kernel(const TiledArgs 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave & 1, wn = wave >> 1;
     const int lrow = lane & 31, lhalf = lane >> 5;
-    int b = xcd_remap(blockIdx.x, gridDim.x);
-    const int mt = b % a.mtiles;
-    b /= a.mtiles;
-    const int pt = b % a.tpi, n = b / a.tpi;
+    int mt, pt, ow0;
+    const int n = divide(divide(xcd_remap(blockIdx.x, gridDim.x), a.by_mtiles, &mt), a.by_tpi, &pt);
     const int m0 = mt * kMT, p0 = pt * NT;
     const int npx = min(NT, a.OHW - p0);
-    const int oh0 = p0 / a.OW;
-    const int nrows = ((p0 + npx - 1) / a.OW - oh0) * a.vsh + R;
+    const int oh0 = divide(p0, a.by_ow, &ow0);
+    const int nrows = (divide(p0 + npx - 1, a.by_ow, &ow0) - oh0) * a.vsh + R;
 
     const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.x), 0, a.x_bytes, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.w), 0, a.w_bytes, kRsrcFlags);
@@ -87,8 +86,8 @@ __global__ __launch_bounds__(256, 2) void conv_f32_tiled_kernel(const TiledArgs 
 #pragma unroll
     for (int k = 0; k < PT; ++k) {
         const int e = tid + k * 256;
-        const int ch = e / a.plane, v = e - ch * a.plane;
-        const int row = v / a.pitch, col = v - row * a.pitch;
+        int v, col;
+        const int ch = divide(e, a.by_plane, &v), row = divide(v, a.by_pitch, &col);
         const int ih = R == 1 ? (oh0 + row) * a.stride : oh0 * a.stride + row - a.ph;
         const int iw = R == 1 ? col * a.stride : col - a.pw;
         const bool ok = ch < CIC && row < nrows && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
@@ -151,7 +150,8 @@ __global__ __launch_bounds__(256, 2) void conv_f32_tiled_kernel(const TiledArgs 
     for (int j = 0; j < NJ; ++j) {
         const int pl = wn * 32 * NJ + j * 32 + lrow;
         const int p = p0 + (pl < npx ? pl : 0);            // (lanes past the end shadow pixel 0; dropped)
-        const int oh = p / a.OW, ow = p - oh * a.OW;
+        int ow;
+        const int oh = divide(p, a.by_ow, &ow);
         bbase[j] = kMT * WP + lhalf * CPH * a.plane + (oh - oh0) * a.vsh * a.pitch + ow * a.csw;
     }
 
@@ -366,6 +366,8 @@ tvg_status launch_conv_f32_tiled(const ConvProblem &p, const F32TiledPlan &t, co
     a.relu = p.relu | (p.stream_out << 1);
     a.vmode = pick_store_vmode(p.dtype, a.OHW, ptr.y, ptr.residual);
     a.buf_floats = t.buf_floats;
+    a.by_mtiles = make_divider(a.mtiles); a.by_tpi = make_divider(a.tpi); a.by_ow = make_divider(a.OW);
+    a.by_plane = make_divider(a.plane); a.by_pitch = make_divider(a.pitch);
     a.x_bytes = (uint32_t)((size_t)p.N * p.IC * a.HW * 4);
     a.w_bytes = (uint32_t)((size_t)p.OC * p.K * 4);
     // 1x1: the fewest chains whose error is not above that of the kernels that ran these problems before (the

@@ -38,13 +38,13 @@ __global__ __launch_bounds__(256) void maxpool3x3s2_kernel(const T *__restrict__
 // Four outputs per lane; grid.y = plane, lanes run over (output row, group of four outputs).
 __global__ __launch_bounds__(256) void maxpool3x3s2_bf16x4_kernel(const bf16_t *__restrict__ x,
                                                                  bf16_t *__restrict__ y, int H, int W,
-                                                                 int OH, int OW, float inv_qw)
+                                                                 int OH, int OW, Divider by_qw)
 {
     const int QW = OW >> 2;
     const int g = blockIdx.x * 256 + threadIdx.x;
     if (g >= OH * QW) return;
     int q;
-    const int oh = fast_div(g, QW, inv_qw, &q);
+    const int oh = divide(g, by_qw, &q);
     const bf16_t *src = x + (size_t)blockIdx.y * H * W + 8 * q;     // input column 2 * (4 q)
     float m[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
@@ -87,7 +87,7 @@ tvg_status launch_maxpool3x3s2(int N, int C, int H, int W, int dtype, const void
             hipLaunchKernelGGL(maxpool3x3s2_bf16x4_kernel, dim3((OH * (OW / 4) + 255) / 256, np), dim3(256),
                                0, stream, static_cast<const bf16_t *>(x) + (size_t)p0 * H * W,
                                static_cast<bf16_t *>(y) + (size_t)p0 * OH * OW, H, W, OH, OW,
-                               1.0f / (float)(OW / 4));
+                               make_divider(OW / 4));
         else if (dtype == TVG_BF16)
             hipLaunchKernelGGL((maxpool3x3s2_kernel<bf16_t>), grid, dim3(256), 0, stream,
                                static_cast<const bf16_t *>(x) + (size_t)p0 * H * W,

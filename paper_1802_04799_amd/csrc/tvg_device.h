@@ -78,8 +78,7 @@ inline Divider make_divider(int d)
 {
     Divider v{(uint32_t)d, 0, 0};
     if (d > 1) {
-        int l = 1;
-        while (((int64_t)1 << l) < d) ++l;                 // ceil(log2 d)
+        const int l = 32 - __builtin_clz((uint32_t)(d - 1));             // ceil(log2 d)
         v.m = (uint32_t)(((uint64_t)1 << (31 + l)) / (uint64_t)d + 1);
         v.s = (uint32_t)(l - 1);
     }
