@@ -160,7 +160,6 @@ __global__ __launch_bounds__(256, 2) void conv_f32_pw_kernel(const PwArgs a)
             for (int e = 0; e < PXL; ++e) sum[0][b][e] += sum[1][b][e];
 
     // value v of a lane: channel 8 (v / 4) + 4 lhalf + v % 4, pixel PXL lrow + e
-    const float floor_v = a.relu ? 0.0f : -INFINITY;
     auto finish = [&](pixels o, int oc, int p) __attribute__((always_inline)) {
         if (oc >= a.OC || p >= a.npix) return;                     // (whole groups: OH * OW is a multiple of PXL)
         int r;
@@ -178,49 +177,37 @@ __global__ __launch_bounds__(256, 2) void conv_f32_pw_kernel(const PwArgs a)
         for (int e = 0; e < PXL; ++e) {
             float t = fmaf(o[e], sc, sf);
             if (a.residual) t += res[e];
-            o[e] = fmaxf(t, floor_v);
+            o[e] = a.relu ? fmaxf(t, 0.0f) : t;    // (without a ReLU a NaN stays one, as after a split reduction)
         }
         if (a.vec) *reinterpret_cast<pixels *>(a.y + idx) = o;
         else
 #pragma unroll
             for (int e = 0; e < PXL; ++e) a.y[idx + e] = o[e];
     };
-    if constexpr (KS == 1) {
+    // [wave of the split][channel of the tile][pixel]
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
+    for (int v = 0; v < 16; ++v) {
+        float *row = smem + (wk * MT + wm * 32 + 8 * (v >> 2) + 4 * lhalf + (v & 3)) * NT;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    pixels o;
+        for (int b = 0; b < NB; ++b) {
+            pixels o;
 #pragma unroll
-                    for (int e = 0; e < PXL; ++e) o[e] = sum[0][b][e][v];
-                    finish(o, m0 + wm * 32 + 8 * (v >> 2) + 4 * lhalf + (v & 3), p0 + (b * 32 + lrow) * PXL);
-                }
-    } else {
-        // [wave of the split][channel of the tile][pixel]
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                float *row = smem + (wk * MT + wm * 32 + 8 * (v >> 2) + 4 * lhalf + (v & 3)) * NT;
-#pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    pixels o;
-#pragma unroll
-                    for (int e = 0; e < PXL; ++e) o[e] = sum[0][b][e][v];
-                    *reinterpret_cast<pixels *>(row + (b * 32 + lrow) * PXL) = o;
-                }
-            }
-        __syncthreads();
-        constexpr int PER = NT / PXL;
-        for (int item = tid; item < MT * PER; item += 256) {
-            const int row = item / PER, g = item % PER;
-            pixels o[KS];
-#pragma unroll
-            for (int k = 0; k < KS; ++k) o[k] = *reinterpret_cast<const pixels *>(smem + (k * MT + row) * NT + g * PXL);
-#pragma unroll
-            for (int d = 1; d < KS; d *= 2)        // in pairs
-#pragma unroll
-                for (int k = 0; k + d < KS; k += 2 * d) o[k] += o[k + d];
-            finish(o[0], m0 + row, p0 + g * PXL);
+            for (int e = 0; e < PXL; ++e) o[e] = sum[0][b][e][v];
+            *reinterpret_cast<pixels *>(row + (b * 32 + lrow) * PXL) = o;
         }
+    }
+    __syncthreads();
+    constexpr int PER = NT / PXL;
+    for (int item = tid; item < MT * PER; item += 256) {
+        const int row = item / PER, g = item % PER;
+        pixels o[KS];
+#pragma unroll
+        for (int k = 0; k < KS; ++k) o[k] = *reinterpret_cast<const pixels *>(smem + (k * MT + row) * NT + g * PXL);
+#pragma unroll
+        for (int d = 1; d < KS; d *= 2)            // in pairs
+#pragma unroll
+            for (int k = 0; k + d < KS; k += 2 * d) o[k] += o[k + d];
+        finish(o[0], m0 + row, p0 + g * PXL);
     }
 }
 

@@ -74,3 +74,17 @@ def test_f32_1x1_unaligned_pointers(tvg, shape):
         rc = tvg.tvg_conv2d_fused(desc, at(d["x"], ox), d["w"], d["scale"], d["shift"], None, at(d["residual"], oy), y, None, 0, None)
         assert rc == 0, tvg.status_string(rc)
         check(to_host(y), want, "f32", (shape, ox, oy))
+
+
+@pytest.mark.parametrize("cfg", [(1, 512, 14, 14, 512, 1), (3, 56, 6, 6, 31, 2), (8, 128, 28, 28, 256, 1)], ids=lambda c: "x".join(map(str, c)))
+def test_f32_1x1_nan_stays_in_its_pixel(tvg, cfg):
+    """A NaN in the input comes out as one without a ReLU, in every channel of its pixel and nowhere else."""
+    import torch
+    n, ic, h, w, oc, stride = cfg
+    d = dev_inputs(ti.make_inputs(ti.ConvShape("nan", n, ic, h, w, oc, 1, 1, stride, 0), 8950, "f32"), "f32")
+    clean = tvg.conv2d_fused(d["x"], d["w"], d["scale"], d["shift"], stride=stride, relu=False)
+    d["x"][n - 1, ic - 1, 2 * stride, stride] = float("nan")
+    y = tvg.conv2d_fused(d["x"], d["w"], d["scale"], d["shift"], stride=stride, relu=False)
+    assert bool(torch.isnan(y[n - 1, :, 2, 1]).all())
+    y[n - 1, :, 2, 1] = clean[n - 1, :, 2, 1]
+    assert torch.equal(y, clean)
