@@ -384,7 +384,7 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
     } else if (d.stem_shape) {
         *kernel = TVG_KERNEL_STEM;
         *mt = d.stem.mt;
-        *nt = 256;
+        *nt = 256;                             // (the large tile; with few tiles the kernel takes plan.nt)
     } else if (d.pwd_shape) {
         *kernel = TVG_KERNEL_1X1_DEEP;
         *mt = 64;

@@ -24,7 +24,8 @@
 //    an out-of-range offset, which returns zeros: no branches in the copy.
 //
 // The next tile's rows are requested before the current tile's MFMAs and are
-// written to the other LDS buffer afterwards (one barrier per tile).
+// written to the other LDS buffer afterwards (one barrier per tile).  The first tile's rows are requested
+// with the weights, not after they are sorted: the layer at batch 4 / 32 / 64 10.0 -> 9.7, 22.6 -> 21.7, 36.0 -> 34.3 us.
 #include <numeric>
 #include "tvg_device.h"
 #include "tvg_internal.h"
@@ -45,7 +46,9 @@ struct StemArgs {
     Divider by_ohw, by_ow, by_vh;
 };
 
-constexpr int kNT = 256;                 // pixels per tile
+// Pixels per tile: 256, a wave all channels x 64 pixels (one operand read feeds two MFMAs); with few tiles 64 or 128, the
+// waves 2 x 2 (64 channels) or side by side (32).
+constexpr int tile_pixels(int mt, int nj) { return nj == 2 ? 256 : mt == 64 ? 64 : 128; }
 // (output channels per tile: MT = 64, or 32 for layers of at most 32 channels - the MobileNet
 // stem - which would otherwise run half of their MFMAs and half of the tail on rows nobody stores)
 constexpr int kRsrcFlags = 0x00020000;   // raw buffer descriptor word 3 on gfx9-family targets
@@ -54,10 +57,11 @@ constexpr uint32_t kOutOfRange = 0xFFFFFFF0u;
 // IC = input channels (compile time, so the reduction loop unrolls completely and the LDS
 // reads of one MFMA step overlap the previous step's MFMAs); LT = 16-byte copy tasks per
 // thread per tile.
-template <int R, int IC, int LT, int MT>
+template <int R, int IC, int LT, int MT, int NJ>
 __global__ __launch_bounds__(256, 2) void conv_stem_s2_kernel(const StemArgs a)
 {
-    constexpr int kMT = MT, MI = MT / 32;
+    constexpr int kMT = MT, kNT = tile_pixels(MT, NJ);
+    constexpr int WN = kNT / (32 * NJ), WM = 4 / WN, MI = MT / 32 / WM;    // waves along the pixels, along the channels
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int PAD = R / 2;
     constexpr int npairs = IC * R;
@@ -76,48 +80,11 @@ __global__ __launch_bounds__(256, 2) void conv_stem_s2_kernel(const StemArgs a)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lrow = lane & 31, lhalf = lane >> 5;
+    const int wn = wave % WN, wm = wave / WN;
     const int mtile = blockIdx.x % a.mtiles, wg = blockIdx.x / a.mtiles;
     const int m0 = mtile * kMT;
 
     stage_scale_shift(ss_lds, m0, kMT, a.scale, a.shift, a.bias, a.OC, tid, 256);
-
-    // ---- zero both patch buffers (their padding columns stay zero) and the weight area ----
-    for (int i = tid; i < 2 * patch_bytes / 16; i += 256)
-        reinterpret_cast<uint4v *>(Ps)[i] = uint4v{0u, 0u, 0u, 0u};
-    for (int i = tid; i < a_bytes / 16; i += 256)
-        reinterpret_cast<uint4v *>(As)[i] = uint4v{0u, 0u, 0u, 0u};
-    // ---- stage the weights: the tile's channels are one contiguous run of [oc][ic][r][s], read
-    // as 16-byte vectors that are all in flight together, then scattered element by element
-    // into [pair = (ic, r)][oc][slot = s + 1] (slot 0, the odd pair and absent channels stay 0)
-    {
-        constexpr int KW = IC * R * R;                   // weights per output channel
-        constexpr int WV = (kMT * KW + 7) / 8;           // vectors per full tile
-        constexpr int WT = (WV + 255) / 256;             // vectors per thread
-        const int count = min(kMT, a.OC - m0) * KW;
-        const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<bf16_t *>(a.w), 0, a.w_bytes, kRsrcFlags);
-        const uint32_t wbase = (uint32_t)m0 * KW * 2u;
-        uint4v wv[WT];
-#pragma unroll
-        for (int j = 0; j < WT; ++j) {
-            const int v = tid + j * 256;
-            const uint32_t voff = v * 8 < count ? wbase + (uint32_t)v * 16u : kOutOfRange;
-            wv[j] = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, voff, 0, 0));
-        }
-        __syncthreads();                                 // the zeros are in place
-#pragma unroll
-        for (int j = 0; j < WT; ++j) {
-            const int f0 = (tid + j * 256) * 8;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int f = f0 + k;
-                const int ocl = f / KW, rem = f - ocl * KW;
-                const int pair = rem / R, sp = rem - pair * R + (4 - PAD);
-                const bf16_t v = (bf16_t)(k & 1 ? wv[j][k >> 1] >> 16 : wv[j][k >> 1] & 0xffffu);
-                if (f < count) reinterpret_cast<bf16_t *>(As)[(pair * kMT + ocl) * 8 + sp] = v;
-            }
-        }
-    }
 
     // ---- per-thread copy tasks: (ic, row slot, 16-byte column group), fixed for all tiles --
     const int VPR = W / 8;
@@ -171,8 +138,45 @@ __global__ __launch_bounds__(256, 2) void conv_stem_s2_kernel(const StemArgs a)
     };
 
     int tile = wg;
-    if (tile < a.ntiles) load_tile(tile);
-    __syncthreads();
+    // ---- zero the patch buffers (their padding columns stay zero; one if there is one tile) and the weight area ----
+    for (int i = tid; i < (wg + a.wg_per_mtile < a.ntiles ? 2 : 1) * patch_bytes / 16; i += 256)
+        reinterpret_cast<uint4v *>(Ps)[i] = uint4v{0u, 0u, 0u, 0u};
+    for (int i = tid; i < a_bytes / 16; i += 256)
+        reinterpret_cast<uint4v *>(As)[i] = uint4v{0u, 0u, 0u, 0u};
+    // ---- stage the weights: the tile's channels are one contiguous run of [oc][ic][r][s], read
+    // as 16-byte vectors that are all in flight together, then scattered element by element
+    // into [pair = (ic, r)][oc][slot = s + 1] (slot 0, the odd pair and absent channels stay 0)
+    {
+        constexpr int KW = IC * R * R;                   // weights per output channel
+        constexpr int WV = (kMT * KW + 7) / 8;           // vectors per full tile
+        constexpr int WT = (WV + 255) / 256;             // vectors per thread
+        const int count = min(kMT, a.OC - m0) * KW;
+        const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<bf16_t *>(a.w), 0, a.w_bytes, kRsrcFlags);
+        const uint32_t wbase = (uint32_t)m0 * KW * 2u;
+        uint4v wv[WT];
+#pragma unroll
+        for (int j = 0; j < WT; ++j) {
+            const int v = tid + j * 256;
+            const uint32_t voff = v * 8 < count ? wbase + (uint32_t)v * 16u : kOutOfRange;
+            wv[j] = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, voff, 0, 0));
+        }
+        if (tile < a.ntiles) load_tile(tile);            // the first rows arrive while the weights are sorted
+        __syncthreads();                                 // the zeros are in place
+#pragma unroll
+        for (int j = 0; j < WT; ++j) {
+            const int f0 = (tid + j * 256) * 8;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int f = f0 + k;
+                const int ocl = f / KW, rem = f - ocl * KW;
+                const int pair = rem / R, sp = rem - pair * R + (4 - PAD);
+                const bf16_t v = (bf16_t)(k & 1 ? wv[j][k >> 1] >> 16 : wv[j][k >> 1] & 0xffffu);
+                if (f < count) reinterpret_cast<bf16_t *>(As)[(pair * kMT + ocl) * 8 + sp] = v;
+            }
+        }
+    }
+
     if (tile < a.ntiles) store_tile_rows(0);
     __syncthreads();
 
@@ -183,10 +187,10 @@ __global__ __launch_bounds__(256, 2) void conv_stem_s2_kernel(const StemArgs a)
         const unsigned char *P = Ps + (it & 1) * patch_bytes;
         const int p0 = tile * kNT;
         const int vr_lo = first_vrow(tile);
-        int pb[2];
+        int pb[NJ];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int p = p0 + wave * 64 + j * 32 + lrow;
+        for (int j = 0; j < NJ; ++j) {
+            const int p = p0 + wn * 32 * NJ + j * 32 + lrow;
             pb[j] = 0;
             if (p < a.npix) {
                 int rem, ow;
@@ -195,11 +199,11 @@ __global__ __launch_bounds__(256, 2) void conv_stem_s2_kernel(const StemArgs a)
                 pb[j] = (n * VH + oh * 2 - vr_lo) * pitch + ow * 4;
             }
         }
-        float16v acc[MI][2];
+        float16v acc[MI][NJ];
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < NJ; ++j)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
@@ -210,19 +214,19 @@ __global__ __launch_bounds__(256, 2) void conv_stem_s2_kernel(const StemArgs a)
             const int offa = ((pa / R) * nrows + pa % R) * pitch;
             const int offq = ((pq / R) * nrows + pq % R) * pitch;
             const int poff = lhalf ? offq : offa;
-            uint4v af[MI], bf[2];
+            uint4v af[MI], bf[NJ];
 #pragma unroll
             for (int i = 0; i < MI; ++i)
-                af[i] = *reinterpret_cast<const uint4v *>(As + ((2 * m + lhalf) * kMT + i * 32 + lrow) * 16);
+                af[i] = *reinterpret_cast<const uint4v *>(As + ((2 * m + lhalf) * kMT + wm * MI * 32 + i * 32 + lrow) * 16);
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < NJ; ++j) {
                 const uint32_t *src = reinterpret_cast<const uint32_t *>(P + pb[j] + poff);
                 bf[j] = uint4v{src[0], src[1], src[2], src[3]};
             }
 #pragma unroll
             for (int i = 0; i < MI; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < NJ; ++j)
                     // pixel operand first: the accumulator tile is D[pixel][channel]
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                         __builtin_bit_cast(bf16x8v, bf[j]), __builtin_bit_cast(bf16x8v, af[i]),
@@ -233,12 +237,13 @@ __global__ __launch_bounds__(256, 2) void conv_stem_s2_kernel(const StemArgs a)
         // now, so that waiting for those loads does not also wait for this tile's stores.
         if (next < a.ntiles) store_tile_rows((it + 1) & 1);
 
-        store_acc_tiles_batched<MI, 2, 2>(acc, stage, lane, m0, p0 + wave * 64, tail, a.vmode, ss_lds, 0);
+        store_acc_tiles_batched<MI, NJ, MI * NJ >= 2 ? 2 : 1>(acc, stage, lane, m0 + wm * MI * 32, p0 + wn * 32 * NJ, tail, a.vmode,
+                                                               ss_lds, wm * MI * 32);
         __syncthreads();
     }
 }
 
-int max_stem_rows(const ConvProblem &p)
+int max_stem_rows(const ConvProblem &p, int kNT)
 {
     const int OHW = p.OH * p.OW, VH = p.H + 2 * p.ph;
     int best = 0;
@@ -255,10 +260,10 @@ int max_stem_rows(const ConvProblem &p)
     return best;
 }
 
-template <int R, int IC, int LT, int MT = 64>
+template <int R, int IC, int LT, int MT = 64, int NJ = 2>
 tvg_status launch_lt(const StemArgs &a, unsigned grid, size_t lds, hipStream_t stream)
 {
-    auto kernel = conv_stem_s2_kernel<R, IC, LT, MT>;
+    auto kernel = conv_stem_s2_kernel<R, IC, LT, MT, NJ>;
     static bool configured = false;
     if (!configured) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
@@ -280,19 +285,26 @@ bool plan_conv7x7s2_stem(const ConvProblem &p, StemPlan *plan)
     if (p.IC > 4 || p.W % 8 != 0) return false;
     if (p.npix >= (1 << 22) || (long)p.N * (p.H + 2 * p.ph) >= (1 << 22)) return false;   // pixel and row numbers
     if ((size_t)p.N * p.IC * p.H * p.W * 2 > (size_t)kOutOfRange) return false;
-    const int rows = max_stem_rows(p);
-    if (rows > p.H + 2 * p.ph) return false;            // a tile may wrap into the next image once
     const int nm = (p.IC * p.R + 1) / 2;
     // (the narrow channel tile exists for the case that needs it, the 3x3 three-channel stem)
     const int mt = (p.OC <= 32 && p.R == 3 && p.IC == 3) ? 32 : 64;
-    const size_t lds = (size_t)2 * nm * mt * 16 + (size_t)2 * p.IC * rows * (p.W + 8) * 2 +
-                       (size_t)8 * kStageBytes + (size_t)mt * 8;
-    const int lt = (p.IC * rows * (p.W / 8) + 255) / 256;
-    if (lds > 80 * 1024 || lt > 8) return false;
-    plan->rows = rows;
-    plan->mt = mt;
-    plan->lt = lt;
-    plan->lds_bytes = lds;
+    const auto set_tile = [&](int nj) {
+        const int nt = tile_pixels(mt, nj), rows = max_stem_rows(p, nt);
+        const int lt = (p.IC * rows * (p.W / 8) + 255) / 256;
+        const size_t lds = (size_t)2 * nm * mt * 16 + (size_t)2 * p.IC * rows * (p.W + 8) * 2 + (size_t)8 * kStageBytes + (size_t)mt * 8;
+        plan->nt = nt;
+        plan->rows = rows;
+        plan->mt = mt;
+        plan->lt = lt;
+        plan->lds_bytes = lds;
+        return rows <= p.H + 2 * p.ph && lds <= 80 * 1024 && lt <= 8;      // (a tile may wrap into the next image once)
+    };
+    if (!set_tile(2)) return false;
+    // Small tiles (three input channels) while each still has a place of its own, two workgroups per CU: a workgroup's time
+    // from its first instruction to its last store is the launch's (with the rows' early request, us before -> now: 224x224,
+    // batch 1, 3 -> 64 9.3 -> 7.5, 3 -> 32 5.6 -> 4.8; at 392 tiles 9.55 -> 8.8).  Beyond that the weights are sorted too often: 256.
+    const long small = (long)((p.npix + tile_pixels(mt, 1) - 1) / tile_pixels(mt, 1)) * ((p.OC + mt - 1) / mt);
+    if (p.IC == 3 && small <= 2 * kComputeUnits && !(set_tile(1) && plan->lt <= 5)) return set_tile(2);
     return true;
 }
 
@@ -316,7 +328,7 @@ tvg_status launch_conv7x7s2_stem(const ConvProblem &p, const StemPlan &plan, con
     a.by_ohw = make_divider(p.OH * p.OW);
     a.by_ow = make_divider(p.OW);
     a.by_vh = make_divider(p.H + 2 * p.ph);
-    a.ntiles = (p.npix + kNT - 1) / kNT;
+    a.ntiles = (p.npix + plan.nt - 1) / plan.nt;
     a.mtiles = (p.OC + plan.mt - 1) / plan.mt;
     // persistent workgroups: two per CU, shared between the output-channel tiles
     int per = 2 * kComputeUnits / a.mtiles;
@@ -329,6 +341,11 @@ tvg_status launch_conv7x7s2_stem(const ConvProblem &p, const StemPlan &plan, con
     // bytes past the tensor lie in the same aligned word as its last element).
     a.w_bytes = ((uint32_t)((size_t)p.OC * p.IC * p.R * p.R * 2) + 3u) & ~3u;
     const unsigned grid = (unsigned)(per * a.mtiles);
+    if (plan.nt < 256) {
+        if (p.R == 7) return launch_lt<7, 3, 5, 64, 1>(a, grid, plan.lds_bytes, stream);
+        return plan.mt == 32 ? launch_lt<3, 3, 5, 32, 1>(a, grid, plan.lds_bytes, stream)
+                             : launch_lt<3, 3, 5, 64, 1>(a, grid, plan.lds_bytes, stream);
+    }
     if (p.R == 3) {
         if (plan.mt == 32)
             return plan.lt <= 5 ? launch_lt<3, 3, 5, 32>(a, grid, plan.lds_bytes, stream)
