@@ -462,13 +462,43 @@ tvg_status tvg_conv2d_fused_dual(const tvg_conv_desc *desc, int32_t k1, uint32_t
     if (!tvg::plan_conv3x3_patch(p, &plan, k1)) return TVG_ERR_UNSUPPORTED;
     const tvg::ConvPointers ptr{x, w, scale, shift, bias, residual1, y1, nullptr};
     if (!tvg::conv3x3_patch_pointers_ok(ptr)) return TVG_ERR_UNSUPPORTED;
-    const tvg::DualHead dual{k1, (int)((flags2 & TVG_RELU ? 1 : 0) | (flags2 & TVG_STREAM_OUT ? 2 : 0)),
-                             (flags2 & TVG_CENTRE_TAP_ONLY) ? 1 : 0, y2};
+    const bool centre = (flags2 & TVG_CENTRE_TAP_ONLY) != 0;
+    const int relu2 = (flags2 & TVG_RELU ? 1 : 0) | (flags2 & TVG_STREAM_OUT ? 2 : 0);
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    // Each head has the bits of a call of its own, so the kernel for few tiles, whose waves split the reduction, takes
+    // exactly the heads that it would take then: both in one launch where their split is the same, or each in one.
+    ConvProblem h1 = p, h2 = p;
+    h1.OC = k1;
+    h2.OC = p.OC - k1;
+    h2.relu = relu2 & 1;
+    h2.stream_out = relu2 >> 1;
+    const ConvProblem h2_3x3 = h2;
+    if (centre) {
+        h2.R = h2.S = 1;
+        h2.ph = h2.pw = 0;
+        h2.K = h2.IC;
+    }
+    const Dispatch d1 = dispatch_for(h1), d2 = dispatch_for(h2);
+    const tvg::ConvPointers ptr2{x, static_cast<const char *>(w) + (size_t)k1 * p.IC * 18, scale + k1, shift + k1,
+                                 bias ? bias + k1 : nullptr, nullptr, y2, nullptr};
+    const bool rows1 = d1.rows_shape && tvg::conv_rows_pointers_ok(ptr), rows2 = d2.rows_shape && tvg::conv_rows_pointers_ok(ptr2);
+    const tvg::DualHead dual{k1, relu2, centre ? 1 : 0, y2};
+    if (!rows1 && !rows2) return tvg::launch_conv3x3_patch(p, plan, ptr, stream, &dual);
     tvg::RowsPlan rows;
-    if (tvg::plan_conv_rows_dual(p, k1, dual.centre2 != 0, &rows) && tvg::conv_rows_pointers_ok(ptr) &&
-        reinterpret_cast<uintptr_t>(y2) % 2 == 0)
-        return tvg::launch_conv_rows(p, rows, ptr, static_cast<hipStream_t>(hip_stream), &dual);
-    return tvg::launch_conv3x3_patch(p, plan, ptr, static_cast<hipStream_t>(hip_stream), &dual);
+    if (rows1 && rows2 && tvg::plan_conv_rows_dual(p, d1.rows, d2.rows, centre, &rows))
+        return tvg::launch_conv_rows(p, rows, ptr, stream, &dual);
+    // One launch each, in the tiles of the head's own call; a 1x1 head's weights lie in 3x3 filters and want instances
+    // that read those.  (The single-stage plan of a head exists where that of both does.)
+    tvg::Patch3x3Plan plan1 = d1.patch, plan2 = d2.patch;
+    if (!d1.patch_shape && !tvg::plan_conv3x3_patch(h1, &plan1, k1)) return TVG_ERR_UNSUPPORTED;
+    if ((centre || !d2.patch_shape) && !tvg::plan_conv3x3_patch(h2_3x3, &plan2, k1)) return TVG_ERR_UNSUPPORTED;
+    if (rows2 && centre && !tvg::plan_conv_rows_centre(h2, &rows)) return TVG_ERR_UNSUPPORTED;
+    st = rows1 ? tvg::launch_conv_rows(h1, d1.rows, ptr, stream) : tvg::launch_conv3x3_patch(h1, plan1, ptr, stream);
+    if (st != TVG_OK) return st;
+    if (rows2) return tvg::launch_conv_rows(h2, centre ? rows : d2.rows, ptr2, stream, nullptr, centre);
+    if (!centre) return tvg::launch_conv3x3_patch(h2, plan2, ptr2, stream);
+    const tvg::DualHead alone{0, relu2, 1, y2};
+    return tvg::launch_conv3x3_patch(h2_3x3, plan2, ptr2, stream, &alone);
 }
 
 tvg_status tvg_conv2d_fused_static(const tvg_conv_desc *desc, const void *x, const void *w,

@@ -51,7 +51,7 @@ struct PatchArgs {
     int ntiles, m_major;
     Divider by_tiles, by_ohw, by_ow, by_vh, by_wpx;      // tile-order divisor, OH*OW, OW, H + 2 and W / PX
     // Two heads (tvg_conv2d_fused_dual): output channels [0, oc1) go to y with `relu` and the
-    // residual, channels [oc1, OC) to y2 with relu2; oc1 = 0: one head.  centre2: the filters of
+    // residual, channels [oc1, OC) to y2 with relu2 (oc1 = 0: head 2 alone); y2 = null: one head.  centre2: the filters of
     // head 2 are zero outside their centre tap (a 1x1 convolution of the same input), its tiles
     // skip the other eight taps.  A tile lies within one head (oc1 is a multiple of MT).
     int oc1, relu2, centre2;
@@ -410,7 +410,7 @@ tvg_status launch_instance_d(const PatchArgs &a, int ntiles, size_t lds, hipStre
 template <int MT, int NT, int STRIDE, int PT, int PX>
 tvg_status launch_instance(const PatchArgs &a, int ntiles, size_t lds, hipStream_t stream)
 {
-    if (a.oc1 > 0) {
+    if (a.y2) {
         if constexpr (MT == 64 && NT >= 128) return launch_instance_d<MT, NT, STRIDE, PT, PX, true>(a, ntiles, lds, stream);
         else return TVG_ERR_UNSUPPORTED;
     }

@@ -69,7 +69,8 @@ __device__ __forceinline__ void wave_fence()
 // R x R filter, stride ST; UNAL: rows of an odd number of pixels; 16 output channels x 16 NJ pixel slots per
 // workgroup, PT load tasks per lane and chunk.
 // RS: a wave takes one filter row of a chunk (waves = 3 x chunks, the rows outermost).  DUAL: two heads.
-template <int R, int ST, bool UNAL, int NJ, int PT, bool RS, bool DUAL>
+// CENTRE (R = 1): the weights are the centre taps of 3x3 filters (a two-head call's second head on its own).
+template <int R, int ST, bool UNAL, int NJ, int PT, bool RS, bool DUAL, bool CENTRE = false>
 __global__ __launch_bounds__(64 * kMaxWaves) void conv_rows_kernel(const RowsArgs a)
 {
     constexpr int NT = 16 * NJ, QT = 4 * NJ;
@@ -110,10 +111,19 @@ __global__ __launch_bounds__(64 * kMaxWaves) void conv_rows_kernel(const RowsArg
             wdst[k] = oc * kWeightRow + piece * 16;
         }
     } else {
-        woff[0] = 2u * (__umul24(m0 + l16, a.IC) + 8 * quad);
+        woff[0] = CENTRE ? __umul24(__umul24(m0 + l16, a.IC) + 8 * quad, 18u) + 8 : 2u * (__umul24(m0 + l16, a.IC) + 8 * quad);
     }
     uint4v wraw[WL];
     auto load_weights = [&](int c) __attribute__((always_inline)) {
+        if constexpr (CENTRE) {
+            uint32_t tap[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                tap[e] = __builtin_amdgcn_raw_buffer_load_b16(wrsrc, woff[0] + 18 * e, c * (2 * kChunk * 9), 0);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) wraw[0][d] = tap[2 * d] | (tap[2 * d + 1] << 16);
+            return;
+        }
 #pragma unroll
         for (int k = 0; k < WL; ++k)
             wraw[k] = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, woff[k], c * (2 * kChunk * R * R), 0));
@@ -364,8 +374,9 @@ __global__ __launch_bounds__(64 * kMaxWaves) void conv_rows_kernel(const RowsArg
     }
 }
 
-// Geometry of a launch for NJ blocks of 16 pixel slots; false where a tile does not fit.
-bool set_geometry(const ConvProblem &p, int nj, bool rs, RowsPlan *g)
+// Geometry of a launch for NJ blocks of 16 pixel slots and at most most_rows output rows; false where a tile does
+// not fit.
+bool set_geometry(const ConvProblem &p, int nj, bool rs, RowsPlan *g, int most_rows = 64)
 {
     // a 1x1 layer without a stride has no rows: an image is one row, tiled across (rows of 4n pixels)
     const bool flat = p.R == 1 && p.sh == 1 && (p.H * p.W) % 4 == 0;
@@ -382,7 +393,7 @@ bool set_geometry(const ConvProblem &p, int nj, bool rs, RowsPlan *g)
         if (all > slots) return false;
         g->groups = all;
         g->cblocks = 1;
-        g->tr = std::min(slots / all, p.N * OH);
+        g->tr = std::min({slots / all, p.N * OH, most_rows});
         g->t8 = (W + 7) / 8;
     }
     const int vs = p.R == 1 ? 1 : p.sh, halo = p.R == 1 ? 0 : 3 - p.sh;       // staged rows per output row, more per image
@@ -404,10 +415,10 @@ bool set_geometry(const ConvProblem &p, int nj, bool rs, RowsPlan *g)
     return true;
 }
 
-template <int R, int ST, bool UNAL, int NJ, int PT, bool RS, bool DUAL>
+template <int R, int ST, bool UNAL, int NJ, int PT, bool RS, bool DUAL, bool CENTRE = false>
 tvg_status launch(const RowsArgs &args, const RowsPlan &plan, hipStream_t stream)
 {
-    const auto kernel = conv_rows_kernel<R, ST, UNAL, NJ, PT, RS, DUAL>;
+    const auto kernel = conv_rows_kernel<R, ST, UNAL, NJ, PT, RS, DUAL, CENTRE>;
     static bool configured = false;                // opt in to > 64 KB of dynamic LDS once per instance
     if (!configured && plan.lds_bytes > 64 * 1024) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
@@ -490,21 +501,19 @@ bool plan_conv_rows(const ConvProblem &p, RowsPlan *plan)
     return false;
 }
 
-bool plan_conv_rows_dual(const ConvProblem &p, int k1, bool centre, RowsPlan *plan)
+bool plan_conv_rows_dual(const ConvProblem &p, const RowsPlan &head1, const RowsPlan &head2, bool centre, RowsPlan *plan)
 {
-    // Where both heads on their own run here, with the same split of the sums: the results have the same bits.
-    if (p.sh != 2 || k1 % 16 != 0) return false;
-    ConvProblem h1 = p, h2 = p;
-    h1.OC = k1;
-    h2.OC = p.OC - k1;
-    if (centre) {
-        h2.R = h2.S = 1;
-        h2.ph = h2.pw = 0;
-        h2.K = h2.IC;
-    }
-    RowsPlan r1, r2;
-    if (!plan_conv_rows(h1, &r1) || !plan_conv_rows(h2, &r2) || (!centre && r1.rs != r2.rs)) return false;
-    return set_geometry(p, r1.nj, r1.rs != 0, plan);
+    // (two heads in one launch are built for stride 2; the same split of the sums has the same bits)
+    if (p.sh != 2 || (!centre && head1.rs != head2.rs)) return false;
+    return set_geometry(p, head1.nj, head1.rs != 0, plan);
+}
+
+bool plan_conv_rows_centre(const ConvProblem &p, RowsPlan *plan)
+{
+    // One instance per stride and row alignment: the widest tile, of as many rows as its loads hold (one always is).
+    for (int rows = 16; rows >= 1; --rows)
+        if (set_geometry(p, 4, false, plan, rows) && plan->pt <= 4 * p.sh) return true;
+    return false;
 }
 
 bool conv_rows_pointers_ok(const ConvPointers &ptr)
@@ -514,7 +523,7 @@ bool conv_rows_pointers_ok(const ConvPointers &ptr)
 }
 
 tvg_status launch_conv_rows(const ConvProblem &p, const RowsPlan &plan, const ConvPointers &ptr, hipStream_t stream,
-                            const DualHead *dual)
+                            const DualHead *dual, bool centre)
 {
     RowsArgs a{};
     a.x = static_cast<const bf16_t *>(ptr.x);
@@ -543,11 +552,15 @@ tvg_status launch_conv_rows(const ConvProblem &p, const RowsPlan &plan, const Co
     a.ptiles = (int)plan.ptiles;
     a.nch = p.IC / kChunk;
     a.x_bytes = ((uint32_t)((int64_t)p.N * p.IC * p.H * p.W) * 2 + 3) & ~3u;   // (up to the end of the last pixel's word)
-    a.w_bytes = (uint32_t)(p.OC * p.IC * p.R * p.S) * 2;
+    a.w_bytes = (uint32_t)(p.OC * p.IC * (centre ? 9 : p.R * p.S)) * 2;
     a.by_ptiles = make_divider(a.ptiles); a.by_oh = make_divider(a.OH); a.by_vh = make_divider(a.vh);
     a.by_t8 = make_divider(a.t8); a.by_rows = make_divider(a.rows); a.by_groups = make_divider(a.groups);
     a.by_cblocks = make_divider(a.cblocks);
     const bool odd = a.W % 2 != 0;
+    if (centre) {
+        if (p.sh == 1) return odd ? launch<1, 1, true, 4, 4, false, false, true>(a, plan, stream) : launch<1, 1, false, 4, 4, false, false, true>(a, plan, stream);
+        return odd ? launch<1, 2, true, 4, 8, false, false, true>(a, plan, stream) : launch<1, 2, false, 4, 8, false, false, true>(a, plan, stream);
+    }
     if (p.R == 1) {
         if (p.sh == 1) return odd ? launch_nj<1, 1, true>(a, plan, stream) : launch_nj<1, 1, false>(a, plan, stream);
         return odd ? launch_nj<1, 2, true>(a, plan, stream) : launch_nj<1, 2, false>(a, plan, stream);

@@ -84,7 +84,7 @@ struct Patch3x3Plan {
 // channel tile that divides this number (the channels of head 1).
 bool plan_conv3x3_patch(const ConvProblem &p, Patch3x3Plan *plan, int single_stage_mt_divides = 0);
 bool conv3x3_patch_pointers_ok(const ConvPointers &ptr);
-// The second head of a two-head launch: output channels [oc1, OC) go to y2 with their own flags.
+// The second head of a two-head launch: output channels [oc1, OC) go to y2 with their own flags (oc1 = 0: all of them).
 struct DualHead {
     int oc1, relu2, centre2;     // relu2: bit 0 ReLU, bit 1 store hint
     void *y2;
@@ -109,11 +109,13 @@ struct RowsPlan {
     size_t lds_bytes;
 };
 bool plan_conv_rows(const ConvProblem &p, RowsPlan *plan);
-// p: both heads together, k1 channels in the first (centre: the second is a 1x1 convolution)
-bool plan_conv_rows_dual(const ConvProblem &p, int k1, bool centre, RowsPlan *plan);
+// Both heads of p in one launch with the bits of separate ones, whose plans these are (centre: head 2 is a 1x1 convolution).
+bool plan_conv_rows_dual(const ConvProblem &p, const RowsPlan &head1, const RowsPlan &head2, bool centre, RowsPlan *plan);
+// p: a 1x1 problem that plan_conv_rows takes, its weights the centre taps of 3x3 filters.
+bool plan_conv_rows_centre(const ConvProblem &p, RowsPlan *plan);
 bool conv_rows_pointers_ok(const ConvPointers &ptr);
 tvg_status launch_conv_rows(const ConvProblem &p, const RowsPlan &plan, const ConvPointers &ptr, hipStream_t stream,
-                            const DualHead *dual = nullptr);
+                            const DualHead *dual = nullptr, bool centre = false);
 
 // bf16 7x7 stride-2 pad-3 kernel for IC <= 4 (the ResNet stem).
 struct StemPlan {

@@ -97,3 +97,41 @@ def test_few_tiles_two_heads_have_the_bits_of_separate_calls(tvg, cfg, centre):
     rc = tvg.tvg_conv2d_fused_dual(desc, k1, tvg.TVG_CENTRE_TAP_ONLY if centre else 0, d1["x"], wt, scale, shift, None, d1["residual"], y1, y2)
     assert rc == 0, tvg.status_string(rc)
     assert torch.equal(y1, want1) and torch.equal(y2, want2)
+
+
+# ..., which of the two heads runs in the kernel for few tiles when it is called by itself
+@pytest.mark.parametrize("cfg,few", [
+    ((6, 64, 56, 56, 128, 128, 2), (False, True)), ((8, 128, 28, 28, 256, 256, 2), (False, True)), ((12, 256, 14, 14, 512, 512, 2), (False, True)),
+    ((4, 64, 28, 28, 64, 2048, 2), (True, False)), ((1, 256, 112, 112, 64, 16, 1), (False, True)), ((2, 96, 13, 11, 64, 70, 1), (True, True)),
+    ((3, 512, 14, 14, 64, 40, 1), (True, True)), ((12, 96, 8, 127, 64, 24, 2), (False, True)), ((12, 96, 8, 128, 64, 17, 2), (False, True)),
+    ((1, 64, 28, 28, 64, 40, 1), (True, False)), ((32, 64, 56, 56, 128, 128, 2), (False, False)),
+], ids=lambda c: "x".join(map(str, c)))
+@pytest.mark.parametrize("centre", [True, False])
+def test_two_heads_have_the_bits_of_separate_calls_whichever_is_split(tvg, cfg, few, centre):
+    import torch
+    n, ic, h, w, k1, k2, stride = cfg
+    r2 = 1 if centre else 3
+    g = torch.Generator(device="cuda").manual_seed(8700 + sum(cfg))
+    def rand(*shape):
+        return torch.rand(shape, generator=g, device="cuda") * 2 - 1
+    x, w1, w2 = (rand(*s).to(torch.bfloat16) for s in ((n, ic, h, w), (k1, ic, 3, 3), (k2, ic, r2, r2)))
+    scale, shift, bias = rand(k1 + k2), rand(k1 + k2), rand(k1 + k2)
+    joined = torch.zeros(k1 + k2, ic, 3, 3, dtype=torch.bfloat16, device="cuda")
+    joined[:k1] = w1
+    if centre:
+        joined[k1:, :, 1, 1] = w2[:, :, 0, 0]
+    else:
+        joined[k1:] = w2
+    if centre:
+        d1 = tvg.ConvDesc(n, ic, h, w, k1, 3, 3, stride, stride, 1, 1, tvg.TVG_BF16, 0)
+        d2 = tvg.ConvDesc(n, ic, h, w, k2, 1, 1, stride, stride, 0, 0, tvg.TVG_BF16, 0)
+        assert (tvg.tvg_conv2d_get_plan(d1)[1] == 16, tvg.tvg_conv2d_get_plan(d2)[1] == 16) == few
+    want1 = tvg.conv2d_fused(x, w1, scale[:k1], shift[:k1], bias[:k1], stride=stride, pad=1, relu=True)
+    residual = rand(*want1.shape).to(torch.bfloat16)
+    want1 = tvg.conv2d_fused(x, w1, scale[:k1], shift[:k1], bias[:k1], residual, stride=stride, pad=1, relu=True)
+    want2 = tvg.conv2d_fused(x, w2, scale[k1:].clone(), shift[k1:].clone(), bias[k1:].clone(), stride=stride, pad=r2 // 2, relu=False)
+    y1, y2 = torch.full_like(want1, float("nan")), torch.full_like(want2, float("nan"))
+    desc = tvg.ConvDesc(n, ic, h, w, k1 + k2, 3, 3, stride, stride, 1, 1, tvg.TVG_BF16, tvg.TVG_RELU)
+    rc = tvg.tvg_conv2d_fused_dual(desc, k1, tvg.TVG_CENTRE_TAP_ONLY if centre else 0, x, joined, scale, shift, bias, residual, y1, y2)
+    assert rc == 0, tvg.status_string(rc)
+    assert torch.equal(y1, want1) and torch.equal(y2, want2)
