@@ -99,9 +99,10 @@ __global__ __launch_bounds__(256, 2) void conv_f32_pw_kernel(const PwArgs a)
         __builtin_amdgcn_sched_barrier(0);
     }
 
-    // Chains of CHAIN steps start from zero and are added to the totals in plain adds, in turn to two of them where
-    // the registers allow.
-    constexpr int TOT = NB * PXL <= 2 && CHAIN == 1 ? 2 : 1;
+    // Chains of CHAIN steps start from zero and are added to the totals in plain adds, in turn to two or four of them
+    // where the registers allow (2048 channels, 7x7, 64 chains per wave: error against 64 bits 1.30e-7 with two totals,
+    // 1.08e-7 with four, 1.22e-7 in the kernel before).
+    constexpr int TOT = CHAIN > 1 ? 1 : NB * PXL == 1 ? 4 : NB * PXL == 2 ? 2 : 1;
     float16v acc[NB][PXL], sum[TOT][NB][PXL];
 #pragma unroll
     for (int t = 0; t < TOT; ++t)
@@ -153,11 +154,14 @@ __global__ __launch_bounds__(256, 2) void conv_f32_pw_kernel(const PwArgs a)
         multiply(2, CHAIN <= 2, true);
     }
 
-    if constexpr (TOT == 2)
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
+    for (int d = 1; d < TOT; d *= 2)
 #pragma unroll
-            for (int e = 0; e < PXL; ++e) sum[0][b][e] += sum[1][b][e];
+        for (int t = 0; t + d < TOT; t += 2 * d)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int e = 0; e < PXL; ++e) sum[t][b][e] += sum[t + d][b][e];
 
     // value v of a lane: channel 8 (v / 4) + 4 lhalf + v % 4, pixel PXL lrow + e
     auto finish = [&](pixels o, int oc, int p) __attribute__((always_inline)) {
@@ -230,10 +234,13 @@ template <int NB, int PXL>
 tvg_status launch_split(const PwArgs &args, const F32PwPlan &plan, hipStream_t stream)
 {
     // Chains no longer than those of the kernels that ran these problems before: 8 channels where four waves split the
-    // reduction (the sums hide behind the loads); where two do, 8 up to 127 channels or under a stride, 16 up to 255, 32.
+    // reduction (the sums hide behind the loads); where two do, 8 up to 127 channels, 16 up to 255, 32, and half of that under
+    // a stride (256 -> 512 at 28x28, stride 2: error against 64 bits 0.97e-7 with 16, 1.14e-7 with 32, 0.98e-7 in the
+    // kernel with rows in LDS).
+    const int channels = args.stride > 1 ? args.IC / 2 : args.IC;
     if (plan.ks == 4) return launch<NB, PXL, 4, 1>(args, plan.tiles, stream);
-    if (args.IC < (args.stride > 1 ? 256 : 128)) return launch<NB, PXL, 2, 1>(args, plan.tiles, stream);
-    if (args.IC < 256) return launch<NB, PXL, 2, 2>(args, plan.tiles, stream);
+    if (channels < 128) return launch<NB, PXL, 2, 1>(args, plan.tiles, stream);
+    if (channels < 256) return launch<NB, PXL, 2, 2>(args, plan.tiles, stream);
     return launch<NB, PXL, 2, 4>(args, plan.tiles, stream);
 }
 

@@ -55,6 +55,22 @@ def test_f32_1x1_sums_in_short_chains(tvg, cfg):
     assert err <= 1.3e-7, (cfg, err)
 
 
+# The same under a stride (16 channels per chain up to 511: 7.1e-8 of a chain, 5e-8 of eight of them added up, 9.2e-8 with
+# the last sums; 32 per chain 1.1e-7) and for long reductions of few tiles (64 chains of 8 per wave: in four totals
+# 5e-8, 7.1e-8 and four levels of sums, 1.0e-7; in two totals 1.2e-7).  The kernels that ran these before: 0.98e-7, 1.22e-7.
+@pytest.mark.parametrize("cfg,bound", [((32, 256, 28, 28, 256, 2), 1.05e-7), ((64, 264, 14, 14, 512, 2), 1.05e-7), ((1, 2048, 7, 7, 512, 1), 1.2e-7)],
+                         ids=lambda c: "x".join(map(str, c)) if isinstance(c, tuple) else "")
+def test_f32_1x1_sums_of_strided_and_long_reductions(tvg, cfg, bound):
+    import torch
+    n, ic, h, w, oc, stride = cfg
+    g = torch.Generator().manual_seed(8850 + sum(cfg))
+    x, wt = torch.rand((n, ic, h, w), generator=g) * 2 - 1, torch.randn((oc, ic, 1, 1), generator=g) * (2.0 / ic) ** 0.5
+    got = tvg.conv2d_fused(x.cuda(), wt.cuda(), torch.ones(oc).cuda(), torch.zeros(oc).cuda(), stride=stride, relu=False)
+    want = torch.matmul(wt.double().view(oc, ic), x[:, :, ::stride, ::stride].double().reshape(n, ic, -1))
+    err = float((got.cpu().double().view(want.shape) - want).norm() / want.norm())
+    assert err <= bound, (cfg, err)
+
+
 @pytest.mark.parametrize("shape", [(2, 64, 8, 8, 40), (1, 512, 14, 14, 512)])
 def test_f32_1x1_unaligned_pointers(tvg, shape):
     """y and the residual at any element; x at any element runs elsewhere, within the workspace that was queried."""
