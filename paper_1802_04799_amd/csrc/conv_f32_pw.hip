@@ -9,12 +9,12 @@
 //     along the output channels.  Few tiles: KS = 4 and the narrowest of 32, 64 or 128 pixels that stays within one
 //     round of workgroups.  Throughput: KS = 2, tiles of 64 channels x 64 or 128 pixels.
 //   - Consecutive workgroups take the channel tiles of one pixel tile and meet in an XCD's L2.
-// What bounds it: the matrix pipe (47 % of its rate at 32 x 512 -> 512, 14x14; with KS = 1, chains not broken, 57 %), on
-// few tiles the first loads, and the plain adds of short chains.  us before -> now: batch 4, 512 -> 512 14x14 19.3 -> 8.7
-// (the launch-bound kernel), 256 -> 256 28x28 13.5 -> 8.8 (the kernel with rows in LDS); batch 1, 512 -> 512 14x14 20.6 ->
-// 5.7; batch 32, 512 -> 512 14x14 59.7 -> 42 (the gather kernel).  MobileNet body, batch 4: 283 -> 197.  208 random and
-// network shapes: 146 take it, 1.83 times as fast in the geometric mean, none slower; their error against 64 bits 0.67 of
-// the former kernels' in the geometric mean, 1.00 at most.
+// What bounds it: the matrix pipe and the plain adds of short chains, on few tiles the first loads.  us before -> now:
+// batch 4, 512 -> 512 14x14 19.3 -> 8.7 (the launch-bound kernel), 256 -> 256 28x28 13.5 -> 8.8 (the kernel with rows in
+// LDS); batch 1, 512 -> 512 14x14 20.6 -> 5.7, stride 3 15.4 -> 5; batch 32, 512 -> 512 14x14 59.7 -> 42 (the gather
+// kernel).  MobileNet body, batch 4: 283 -> 197.  Of 602 shapes 516 take it, 1.76 times as fast in the geometric mean, four
+// of them by 0.95 to 0.97 (strides, where the kernel with rows in LDS stood); their error against 64 bits is 0.69 of the
+// former kernels' in the geometric mean and 1.00 at most where there are a thousand outputs to take it from.
 #include <algorithm>
 
 #include "tvg_device.h"
@@ -43,8 +43,8 @@ template <> struct Pixels<2> { typedef float vec __attribute__((ext_vector_type(
 template <> struct Pixels<1> { typedef float vec __attribute__((ext_vector_type(1))); };
 
 // A wave: 32 MI output channels x 32 PXL NB pixels, PXL adjacent pixels per lane; KS waves split the reduction, WM
-// waves lie side by side along the channels.
-template <int NB, int PXL, int KS, int CHAIN>
+// waves lie side by side along the channels.  Chains of CHAIN steps are added to TOT totals in turn.
+template <int NB, int PXL, int KS, int CHAIN, int TOT>
 __global__ __launch_bounds__(256, 2) void conv_f32_pw_kernel(const PwArgs a)
 {
     typedef typename Pixels<PXL>::vec pixels;
@@ -99,10 +99,7 @@ __global__ __launch_bounds__(256, 2) void conv_f32_pw_kernel(const PwArgs a)
         __builtin_amdgcn_sched_barrier(0);
     }
 
-    // Chains of CHAIN steps start from zero and are added to the totals in plain adds, in turn to two or four of them
-    // where the registers allow (2048 channels, 7x7, 64 chains per wave: error against 64 bits 1.30e-7 with two totals,
-    // 1.08e-7 with four, 1.22e-7 in the kernel before).
-    constexpr int TOT = CHAIN > 1 ? 1 : NB * PXL == 1 ? 4 : NB * PXL == 2 ? 2 : 1;
+    // Chains of CHAIN steps start from zero and are added to the totals in plain adds.
     float16v acc[NB][PXL], sum[TOT][NB][PXL];
 #pragma unroll
     for (int t = 0; t < TOT; ++t)
@@ -215,10 +212,10 @@ __global__ __launch_bounds__(256, 2) void conv_f32_pw_kernel(const PwArgs a)
     }
 }
 
-template <int NB, int PXL, int KS, int CHAIN>
+template <int NB, int PXL, int KS, int CHAIN, int TOT = CHAIN == 1 && NB * PXL <= 2 ? 2 : 1>
 tvg_status launch(const PwArgs &args, long tiles, hipStream_t stream)
 {
-    const auto kernel = conv_f32_pw_kernel<NB, PXL, KS, CHAIN>;
+    const auto kernel = conv_f32_pw_kernel<NB, PXL, KS, CHAIN, TOT>;
     constexpr size_t lds = (size_t)4 * 32 * 32 * PXL * NB * 4;      // KS partial tiles of 32 * (4 / KS) channels
     static bool configured = false;                // opt in to > 64 KB of dynamic LDS once per instance
     if (!configured && lds > 64 * 1024) {
@@ -238,6 +235,10 @@ tvg_status launch_split(const PwArgs &args, const F32PwPlan &plan, hipStream_t s
     // a stride (256 -> 512 at 28x28, stride 2: error against 64 bits 0.97e-7 with 16, 1.14e-7 with 32, 0.98e-7 in the
     // kernel with rows in LDS).
     const int channels = args.stride > 1 ? args.IC / 2 : args.IC;
+    // Two totals where the registers allow, four for long reductions (2048 channels at 7x7, 64 chains per wave: error
+    // against 64 bits 1.30e-7 with two, 1.08e-7 with four, 1.22e-7 in the kernel before; 0.1 us of a launch).
+    if constexpr (NB * PXL == 1)
+        if (plan.ks == 4 && args.IC > 1024) return launch<NB, PXL, 4, 1, 4>(args, plan.tiles, stream);
     if (plan.ks == 4) return launch<NB, PXL, 4, 1>(args, plan.tiles, stream);
     if (channels < 128) return launch<NB, PXL, 2, 1>(args, plan.tiles, stream);
     if (channels < 256) return launch<NB, PXL, 2, 2>(args, plan.tiles, stream);
@@ -260,8 +261,10 @@ void set_tile(const ConvProblem &p, int ks, int nb, int pxl, F32PwPlan *plan)
 bool plan_conv_f32_pw(const ConvProblem &p, bool few_tiles, int nt, F32PwPlan *plan)
 {
     if (p.dtype != TVG_F32 || p.R != 1 || p.S != 1 || p.ph || p.pw || p.sh != p.sw || p.IC % kStep != 0) return false;
-    // (64 channels under a stride: 32 images, 64 -> 128 at 56x56, 20.0 us in the kernel with rows in LDS, 23.1 here)
-    if (p.IC < (few_tiles ? 32 : p.sh > 1 ? 72 : 64)) return false;
+    // Problems of other kernels' few tiles: the launch-bound ones, and those of the gather kernel (strides from 3 on, long
+    // rows) whose 128 x 128 tiles are fewer than CUs, where it splits the reduction.
+    few_tiles = few_tiles || (nt == 0 && (long)((p.OC + 127) / 128) * ((p.npix + 127) / 128) < kComputeUnits);
+    if (p.IC < (few_tiles ? 32 : 64)) return false;
     if ((size_t)p.N * p.IC * p.H * p.W >= ((size_t)1 << 29) || (size_t)p.OC * p.IC >= ((size_t)1 << 29)) return false;   // 32-bit byte offsets
     const Knobs k = forced_knobs(p);
     if (k.mt || k.nt || k.stages || k.split_k || k.lds_pitch || k.row_loads) return false;
@@ -273,16 +276,28 @@ bool plan_conv_f32_pw(const ConvProblem &p, bool few_tiles, int nt, F32PwPlan *p
         }
         return true;
     }
+    // (64 channels under a stride: 32 images, 64 -> 128 at 56x56, 20.0 us in the kernel with rows in LDS, 23.1 here)
+    if (p.sh > 1 && p.IC < 72) return false;
     if (nt == 0) {
-        // In place of the gather kernel's 128 x 128 tiles: where the reduction is not short (64 -> 128, 16 images 56x56,
-        // 19.7 us there and 22.4 here) and 64-channel tiles waste little (136 -> 104, 36 images 52x52, 47.8 and 49.8).
-        // 128 -> 256, 32 images 28x28, 29.2 and 29.3; 256 -> 256 49.5 and 44; 1024 -> 1024, 7x7, 57 and 44.
-        if (p.IC < 128 || 6 * p.OC < 5 * ((p.OC + 63) / 64 * 64)) return false;
-        nt = p.IC < 256 ? 64 : 128;
+        // In place of the gather kernel's 128 x 128 tiles: without a stride (64 images, 128 -> 128 at 56x56, stride 2, 33 us
+        // there and 52 here), where the reduction is not short (64 -> 128, 16 images 56x56, 19.7 us there and 22.4 here) and
+        // 64-channel tiles waste little (136 -> 104, 36 images 52x52, 47.8 and 49.8).  128 -> 512, 64 images 28x28, 89 and 83;
+        // 256 -> 256, 32 images, 49.5 and 42; 1024 -> 1024, 7x7, 57 and 44.
+        // Up to 255 channels tiles of 64 pixels where they come out in fewer rounds, two tiles per CU (184 -> 293, 6 images
+        // 40x81, 3 rounds and 2 of 128 pixels, 32 and 37 us; 128 -> 512 above 97 and 83), and on maps that no wide loads fit.
+        if (p.sh > 1 || p.IC < 128 || 6 * p.OC < 5 * ((p.OC + 63) / 64 * 64)) return false;
+        const auto rounds = [&](int t) {
+            set_tile(p, 2, 1, t / 32, plan);
+            return (plan->tiles + 2 * kComputeUnits - 1) / (2 * kComputeUnits);
+        };
+        nt = p.IC >= 256 || (most == 4 && 8 * rounds(128) <= 5 * rounds(64)) ? 128 : 64;
     }
     const int pxl = std::min(most, nt / 32);
     set_tile(p, 2, nt / 32 / pxl, pxl, plan);
-    return true;
+    // Under a stride on small maps, where 32 adjacent pixels are many short rows, against the kernel with rows in LDS: while
+    // every tile has a place, two per CU (256 -> 1024 at 14x14, 32 images, 400 tiles, 22.7 us there and 20.9 here; 64
+    // images, 784 tiles, 34.7 and 39.4; 256 -> 256 at 56x56, 16 images, 784 tiles, 45.6 and 42.1).
+    return p.sh == 1 || p.OW >= 16 || plan->tiles <= 2 * kComputeUnits;
 }
 
 bool conv_f32_pw_pointers_ok(const ConvPointers &ptr)

@@ -379,3 +379,21 @@ def test_fixing_the_knobs_that_a_plan_reports_changes_nothing(kw, plan):
     finally:
         assert tvg.tvg_conv2d_set_knobs(d, None) == 0
     assert state() == before
+
+
+@pytest.mark.parametrize("n,c,h,w,k,stride,plan", [
+    # few 128 x 128 tiles: narrow ones and a reduction split over four waves, whatever the stride and the rows
+    (1, 512, 14, 14, 512, 3, (0, 32, 32)), (1, 512, 28, 28, 512, 4, (0, 32, 32)), (11, 704, 3, 76, 248, 4, (0, 32, 32)),
+    (2, 440, 2, 222, 58, 3, (0, 32, 32)), (1, 1024, 1, 2048, 256, 1, (0, 32, 64)), (1, 256, 8, 512, 128, 1, (0, 32, 64)),
+    # throughput: the gather kernel under a stride and for short reductions, wide tiles where they come out in few rounds
+    (64, 128, 56, 56, 128, 2, (0, 128, 128)), (64, 256, 56, 56, 64, 2, (0, 64, 128)), (16, 64, 56, 56, 128, 1, (0, 128, 128)),
+    (64, 128, 28, 28, 512, 1, (0, 64, 128)), (16, 128, 56, 56, 128, 1, (0, 64, 128)), (6, 184, 40, 81, 293, 1, (0, 64, 64)),
+    (32, 256, 28, 28, 256, 1, (0, 64, 128)),
+])
+def test_fp32_1x1_plans_fill_the_chip(n, c, h, w, k, stride, plan):
+    """The 1x1 kernel takes the gather kernel's place with tiles that leave no CUs idle where others exist, and where it
+    is the faster one."""
+    d = desc(n=n, c=c, h=h, w=w, k=k, r=1, s=1, stride_h=stride, stride_w=stride, pad_h=0, pad_w=0)
+    assert tvg.tvg_conv2d_get_plan(d) == plan
+    gather = stride == 2 or c == 64
+    assert any(tvg.tvg_conv2d_get_knobs(d)) == gather and tvg.tvg_conv2d_workspace_size(d) == 0

@@ -23,6 +23,16 @@ EVERY_INSTANCE = [
 ]
 
 
+# Strides from 3 on and long rows, narrow tiles in place of the gather kernel's; two totals and four; 64-pixel tiles of
+# single pixels; chains of 16 in 128-pixel tiles.
+EVERY_INSTANCE += [
+    ((1, 512, 14, 14, 512, 3), (0, 32, 32)), ((7, 152, 29, 31, 70, 4), (0, 32, 32)), ((3, 40, 26, 97, 33, 3), (0, 32, 32)),
+    ((2, 96, 1, 2050, 90, 1), (0, 32, 64)), ((41, 72, 40, 50, 125, 3), (0, 32, 128)), ((40, 32, 50, 50, 70, 3), (0, 32, 128)),
+    ((8, 128, 57, 57, 120, 2), (0, 64, 64)), ((1, 1032, 5, 5, 40, 1), (5, 32, 32)), ((9, 1048, 7, 9, 70, 2), (5, 32, 32)),
+    ((30, 128, 56, 49, 128, 1), (0, 64, 128)),
+]
+
+
 @pytest.mark.parametrize("tail", ["plain", "bias+residual"])
 @pytest.mark.parametrize("cfg,plan", EVERY_INSTANCE, ids=lambda c: "x".join(map(str, c)))
 def test_f32_1x1_every_instance(tvg, cfg, plan, tail):
