@@ -481,23 +481,39 @@ bool plan_conv_rows(const ConvProblem &p, RowsPlan *plan)
     const int nch = p.IC / kChunk;
     // What fits one round: at most 2048 waves, eight per CU, in the narrowest tile that keeps to it.  Beyond it the other
     // kernels' larger tiles win (256 -> 256 14x14: 13.8 us there against 13.1 at batch 6 and 2688 waves; 128 -> 128
-    // 28x28 at batch 16, 7168 waves, 12.3 against 19.7), except where those have few tiles and a long chain: deep
+    // 28x28 at batch 16, 7168 waves, 12.3 against 19.7), except where those have few tiles and a long chain: 3x3, deep
     // and strided layers up to 3584 waves (512 -> 512 7x7, batch 16, 20.5 against 16.7; 256 -> 512 s2, batch 8, 19.6 against
-    // 12.6), 1x1 up to 4096 (512 -> 512 14x14, batch 4, 7.9 against 6.4; 8192 waves 8.0 against 9.6).
+    // 12.6), deep 1x1 layers without a stride up to 4096 (512 -> 512 14x14, batch 4, 7.9 against 6.4; 8192 waves 8.0 against
+    // 9.6).
     // 1x1 without a stride: reductions of 1, 2 and 4 chunks are whole in flight in the other kernel (64 -> 128 56x56 at
-    // batch 1 3.1 us against 3.6); strided ones are even (3.4 and 3.5; 4 chunks 4.1 and 3.5).
-    // Two chunks, 3x3, without a stride: beyond the split into filter rows the other kernel is as fast (7.3, 7.4).
-    int most_first = 2048;
-    int most = p.R == 1 ? (nch >= 16 || (nch >= 8 && p.sh == 2) ? 4096 : 2048) : nch >= 16 || (nch >= 8 && p.sh == 2) ? 3584 : 2048;
-    if (p.R == 1 && p.sh == 1 && (nch == 1 || nch == 2 || nch == 4)) return false;
-    // (maps of an odd number of pixels are tiled by rows: 96 -> 160, 5 images 19x19, 4.7 us there against 5.7)
-    if (p.R == 1 && p.sh == 1 && nch < 16 && p.H * p.W % 4 != 0) most_first = most = 512;
-    for (int limit : {most_first, most})
-        for (int rs = p.R == 3 && nch <= 2 ? 1 : 0; rs >= 0; --rs) {
-            if (p.R == 3 && p.sh == 1 && nch <= 2 && !rs) break;
-            for (int nj : {1, 2, 4})
-                if (set_geometry(p, nj, rs != 0, plan) && plan->tiles * plan->nw <= limit) return true;
+    // batch 1 3.1 us against 3.6).  With one they are too, and only narrow tiles gain on it, at one chunk the narrowest
+    // (32 -> 192, 29 images 31x19, 64 pixels, 3.4 there and 6.3 here; 128 -> 192, 6 images 20x51, 4.4 and 5.5, 2 images 18x18,
+    // 16 pixels, 4.7 and 3.4).
+    // 3x3, up to three chunks: workgroups of a few waves, which wide tiles keep busy.  One chunk, in filter rows or, in
+    // the narrowest tile, whole (32 -> 256, 17 images 44x11, stride 2, whole in 32-pixel tiles, 6.7 us there and 9.1
+    // here): 32 pixels up to two workgroups per CU, 64 one (32 -> 192, 7 images 10x10, 420 workgroups of 32, 5.5 and 4.5, 32 ->
+    // 48, 34 images 12x11, 612, 5.4 and 6.4; 32 -> 289, 10 images 12x12, 456 of 64, 5.6 and 6.3).  Two, in filter rows: one per CU,
+    // each 57 KB of LDS (64 -> 128, 8 images 17x17, stride 2, 288 workgroups, 9.3 and 12.3), and none whole at stride 1
+    // (7.3, 7.4).  Three: two per CU of 64 pixels, or 32 under a stride (96 -> 500, 2 images 31x31, 512 workgroups, 11.1 and
+    // 8.3, 96 -> 192, 20 images 35x7, 540, 9.9 and 12.3).
+    const auto most_waves = [&](int nj, bool rs) {
+        if (p.R == 1 && p.sh == 2) return nch <= 4 && nj > (nch == 1 ? 1 : 2) ? 0 : 2048;
+        if (p.R == 1) {
+            if (nch == 3 && nj == 4) return 1200;              // (96 -> 96, 9 images 26x26, 1782 waves, 4.4 and 4.7)
+            // (maps of an odd number of pixels are tiled by rows: 96 -> 160, 5 images 19x19, 4.7 us there against 5.7)
+            if (p.H * p.W % 4 != 0 && nch < 16) return 512;
+            return nch < 16 ? 2048 : 4096;
         }
+        if (nch == 1) return nj == 1 ? (rs || p.sh == 2 ? 2048 : 0) : !rs ? 0 : 3 * kComputeUnits * (nj == 2 ? 2 : 1);
+        if (nch == 2) return rs ? 6 * kComputeUnits : p.sh == 1 ? 0 : 2048;
+        if (nch == 3 && nj * p.sh >= 4) return 3 * kComputeUnits * 2;
+        return nch >= 16 || (nch >= 8 && p.sh == 2) ? 3584 : 2048;
+    };
+    if (p.R == 1 && p.sh == 1 && (nch == 1 || nch == 2 || nch == 4)) return false;
+    for (int round : {2048, 4096})
+        for (int rs = p.R == 3 && nch <= 2 ? 1 : 0; rs >= 0; --rs)
+            for (int nj : {1, 2, 4})
+                if (set_geometry(p, nj, rs != 0, plan) && plan->tiles * plan->nw <= std::min(round, most_waves(nj, rs != 0))) return true;
     return false;
 }
 

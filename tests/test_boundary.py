@@ -397,3 +397,20 @@ def test_fp32_1x1_plans_fill_the_chip(n, c, h, w, k, stride, plan):
     assert tvg.tvg_conv2d_get_plan(d) == plan
     gather = stride == 2 or c == 64
     assert any(tvg.tvg_conv2d_get_knobs(d)) == gather and tvg.tvg_conv2d_workspace_size(d) == 0
+
+
+@pytest.mark.parametrize("n,c,h,w,k,r,stride,few", [
+    # 1x1 under a stride: one round, narrow tiles where the other kernel has the whole reduction in flight
+    (8, 256, 14, 14, 512, 1, 2, True), (16, 384, 24, 24, 128, 1, 2, False), (12, 512, 50, 50, 48, 1, 2, False),
+    (4, 128, 28, 28, 256, 1, 2, True), (8, 128, 28, 28, 256, 1, 2, False), (39, 32, 22, 22, 32, 1, 2, True), (29, 32, 31, 19, 192, 1, 2, False),
+    (7, 96, 18, 18, 96, 1, 1, True), (9, 96, 26, 26, 96, 1, 1, False), (4, 512, 14, 14, 512, 1, 1, True),
+    # 3x3 of one, two and three chunks: as many workgroups as stay in one round
+    (7, 32, 10, 10, 192, 3, 1, True), (34, 32, 12, 11, 48, 3, 1, False), (1, 32, 64, 64, 64, 3, 1, True), (10, 32, 16, 16, 233, 3, 1, False),
+    (2, 32, 61, 60, 128, 3, 2, True), (17, 32, 44, 11, 256, 3, 2, False), (3, 64, 14, 14, 192, 3, 1, True), (10, 64, 13, 13, 70, 3, 1, False),
+    (2, 96, 31, 31, 500, 3, 2, True), (20, 96, 35, 7, 192, 3, 2, False), (8, 256, 14, 14, 512, 3, 2, True),
+])
+def test_bf16_kernel_for_few_tiles_takes_them_where_it_is_faster(n, c, h, w, k, r, stride, few):
+    """16-channel tiles on both sides of each line of its rule."""
+    d = desc(n=n, c=c, h=h, w=w, k=k, r=r, s=r, stride_h=stride, stride_w=stride, pad_h=r // 2, pad_w=r // 2, dtype=1)
+    assert (tvg.tvg_conv2d_get_plan(d)[1] == 16) == few
+    assert any(tvg.tvg_conv2d_get_knobs(d)) != few

@@ -101,10 +101,10 @@ def test_few_tiles_two_heads_have_the_bits_of_separate_calls(tvg, cfg, centre):
 
 # ..., which of the two heads runs in the kernel for few tiles when it is called by itself
 @pytest.mark.parametrize("cfg,few", [
-    ((6, 64, 56, 56, 128, 128, 2), (False, True)), ((8, 128, 28, 28, 256, 256, 2), (False, True)), ((12, 256, 14, 14, 512, 512, 2), (False, True)),
+    ((6, 64, 56, 56, 128, 128, 2), (False, False)), ((12, 256, 14, 14, 512, 512, 2), (False, False)), ((8, 160, 14, 14, 512, 512, 2), (False, True)),
     ((4, 64, 28, 28, 64, 2048, 2), (True, False)), ((1, 256, 112, 112, 64, 16, 1), (False, True)), ((2, 96, 13, 11, 64, 70, 1), (True, True)),
-    ((3, 512, 14, 14, 64, 40, 1), (True, True)), ((12, 96, 8, 127, 64, 24, 2), (False, True)), ((12, 96, 8, 128, 64, 17, 2), (False, True)),
-    ((1, 64, 28, 28, 64, 40, 1), (True, False)), ((32, 64, 56, 56, 128, 128, 2), (False, False)),
+    ((3, 512, 14, 14, 64, 40, 1), (True, True)), ((5, 160, 8, 127, 64, 24, 2), (False, True)), ((5, 160, 8, 128, 64, 17, 2), (False, True)),
+    ((2, 64, 28, 28, 64, 1024, 2), (True, True)), ((1, 64, 28, 28, 64, 40, 1), (True, False)), ((4, 128, 28, 28, 256, 256, 2), (True, True)), ((32, 64, 56, 56, 128, 128, 2), (False, False)),
 ], ids=lambda c: "x".join(map(str, c)))
 @pytest.mark.parametrize("centre", [True, False])
 def test_two_heads_have_the_bits_of_separate_calls_whichever_is_split(tvg, cfg, few, centre):
