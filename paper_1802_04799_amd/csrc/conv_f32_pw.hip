@@ -302,7 +302,8 @@ bool plan_conv_f32_pw(const ConvProblem &p, bool few_tiles, int nt, F32PwPlan *p
 
 bool conv_f32_pw_pointers_ok(const ConvPointers &ptr)
 {
-    return reinterpret_cast<uintptr_t>(ptr.x) % 16 == 0 && reinterpret_cast<uintptr_t>(ptr.w) % 16 == 0;
+    // (buffer loads of any width want 4 bytes: weights that are views into one parameter buffer run here too)
+    return reinterpret_cast<uintptr_t>(ptr.x) % 4 == 0 && reinterpret_cast<uintptr_t>(ptr.w) % 4 == 0;
 }
 
 tvg_status launch_conv_f32_pw(const ConvProblem &p, const F32PwPlan &plan, const ConvPointers &ptr, hipStream_t stream)

@@ -83,7 +83,7 @@ def test_f32_1x1_sums_of_strided_and_long_reductions(tvg, cfg, bound):
 
 @pytest.mark.parametrize("shape", [(2, 64, 8, 8, 40), (1, 512, 14, 14, 512)])
 def test_f32_1x1_unaligned_pointers(tvg, shape):
-    """y and the residual at any element; x at any element runs elsewhere, within the workspace that was queried."""
+    """x, y and the residual at any element, without a workspace as queried."""
     import torch
     n, ic, h, w, oc = shape
     inp = ti.make_inputs(ti.ConvShape("pwa", n, ic, h, w, oc, 1, 1, 1, 0), 8900, "f32", residual=True)
@@ -114,3 +114,22 @@ def test_f32_1x1_nan_stays_in_its_pixel(tvg, cfg):
     assert bool(torch.isnan(y[n - 1, :, 2, 1]).all())
     y[n - 1, :, 2, 1] = clean[n - 1, :, 2, 1]
     assert torch.equal(y, clean)
+
+
+@pytest.mark.parametrize("cfg", [(1, 512, 14, 14, 512, 1), (1, 1024, 7, 7, 200, 1), (3, 56, 6, 6, 31, 2), (8, 128, 28, 28, 256, 1), (1, 512, 14, 14, 128, 3)],
+                         ids=lambda c: "x".join(map(str, c)))
+def test_f32_1x1_weights_in_a_parameter_buffer(tvg, cfg):
+    """Weights and x that begin at any element of a larger buffer have the bits of aligned ones: no other kernel, whose
+    sums come in another order, takes their place."""
+    import torch
+    n, ic, h, w, oc, stride = cfg
+    d = dev_inputs(ti.make_inputs(ti.ConvShape("flat", n, ic, h, w, oc, 1, 1, stride, 0), 8970, "f32"), "f32")
+    want = tvg.conv2d_fused(d["x"], d["w"], d["scale"], d["shift"], stride=stride, relu=False)
+    def at(t, off):
+        store = torch.full((t.numel() + 8,), float("nan"), device="cuda")
+        v = store[off:off + t.numel()].view(t.shape)
+        v.copy_(t)
+        return v
+    for ox, ow in ((0, 1), (0, 2), (3, 3), (1, 0)):
+        y = tvg.conv2d_fused(at(d["x"], ox), at(d["w"], ow), d["scale"], d["shift"], stride=stride, relu=False)
+        assert torch.equal(y, want), (ox, ow)
