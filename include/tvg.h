@@ -71,9 +71,10 @@ typedef enum { TVG_F32 = 0, TVG_BF16 = 1 } tvg_dtype;
  *                 then run faster, since y neither displaces the operands in L2 nor waits
  *                 there to be written back.  Wrong between the layers of a network whose
  *                 activations fit the memory-side cache: the next layer would fetch from
- *                 HBM what it could have found there.  Off by default.  Kernels without wide
- *                 stores (the generic kernel that takes fp32 and odd shapes, the element-wise
- *                 tail of unaligned maps) ignore it. */
+ *                 HBM what it could have found there.  Off by default.  Kernels without
+ *                 16-byte stores of bf16 (the generic kernel and the fp32 kernels, the bf16 kernel for
+ *                 few tiles, whose outputs the caches hold anyway, the element-wise tail of
+ *                 unaligned maps) ignore it; depthwise kernels take it in both dtypes. */
 enum { TVG_RELU = 1u, TVG_STREAM_OUT = 2u };
 /* Only in the flags2 argument of tvg_conv2d_fused_dual: see there. */
 enum { TVG_CENTRE_TAP_ONLY = 4u };

@@ -180,6 +180,7 @@ __global__ __launch_bounds__(256, 2) void conv_f32_pw_kernel(const PwArgs a)
             if (a.residual) t += res[e];
             o[e] = a.relu ? fmaxf(t, 0.0f) : t;    // (without a ReLU a NaN stays one, as after a split reduction)
         }
+        // (the store hint of a call changes nothing here, 202 us with and without for six layers at batch 32, and is not taken)
         if (a.vec) *reinterpret_cast<pixels *>(a.y + idx) = o;
         else
 #pragma unroll

@@ -338,7 +338,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) void conv_rows_kernel(const RowsArg
     }
     __syncthreads();
 
-    // ---- sum over the waves, tail, stores: four pixels of one channel per item ------------------
+    // ---- sum over the waves, tail, stores: four pixels of one channel per item.  Plain ones under the store hint too, as
+    // all 8-byte stores are: with it eleven layers of a network take 48.8 us against 47.1 at batch 1, 69.1 against 68.3 at 4.
     const float *sum = reinterpret_cast<const float *>(body);
     const float floor_v = ((head2 ? a.relu2 : a.relu) & 1) ? 0.0f : -INFINITY;
     bf16_t *y = head2 ? a.y2 : a.y;

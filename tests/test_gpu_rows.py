@@ -135,3 +135,18 @@ def test_two_heads_have_the_bits_of_separate_calls_whichever_is_split(tvg, cfg, 
     rc = tvg.tvg_conv2d_fused_dual(desc, k1, tvg.TVG_CENTRE_TAP_ONLY if centre else 0, x, joined, scale, shift, bias, residual, y1, y2)
     assert rc == 0, tvg.status_string(rc)
     assert torch.equal(y1, want1) and torch.equal(y2, want2)
+
+
+@pytest.mark.parametrize("dtype,cfg", [("bf16", (2, 128, 28, 28, 128, 1, 3)), ("bf16", (2, 96, 13, 11, 33, 1, 1)), ("bf16", (8, 512, 14, 14, 512, 1, 1)),
+                                       ("f32", (1, 512, 14, 14, 512, 1, 1)), ("f32", (8, 256, 28, 28, 256, 1, 1))],
+                         ids=lambda c: "x".join(map(str, c)) if isinstance(c, tuple) else c)
+def test_store_hint_changes_no_bits(tvg, dtype, cfg):
+    import torch
+    n, ic, h, w, oc, stride, r = cfg
+    d = dev_inputs(ti.make_inputs(ti.ConvShape("hint", n, ic, h, w, oc, r, r, stride, r // 2), 8800 + sum(cfg), dtype, residual=True), dtype)
+    for relu in (True, False):
+        y, z = (tvg.conv2d_fused(d["x"], d["w"], d["scale"], d["shift"], None, d["residual"], stride=stride, pad=r // 2, relu=relu, stream_out=hint)
+                for hint in (True, False))
+        assert torch.equal(y, z)
+        if not relu:
+            assert bool((y < 0).any())
