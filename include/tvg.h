@@ -305,7 +305,7 @@ typedef enum {
     TVG_KERNEL_GENERIC = 0,        /* implicit GEMM, any shape: three kernels, see tvg_conv2d_get_knobs */
     TVG_KERNEL_3X3 = 1,            /* bf16 3x3, input patch in LDS, one stage              */
     TVG_KERNEL_3X3_PIPELINED = 2,  /* bf16 3x3, two LDS stages, software-pipelined         */
-    TVG_KERNEL_STEM = 3,           /* bf16 7x7 or 3x3 stride 2, few input channels (mt 64|32) */
+    TVG_KERNEL_STEM = 3,           /* bf16 7x7 or 3x3 stride 2, few input channels (mt 64|32; nt 256, few tiles 64|128) */
     TVG_KERNEL_1X1 = 4,            /* bf16 1x1                                             */
     TVG_KERNEL_F32_SMALL = 5,      /* fp32 1x1 / 3x3 / 7x7 stem of launch-bound problems (mt = nt = 32 or 16; stem 32 x 64; 1x1 also 32 x 64 and 32 x 128) */
     TVG_KERNEL_1X1_DEEP = 6        /* bf16 1x1 stride 1, reductions of 128 n channels       */

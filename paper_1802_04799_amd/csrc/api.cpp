@@ -336,7 +336,7 @@ tvg_status tvg_conv2d_get_knobs(const tvg_conv_desc *desc, tvg_conv_knobs *knobs
         }
     } else if (d.stem_shape) {
         k.mt = d.stem.mt;
-        k.nt = 256;
+        k.nt = d.stem.nt;
         k.stages = 1;
     } else if (d.pwd_shape) {
         k.mt = 64;
@@ -384,7 +384,7 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
     } else if (d.stem_shape) {
         *kernel = TVG_KERNEL_STEM;
         *mt = d.stem.mt;
-        *nt = 256;                             // (the large tile; with few tiles the kernel takes plan.nt)
+        *nt = d.stem.nt;
     } else if (d.pwd_shape) {
         *kernel = TVG_KERNEL_1X1_DEEP;
         *mt = 64;

@@ -414,3 +414,11 @@ def test_bf16_kernel_for_few_tiles_takes_them_where_it_is_faster(n, c, h, w, k, 
     d = desc(n=n, c=c, h=h, w=w, k=k, r=r, s=r, stride_h=stride, stride_w=stride, pad_h=r // 2, pad_w=r // 2, dtype=1)
     assert (tvg.tvg_conv2d_get_plan(d)[1] == 16) == few
     assert any(tvg.tvg_conv2d_get_knobs(d)) != few
+
+
+@pytest.mark.parametrize("n,h,w,k,r,tile", [(1, 224, 224, 64, 7, (64, 64)), (9, 128, 112, 64, 7, (64, 64)), (10, 128, 104, 64, 7, (64, 256)),
+                                            (1, 224, 224, 32, 3, (32, 128)), (20, 128, 104, 32, 3, (32, 256)), (8, 128, 128, 50, 3, (64, 64))])
+def test_stem_plan_reports_the_tile_that_runs(n, h, w, k, r, tile):
+    """Few tiles (512 of 64 pixels, 128 for 32 channels): narrow ones."""
+    d = desc(n=n, c=3, h=h, w=w, k=k, r=r, s=r, stride_h=2, stride_w=2, pad_h=r // 2, pad_w=r // 2, dtype=1)
+    assert tvg.tvg_conv2d_get_plan(d) == (3, *tile) and tvg.tvg_conv2d_get_knobs(d) == (*tile, 1, 0, 0, 0)
