@@ -200,7 +200,7 @@ __global__ __launch_bounds__(256) void conv1x1_rows_kernel(const PwRowsArgs a)
             }
     }
     __syncthreads();
-    const float floor_v = (a.relu & 1) ? 0.0f : -INFINITY;
+    const float floor_v = relu_floor(a.relu & 1);
     if (UNAL || !a.vec) {                          // adjacent lanes adjacent pixels
         for (int id = tid; id < MT * NT; id += 256) {
             const int p = id % NT, row = id / NT;

@@ -231,7 +231,7 @@ __global__ __launch_bounds__(BIG ? 1024 : 512) void conv_f32_small_kernel(const 
         }
         const float sc = a.scale[oc];
         const float sf = a.bias ? fmaf(a.bias[oc], sc, a.shift[oc]) : a.shift[oc];
-        const float floor_v = a.relu ? 0.0f : -INFINITY;
+        const float floor_v = relu_floor(a.relu);
         const int idx = (n * a.OC + oc) * OHW + p0 + pb;
         if (a.vec_out) {                               // OHW % 4 == 0: the whole group is inside
             float4v r4 = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -414,7 +414,7 @@ __global__ __launch_bounds__(kStemThreads) void conv_f32_stem_kernel(const F32St
         if (oc >= a.OC || px >= npx) continue;
         const float sc = a.scale[oc];
         const float sf = a.bias ? fmaf(a.bias[oc], sc, a.shift[oc]) : a.shift[oc];
-        const float floor_v = a.relu ? 0.0f : -INFINITY;
+        const float floor_v = relu_floor(a.relu);
         const int idx = (n * a.OC + oc) * OHW + p0 + px;
         if (a.vec_out) {                                     // OHW % 4 == 0: the whole group is inside
             float4v r4 = {0.0f, 0.0f, 0.0f, 0.0f};

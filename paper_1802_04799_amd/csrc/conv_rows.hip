@@ -341,7 +341,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void conv_rows_kernel(const RowsArg
     // ---- sum over the waves, tail, stores: four pixels of one channel per item.  Plain ones under the store hint too, as
     // all 8-byte stores are: with it eleven layers of a network take 48.8 us against 47.1 at batch 1, 69.1 against 68.3 at 4.
     const float *sum = reinterpret_cast<const float *>(body);
-    const float floor_v = ((head2 ? a.relu2 : a.relu) & 1) ? 0.0f : -INFINITY;
+    const float floor_v = relu_floor((head2 ? a.relu2 : a.relu) & 1);
     bf16_t *y = head2 ? a.y2 : a.y;
     const bf16_t *residual = head2 ? nullptr : a.residual;
     const int k0 = head2 ? a.k1 : 0, kn = head2 ? a.OC - a.k1 : a.k1;           // (k1 = OC without a second head)

@@ -213,7 +213,7 @@ __global__ __launch_bounds__(256) void dwconv3x3_direct_kernel(const DwDirectArg
         }
     }
 
-    const float floor_v = a.relu ? 0.0f : -INFINITY;
+    const float floor_v = relu_floor(a.relu);
 #pragma unroll
     for (int o = 0; o < RB; ++o) {
         const int oh = oh0 + o;
@@ -315,7 +315,7 @@ __global__ __launch_bounds__(256) void dwconv3x3_direct_bf16_kernel(const DwDire
     }
 
     typedef uint32_t outv __attribute__((ext_vector_type(CW / 2)));
-    const float floor_v = a.relu ? 0.0f : -INFINITY;
+    const float floor_v = relu_floor(a.relu);
 #pragma unroll
     for (int o = 0; o < RB; ++o) {
         const int oh = oh0 + o;
@@ -430,7 +430,7 @@ __global__ __launch_bounds__(256) void dwconv3x3_smallplane_kernel(const DwSmall
 
     const T *res = static_cast<const T *>(a.residual);
     T *yg = static_cast<T *>(a.y);
-    const float floor_v = a.relu ? 0.0f : -INFINITY;
+    const float floor_v = relu_floor(a.relu);
     for (int p = sub; p < np; p += G) {
         const float *pl = tile + p * HW;
         const float *pp = prm + p * 12;
@@ -608,7 +608,7 @@ __global__ __launch_bounds__(256) void dwconv3x3_rows_kernel(const DwRowsArgs a)
     }
 
     const size_t idx = ((size_t)plane * a.OH + oh) * OW;
-    const float floor_v = a.relu ? 0.0f : -INFINITY;
+    const float floor_v = relu_floor(a.relu);
     T *yp = static_cast<T *>(a.y) + idx;
     const T *rp = a.residual ? static_cast<const T *>(a.residual) + idx : nullptr;
     constexpr bool kWords = (OW * sizeof(T)) % 4 == 0;      // the output row is whole words

@@ -239,7 +239,7 @@ __global__ __launch_bounds__(256, MT <= 128 ? 2 : 1) void dwpw_kernel(const DwPw
     store_weights(0);
     __syncthreads();
 
-    const float floor_dw = a.relu_dw ? 0.0f : -INFINITY;
+    const float floor_dw = relu_floor(a.relu_dw);
     // One chunk: `steady` = inside the main loop, where every load and store below happens
     // (no conditions: the compiler then knows how many loads are in flight at each wait; with
     // conditional loads it waits for all of them, i.e. for the newest, and the look-ahead is

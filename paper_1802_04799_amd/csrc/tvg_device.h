@@ -92,6 +92,14 @@ __device__ __forceinline__ int divide(int n, const Divider &v, int *rem)
     return q;
 }
 
+// The last step of a tail is fmaxf with this: zero for ReLU, else a NaN, which leaves the other operand as it is - and of
+// two NaNs is one, where minus infinity made minus infinity of a NaN.  (The compiler does not see through readfirstlane,
+// else it makes a select on the flag of every value: 1 % of a network.)
+__device__ __forceinline__ float relu_floor(bool relu)
+{
+    return __uint_as_float(__builtin_amdgcn_readfirstlane(relu ? 0u : 0x7FC00000u));
+}
+
 template <typename T> struct Elem;
 template <> struct Elem<float> {
     static __device__ __forceinline__ float load(const float *p, int i) { return p[i]; }
@@ -203,7 +211,7 @@ __device__ __forceinline__ void store_tile(const float16v &acc, unsigned char *s
     const int lrow = lane & 31, lhalf = lane >> 5;
     const int oc = oc0 + lrow;
     const float sc = ss[2 * (row0 + lrow)], sf = ss[2 * (row0 + lrow) + 1];
-    const float floor_v = (t.relu & 1) ? 0.0f : -INFINITY;     // no ReLU = clamp at minus infinity
+    const float floor_v = relu_floor(t.relu & 1);
     const T *res = static_cast<const T *>(t.residual);
     T *y = static_cast<T *>(t.y);
     // image index of the tile's first pixel: uniform, one scalar division; later pixels
@@ -373,7 +381,7 @@ __device__ __forceinline__ void store_fast_tiles(const float16v (&acc)[MI][NJ], 
     // a short last batch would let the pair store below pick up a stale staged tile
     static_assert(T % BT == 0, "the batch size must divide the number of tiles of a wave");
     const int lrow = lane & 31, lhalf = lane >> 5;
-    const float floor_v = (t.relu & 1) ? 0.0f : -INFINITY;
+    const float floor_v = relu_floor(t.relu & 1);
     const bf16_t *res = static_cast<const bf16_t *>(t.residual);
     bf16_t *y = static_cast<bf16_t *>(t.y);
     const int row = lane >> 2, g = lane & 3;
