@@ -44,7 +44,7 @@ struct PwRowsArgs {
 template <int MT, int NT, int CH, bool UNAL>
 __global__ __launch_bounds__(256) void conv1x1_rows_kernel(const PwRowsArgs a)
 {
-    constexpr int WM = MT == 128 && NT == 64 ? 4 : 2, WN = 4 / WM;       // waves along channels, along pixels
+    constexpr int WM = 2, WN = 2;                  // waves along channels, along pixels
     constexpr int MI = MT / WM / 32, NJ = NT / WN / 32;
     constexpr int GT = NT / 8;                     // pixel groups per tile
     constexpr int XT = CH * GT / 256, WT = MT * (CH / 8) / 256;          // load tasks per thread

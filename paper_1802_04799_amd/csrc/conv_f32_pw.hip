@@ -217,13 +217,8 @@ template <int NB, int PXL, int KS, int CHAIN, int TOT = CHAIN == 1 && NB * PXL <
 tvg_status launch(const PwArgs &args, long tiles, hipStream_t stream)
 {
     const auto kernel = conv_f32_pw_kernel<NB, PXL, KS, CHAIN, TOT>;
-    constexpr size_t lds = (size_t)4 * 32 * 32 * PXL * NB * 4;      // KS partial tiles of 32 * (4 / KS) channels
-    static bool configured = false;                // opt in to > 64 KB of dynamic LDS once per instance
-    if (!configured && lds > 64 * 1024) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
-            return TVG_ERR_LAUNCH;
-        configured = true;
-    }
+    constexpr size_t lds = (size_t)4 * 32 * 32 * PXL * NB * 4;      // KS partial tiles of 32 * (4 / KS) channels: 64 KB at most
+    static_assert(lds <= 64 * 1024, "more wants an opt-in");
     kernel<<<dim3((unsigned)tiles), dim3(256), lds, stream>>>(args);
     return hipGetLastError() == hipSuccess ? TVG_OK : TVG_ERR_LAUNCH;
 }
