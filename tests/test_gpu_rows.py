@@ -31,6 +31,8 @@ EVERY_INSTANCE = [
     ((2, 32, 5, 5, 33, 2, 3), 16), ((2, 96, 4, 5, 17, 2, 3), 16), ((4, 32, 1, 1, 33, 2, 3), 16),
     ((1, 32, 1, 33, 17, 2, 3), 32), ((1, 128, 1, 35, 33, 2, 3), 32), ((16, 64, 21, 21, 17, 2, 3), 32),
     ((1, 96, 1, 47, 17, 2, 3), 32),
+    # (twelve loads per lane in tiles of 32 pixels)
+    ((33, 576, 1, 1, 579, 1, 3), 32), ((62, 384, 1, 2, 324, 1, 3), 32),
     # reductions longer than a workgroup's waves: several turns per wave
     ((2, 512, 7, 7, 40, 1, 3), 16), ((1, 800, 9, 12, 33, 2, 3), 16), ((3, 1024, 7, 7, 50, 1, 1), 16),
 ]
@@ -104,6 +106,11 @@ def test_few_tiles_two_heads_have_the_bits_of_separate_calls(tvg, cfg, centre):
     ((6, 64, 56, 56, 128, 128, 2), (False, False)), ((12, 256, 14, 14, 512, 512, 2), (False, False)), ((8, 160, 14, 14, 512, 512, 2), (False, True)),
     ((4, 64, 28, 28, 64, 2048, 2), (True, False)), ((1, 256, 112, 112, 64, 16, 1), (False, True)), ((2, 96, 13, 11, 64, 70, 1), (True, True)),
     ((3, 512, 14, 14, 64, 40, 1), (True, True)), ((5, 160, 8, 127, 64, 24, 2), (False, True)), ((5, 160, 8, 128, 64, 17, 2), (False, True)),
+    # both in one launch: the other instances (one or two blocks of pixels, loads per lane, even and odd rows, filter rows)
+    ((1, 256, 2, 12, 64, 1, 2), (True, True)), ((16, 64, 1, 8, 64, 1, 2), (True, True)), ((3, 512, 11, 36, 128, 64, 2), (True, True)),
+    ((16, 64, 16, 24, 64, 1, 2), (True, True)), ((2, 192, 2, 5, 256, 1, 2), (True, True)), ((18, 32, 14, 5, 64, 17, 2), (True, True)),
+    ((54, 32, 2, 3, 128, 128, 2), (True, True)), ((3, 256, 27, 15, 256, 128, 2), (True, True)), ((5, 32, 26, 35, 64, 17, 2), (True, False)),
+    ((2, 512, 13, 35, 256, 17, 2), (True, True)), ((3, 64, 18, 29, 256, 1, 2), (True, True)),
     ((2, 64, 28, 28, 64, 1024, 2), (True, True)), ((1, 64, 28, 28, 64, 40, 1), (True, False)), ((4, 128, 28, 28, 256, 256, 2), (True, True)), ((32, 64, 56, 56, 128, 128, 2), (False, False)),
 ], ids=lambda c: "x".join(map(str, c)))
 @pytest.mark.parametrize("centre", [True, False])
