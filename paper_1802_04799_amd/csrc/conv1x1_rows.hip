@@ -9,11 +9,11 @@
 //     aligned words around a group, shifted into place, and stores of single pixels with adjacent lanes on adjacent ones.
 //   - Chunks of 32 channels (64 from 1024 on), two LDS stages, one barrier per chunk, 2 or 4 chunks in flight in registers.
 //   - The tail goes through LDS as fp32, so that residual and output move in 16-byte pieces of a channel row.
-// What bounds it: on the layers of a network a fixed 6 us (launch, first loads, tail) and then the LDS: 300 cycles per
-// chunk and 128 x 64 tile against 128 of the matrix pipe.  us before -> now at batch 32: 512 -> 512 14x14 12.2 -> 11.2, 1024 ->
-// 1024 7x7 14.9 -> 12.1, 256 -> 256 28x28 12.6 -> 11.1; batch 8: 256 -> 256 28x28 6.8 -> 5.2; batch 128: 512 -> 512 37.6 -> 30;
-// 96 -> 143, 26 images 83x26: 45.5 -> 12.8.  230 shapes: 173 take it (or the kernel for few tiles), 1.30 times as fast in the
-// geometric mean.
+// What bounds it: on the layers of a network a fixed 6 us (launch, first loads, tail) and then the LDS: 224 cycles per
+// chunk and tile of 64 channels x 128 pixels against 128 of the matrix pipe.  us before -> now at batch 32: 512 -> 512
+// 14x14 12.2 -> 11.2, 1024 -> 1024 7x7 14.9 -> 12.1, 256 -> 256 28x28 12.6 -> 11.1; batch 8: 256 -> 256 28x28 6.8 -> 5.2; batch
+// 128: 512 -> 512 37.6 -> 30; 96 -> 143, 26 images 83x26: 45.5 -> 12.8.  Of 253 shapes 179 take it (or the kernel for few
+// tiles), 1.32 times as fast in the geometric mean.
 #include "tvg_device.h"
 #include "tvg_internal.h"
 
@@ -289,13 +289,14 @@ bool plan_conv1x1_rows(const ConvProblem &p, Pw1x1Plan *plan)
         if (!((mt == 64 && (nt == 64 || nt == 128)) || (mt == 128 && nt == 128))) return false;
     } else {
         // Where the kernel that packs pixels in registers stays: reductions of one or two chunks, which it has in flight as a
-        // whole (64 -> 128, 8 images 56x56, 4.6 us there, 5.1 here; one chunk and a large map: 18.5 and 16.4), four chunks on
-        // few tiles (128 -> 256, one image 28x28, 4.1 and 5.2), large odd maps (672 -> 88, 16 images 73x73, 39.8 and 42.6).
+        // whole (64 -> 128, 8 images 56x56, 4.3 us there, 4.8 here; 41 shapes of two chunks 0.79 to 1.9 times as fast here, half of
+        // them below 0.97; one chunk and a large map: 18.5 and 16.4), large odd maps (19 shapes 0.81 to 1.5, half of them below 1).
+        // Not four chunks on few tiles (ten shapes 1.00 to 1.18; 128 -> 256, one image 28x28, 3.9 and 3.4).
         // Wider tiles from where they still cover the chip (128 images, 512 -> 512 14x14, 31 -> 30; 1024 -> 1024 7x7, 35.6 ->
         // 30.7; 32 images, 256 -> 512 14x14, 8.5 but 8.7).
         const bool odd = p.H * p.W % 2 != 0;
         const long t = tiles(64, 64);
-        if ((odd && p.H * p.W > 1024) || p.IC == 64 || (p.IC == 32 && (odd || t < 3000)) || (p.IC == 128 && t < 400)) return false;
+        if ((odd && p.H * p.W > 1024) || p.IC == 64 || (p.IC == 32 && (odd || t < 3000))) return false;
         if (p.IC >= 1024 && t >= 1500) mt = nt = 128;
         else if (!odd && (p.IC >= 512 ? t >= 800 : p.IC >= 256 ? t >= 1500 : p.IC == 32)) nt = 128;
     }

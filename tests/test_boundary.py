@@ -422,3 +422,11 @@ def test_stem_plan_reports_the_tile_that_runs(n, h, w, k, r, tile):
     """Few tiles (512 of 64 pixels, 128 for 32 channels): narrow ones."""
     d = desc(n=n, c=3, h=h, w=w, k=k, r=r, s=r, stride_h=2, stride_w=2, pad_h=r // 2, pad_w=r // 2, dtype=1)
     assert tvg.tvg_conv2d_get_plan(d) == (3, *tile) and tvg.tvg_conv2d_get_knobs(d) == (*tile, 1, 0, 0, 0)
+
+
+@pytest.mark.parametrize("n,c,h,w,k,rows", [(1, 128, 28, 28, 256, True), (21, 128, 28, 28, 39, True), (8, 64, 56, 56, 128, False),
+                                            (1, 32, 112, 112, 64, False), (1, 64, 47, 71, 215, False), (32, 256, 28, 28, 256, True)])
+def test_bf16_1x1_kernel_with_rows_as_they_lie(n, c, h, w, k, rows):
+    """It stays away from reductions that the kernel beside it has in flight as a whole, and from large odd maps."""
+    d = desc(n=n, c=c, h=h, w=w, k=k, r=1, s=1, pad_h=0, pad_w=0, dtype=1)
+    assert (tvg.tvg_conv2d_get_knobs(d)[5] == 2) == rows

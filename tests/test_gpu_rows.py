@@ -111,7 +111,7 @@ def test_few_tiles_two_heads_have_the_bits_of_separate_calls(tvg, cfg, centre):
     ((16, 64, 16, 24, 64, 1, 2), (True, True)), ((2, 192, 2, 5, 256, 1, 2), (True, True)), ((18, 32, 14, 5, 64, 17, 2), (True, True)),
     ((54, 32, 2, 3, 128, 128, 2), (True, True)), ((3, 256, 27, 15, 256, 128, 2), (True, True)), ((5, 32, 26, 35, 64, 17, 2), (True, False)),
     ((2, 512, 13, 35, 256, 17, 2), (True, True)), ((3, 64, 18, 29, 256, 1, 2), (True, True)),
-    ((2, 64, 28, 28, 64, 1024, 2), (True, True)), ((1, 64, 28, 28, 64, 40, 1), (True, False)), ((4, 128, 28, 28, 256, 256, 2), (True, True)), ((32, 64, 56, 56, 128, 128, 2), (False, False)),
+    ((2, 64, 28, 28, 64, 1024, 2), (True, True)), ((1, 64, 28, 28, 64, 40, 1), (True, False)), ((2, 128, 28, 28, 192, 70, 1), (True, False)), ((8, 128, 28, 28, 192, 70, 1), (False, False)), ((4, 128, 28, 28, 256, 256, 2), (True, True)), ((32, 64, 56, 56, 128, 128, 2), (False, False)),
 ], ids=lambda c: "x".join(map(str, c)))
 @pytest.mark.parametrize("centre", [True, False])
 def test_two_heads_have_the_bits_of_separate_calls_whichever_is_split(tvg, cfg, few, centre):
