@@ -9,11 +9,12 @@
 //     along the output channels.  Few tiles: KS = 4 and the narrowest of 32, 64 or 128 pixels that stays within one
 //     round of workgroups.  Throughput: KS = 2, tiles of 64 channels x 64 or 128 pixels.
 //   - Consecutive workgroups take the channel tiles of one pixel tile and meet in an XCD's L2.
-// What bounds it: the matrix pipe and the plain adds of short chains, on few tiles the first loads.  us before -> now:
+// What bounds it: the matrix pipe (51 % of its rate at 32 x 512 -> 512, 14x14) and the plain adds of short chains, on few
+// tiles the first loads.  us before -> now:
 // batch 4, 512 -> 512 14x14 19.3 -> 8.7 (the launch-bound kernel), 256 -> 256 28x28 13.5 -> 8.8 (the kernel with rows in
 // LDS); batch 1, 512 -> 512 14x14 20.6 -> 5.7, stride 3 15.4 -> 6.8; batch 32, 512 -> 512 14x14 59.7 -> 42 (the gather
-// kernel).  MobileNet body, batch 4: 283 -> 197.  Of 602 shapes 516 take it, 1.76 times as fast in the geometric mean, four
-// of them by 0.95 to 0.97 (strides, where the kernel with rows in LDS stood); their error against 64 bits is 0.69 of the
+// kernel).  MobileNet body, batch 4: 283 -> 197.  Of 602 shapes 516 take it, 1.75 times as fast in the geometric mean, three
+// of them by 0.94 to 0.97 (strides, where the kernel with rows in LDS stood); their error against 64 bits is 0.69 of the
 // former kernels' in the geometric mean and 1.00 at most where there are a thousand outputs to take it from.
 #include <algorithm>
 
