@@ -137,7 +137,8 @@ tvg_status tvg_conv2d_fused(const tvg_conv_desc *desc, const void *x, const void
  * (w[k1 + j][i][1][1] = the 1x1 weight, the caller builds the tensor once); TVG_CENTRE_TAP_ONLY in
  * flags2 is the caller's promise of exactly that, and head 2's tiles then skip the other eight
  * taps.  Without the flag head 2 is a full 3x3 convolution.  One launch and one pass over x
- * instead of two.
+ * instead of two; few tiles, where one head only runs in the kernel for them or there is no stride, take a
+ * launch for each head.
  * Errors: TVG_ERR_BAD_SHAPE unless 0 < k1 < desc->k; TVG_ERR_UNSUPPORTED for problems outside the
  * single-stage 3x3 kernel (other dtype, filter, padding; k1 no multiple of 64; x or w not
  * 16-byte aligned) - run the two convolutions separately then.  y1, y2 must not overlap x, w or
@@ -349,7 +350,7 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
  * fp32 kernel for throughput sizes have none: get_knobs reports zeros, which set_knobs takes as
  * "leave it to the library", and fixing mt, nt or split_k selects the gather kernel.  The same goes for
  * bf16 3x3 and 1x1 problems with few tiles, whose waves split the reduction: get_plan reports TVG_KERNEL_3X3
- * or TVG_KERNEL_1X1 with mt = 16, get_knobs zeros, and fixing any knob selects the kernels above.  And for fp32
+ * or TVG_KERNEL_1X1 with mt = 16, get_knobs zeros, and fixing any knob selects the kernels above.  And for most fp32
  * 1x1 problems with 8 n channels (TVG_KERNEL_F32_SMALL or TVG_KERNEL_GENERIC, zeros).
  */
 typedef struct {

@@ -154,7 +154,7 @@ Dispatch dispatch_for(const ConvProblem &p)
     d.tiled_shape = tvg::plan_conv_f32_tiled(p, &d.tiled);
     d.f32_shape = !d.tiled_shape && tvg::plan_conv_f32_small(p, &d.f32);
     // fp32 1x1 by what it takes the place of: tiles as the throughput kernel cuts them, narrow ones where the
-    // launch-bound kernel would run, its own where the gather kernel would have 128 x 128 tiles for every CU
+    // launch-bound kernel would run or the gather kernel's 128 x 128 tiles are fewer than CUs, its own where there are more
     d.pw32_shape = tvg::plan_conv_f32_pw(p, d.f32_shape, d.tiled_shape ? d.tiled.nt : 0, &d.pw32);
     d.generic = tvg::plan_conv(p, true);
     d.generic_single = tvg::plan_conv(p, false);
