@@ -157,3 +157,33 @@ def test_store_hint_changes_no_bits(tvg, dtype, cfg):
         assert torch.equal(y, z)
         if not relu:
             assert bool((y < 0).any())
+
+
+@pytest.mark.parametrize("cfg", [(8, 160, 14, 14, 512, 64, 2), (2, 96, 13, 11, 64, 70, 1)], ids=lambda c: "x".join(map(str, c)))
+def test_two_heads_of_a_launch_each_in_a_graph(tvg, cfg):
+    """Captured once, replayed with other inputs and eager work between: the bits of an eager call every time."""
+    import torch
+    n, ic, h, w, k1, k2, stride = cfg
+    g = torch.Generator(device="cuda").manual_seed(8900 + sum(cfg))
+    def rand(*shape):
+        return torch.rand(shape, generator=g, device="cuda") * 2 - 1
+    x, joined = rand(n, ic, h, w).bfloat16(), torch.zeros(k1 + k2, ic, 3, 3, dtype=torch.bfloat16, device="cuda")
+    joined[:k1], joined[k1:, :, 1, 1] = rand(k1, ic, 3, 3).bfloat16(), rand(k2, ic).bfloat16()
+    scale, shift = rand(k1 + k2), rand(k1 + k2)
+    oh, ow = (h - 1) // stride + 1, (w - 1) // stride + 1
+    out = [torch.empty(n, k, oh, ow, dtype=torch.bfloat16, device="cuda") for k in (k1, k2, k1, k2)]
+    desc = tvg.ConvDesc(n, ic, h, w, k1 + k2, 3, 3, stride, stride, 1, 1, tvg.TVG_BF16, tvg.TVG_RELU)
+    def call(y1, y2):
+        assert tvg.tvg_conv2d_fused_dual(desc, k1, tvg.TVG_CENTRE_TAP_ONLY, x, joined, scale, shift, None, None, y1, y2) == 0
+    call(*out[2:])
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        call(*out[:2])
+    for _ in range(3):
+        x.copy_(rand(n, ic, h, w))
+        call(*out[2:])
+        out[0].zero_(), out[1].zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
