@@ -20,7 +20,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtvg.so")
 NATIVE = os.path.join(HERE, "_native.so")
-SOURCES = ["api.cpp", "conv_igemm.hip", "conv3x3_patch.hip", "conv3x3_dbuf.hip", "conv7x7s2_stem.hip", "conv1x1.hip", "dwconv.hip", "dwpw.hip", "pool.hip", "probe.hip", "conv_f32_small.hip", "conv3x3_winograd.hip", "conv1x1_deep.hip", "conv_bf16_any.hip", "conv_f32_tiled.hip", "conv_rows.hip", "conv_f32_pw.hip", "conv1x1_rows.hip"]
+SOURCES = ["api.cpp", "conv_igemm.hip", "conv3x3_patch.hip", "conv3x3_dbuf.hip", "conv7x7s2_stem.hip", "conv1x1.hip", "dwconv.hip", "dwpw.hip", "pool.hip", "probe.hip", "conv_f32_small.hip", "conv3x3_winograd.hip", "conv1x1_deep.hip", "conv_bf16_any.hip", "conv_f32_tiled.hip", "conv_rows.hip", "conv_f32_pw.hip", "conv1x1_rows.hip", "conv3x3_strips.hip"]
 HEADERS = [os.path.join(CSRC, "tvg_internal.h"), os.path.join(CSRC, "tvg_device.h"),
            os.path.join(ROOT, "include", "tvg.h")]
 

@@ -99,8 +99,9 @@ void tile_key(const ConvProblem &p, int (&key)[12])
 // 257th distinct problem.  The launch-bound batch-1 layers spend 1-5 us per call in planning
 // otherwise.
 struct Dispatch {
-    bool rows_shape, patch_shape, stem_shape, pw_shape, pwr_shape, pwd_shape, f32_shape, any_shape, tiled_shape, pw32_shape;
+    bool rows_shape, patch_shape, stem_shape, pw_shape, pwr_shape, pwd_shape, f32_shape, any_shape, tiled_shape, pw32_shape, strips_shape;
     tvg::RowsPlan rows;             // few tiles: in front of the 3x3 and 1x1 kernels
+    tvg::StripsPlan strips;         // in front of the 3x3 kernels
     tvg::Patch3x3Plan patch;
     tvg::StemPlan stem;
     tvg::Pw1x1Plan pw, pwr;         // pwr: in front of pw
@@ -143,6 +144,7 @@ Dispatch dispatch_for(const ConvProblem &p)
     d.pw_shape = !d.patch_shape && !d.stem_shape && tvg::plan_conv1x1(p, &d.pw);
     d.pwr_shape = d.pw_shape && tvg::plan_conv1x1_rows(p, &d.pwr);
     d.rows_shape = (d.patch_shape || d.pw_shape) && tvg::plan_conv_rows(p, &d.rows);
+    d.strips_shape = d.patch_shape && !d.rows_shape && tvg::plan_conv3x3_strips(p, d.patch, &d.strips);
     {
         // stages knob of a 1x1 problem: 2 = the deep-reduction kernel.  No rule picks it: measured at
         // batch 32 / 64 over thirteen MobileNet and ResNet-50 pointwise shapes it takes 1.15-1.5 times
@@ -182,6 +184,7 @@ tvg_status run_dense(const ConvProblem &p, const Dispatch &d, const tvg::ConvPoi
                      hipStream_t stream)
 {
     if (d.rows_shape && tvg::conv_rows_pointers_ok(ptr)) return tvg::launch_conv_rows(p, d.rows, ptr, stream);
+    if (d.strips_shape && tvg::conv3x3_strips_pointers_ok(ptr)) return tvg::launch_conv3x3_strips(p, d.strips, ptr, stream);
     if (d.patch_shape && tvg::conv3x3_patch_pointers_ok(ptr))
         return tvg::launch_conv3x3_patch(p, d.patch, ptr, stream);
     if (d.stem_shape && tvg::conv7x7s2_stem_pointers_ok(ptr))
@@ -315,6 +318,12 @@ tvg_status tvg_conv2d_set_knobs(const tvg_conv_desc *desc, const tvg_conv_knobs 
                                      knobs->lds_pitch, knobs->row_loads});
 }
 
+// The kernel of strips is reported where the knobs name it; by rule it stands in for the kernel that is reported.
+static bool named_strips(const ConvProblem &p, const Dispatch &d)
+{
+    return d.strips_shape && tvg::forced_knobs(p).row_loads == 2;
+}
+
 tvg_status tvg_conv2d_get_knobs(const tvg_conv_desc *desc, tvg_conv_knobs *knobs)
 {
     if (!knobs) return TVG_ERR_NULL;
@@ -325,6 +334,10 @@ tvg_status tvg_conv2d_get_knobs(const tvg_conv_desc *desc, tvg_conv_knobs *knobs
     tvg_conv_knobs k = {0, 0, 0, 0, 0, 0};
     if (d.rows_shape) {
         // no knobs: fixing one selects the 3x3 or 1x1 kernel behind it
+    } else if (named_strips(p, d)) {
+        k.stages = 1;
+        k.split_k = d.strips.kg;
+        k.row_loads = 2;
     } else if (d.patch_shape) {
         k.mt = d.patch.mt;
         k.nt = d.patch.nt;
@@ -377,6 +390,10 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
         *kernel = d.patch_shape ? TVG_KERNEL_3X3 : TVG_KERNEL_1X1;
         *mt = 16;
         *nt = 16 * d.rows.nj;
+    } else if (named_strips(p, d)) {
+        *kernel = TVG_KERNEL_3X3;
+        *mt = 64;
+        *nt = 32 * d.strips.b;
     } else if (d.patch_shape) {
         *kernel = d.patch.dbuf ? TVG_KERNEL_3X3_PIPELINED : TVG_KERNEL_3X3;
         *mt = d.patch.mt;
@@ -466,7 +483,8 @@ tvg_status tvg_conv2d_fused_dual(const tvg_conv_desc *desc, int32_t k1, uint32_t
     const int relu2 = (flags2 & TVG_RELU ? 1 : 0) | (flags2 & TVG_STREAM_OUT ? 2 : 0);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     // Each head has the bits of a call of its own, so the kernel for few tiles, whose waves split the reduction, takes
-    // exactly the heads that it would take then: both in one launch where their split is the same, or each in one.
+    // exactly the heads that it would take then: both in one launch where their split is the same, or each in one.  So does
+    // the kernel of strips, which has no two-head launches.
     ConvProblem h1 = p, h2 = p;
     h1.OC = k1;
     h2.OC = p.OC - k1;
@@ -482,8 +500,10 @@ tvg_status tvg_conv2d_fused_dual(const tvg_conv_desc *desc, int32_t k1, uint32_t
     const tvg::ConvPointers ptr2{x, static_cast<const char *>(w) + (size_t)k1 * p.IC * 18, scale + k1, shift + k1,
                                  bias ? bias + k1 : nullptr, nullptr, y2, nullptr};
     const bool rows1 = d1.rows_shape && tvg::conv_rows_pointers_ok(ptr), rows2 = d2.rows_shape && tvg::conv_rows_pointers_ok(ptr2);
+    const bool strips1 = !rows1 && d1.strips_shape && tvg::conv3x3_strips_pointers_ok(ptr);
+    const bool strips2 = !rows2 && d2.strips_shape && tvg::conv3x3_strips_pointers_ok(ptr2);
     const tvg::DualHead dual{k1, relu2, centre ? 1 : 0, y2};
-    if (!rows1 && !rows2) return tvg::launch_conv3x3_patch(p, plan, ptr, stream, &dual);
+    if (!rows1 && !rows2 && !strips1 && !strips2) return tvg::launch_conv3x3_patch(p, plan, ptr, stream, &dual);
     tvg::RowsPlan rows;
     if (rows1 && rows2 && tvg::plan_conv_rows_dual(p, d1.rows, d2.rows, centre, &rows))
         return tvg::launch_conv_rows(p, rows, ptr, stream, &dual);
@@ -493,8 +513,10 @@ tvg_status tvg_conv2d_fused_dual(const tvg_conv_desc *desc, int32_t k1, uint32_t
     if (!d1.patch_shape && !tvg::plan_conv3x3_patch(h1, &plan1, k1)) return TVG_ERR_UNSUPPORTED;
     if ((centre || !d2.patch_shape) && !tvg::plan_conv3x3_patch(h2_3x3, &plan2, k1)) return TVG_ERR_UNSUPPORTED;
     if (rows2 && centre && !tvg::plan_conv_rows_centre(h2, &rows)) return TVG_ERR_UNSUPPORTED;
-    st = rows1 ? tvg::launch_conv_rows(h1, d1.rows, ptr, stream) : tvg::launch_conv3x3_patch(h1, plan1, ptr, stream);
+    st = rows1 ? tvg::launch_conv_rows(h1, d1.rows, ptr, stream)
+               : strips1 ? tvg::launch_conv3x3_strips(h1, d1.strips, ptr, stream) : tvg::launch_conv3x3_patch(h1, plan1, ptr, stream);
     if (st != TVG_OK) return st;
+    if (strips2) return tvg::launch_conv3x3_strips(h2, d2.strips, ptr2, stream);
     if (rows2) return tvg::launch_conv_rows(h2, centre ? rows : d2.rows, ptr2, stream, nullptr, centre);
     if (!centre) return tvg::launch_conv3x3_patch(h2, plan2, ptr2, stream);
     const tvg::DualHead alone{0, relu2, 1, y2};

@@ -117,6 +117,20 @@ bool conv_rows_pointers_ok(const ConvPointers &ptr);
 tvg_status launch_conv_rows(const ConvProblem &p, const RowsPlan &plan, const ConvPointers &ptr, hipStream_t stream,
                             const DualHead *dual = nullptr, bool centre = false);
 
+// bf16 3x3 without a stride, rows of at most 32 pixels, at throughput size: a wave owns 16 channels of four strips of
+// b rows x 8 pixels, a group of four waves 64 channels of them.
+struct StripsPlan {
+    int b, kg;                        // rows of a strip, groups that split the reduction (1 or 2)
+    int t8, spi, sr, rows;            // strips per row, strip rows per image and per tile, staged rows per tile
+    int row_bytes, strip_bytes, half, plane, rows_bytes;
+    long ptiles, tiles, workgroups;
+    size_t lds_bytes;
+};
+// (patch: the plan of the kernels that it would run in otherwise)
+bool plan_conv3x3_strips(const ConvProblem &p, const Patch3x3Plan &patch, StripsPlan *plan);
+bool conv3x3_strips_pointers_ok(const ConvPointers &ptr);
+tvg_status launch_conv3x3_strips(const ConvProblem &p, const StripsPlan &plan, const ConvPointers &ptr, hipStream_t stream);
+
 // bf16 7x7 stride-2 pad-3 kernel for IC <= 4 (the ResNet stem).
 struct StemPlan {
     int rows;           // virtual input rows staged per tile
