@@ -300,9 +300,9 @@ tvg_status tvg_plan_arena(const tvg_tensor_life *tensors, int32_t count, uint64_
  * cannot use makes the call fall back to the generic kernel, which is correct but slow: time
  * before you fix.  At most 1024 problems are remembered.
  * tvg_conv2d_get_plan: which kernel and tile shape a call with this descriptor would use now
- * (alignment of the pointers aside).  kernel, mt, nt are host pointers.  bf16 3x3 problems without a
- * stride whose rows have at most 32 pixels may run in the kernel of strips instead, where that is
- * the faster one by rule and no knob is fixed: see tvg_conv2d_get_knobs.
+ * (alignment of the pointers aside).  kernel, mt, nt are host pointers.  bf16 3x3 problems of 32 n
+ * input channels may run in the kernel of strips instead, where that is the faster one by rule and
+ * no knob is fixed: see tvg_conv2d_get_knobs.
  */
 typedef enum {
     TVG_KERNEL_GENERIC = 0,        /* implicit GEMM, any shape: three kernels, see tvg_conv2d_get_knobs */
@@ -354,10 +354,10 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
  * bf16 3x3 and 1x1 problems with few tiles, whose waves split the reduction: get_plan reports TVG_KERNEL_3X3
  * or TVG_KERNEL_1X1 with mt = 16, get_knobs zeros, and fixing any knob selects the kernels above.  And for most fp32
  * 1x1 problems with 8 n channels (TVG_KERNEL_F32_SMALL or TVG_KERNEL_GENERIC, zeros).
- * The bf16 3x3 kernel of strips (stride 1, c a multiple of 32, rows of at most 32 pixels) stands in by rule for the 3x3
+ * The bf16 3x3 kernel of strips (c a multiple of 32; rows of more than 32 pixels: of 4 n) stands in by rule for the 3x3
  * kernel that get_plan and get_knobs report; fixing any of that kernel's knobs selects it.  stages = 1 with row_loads = 2,
- * no tile and no pitch, names the kernel of strips (split_k: 0, or 1 or 2 groups of waves, 2 for rows of an odd number of
- * pixels), and is reported as such: TVG_KERNEL_3X3, 64 x 32 times the rows of a strip.
+ * no tile and no pitch, names the kernel of strips (split_k: 0, or 1 or 2 groups of waves, 2 for stride 1 and rows of an odd
+ * number of pixels), and is reported as such: TVG_KERNEL_3X3, 64 x 32 times the rows of a strip.
  */
 typedef struct {
     int32_t mt, nt, stages, split_k, lds_pitch, row_loads;

@@ -1,4 +1,4 @@
-// bf16 3x3 convolutions (pad 1, stride 1) of rows of at most 32 pixels at throughput size.
+// bf16 3x3 convolutions (pad 1, stride 1 or 2) at throughput size.
 //
 // Bound: the matrix pipe at the clock that its power leaves (1.9 GHz under this load, 2.4 without), with the set-up and
 // the tail of a tile around it.  The 64 x 256 tiles of the pipelined kernel read 1 KB of LDS per 32x32x16 MFMA, as much as
@@ -16,9 +16,13 @@
 //     but barriers waits for other waves, both barriers are amid MFMAs, and a workgroup goes on to its next tile without one.
 //   - What a tile's set-up and tail need is read anew there (kernel arguments, lane numbers), not kept through the loop.
 // Rows of an odd number of pixels take funnel shifts to lay down, and with few tiles two groups of waves split the reduction.
-// us, warm, in the kernels behind and here, without and with a residual: 128 -> 128 at 28x28, batch 32 14.5 / 15.9 -> 12.8 /
-// 12.5, batch 128 37.4 / 42.9 -> 32.7 / 35.3 (840 TFLOP/s with it); 256 -> 256 at 14x14, batch 128 35.6 / 40 -> 32.7 / 33.4; 512 ->
-// 512 at 7x7, batch 128 36.7 / 54.7 -> 34.1 / 37.3.
+// Rows of more than 32 pixels are cut into windows of four strips that overlap by one.
+// Under a stride the two halves are what a filter's columns take anyway: two sums (ae, se), each pixel of them fed by every
+// other row, and the LDS is the bound: 0.76 KB per MFMA, 1.6 us per chunk and pair of workgroups against 1.0 of MFMAs.
+// us, warm, in the kernels behind and here, without and with a residual: 128 -> 128 at 28x28, batch 32 13.9 / 15.8 -> 13.6 /
+// 13.7, batch 128 38.6 / 43.3 -> 34.7 / 39.5 (850 TFLOP/s without); 256 -> 256 at 14x14, batch 128 36.3 / 40.4 -> 34.9 / 34.6; 512 ->
+// 512 at 7x7, batch 128 36.1 / 54.8 -> 36.5 / 37.7; 192 -> 192 at 56x56, batch 16 59.1 / 59.1 -> 41.0 / 45.6; stride 2, 256 -> 512 at
+// 14x14, batch 128 36.8 / 45.1 -> 32.4 / 33.4, 512 -> 512 at 28x28, batch 16 36.2 / 38.2 -> 28.1 / 29.6.
 #include <algorithm>
 #include <type_traits>
 
@@ -49,15 +53,16 @@ struct StripsArgs {
     const float *scale, *shift, *bias;
     const bf16_t *residual;
     bf16_t *y;
-    int N, IC, H, W, OC, relu, nt;
+    int N, IC, H, W, OC, OH, OW, relu, nt;
     int t8, spi, sr, rows;             // strips per row, strip rows per image and per tile, staged rows per tile
+    int windows;                       // parts of a row (strip rows of their own) where it has more than four strips
     int dg, drow, dch;                 // 256 load tasks further: pieces, rows, channels
     int row_bytes, strip_bytes, half, plane;       // LDS: a staged row's even columns, a strip row, the odd columns, a channel
     int rows_bytes;                    // the staged rows of a group and stage
     int ptiles, nch;
     int tiles_per, tiles_more;         // tiles per workgroup, workgroups with one more
     uint32_t x_bytes, w_bytes, y_bytes;
-    Divider by_ptiles, by_spi, by_t8, by_rows;
+    Divider by_ptiles, by_spi, by_t8, by_rows, by_windows;
 };
 
 // 16 bytes per lane from a buffer straight into LDS at `lds` + 16 lane.  In assembly because the compiler waits for all
@@ -96,10 +101,17 @@ __device__ __forceinline__ int divide(int n, const __attribute__((address_space(
 // until at most N younger memory operations are in flight
 template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 
-template <int B, bool UNAL, int KG>
+// Windows of a row of more than four strips: four strips each, which overlap by one, since the sums of a window's first
+// column (and without a stride those of its last) miss the column beside it.
+template <int ST> __device__ __forceinline__ int window_step() { return 24; }       // columns; (of the input)
+
+template <int B, int ST, bool UNAL, int KG>
 __global__ __launch_bounds__(64 * kWaves * KG, 2) void conv3x3_strips_kernel(const StripsArgs a)
 {
-    constexpr int PT = (B + 3) / 2;                       // load tasks per thread: 32 channels of B + 2 rows of 4 strips
+    constexpr int kIn = ST == 1 ? B + 2 : 2 * B + 1;      // input rows of a strip
+    constexpr int PT = (kIn + 1) / 2;                     // load tasks per thread: 32 channels of as many rows of 4 strips
+    constexpr int kStages = ST == 1 ? 2 : 1;              // of staged rows
+    constexpr int BO = ST == 1 ? B : 1;                   // (sums of odd columns: without a stride)
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -118,8 +130,8 @@ __global__ __launch_bounds__(64 * kWaves * KG, 2) void conv3x3_strips_kernel(con
 
     const int weights_at = wave * kWeightBytes;
     unsigned char *weights = smem + weights_at;
-    unsigned char *staged = smem + KG * kWaves * kWeightBytes + kg * 2 * a.rows_bytes;
-    int to_other = a.rows_bytes;                          // (from the stage read to the one written)
+    unsigned char *staged = smem + KG * kWaves * kWeightBytes + kg * kStages * a.rows_bytes;
+    int to_other = kStages == 2 ? a.rows_bytes : 0;       // (from the stage read to the one written)
 
     const uint64_t waddr = reinterpret_cast<uint64_t>(a.w);
 
@@ -159,15 +171,15 @@ __global__ __launch_bounds__(64 * kWaves * KG, 2) void conv3x3_strips_kernel(con
         ch = divide(ch, a.by_rows, &row);
 #pragma unroll
         for (int k = 0; k < PT; ++k) {
-            int rho, rb;
+            int rb, window;
             ch &= kChunk - 1;                                    // tasks beyond the last repeat the first ones
-            const int s = row / (B + 2);
-            rho = row - s * (B + 2);
+            const int s = row / kIn, rho = row - s * kIn;
             const int n = divide(pt * a.sr + s, a.by_spi, &rb);
-            const int ih = rb * B + rho - 1;
+            rb = divide(rb, a.by_windows, &window);
+            const int ih = rb * B * ST + rho - 1;
             goff[k] = kOutOfRange;
             if (ih >= 0 && ih < a.H && n < a.N)
-                goff[k] = 2u * (__umul24(__umul24(n, a.IC) + ch, HW) + __umul24(ih, a.W) + g8 * 8);
+                goff[k] = 2u * (__umul24(__umul24(n, a.IC) + ch, HW) + __umul24(ih, a.W) + window * window_step<ST>() + g8 * 8);
             if (first) {
                 dst[k] = __umul24(ch, a.plane) + (ch >> 3) * kOctetGap + __umul24(s, a.strip_bytes) + __umul24(rho, a.row_bytes) + g8 * 8;
                 if constexpr (UNAL) dst[k] = dst[k] * 16 + g8;     // (t8 <= 16)
@@ -257,9 +269,9 @@ __global__ __launch_bounds__(64 * kWaves * KG, 2) void conv3x3_strips_kernel(con
     __syncthreads();
 
     for (; tile < end; ++tile) {
-        float4v ae[B], ao[B], se[B], so[B];
+        float4v ae[B], se[B], ao[BO], so[BO];
 #pragma unroll
-        for (int b = 0; b < B; ++b) ae[b] = ao[b] = se[b] = so[b] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int b = 0; b < B; ++b) ae[b] = se[b] = ao[b < BO ? b : 0] = so[b < BO ? b : 0] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
 
         float sc = 0.0f, sf = 0.0f, bias = 0.0f;
         int rem;
@@ -296,48 +308,62 @@ __global__ __launch_bounds__(64 * kWaves * KG, 2) void conv3x3_strips_kernel(con
                 sf = a.shift[oc];
                 if (a.bias) bias = a.bias[oc];
             }
+            const auto tap = [&](int t) __attribute__((always_inline)) { return __builtin_bit_cast(bf16x8v, wop[t]); };
 #pragma unroll
-            for (int rho = 0; rho < B + 2; ++rho) {
+            for (int rho = 0; rho < kIn; ++rho) {
                 const bf16x8v e = even, o = odd;
                 p += a.row_bytes;
-                if (rho + 1 < B + 2) {
+                if (rho + 1 < kIn) {
                     even = read(p);
                     odd = read(p + a.half);
                 }
+                // (filter row r of output row b; under a stride odd input rows are the middle rows of filters)
 #pragma unroll
                 for (int r = 0; r < 3; ++r) {
-                    const int b = rho - r;
-                    if (b < 0 || b >= B) continue;
-                    ao[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e, __builtin_bit_cast(bf16x8v, wop[3 * r]), ao[b], 0, 0, 0);
-                    ae[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e, __builtin_bit_cast(bf16x8v, wop[3 * r + 1]), ae[b], 0, 0, 0);
-                    so[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e, __builtin_bit_cast(bf16x8v, wop[3 * r + 2]), so[b], 0, 0, 0);
+                    const int b = (rho - r) / ST;
+                    if (rho < r || b >= B || (rho - r) % ST != 0) continue;
+                    if constexpr (ST == 1) ao[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e, tap(3 * r), ao[b], 0, 0, 0);
+                    ae[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e, tap(3 * r + 1), ae[b], 0, 0, 0);
+                    if constexpr (ST == 1) so[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e, tap(3 * r + 2), so[b], 0, 0, 0);
                 }
 #pragma unroll
                 for (int r = 0; r < 3; ++r) {
-                    const int b = rho - r;
-                    if (b < 0 || b >= B) continue;
-                    se[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o, __builtin_bit_cast(bf16x8v, wop[3 * r]), se[b], 0, 0, 0);
-                    ao[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o, __builtin_bit_cast(bf16x8v, wop[3 * r + 1]), ao[b], 0, 0, 0);
-                    ae[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o, __builtin_bit_cast(bf16x8v, wop[3 * r + 2]), ae[b], 0, 0, 0);
+                    const int b = (rho - r) / ST;
+                    if (rho < r || b >= B || (rho - r) % ST != 0) continue;
+                    se[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o, tap(3 * r), se[b], 0, 0, 0);
+                    if constexpr (ST == 1) ao[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o, tap(3 * r + 1), ao[b], 0, 0, 0);
+                    ae[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o, tap(3 * r + 2), ae[b], 0, 0, 0);
                 }
-                constexpr int kFirst = (B + 3) / 2, kRows = B + 1 - kFirst;        // the rows that lay rows down
-                if (rho < 3) {
+                // (from the second row on: the first one's MFMAs have the weights read in registers)
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) load_weights(3 * rho + k, weights_tile < end ? a.w_bytes : 0, weights_c);
-                    if (rho == 2) next_weights();
-                }
-                if (rho == kFirst - 1) __syncthreads();
+                for (int k = 0; k < 9; ++k)
+                    if (rho == 1 + k * (kIn / 3) / 9) load_weights(k, weights_tile < end ? a.w_bytes : 0, weights_c);
+                if (rho == kIn / 3) next_weights();
+                if constexpr (kStages == 2) {
+                    constexpr int kFirst = (B + 3) / 2, kRows = B + 1 - kFirst;    // the rows that lay rows down
+                    if (rho == kFirst - 1) __syncthreads();
 #pragma unroll
-                for (int k = 0; k < PT; ++k)
-                    if (rho == kFirst + k * kRows / PT) {
-                        store_row(k, other);
-                        load_row(k, rows_rsrc(), rows_c);
+                    for (int k = 0; k < PT; ++k)
+                        if (rho == kFirst + k * kRows / PT) {
+                            store_row(k, other);
+                            load_row(k, rows_rsrc(), rows_c);
+                        }
+                    if (rho == B) {
+                        next_rows();
+                        __syncthreads();
                     }
-                if (rho == B) {
-                    next_rows();
-                    __syncthreads();
                 }
                 __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (kStages == 1) {
+                __syncthreads();
+#pragma unroll
+                for (int k = 0; k < PT; ++k) {
+                    store_row(k, staged);
+                    load_row(k, rows_rsrc(), rows_c);
+                }
+                next_rows();
+                __syncthreads();
             }
             staged = other;
             wait_loads<PT * (UNAL ? 2 : 1)>();             // the next step's weights are there, the rows requested after them may not be
@@ -348,60 +374,79 @@ __global__ __launch_bounds__(64 * kWaves * KG, 2) void conv3x3_strips_kernel(con
         const auto &f = *fresh_args();
         const int lane = fresh(tid & 63), l16 = lane & 15, quad = lane >> 4;
         const int wm = fresh_uniform(wave_m);
-        const int H = f.H, W = f.W, OC = f.OC, sr = f.sr;
+        const int OH = f.OH, OW = f.OW, OC = f.OC, sr = f.sr, windows = f.windows;
         const bf16_t *residual = f.residual;
         bf16_t *y = f.y;
         const bool nt = f.nt != 0;
-        int pt, my_g8, my_rb;
+        constexpr int PX = 8 / ST;                                    // output pixels of a strip's row
+        int pt, my_g8, my_rb, window;
         const int cb = divide(tile, f.by_ptiles, &pt);
         const int my_s = divide(quad, f.by_t8, &my_g8);
         const int my_n = divide(pt * sr + my_s, f.by_spi, &my_rb);
-        const int oc0 = (cb * kWaves + wm) * 16, oc = oc0 + l16;
-        const bool mine = my_s < sr && my_n < f.N && oc < OC;
-        const int rest = W - 8 * my_g8, row0 = my_rb * B;            // columns from the strip's first on, first row
+        my_rb = divide(my_rb, f.by_windows, &window);
+        const int oc0 = (cb * kWaves + wm) * 16, oc = oc0 + l16, col0 = window * (window_step<ST>() / ST) + PX * my_g8;
+        const int rest = OW - col0, row0 = my_rb * B;                 // columns from the strip's first on, first row
+        // pixels [from, to) of the strip's row: windows meet inside a strip without a stride, and at its end with one
+        const int from = window > 0 && my_g8 == 0 ? (ST == 1 ? 4 : PX) : 0;
+        const int to = min(ST == 1 && window + 1 < windows && my_g8 == 3 ? 4 : PX, rest);
+        const bool mine = my_s < sr && my_n < f.N && oc < OC && from < to;
         // bytes of the strip's row b from the tensor's start; what is not there is out of range
-        const uint32_t y_at = mine ? 2u * (uint32_t)(((my_n * OC + oc) * H + row0) * W + 8 * my_g8) : kOutOfRange;
-        const auto row_at = [&](int b) __attribute__((always_inline)) { return row0 + b < H ? y_at + 2 * b * W : kOutOfRange; };
+        const uint32_t y_at = mine ? 2u * (uint32_t)(((my_n * OC + oc) * OH + row0) * OW + col0) : kOutOfRange;
+        const auto row_at = [&](int b) __attribute__((always_inline)) { return row0 + b < OH ? y_at + 2 * b * OW : kOutOfRange; };
         const auto kept = [&](int b) __attribute__((always_inline)) { return KG == 1 || b % KG == kg; };
+        const bool any = UNAL || (ST == 2 && OW % 2 != 0);            // output rows start at any element
 
         uint4v res[B];
 #pragma unroll
         for (int b = 0; b < B; ++b) res[b] = uint4v{0, 0, 0, 0};
         if (residual) {
-            if constexpr (UNAL) {
+            if (any) {
 #pragma unroll
                 for (int b = 0; b < B; ++b) {
                     const uint32_t at = row_at(b);
                     if (!kept(b) || at >= kOutOfRange) continue;
                     const bf16_t *r = residual + at / 2;
-                    if (rest >= 8) {
-                        res[b] = *reinterpret_cast<const uint4e *>(r);
-                    } else {
-                        if (rest & 4) {
+                    if (to >= PX) {
+                        if constexpr (ST == 1) {
+                            res[b] = *reinterpret_cast<const uint4e *>(r);
+                        } else {
                             const uint2v v = *reinterpret_cast<const uint2e *>(r);
                             res[b][0] = v[0];
                             res[b][1] = v[1];
                         }
-                        uint32_t last = 0;
-                        if (rest & 2) last = *reinterpret_cast<const uint1e *>(r + (rest & 4));
-                        const uint32_t one = r[rest - 1];
-                        // 7: words 0 1, 2, 3;  5: 0 1, 2;  3: 0, 1;  1: 0
-                        if (rest == 7) { res[b][2] = last; res[b][3] = one; }
-                        else if (rest == 5) res[b][2] = one;
-                        else if (rest == 3) { res[b][0] = last; res[b][1] = one; }
-                        else res[b][0] = one;
+                    } else {
+                        if (to & 4) {
+                            const uint2v v = *reinterpret_cast<const uint2e *>(r);
+                            res[b][0] = v[0];
+                            res[b][1] = v[1];
+                        }
+                        uint32_t last = 0, one = 0;
+                        if (to & 2) last = *reinterpret_cast<const uint1e *>(r + (to & 4));
+                        if (to & 1) one = r[to - 1];
+                        // the pair after the first four or none, then the single pixel
+                        const uint32_t w0 = to & 2 ? last : one, w1 = to & 2 ? one : 0u;
+                        if (to & 4) { res[b][2] = w0; res[b][3] = w1; }
+                        else { res[b][0] = w0; res[b][1] = w1; }
                     }
                 }
             } else {
                 const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(residual), 0, f.y_bytes, kRsrcFlags);
 #pragma unroll
-                for (int b = 0; b < B; ++b)
-                    if (kept(b)) res[b] = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(rsrc, row_at(b), 0, 0));
+                for (int b = 0; b < B; ++b) {
+                    if (!kept(b)) continue;
+                    if constexpr (ST == 1) {
+                        res[b] = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(rsrc, row_at(b), 0, 0));
+                    } else {
+                        const uint2v v = __builtin_bit_cast(uint2v, __builtin_amdgcn_raw_buffer_load_b64(rsrc, row_at(b), 0, 0));
+                        res[b][0] = v[0];
+                        res[b][1] = v[1];
+                    }
+                }
             }
         }
 
-        // ---- the shifted sums: even column i takes se[i - 1], odd column i so[i + 1]; those of the neighbouring
-        // strips are the lanes' 16 further on either side
+        // ---- the shifted sums: even column i takes se[i - 1], odd column i so[i + 1] (with a stride, every column se[i - 1]);
+        // those of the neighbouring strips are the lanes' 16 further on either side
         {
             const bool has_left = my_g8 > 0, has_right = rest > 8;
             const int from_left = ((lane + 48) & 63) * 4, from_right = ((lane + 16) & 63) * 4;
@@ -409,21 +454,23 @@ __global__ __launch_bounds__(64 * kWaves * KG, 2) void conv3x3_strips_kernel(con
 #pragma unroll
             for (int b = 0; b < B; ++b) {
                 l[b] = __uint_as_float(__builtin_amdgcn_ds_bpermute(from_left, __float_as_uint(se[b][3])));
-                r[b] = __uint_as_float(__builtin_amdgcn_ds_bpermute(from_right, __float_as_uint(so[b][0])));
+                if constexpr (ST == 1) r[b] = __uint_as_float(__builtin_amdgcn_ds_bpermute(from_right, __float_as_uint(so[b][0])));
             }
 #pragma unroll
             for (int b = 0; b < B; ++b) {
                 ae[b][0] += has_left ? l[b] : 0.0f;
 #pragma unroll
                 for (int v = 1; v < 4; ++v) ae[b][v] += se[b][v - 1];
+                if constexpr (ST == 1) {
 #pragma unroll
-                for (int v = 0; v < 3; ++v) ao[b][v] += 2 * v + 2 < rest ? so[b][v + 1] : 0.0f;
-                ao[b][3] += has_right ? r[b] : 0.0f;
+                    for (int v = 0; v < 3; ++v) ao[b][v] += 2 * v + 2 < rest ? so[b][v + 1] : 0.0f;
+                    ao[b][3] += has_right ? r[b] : 0.0f;
+                }
             }
         }
 
         // ---- groups that split the reduction: group k keeps the rows b = k (mod groups) and adds all groups' sums in order
-        if constexpr (KG > 1) {
+        if constexpr (KG > 1 && ST == 1) {
             __syncthreads();
             float4v *all = reinterpret_cast<float4v *>(smem);
 #pragma unroll
@@ -447,58 +494,72 @@ __global__ __launch_bounds__(64 * kWaves * KG, 2) void conv3x3_strips_kernel(con
             }
         }
 
-        // ---- tail: a lane holds eight adjacent pixels of row b of its strip, of channel oc
+        // ---- tail: a lane holds PX adjacent pixels of row b of its strip, of channel oc
         sf = fmaf(bias, sc, sf);
         const float floor_v = relu_floor(f.relu & 1);
         auto finish = [&](int b) __attribute__((always_inline)) {
-            uint4v out;
+            uint4v out = {0, 0, 0, 0};
 #pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const float lo = fmaxf(fmaf(ae[b][d], sc, sf) + __uint_as_float(res[b][d] << 16), floor_v);
-                const float hi = fmaxf(fmaf(ao[b][d], sc, sf) + __uint_as_float(res[b][d] & 0xFFFF0000u), floor_v);
+            for (int d = 0; d < PX / 2; ++d) {
+                const float first = ST == 1 ? ae[b][d] : ae[b][(2 * d) & 3], second = ST == 1 ? ao[b < BO ? b : 0][d] : ae[b][(2 * d + 1) & 3];
+                const float lo = fmaxf(fmaf(first, sc, sf) + __uint_as_float(res[b][d] << 16), floor_v);
+                const float hi = fmaxf(fmaf(second, sc, sf) + __uint_as_float(res[b][d] & 0xFFFF0000u), floor_v);
                 out[d] = f32x2_to_bf16x2(lo, hi);
             }
             return out;
         };
-        if constexpr (UNAL) {
+        if (any) {
 #pragma unroll
             for (int b = 0; b < B; ++b) {
                 const uint32_t at = row_at(b);
                 if (!kept(b) || at >= kOutOfRange) continue;
                 const uint4v out = finish(b);
-                bf16_t *to = y + at / 2;
-                if (rest >= 8) {
-                    *reinterpret_cast<uint4e *>(to) = out;
+                bf16_t *p = y + at / 2;
+                if (to >= PX) {
+                    if constexpr (ST == 1) *reinterpret_cast<uint4e *>(p) = out;
+                    else *reinterpret_cast<uint2e *>(p) = uint2v{out[0], out[1]};
                 } else {
-                    if (rest & 4) *reinterpret_cast<uint2e *>(to) = uint2v{out[0], out[1]};
-                    if (rest & 2) *reinterpret_cast<uint1e *>(to + (rest & 4)) = rest & 4 ? out[2] : out[0];
-                    to[rest - 1] = (bf16_t)(rest == 7 ? out[3] : rest == 5 ? out[2] : rest == 3 ? out[1] : out[0]);
+                    if (to & 4) *reinterpret_cast<uint2e *>(p) = uint2v{out[0], out[1]};
+                    const uint32_t pair = to & 4 ? out[2] : out[0], after = to & 4 ? out[3] : out[1];
+                    if (to & 2) *reinterpret_cast<uint1e *>(p + (to & 4)) = pair;
+                    if (to & 1) p[to - 1] = (bf16_t)(to & 2 ? after : pair);
                 }
             }
         } else {
             const __amdgpu_buffer_rsrc_t yrsrc = __builtin_amdgcn_make_buffer_rsrc(y, 0, f.y_bytes, kRsrcFlags);
+            const bool halves = (OW & 4) != 0 || windows > 1;
             auto store = [&](auto hint) __attribute__((always_inline)) {
 #pragma unroll
                 for (int b = 0; b < B; ++b) {
                     if (!kept(b)) continue;
                     const uint4v out = finish(b);
                     const uint32_t at = row_at(b);
-                    __builtin_amdgcn_raw_buffer_store_b128(out, yrsrc, rest >= 8 ? at : kOutOfRange, 0, hint);
-                    // the last strip of a row: its first 4, its next 2 pixels
-                    if (W & 4) __builtin_amdgcn_raw_buffer_store_b64(uint2v{out[0], out[1]}, yrsrc, rest < 8 ? at : kOutOfRange, 0, 0);
-                    if (W & 2) __builtin_amdgcn_raw_buffer_store_b32(W & 4 ? out[2] : out[0], yrsrc, rest < 8 ? at + 2 * (W & 4) : kOutOfRange, 0, 0);
+                    if constexpr (ST == 1) {
+                        __builtin_amdgcn_raw_buffer_store_b128(out, yrsrc, to - from == 8 ? at : kOutOfRange, 0, hint);
+                        // strips in part: four pixels, the first or the last, and a row's last two
+                        if (halves) {
+                            const bool upper = from > 0;
+                            __builtin_amdgcn_raw_buffer_store_b64(uint2v{upper ? out[2] : out[0], upper ? out[3] : out[1]}, yrsrc,
+                                                                  to - from < 8 && to - from >= 4 ? at + 2 * from : kOutOfRange, 0, 0);
+                        }
+                        if (OW & 2)
+                            __builtin_amdgcn_raw_buffer_store_b32(to & 4 ? out[2] : out[0], yrsrc, to & 2 ? at + 2 * (to & 4) : kOutOfRange, 0, 0);
+                    } else {
+                        __builtin_amdgcn_raw_buffer_store_b64(uint2v{out[0], out[1]}, yrsrc, to == 4 ? at : kOutOfRange, 0, 0);
+                        if (OW & 2) __builtin_amdgcn_raw_buffer_store_b32(out[0], yrsrc, to == 2 ? at : kOutOfRange, 0, 0);
+                    }
                 }
             };
-            if (nt) store(std::integral_constant<int, 2>{});
+            if (ST == 1 && nt) store(std::integral_constant<int, 2>{});
             else store(std::integral_constant<int, 0>{});
         }
     }
 }
 
-template <int B, bool UNAL, int KG>
+template <int B, int ST, bool UNAL, int KG>
 tvg_status launch(const StripsArgs &args, const StripsPlan &plan, hipStream_t stream)
 {
-    const auto kernel = conv3x3_strips_kernel<B, UNAL, KG>;
+    const auto kernel = conv3x3_strips_kernel<B, ST, UNAL, KG>;
     static bool configured = false;                // opt in to > 64 KB of dynamic LDS once per instance
     if (!configured && plan.lds_bytes > 64 * 1024) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
@@ -509,40 +570,46 @@ tvg_status launch(const StripsArgs &args, const StripsPlan &plan, hipStream_t st
     return hipGetLastError() == hipSuccess ? TVG_OK : TVG_ERR_LAUNCH;
 }
 
-template <bool UNAL, int KG>
+template <int ST, bool UNAL, int KG>
 tvg_status launch_b(const StripsArgs &args, const StripsPlan &plan, hipStream_t stream)
 {
     switch (plan.b) {
-    case 4: return launch<4, UNAL, KG>(args, plan, stream);
-    case 5: return launch<5, UNAL, KG>(args, plan, stream);
-    case 6: return launch<6, UNAL, KG>(args, plan, stream);
-    case 7: return launch<7, UNAL, KG>(args, plan, stream);
-    default: return launch<8, UNAL, KG>(args, plan, stream);
+    case 4: return launch<4, ST, UNAL, KG>(args, plan, stream);
+    case 5: return launch<5, ST, UNAL, KG>(args, plan, stream);
+    case 6: return launch<6, ST, UNAL, KG>(args, plan, stream);
+    case 7: return launch<7, ST, UNAL, KG>(args, plan, stream);
+    default:
+        if constexpr (ST == 1) return launch<8, ST, UNAL, KG>(args, plan, stream);
+        else return TVG_ERR_UNSUPPORTED;
     }
 }
 
 // Geometry of a launch with strips of b rows; false where a tile does not fit.
 bool set_geometry(const ConvProblem &p, int b, int kg, StripsPlan *g)
 {
+    const int strips = (p.W + 7) / 8, in = p.sh == 1 ? b + 2 : 2 * b + 1;
     g->b = b;
     g->kg = kg;
-    g->t8 = (p.W + 7) / 8;
-    if (g->t8 > 4 || p.IC / kChunk % kg != 0 || (kg == 2 && p.W % 2 == 0)) return false;
-    g->spi = (p.H + b - 1) / b;
+    g->t8 = std::min(strips, 4);
+    if (p.IC / kChunk % kg != 0 || (kg == 2 && (p.W % 2 == 0 || p.sh == 2))) return false;
+    // (a window's first column, and without a stride its last, is its neighbour's)
+    g->windows = strips <= 4 ? 1 : p.sh == 1 ? (p.W - 8 + 23) / 24 : (strips - 1 + 2) / 3;
+    if (g->windows > 1 && p.W % 4 != 0) return false;
+    g->spi = (p.OH + b - 1) / b * g->windows;
     g->sr = std::min(4 / g->t8, p.N * g->spi);
-    g->rows = g->sr * (b + 2);
+    g->rows = g->sr * in;
     g->row_bytes = g->t8 * 8;
     // the channels of a read are an odd number of 32 bytes apart, its four strips in a row on four eighths of 32 bytes,
     // also across strip rows: distinct banks
     // (unless that leaves no room for a second workgroup: strips of 8 rows, reads of two turns)
-    const int strip = (b + 2) * g->row_bytes;
+    const int strip = in * g->row_bytes, stages = p.sh == 1 ? 2 : 1;
     for (int pad : {((8 * g->t8 - strip) % 32 + 32) % 32, 0}) {
         g->strip_bytes = strip + pad;
         g->half = g->sr * g->strip_bytes;
         g->plane = (2 * g->half + 31) / 64 * 64 + 32;
         g->rows_bytes = kChunk * g->plane + 4 * kOctetGap;
-        // two stages of rows, and the weights; at the end what two groups exchange
-        g->lds_bytes = kg * (kWaves * kWeightBytes + 2 * (size_t)g->rows_bytes);
+        // two stages of rows (under a stride, where they are twice as many, one), and the weights; at the end what two groups exchange
+        g->lds_bytes = kg * (kWaves * kWeightBytes + stages * (size_t)g->rows_bytes);
         if (g->lds_bytes <= kg * (size_t)80 * 1024) break;
     }
     if (kg > 1) g->lds_bytes = std::max(g->lds_bytes, (size_t)kg * kWaves * b * 2048);
@@ -553,43 +620,65 @@ bool set_geometry(const ConvProblem &p, int b, int kg, StripsPlan *g)
     return true;
 }
 
-// Times in us on both sides of the dispatch, fitted to 3800 shapes of 64 to 512 input channels that were timed in this
-// kernel (every b) and in the kernels behind it (maps of 3 to 32 rows and columns, 32 to 512 output channels, batches of 1
-// to 128; standard deviation of the fits 6 and 8 to 15 %).  A CU's tiles run in pairs, two waves on a SIMD.
+// Times in us on both sides of the dispatch, fitted to 7900 shapes of 64 to 512 input channels that were timed in this
+// kernel (every b) and in the kernels behind it (maps of 3 to 112 rows and columns, 32 to 512 output channels, batches of 1
+// to 128; standard deviation of the fits 5 to 9 and 5 to 15 %).  A CU's tiles run in pairs, two waves on a SIMD.
 struct Fit { float launch, tile, pair0, pair1, single0, single1, mbyte; };
 constexpr Fit kEven = {4.2f, 0.9f, 0.37f, 0.30f, 0.22f, 0.18f, 0.14f};            // rows of 2n pixels
+constexpr Fit kWindows = {3.4f, 1.15f, 0.28f, 0.33f, 0.28f, 0.19f, 0.23f};        // ... of more than 32
 constexpr Fit kOdd[2] = {{5.2f, 0.8f, 0.40f, 0.31f, 0.06f, 0.24f, 0.46f}, {2.4f, 4.4f, -0.10f, 0.41f, 0.0f, 0.0f, 0.5f}};
+constexpr Fit kStride2[2] = {{4.3f, 0.45f, 0.57f, 0.234f, 0.29f, 0.16f, 0.61f}, {4.25f, 1.3f, 0.51f, 0.27f, 0.22f, 0.23f, 0.6f}};   // even, odd rows
 
 float strips_us(const ConvProblem &p, const StripsPlan &g)
 {
-    const Fit &f = p.W % 2 == 0 ? kEven : kOdd[g.kg - 1];
+    const bool odd = p.W % 2 != 0;
+    const Fit &f = p.sh == 2 ? kStride2[odd] : g.windows > 1 ? kWindows : odd ? kOdd[g.kg - 1] : kEven;
     const long q = (g.tiles + kComputeUnits - 1) / kComputeUnits;
     const bool two = g.kg == 1 && g.lds_bytes <= 80 * 1024;
     const float pairs = g.kg == 2 ? q : two ? q / 2 : 0, singles = g.kg == 2 ? 0 : two ? q % 2 : q;
-    return f.launch + f.tile * q + p.IC / kChunk / g.kg * (pairs * (f.pair0 + f.pair1 * g.b) + singles * (f.single0 + f.single1 * g.b)) +
-           f.mbyte * 2e-6f * p.OC * p.npix;
+    const float us = f.launch + f.tile * q + p.IC / kChunk / g.kg * (pairs * (f.pair0 + f.pair1 * g.b) + singles * (f.single0 + f.single1 * g.b)) +
+                     f.mbyte * 2e-6f * p.OC * p.npix;
+    return p.sh == 2 && g.windows > 1 ? 1.15f * us : us;
 }
 
 float patch_us(const ConvProblem &p, const Patch3x3Plan &g)
 {
     const bool odd = p.W % 2 != 0;
     const long q = (((long)p.npix + g.nt - 1) / g.nt * ((p.OC + g.mt - 1) / g.mt) + kComputeUnits - 1) / kComputeUnits;
-    float pair = odd ? 0.92f : 1.08f, single = odd ? 0.50f : 0.58f;               // per 16 channels; 64 pixels
-    if (g.nt == 128) pair = odd ? 1.16f : 1.3f, single = odd ? 0.60f : 0.71f;
-    if (g.nt == 256) pair = odd ? 1.85f : 1.75f, single = odd ? 1.0f : 0.97f;
-    if (g.nt == 512) pair = 3.2f, single = 1.7f;
+    float base = 5.0f, mbyte = odd ? 0.6f : 0.22f, pair, single;                  // (pair, single: per 16 channels)
+    if (p.sh == 2) {
+        base = 4.0f;
+        mbyte = 0.24f;
+        pair = odd ? 1.44f : 1.22f, single = odd ? 1.1f : 0.99f;                  // 64 pixels
+        if (g.nt == 128) pair = odd ? 2.5f : 1.73f, single = odd ? 1.9f : 0.82f;
+        if (g.nt >= 256) pair = odd ? 3.8f : 2.65f, single = odd ? 2.8f : 1.95f;
+        if (g.dbuf) pair = 9.0f, single = 1.03f;
+    } else if (p.W > 32) {
+        mbyte = 0.15f;
+        pair = 1.12f, single = 0.68f;
+        if (g.nt == 128) pair = 1.35f, single = 0.85f;
+        if (g.nt == 256) pair = g.dbuf ? 1.89f : 2.45f, single = g.dbuf ? 1.08f : 1.43f;
+        if (g.nt == 512) pair = 3.6f, single = 2.07f;
+        if (g.dbuf && p.W % 8 == 0) pair += g.nt < 256 ? 1.0f : 0.6f, single += g.nt < 256 ? 0.5f : 0.3f;
+    } else {
+        if (odd) base -= 0.5f * (q - 1);
+        pair = odd ? 0.92f : 1.08f, single = odd ? 0.50f : 0.58f;
+        if (g.nt == 128) pair = odd ? 1.16f : 1.3f, single = odd ? 0.60f : 0.71f;
+        if (g.nt == 256) pair = odd ? 1.85f : 1.75f, single = odd ? 1.0f : 0.97f;
+        if (g.nt == 512) pair = 3.2f, single = 1.7f;
+        if (p.W % 8 == 0 && g.nt >= 128) pair += 0.8f, single += 0.4f;            // (their patch rows meet on banks)
+    }
     if (g.mt == 128) pair *= 1.9f, single *= 1.9f;
-    if (p.W % 8 == 0 && g.nt >= 128) pair += 0.8f, single += 0.4f;                // (their patch rows meet on banks)
-    return 5.0f - (odd ? 0.5f * (q - 1) : 0.0f) + p.IC / 16 * (q / 2 * pair + q % 2 * single) + (odd ? 0.6f : 0.22f) * 2e-6f * p.OC * p.npix;
+    return base + p.IC / 16 * (q / 2 * pair + q % 2 * single) + mbyte * 2e-6f * p.OC * p.npix;
 }
 
 }  // namespace
 
 bool plan_conv3x3_strips(const ConvProblem &p, const Patch3x3Plan &patch, StripsPlan *plan)
 {
-    if (p.dtype != TVG_BF16 || p.R != 3 || p.S != 3 || p.ph != 1 || p.pw != 1 || p.sh != 1 || p.sw != 1 || p.IC % kChunk != 0) return false;
+    if (p.dtype != TVG_BF16 || p.R != 3 || p.S != 3 || p.ph != 1 || p.pw != 1 || p.sh > 2 || p.sw != p.sh || p.IC % kChunk != 0) return false;
     if ((int64_t)p.N * p.IC * p.H * p.W >= (1 << 30) || (int64_t)p.OC * p.IC * 9 >= (1 << 30) ||
-        (int64_t)p.N * p.OC * p.H * p.W >= (1 << 30)) return false;
+        (int64_t)p.N * p.OC * p.OH * p.OW >= (1 << 30)) return false;
     if ((int64_t)p.N * p.IC >= (1 << 22) || (int64_t)p.OC * p.IC >= (1 << 22) || p.H * p.W >= (1 << 22)) return false;   // 24-bit products
     const Knobs k = forced_knobs(p);
     const bool named = !k.mt && !k.nt && !k.lds_pitch && k.stages == 1 && k.row_loads == 2 && k.split_k <= 2;
@@ -600,15 +689,15 @@ bool plan_conv3x3_strips(const ConvProblem &p, const Patch3x3Plan &patch, Strips
     float best = 0.0f;
     StripsPlan g;
     for (int kg = 1; kg <= 2; ++kg)
-        for (int b = 4; b <= 8; ++b) {
+        for (int b = 4; b <= (p.sh == 1 ? 8 : 7); ++b) {
             if (named && k.split_k && kg != k.split_k) continue;
             if (!set_geometry(p, b, kg, &g)) continue;
             const float us = strips_us(p, g);
             if (best == 0.0f || us < best) best = us, *plan = g;
         }
-    // What the fits leave open goes to the kernels behind: of 3777 shapes this takes 2302, which run 1.32 (even rows) and 1.27 (odd)
-    // times as fast in the geometric mean.
-    return best > 0.0f && (named || best * (p.W % 2 == 0 ? 1.05f : 1.08f) < patch_us(p, patch));
+    // What the fits leave open goes to the kernels behind.  Of 7900 shapes this takes 4900, which run 1.32 (even rows), 1.27 (odd),
+    // 1.39 (rows of more than 32 pixels) and 1.34 (stride 2) times as fast in the geometric mean.
+    return best > 0.0f && (named || best * (p.W % 2 == 0 || p.sh == 2 ? 1.05f : 1.08f) < patch_us(p, patch));
 }
 
 bool conv3x3_strips_pointers_ok(const ConvPointers &ptr)
@@ -625,9 +714,9 @@ tvg_status launch_conv3x3_strips(const ConvProblem &p, const StripsPlan &plan, c
     a.scale = ptr.scale; a.shift = ptr.shift; a.bias = ptr.bias;
     a.residual = static_cast<const bf16_t *>(ptr.residual);
     a.y = static_cast<bf16_t *>(ptr.y);
-    a.N = p.N; a.IC = p.IC; a.H = p.H; a.W = p.W; a.OC = p.OC;
+    a.N = p.N; a.IC = p.IC; a.H = p.H; a.W = p.W; a.OC = p.OC; a.OH = p.OH; a.OW = p.OW;
     a.relu = p.relu; a.nt = p.stream_out;
-    a.t8 = plan.t8; a.spi = plan.spi; a.sr = plan.sr; a.rows = plan.rows;
+    a.t8 = plan.t8; a.spi = plan.spi; a.sr = plan.sr; a.rows = plan.rows; a.windows = plan.windows;
     a.dg = 64 * kWaves % plan.t8;
     a.drow = 64 * kWaves / plan.t8 % plan.rows;
     a.dch = 64 * kWaves / plan.t8 / plan.rows;
@@ -638,11 +727,12 @@ tvg_status launch_conv3x3_strips(const ConvProblem &p, const StripsPlan &plan, c
     a.tiles_per = (int)(plan.tiles / plan.workgroups); a.tiles_more = (int)(plan.tiles % plan.workgroups);
     a.x_bytes = ((uint32_t)((int64_t)p.N * p.IC * p.H * p.W) * 2 + 3) & ~3u;   // (up to the end of the last pixel's word)
     a.w_bytes = (uint32_t)(p.OC * p.IC * 9) * 2;
-    a.y_bytes = (uint32_t)((int64_t)p.N * p.OC * p.H * p.W) * 2;
+    a.y_bytes = (uint32_t)((int64_t)p.N * p.OC * p.OH * p.OW) * 2;
     a.by_ptiles = make_divider(a.ptiles); a.by_spi = make_divider(a.spi); a.by_t8 = make_divider(a.t8);
-    a.by_rows = make_divider(a.rows);
-    if (p.W % 2 != 0) return plan.kg == 2 ? launch_b<true, 2>(a, plan, stream) : launch_b<true, 1>(a, plan, stream);
-    return launch_b<false, 1>(a, plan, stream);
+    a.by_rows = make_divider(a.rows); a.by_windows = make_divider(a.windows);
+    if (p.sh == 2) return p.W % 2 != 0 ? launch_b<2, true, 1>(a, plan, stream) : launch_b<2, false, 1>(a, plan, stream);
+    if (p.W % 2 != 0) return plan.kg == 2 ? launch_b<1, true, 2>(a, plan, stream) : launch_b<1, true, 1>(a, plan, stream);
+    return launch_b<1, false, 1>(a, plan, stream);
 }
 
 }  // namespace tvg

@@ -121,7 +121,7 @@ tvg_status launch_conv_rows(const ConvProblem &p, const RowsPlan &plan, const Co
 // b rows x 8 pixels, a group of four waves 64 channels of them.
 struct StripsPlan {
     int b, kg;                        // rows of a strip, groups that split the reduction (1 or 2)
-    int t8, spi, sr, rows;            // strips per row, strip rows per image and per tile, staged rows per tile
+    int t8, windows, spi, sr, rows;   // strips per row or part of a row, such parts, strip rows per image and per tile, staged rows per tile
     int row_bytes, strip_bytes, half, plane, rows_bytes;
     long ptiles, tiles, workgroups;
     size_t lds_bytes;

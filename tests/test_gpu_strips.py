@@ -1,6 +1,6 @@
 """The bf16 3x3 kernel of strips (knobs stages = 1, row_loads = 2; by rule it stands in for the kernels that are reported)
-against the oracle, every output: strips of 4 to 8 rows, rows of one to four strips of an even and an odd number of pixels,
-one and two groups of waves, the last strip and the last tile partly outside, channels that end inside a tile, reductions
+against the oracle, every output: strips of 4 to 8 rows, rows of one to four strips of an even and an odd number of pixels
+and rows cut into windows, both strides, one and two groups of waves, the last strip and the last tile partly outside, channels that end inside a tile, reductions
 of one to sixteen chunks, several tiles per workgroup.  Bounds as for every single operator."""
 import pytest
 
@@ -18,23 +18,34 @@ SHAPES = [
     ((130, 64, 6, 20, 16), 6), ((520, 64, 6, 6, 40), 6), ((260, 64, 6, 13, 16), 6), ((130, 64, 6, 29, 16), 6),
     ((130, 64, 7, 28, 20), 7), ((260, 32, 7, 14, 16), 7), ((520, 64, 7, 7, 16), 7), ((130, 64, 7, 25, 16), 7),
     ((130, 64, 8, 30, 16), 8), ((520, 64, 8, 8, 16), 8), ((260, 64, 8, 16, 16), 8), ((260, 64, 8, 15, 16), 8), ((520, 64, 8, 3, 16), 8),
+    # windows: rows of 36 to 112 pixels
+    ((1, 64, 5, 36, 16), 4), ((2, 96, 13, 56, 70), 4), ((1, 32, 9, 112, 20), 4), ((70, 64, 5, 36, 16), 5), ((70, 64, 16, 36, 16), 6), ((70, 64, 7, 40, 16), 7), ((70, 64, 8, 60, 16), 8),
     # two and three tiles per workgroup, of one and of several channel tiles
     ((1100, 64, 7, 28, 16), 7), ((300, 32, 14, 14, 200), 7), ((700, 96, 8, 10, 130), 8),
 ]
 
+# ... under a stride of 2
+STRIDE2 = [
+    ((1, 64, 5, 6, 16), 4), ((3, 160, 14, 14, 130), 4), ((1, 96, 13, 18, 40), 4), ((2, 128, 28, 28, 72), 4), ((1, 512, 3, 8, 17), 4), ((1, 32, 1, 1, 1), 4),
+    ((70, 64, 3, 2, 16), 4), ((1, 64, 9, 3, 33), 4), ((3, 128, 7, 7, 130), 4), ((2, 64, 13, 13, 80), 4), ((1, 192, 17, 21, 64), 4), ((2, 64, 9, 31, 20), 4), ((1, 64, 6, 32, 24), 4),
+    ((1, 64, 5, 40, 16), 4), ((2, 96, 14, 56, 70), 4), ((1, 32, 9, 112, 20), 4), ((1, 64, 6, 36, 16), 4),
+    ((260, 64, 9, 14, 16), 5), ((130, 64, 9, 21, 16), 5), ((70, 64, 9, 40, 16), 5), ((130, 64, 11, 26, 16), 6), ((520, 64, 11, 3, 16), 6),
+    ((520, 64, 13, 6, 16), 7), ((130, 64, 13, 28, 40), 7), ((260, 64, 13, 13, 16), 7), ((70, 64, 13, 40, 16), 7), ((300, 32, 28, 28, 100), 7),
+]
 
-def _check(tvg, cfg, b, kg, residual, bias, relu):
+
+def _check(tvg, cfg, b, kg, residual, bias, relu, stride=1):
     n, ic, h, w, oc = cfg
-    desc = tvg.ConvDesc(n, ic, h, w, oc, 3, 3, 1, 1, 1, 1, tvg.TVG_BF16, 0)
-    inp = ti.make_inputs(ti.ConvShape("strips", n, ic, h, w, oc, 3, 3, 1, 1), 10300 + sum(cfg), "bf16", residual=residual, bias=bias)
+    desc = tvg.ConvDesc(n, ic, h, w, oc, 3, 3, stride, stride, 1, 1, tvg.TVG_BF16, 0)
+    inp = ti.make_inputs(ti.ConvShape("strips", n, ic, h, w, oc, 3, 3, stride, 1), 10300 + sum(cfg), "bf16", residual=residual, bias=bias)
     d = dev_inputs(inp, "bf16")
     want = oracle.conv2d_fused(inp["x"], inp["w"], inp["scale"], inp["shift"], inp["bias"] if bias else None,
-                               inp["residual"] if residual else None, stride=(1, 1), pad=(1, 1), relu=relu)
+                               inp["residual"] if residual else None, stride=(stride, stride), pad=(1, 1), relu=relu)
     assert tvg.tvg_conv2d_set_knobs(desc, (0, 0, 1, kg, 0, 2)) == 0
     try:
         assert tvg.tvg_conv2d_get_plan(desc) == (1, 64, 32 * b) and tvg.tvg_conv2d_get_knobs(desc) == (0, 0, 1, kg, 0, 2)
         ys = [tvg.conv2d_fused(d["x"], d["w"], d["scale"], d["shift"], d["bias"] if bias else None, d["residual"] if residual else None,
-                               stride=1, pad=1, relu=relu, stream_out=hint) for hint in (False, True)]
+                               stride=stride, pad=1, relu=relu, stream_out=hint) for hint in (False, True)]
     finally:
         tvg.tvg_conv2d_set_knobs(desc, None)
     assert ys[0].view(-1).equal(ys[1].view(-1))                        # the store hint changes no bits, nor does a repetition
@@ -49,6 +60,13 @@ def test_strips_every_instance(tvg, cfg, b, tail, kg):
         pytest.skip("one group: even rows, or an odd number of chunks")
     full = tail != "plain"
     _check(tvg, cfg, b, kg, full, full, full)
+
+
+@pytest.mark.parametrize("tail", ["plain", "bias+residual"])
+@pytest.mark.parametrize("cfg,b", STRIDE2, ids=lambda c: "x".join(map(str, c)) if isinstance(c, tuple) else str(c))
+def test_strips_every_instance_stride_2(tvg, cfg, b, tail):
+    full = tail != "plain"
+    _check(tvg, cfg, b, 1, full, full, full, 2)
 
 
 @pytest.mark.parametrize("cfg", [(3, 128, 28, 28, 64), (5, 128, 7, 7, 128)], ids=lambda c: "x".join(map(str, c)))
@@ -75,12 +93,13 @@ def test_strips_unaligned_pointers_get_the_kernel_behind(tvg, cfg):
         tvg.tvg_conv2d_set_knobs(desc, None)
 
 
-# n, ic, h, w, channels of the two heads
-@pytest.mark.parametrize("cfg", [(32, 128, 28, 28, 128, 64), (64, 256, 14, 14, 64, 256), (64, 128, 16, 16, 128, 40)], ids=lambda c: "x".join(map(str, c)))
+# n, ic, h, w, channels of the two heads, stride
+@pytest.mark.parametrize("cfg", [(32, 128, 28, 28, 128, 64, 1), (64, 256, 14, 14, 64, 256, 1), (64, 128, 16, 16, 128, 40, 1), (128, 256, 14, 14, 512, 512, 2),
+                                 (24, 192, 56, 56, 64, 40, 1)], ids=lambda c: "x".join(map(str, c)))
 @pytest.mark.parametrize("centre", [True, False])
 def test_two_heads_have_the_bits_of_separate_calls_in_strips(tvg, cfg, centre):
     import torch
-    n, ic, h, w, k1, k2 = cfg
+    n, ic, h, w, k1, k2, stride = cfg
     r2 = 1 if centre else 3
     g = torch.Generator(device="cuda").manual_seed(10600 + sum(cfg))
     def rand(*shape):
@@ -93,10 +112,10 @@ def test_two_heads_have_the_bits_of_separate_calls_in_strips(tvg, cfg, centre):
         joined[k1:, :, 1, 1] = w2[:, :, 0, 0]
     else:
         joined[k1:] = w2
-    want1 = tvg.conv2d_fused(x, w1, scale[:k1], shift[:k1], stride=1, pad=1, relu=True)
-    want2 = tvg.conv2d_fused(x, w2, scale[k1:].clone(), shift[k1:].clone(), stride=1, pad=r2 // 2, relu=False)
+    want1 = tvg.conv2d_fused(x, w1, scale[:k1], shift[:k1], stride=stride, pad=1, relu=True)
+    want2 = tvg.conv2d_fused(x, w2, scale[k1:].clone(), shift[k1:].clone(), stride=stride, pad=r2 // 2, relu=False)
     y1, y2 = torch.full_like(want1, float("nan")), torch.full_like(want2, float("nan"))
-    desc = tvg.ConvDesc(n, ic, h, w, k1 + k2, 3, 3, 1, 1, 1, 1, tvg.TVG_BF16, tvg.TVG_RELU)
+    desc = tvg.ConvDesc(n, ic, h, w, k1 + k2, 3, 3, stride, stride, 1, 1, tvg.TVG_BF16, tvg.TVG_RELU)
     rc = tvg.tvg_conv2d_fused_dual(desc, k1, tvg.TVG_CENTRE_TAP_ONLY if centre else 0, x, joined, scale, shift, None, None, y1, y2)
     assert rc == 0, tvg.status_string(rc)
     assert torch.equal(y1, want1) and torch.equal(y2, want2)
@@ -105,14 +124,14 @@ def test_two_heads_have_the_bits_of_separate_calls_in_strips(tvg, cfg, centre):
 def test_strips_infinity_stays_in_its_window(tvg):
     """Pixels at the end of a row and of a strip, whose neighbours in LDS belong to other rows and images."""
     import torch
-    for h, w in ((14, 14), (28, 28), (7, 7), (9, 18)):
+    for h, w in ((14, 14), (28, 28), (7, 7), (9, 18), (6, 56)):
         desc = tvg.ConvDesc(3, 64, h, w, 64, 3, 3, 1, 1, 1, 1, tvg.TVG_BF16, 0)
         d = dev_inputs(ti.make_inputs(ti.ConvShape("strips", 3, 64, h, w, 64, 3, 3, 1, 1), 10700, "bf16"), "bf16")
         assert tvg.tvg_conv2d_set_knobs(desc, (0, 0, 1, 1, 0, 2)) == 0
         try:
             call = lambda x: tvg.conv2d_fused(x, d["w"], d["scale"], d["shift"], stride=1, pad=1, relu=False)
             clean = call(d["x"])
-            for row, col in ((3, w - 1), (4, 0), (h - 1, w - 1), (0, 0)):
+            for row, col in ((3, w - 1), (4, 0), (h - 1, w - 1), (0, 0), (2, w // 2), (2, w // 2 - 1)):
                 x = d["x"].clone()
                 x[1, 5, row, col] = float("inf")
                 y = call(x)
