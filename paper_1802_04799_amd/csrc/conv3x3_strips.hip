@@ -60,6 +60,7 @@ struct StripsArgs {
     int row_bytes, strip_bytes, half, plane;       // LDS: a staged row's even columns, a strip row, the odd columns, a channel
     int rows_bytes;                    // the staged rows of a group and stage
     int ptiles, nch;
+    uint32_t dump;                     // LDS: 256 bytes that nothing reads
     int tiles_per, tiles_more;         // tiles per workgroup, workgroups with one more
     uint32_t x_bytes, w_bytes, y_bytes;
     Divider by_ptiles, by_spi, by_t8, by_rows, by_windows;
@@ -133,15 +134,12 @@ __global__ __launch_bounds__(64 * kWaves * KG, 2) void conv3x3_strips_kernel(con
     unsigned char *staged = smem + KG * kWaves * kWeightBytes + kg * kStages * a.rows_bytes;
     int to_other = kStages == 2 ? a.rows_bytes : 0;       // (from the stage read to the one written)
 
-    const uint64_t waddr = reinterpret_cast<uint64_t>(a.w);
-
     // ---- weights: 36 pieces of 16 bytes per output channel and chunk, four lanes on adjacent pieces; a piece's place
     // among its four changes with the channel (distinct banks for the reads below).  Channels past the last: zeros.
     const uint32_t lds_weights = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)weights;
     uint32_t woff;
     auto load_weights = [&](int k, uint32_t bytes, int c) __attribute__((always_inline)) {
-        const uint4v rsrc = {(uint32_t)waddr, (uint32_t)(waddr >> 32) & 0xFFFFu, bytes, (uint32_t)kRsrcFlags};
-        load_to_lds(lds_weights + 1024 * k, woff, rsrc, c * (2 * kChunk * 9) + 64 * k);
+        load_to_lds(lds_weights + 1024 * k, woff, raw_buffer(a.w, bytes), c * (2 * kChunk * 9) + 64 * k);
     };
     // a lane's run: channels 8 quad .. + 7 of output channel l16, pieces 9 quad .. + 8
     int wrun[4];
@@ -260,6 +258,17 @@ __global__ __launch_bounds__(64 * kWaves * KG, 2) void conv3x3_strips_kernel(con
 #pragma unroll
     for (int k = 0; k < PT; ++k) load_row(k, rows_rsrc(), kg);
     next_rows();
+    // The weights of the later steps are on their way from memory into the XCD's L2 meanwhile: its workgroups, which walk the
+    // same ones, touch a share of their lines each.  (Weights that the call before has not left there cost a memory
+    // latency per step otherwise: ResNet-18 body at batch 32 346 -> 327 us, at batch 128 767 -> 760.)
+    if (a.nch > 2 * KG) {
+        int pt;
+        const int cb = divide(tile, a.by_ptiles, &pt), shares = gridDim.x >= 128 ? 16 : gridDim.x >= 32 ? 4 : 1;
+        const uint4v rsrc = raw_buffer(a.w, a.w_bytes);
+        const uint32_t first = cb * (16 * kWaves * 18) * a.IC;                 // 9 lines of 128 bytes per input channel
+        for (int at = ((blockIdx.x >> 3) & (shares - 1)) * (64 * kWaves * KG) + tid; at < 9 * a.IC; at += shares * 64 * kWaves * KG)
+            touch_line(a.dump, first + 128 * at, rsrc);
+    }
     wait_loads<0>();
 #pragma unroll
     for (int k = 0; k < PT; ++k) store_row(k, staged);
@@ -609,10 +618,10 @@ bool set_geometry(const ConvProblem &p, int b, int kg, StripsPlan *g)
         g->plane = (2 * g->half + 31) / 64 * 64 + 32;
         g->rows_bytes = kChunk * g->plane + 4 * kOctetGap;
         // two stages of rows (under a stride, where they are twice as many, one), and the weights; at the end what two groups exchange
-        g->lds_bytes = kg * (kWaves * kWeightBytes + stages * (size_t)g->rows_bytes);
+        g->lds_bytes = kg * (kWaves * kWeightBytes + stages * (size_t)g->rows_bytes) + 256;
         if (g->lds_bytes <= kg * (size_t)80 * 1024) break;
     }
-    if (kg > 1) g->lds_bytes = std::max(g->lds_bytes, (size_t)kg * kWaves * b * 2048);
+    if (kg > 1) g->lds_bytes = std::max(g->lds_bytes, (size_t)kg * kWaves * b * 2048 + 256);
     if (g->lds_bytes > 160 * 1024) return false;
     g->ptiles = ((long)p.N * g->spi + g->sr - 1) / g->sr;
     g->tiles = g->ptiles * ((p.OC + 16 * kWaves - 1) / (16 * kWaves));
@@ -724,6 +733,7 @@ tvg_status launch_conv3x3_strips(const ConvProblem &p, const StripsPlan &plan, c
     a.rows_bytes = plan.rows_bytes;
     a.ptiles = (int)plan.ptiles;
     a.nch = p.IC / kChunk;
+    a.dump = (uint32_t)plan.lds_bytes - 256;
     a.tiles_per = (int)(plan.tiles / plan.workgroups); a.tiles_more = (int)(plan.tiles % plan.workgroups);
     a.x_bytes = ((uint32_t)((int64_t)p.N * p.IC * p.H * p.W) * 2 + 3) & ~3u;   // (up to the end of the last pixel's word)
     a.w_bytes = (uint32_t)(p.OC * p.IC * 9) * 2;

@@ -27,6 +27,20 @@ __device__ __forceinline__ int xcd_remap(int bid, int nb)
     return xcd < rem ? xcd * (q + 1) + local : rem * (q + 1) + (xcd - rem) * q + local;
 }
 
+// Requests the cache line at `offset` of a buffer, for the sake of the L2: four bytes per lane go to 256 bytes of LDS that
+// nothing reads.  The compiler does not count the load; its waits for loads of its own, which return in order, cover it.
+__device__ __forceinline__ void touch_line(uint32_t lds, uint32_t offset, const uint4v &rsrc)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" :: "s"(lds), "v"(offset), "s"(rsrc) : "memory");
+}
+
+// Raw buffer descriptor of `bytes` at p.
+__device__ __forceinline__ uint4v raw_buffer(const void *p, uint32_t bytes)
+{
+    const uint64_t at = reinterpret_cast<uint64_t>(p);
+    return uint4v{(uint32_t)at, (uint32_t)(at >> 32) & 0xFFFFu, bytes, 0x00020000u};
+}
+
 __device__ __forceinline__ float bf16_to_f32(bf16_t b) { return __uint_as_float(uint32_t(b) << 16); }
 
 // fp32 -> bf16, round to nearest, ties to even: the hardware conversion of gfx950
