@@ -356,8 +356,8 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
  * 1x1 problems with 8 n channels (TVG_KERNEL_F32_SMALL or TVG_KERNEL_GENERIC, zeros).
  * The bf16 3x3 kernel of strips (c a multiple of 32; rows of more than 32 pixels: of 4 n) stands in by rule for the 3x3
  * kernel that get_plan and get_knobs report; fixing any of that kernel's knobs selects it.  stages = 1 with row_loads = 2,
- * no tile and no pitch, names the kernel of strips (split_k: 0, or 1 or 2 groups of waves, 2 for stride 1 and rows of an odd
- * number of pixels), and is reported as such: TVG_KERNEL_3X3, 64 x 32 times the rows of a strip.
+ * no tile and no pitch, names the kernel of strips (split_k: 0, or 1, 2 or 4 groups of waves; 2 and 4 for stride 1, 2 for
+ * rows of an odd number of pixels, 4 for a multiple of 128 channels), and is reported as such: TVG_KERNEL_3X3, 64 x 32 times the rows of a strip.
  */
 typedef struct {
     int32_t mt, nt, stages, split_k, lds_pitch, row_loads;

@@ -16,13 +16,16 @@
 //     but barriers waits for other waves, both barriers are amid MFMAs, and a workgroup goes on to its next tile without one.
 //   - What a tile's set-up and tail need is read anew there (kernel arguments, lane numbers), not kept through the loop.
 // Rows of an odd number of pixels take funnel shifts to lay down, and with few tiles two groups of waves split the reduction.
+// With fewer still four groups of two waves do, on 32 output channels: twice the workgroups, a quarter of the chain of chunks.
 // Rows of more than 32 pixels are cut into windows of four strips that overlap by one.
 // Under a stride the two halves are what a filter's columns take anyway: two sums (ae, se), each pixel of them fed by every
 // other row, and the LDS is the bound: 0.76 KB per MFMA, 1.6 us per chunk and pair of workgroups against 1.0 of MFMAs.
 // us, warm, in the kernels behind and here, without and with a residual: 128 -> 128 at 28x28, batch 32 13.9 / 15.8 -> 13.6 /
 // 13.7, batch 128 38.6 / 43.3 -> 34.7 / 39.5 (850 TFLOP/s without); 256 -> 256 at 14x14, batch 128 36.3 / 40.4 -> 34.9 / 34.6; 512 ->
 // 512 at 7x7, batch 128 36.1 / 54.8 -> 36.5 / 37.7; 192 -> 192 at 56x56, batch 16 59.1 / 59.1 -> 41.0 / 45.6; stride 2, 256 -> 512 at
-// 14x14, batch 128 36.8 / 45.1 -> 32.4 / 33.4, 512 -> 512 at 28x28, batch 16 36.2 / 38.2 -> 28.1 / 29.6.
+// 14x14, batch 128 36.8 / 45.1 -> 32.4 / 33.4, 512 -> 512 at 28x28, batch 16 36.2 / 38.2 -> 28.1 / 29.6.  Four groups (behind
+// or two and one, cold -> four): 256 -> 256 at 14x14, batch 16 13.1 -> 10.7; 512 -> 512 at 14x14, batch 8 22.4 -> 15.9, at 7x7,
+// batch 32 20.5 -> 18.1.
 #include <algorithm>
 #include <type_traits>
 
@@ -38,7 +41,6 @@ constexpr uint32_t kOutOfRange = 0x80000000u;      // and everything above: tens
 constexpr int kChunk = 32;                         // input channels per step: the depth of one MFMA
 constexpr int kWeightBytes = 16 * kChunk * 9 * 2;  // a wave's weights of a chunk
 constexpr int kOctetGap = 128;                     // between channel octets of the staged rows: distinct banks
-constexpr int kWaves = 4;                          // of a group: 16 output channels each
 
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef short short8v __attribute__((ext_vector_type(8)));
@@ -106,12 +108,14 @@ template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_
 // column (and without a stride those of its last) miss the column beside it.
 template <int ST> __device__ __forceinline__ int window_step() { return 24; }       // columns; (of the input)
 
-template <int B, int ST, bool UNAL, int KG>
-__global__ __launch_bounds__(64 * kWaves * KG, 2) void conv3x3_strips_kernel(const StripsArgs a)
+// WM waves along the output channels, 16 each, in each of KG groups that split the reduction.
+template <int B, int ST, bool UNAL, int KG, int WM>
+__global__ __launch_bounds__(64 * WM * KG, 2) void conv3x3_strips_kernel(const StripsArgs a)
 {
     constexpr int kIn = ST == 1 ? B + 2 : 2 * B + 1;      // input rows of a strip
-    constexpr int PT = (kIn + 1) / 2;                     // load tasks per thread: 32 channels of as many rows of 4 strips
-    constexpr int kStages = ST == 1 ? 2 : 1;              // of staged rows
+    constexpr int kWaves = WM;
+    constexpr int PT = (2 * kIn + WM - 1) / WM;           // load tasks per thread: 32 channels of as many rows of 4 strips
+    constexpr int kStages = ST == 1 && KG <= 2 ? 2 : 1;   // of staged rows
     constexpr int BO = ST == 1 ? B : 1;                   // (sums of odd columns: without a stride)
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -266,7 +270,7 @@ __global__ __launch_bounds__(64 * kWaves * KG, 2) void conv3x3_strips_kernel(con
         const int cb = divide(tile, a.by_ptiles, &pt), shares = gridDim.x >= 128 ? 16 : gridDim.x >= 32 ? 4 : 1;
         const uint4v rsrc = raw_buffer(a.w, a.w_bytes);
         const uint32_t first = cb * (16 * kWaves * 18) * a.IC;                 // 9 lines of 128 bytes per input channel
-        for (int at = ((blockIdx.x >> 3) & (shares - 1)) * (64 * kWaves * KG) + tid; at < 9 * a.IC; at += shares * 64 * kWaves * KG)
+        for (int at = ((blockIdx.x >> 3) & (shares - 1)) * (64 * kWaves * KG) + tid; at < 9 * a.IC * kWaves / 4; at += shares * 64 * kWaves * KG)
             touch_line(a.dump, first + 128 * at, rsrc);
     }
     wait_loads<0>();
@@ -479,7 +483,7 @@ __global__ __launch_bounds__(64 * kWaves * KG, 2) void conv3x3_strips_kernel(con
         }
 
         // ---- groups that split the reduction: group k keeps the rows b = k (mod groups) and adds all groups' sums in order
-        if constexpr (KG > 1 && ST == 1) {
+        if constexpr (KG > 1) {
             __syncthreads();
             float4v *all = reinterpret_cast<float4v *>(smem);
 #pragma unroll
@@ -565,17 +569,17 @@ __global__ __launch_bounds__(64 * kWaves * KG, 2) void conv3x3_strips_kernel(con
     }
 }
 
-template <int B, int ST, bool UNAL, int KG>
+template <int B, int ST, bool UNAL, int KG, int WM = 4>
 tvg_status launch(const StripsArgs &args, const StripsPlan &plan, hipStream_t stream)
 {
-    const auto kernel = conv3x3_strips_kernel<B, ST, UNAL, KG>;
+    const auto kernel = conv3x3_strips_kernel<B, ST, UNAL, KG, WM>;
     static bool configured = false;                // opt in to > 64 KB of dynamic LDS once per instance
     if (!configured && plan.lds_bytes > 64 * 1024) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
             return TVG_ERR_LAUNCH;
         configured = true;
     }
-    kernel<<<dim3((unsigned)plan.workgroups), dim3(64 * kWaves * KG), plan.lds_bytes, stream>>>(args);
+    kernel<<<dim3((unsigned)plan.workgroups), dim3(64 * WM * KG), plan.lds_bytes, stream>>>(args);
     return hipGetLastError() == hipSuccess ? TVG_OK : TVG_ERR_LAUNCH;
 }
 
@@ -596,11 +600,12 @@ tvg_status launch_b(const StripsArgs &args, const StripsPlan &plan, hipStream_t 
 // Geometry of a launch with strips of b rows; false where a tile does not fit.
 bool set_geometry(const ConvProblem &p, int b, int kg, StripsPlan *g)
 {
+    const int waves = kg == 4 ? 2 : 4;                 // along the channels
     const int strips = (p.W + 7) / 8, in = p.sh == 1 ? b + 2 : 2 * b + 1;
     g->b = b;
     g->kg = kg;
     g->t8 = std::min(strips, 4);
-    if (p.IC / kChunk % kg != 0 || (kg == 2 && (p.W % 2 == 0 || p.sh == 2))) return false;
+    if (p.IC / kChunk % kg != 0 || (kg == 2 && p.W % 2 == 0) || (kg > 1 && p.sh == 2) || (kg == 4 && b != 4)) return false;
     // (a window's first column, and without a stride its last, is its neighbour's)
     g->windows = strips <= 4 ? 1 : p.sh == 1 ? (p.W - 8 + 23) / 24 : (strips - 1 + 2) / 3;
     if (g->windows > 1 && p.W % 4 != 0) return false;
@@ -611,20 +616,20 @@ bool set_geometry(const ConvProblem &p, int b, int kg, StripsPlan *g)
     // the channels of a read are an odd number of 32 bytes apart, its four strips in a row on four eighths of 32 bytes,
     // also across strip rows: distinct banks
     // (unless that leaves no room for a second workgroup: strips of 8 rows, reads of two turns)
-    const int strip = in * g->row_bytes, stages = p.sh == 1 ? 2 : 1;
+    const int strip = in * g->row_bytes, stages = p.sh == 1 && kg <= 2 ? 2 : 1;
     for (int pad : {((8 * g->t8 - strip) % 32 + 32) % 32, 0}) {
         g->strip_bytes = strip + pad;
         g->half = g->sr * g->strip_bytes;
         g->plane = (2 * g->half + 31) / 64 * 64 + 32;
         g->rows_bytes = kChunk * g->plane + 4 * kOctetGap;
         // two stages of rows (under a stride, where they are twice as many, one), and the weights; at the end what two groups exchange
-        g->lds_bytes = kg * (kWaves * kWeightBytes + stages * (size_t)g->rows_bytes) + 256;
-        if (g->lds_bytes <= kg * (size_t)80 * 1024) break;
+        g->lds_bytes = kg * (waves * kWeightBytes + stages * (size_t)g->rows_bytes) + 256;
+        if (g->lds_bytes <= std::min(kg, 2) * (size_t)80 * 1024) break;
     }
-    if (kg > 1) g->lds_bytes = std::max(g->lds_bytes, (size_t)kg * kWaves * b * 2048 + 256);
+    if (kg > 1) g->lds_bytes = std::max(g->lds_bytes, (size_t)kg * waves * b * 2048 + 256);
     if (g->lds_bytes > 160 * 1024) return false;
     g->ptiles = ((long)p.N * g->spi + g->sr - 1) / g->sr;
-    g->tiles = g->ptiles * ((p.OC + 16 * kWaves - 1) / (16 * kWaves));
+    g->tiles = g->ptiles * ((p.OC + 16 * waves - 1) / (16 * waves));
     g->workgroups = kg == 1 && p.W % 2 == 0 ? std::min(g->tiles, 2L * kComputeUnits) : g->tiles;
     return true;
 }
@@ -636,15 +641,16 @@ struct Fit { float launch, tile, pair0, pair1, single0, single1, mbyte; };
 constexpr Fit kEven = {4.2f, 0.9f, 0.37f, 0.30f, 0.22f, 0.18f, 0.14f};            // rows of 2n pixels
 constexpr Fit kWindows = {3.4f, 1.15f, 0.28f, 0.33f, 0.28f, 0.19f, 0.23f};        // ... of more than 32
 constexpr Fit kOdd[2] = {{5.2f, 0.8f, 0.40f, 0.31f, 0.06f, 0.24f, 0.46f}, {2.4f, 4.4f, -0.10f, 0.41f, 0.0f, 0.0f, 0.5f}};
+constexpr Fit kQuarters[2] = {{1.2f, 4.3f, 1.97f, 0.0f, 0.0f, 0.0f, 0.57f}, {1.55f, 5.2f, 2.29f, 0.0f, 0.0f, 0.0f, 0.98f}};    // four groups: even, odd rows
 constexpr Fit kStride2[2] = {{4.3f, 0.45f, 0.57f, 0.234f, 0.29f, 0.16f, 0.61f}, {4.25f, 1.3f, 0.51f, 0.27f, 0.22f, 0.23f, 0.6f}};   // even, odd rows
 
 float strips_us(const ConvProblem &p, const StripsPlan &g)
 {
     const bool odd = p.W % 2 != 0;
-    const Fit &f = p.sh == 2 ? kStride2[odd] : g.windows > 1 ? kWindows : odd ? kOdd[g.kg - 1] : kEven;
+    const Fit &f = g.kg == 4 ? kQuarters[odd] : p.sh == 2 ? kStride2[odd] : g.windows > 1 ? kWindows : odd ? kOdd[g.kg - 1] : kEven;
     const long q = (g.tiles + kComputeUnits - 1) / kComputeUnits;
     const bool two = g.kg == 1 && g.lds_bytes <= 80 * 1024;
-    const float pairs = g.kg == 2 ? q : two ? q / 2 : 0, singles = g.kg == 2 ? 0 : two ? q % 2 : q;
+    const float pairs = g.kg > 1 ? q : two ? q / 2 : 0, singles = g.kg > 1 ? 0 : two ? q % 2 : q;
     const float us = f.launch + f.tile * q + p.IC / kChunk / g.kg * (pairs * (f.pair0 + f.pair1 * g.b) + singles * (f.single0 + f.single1 * g.b)) +
                      f.mbyte * 2e-6f * p.OC * p.npix;
     return p.sh == 2 && g.windows > 1 ? 1.15f * us : us;
@@ -690,16 +696,20 @@ bool plan_conv3x3_strips(const ConvProblem &p, const Patch3x3Plan &patch, Strips
         (int64_t)p.N * p.OC * p.OH * p.OW >= (1 << 30)) return false;
     if ((int64_t)p.N * p.IC >= (1 << 22) || (int64_t)p.OC * p.IC >= (1 << 22) || p.H * p.W >= (1 << 22)) return false;   // 24-bit products
     const Knobs k = forced_knobs(p);
-    const bool named = !k.mt && !k.nt && !k.lds_pitch && k.stages == 1 && k.row_loads == 2 && k.split_k <= 2;
+    const bool named = !k.mt && !k.nt && !k.lds_pitch && k.stages == 1 && k.row_loads == 2 && k.split_k <= 4;
     if (!named && (k.mt || k.nt || k.stages || k.split_k || k.lds_pitch || k.row_loads)) return false;
-    // One chunk is not worth the set-up (306 shapes: 1.01 times as fast in the geometric mean, 99 slower).  Groups that split
-    // the reduction pay where rows are odd, whose pixels take more instructions to lay down.
+    // One chunk is not worth the set-up (306 shapes: 1.01 times as fast in the geometric mean, 99 slower).  Two groups
+    // that split the reduction pay where rows are odd, whose pixels take more instructions to lay down.  Four, of half the output
+    // channels, pay where the tiles of the others leave compute units idle and a workgroup's serial chain of chunks is the time:
+    // of 3220 shapes of even rows 1472 go to them and run 1.34 times as fast in the geometric mean, none more than 5 % slower; of
+    // 1394 of odd rows 566, 1.17 times (rows of less than 8 pixels against less than 384 channels: 0.75 to 0.95, so not those).
     if (!named && p.IC < 2 * kChunk) return false;
     float best = 0.0f;
     StripsPlan g;
-    for (int kg = 1; kg <= 2; ++kg)
+    for (int kg : {1, 2, 4})
         for (int b = 4; b <= (p.sh == 1 ? 8 : 7); ++b) {
             if (named && k.split_k && kg != k.split_k) continue;
+            if (!named && kg == 4 && p.W % 2 != 0 && p.W < 8 && p.IC < 384) continue;
             if (!set_geometry(p, b, kg, &g)) continue;
             const float us = strips_us(p, g);
             if (best == 0.0f || us < best) best = us, *plan = g;
@@ -726,9 +736,10 @@ tvg_status launch_conv3x3_strips(const ConvProblem &p, const StripsPlan &plan, c
     a.N = p.N; a.IC = p.IC; a.H = p.H; a.W = p.W; a.OC = p.OC; a.OH = p.OH; a.OW = p.OW;
     a.relu = p.relu; a.nt = p.stream_out;
     a.t8 = plan.t8; a.spi = plan.spi; a.sr = plan.sr; a.rows = plan.rows; a.windows = plan.windows;
-    a.dg = 64 * kWaves % plan.t8;
-    a.drow = 64 * kWaves / plan.t8 % plan.rows;
-    a.dch = 64 * kWaves / plan.t8 / plan.rows;
+    const int threads = plan.kg == 4 ? 128 : 256;                              // of a group
+    a.dg = threads % plan.t8;
+    a.drow = threads / plan.t8 % plan.rows;
+    a.dch = threads / plan.t8 / plan.rows;
     a.row_bytes = plan.row_bytes; a.strip_bytes = plan.strip_bytes; a.half = plan.half; a.plane = plan.plane;
     a.rows_bytes = plan.rows_bytes;
     a.ptiles = (int)plan.ptiles;
@@ -740,6 +751,7 @@ tvg_status launch_conv3x3_strips(const ConvProblem &p, const StripsPlan &plan, c
     a.y_bytes = (uint32_t)((int64_t)p.N * p.OC * p.OH * p.OW) * 2;
     a.by_ptiles = make_divider(a.ptiles); a.by_spi = make_divider(a.spi); a.by_t8 = make_divider(a.t8);
     a.by_rows = make_divider(a.rows); a.by_windows = make_divider(a.windows);
+    if (plan.kg == 4) return p.W % 2 != 0 ? launch<4, 1, true, 4, 2>(a, plan, stream) : launch<4, 1, false, 4, 2>(a, plan, stream);
     if (p.sh == 2) return p.W % 2 != 0 ? launch_b<2, true, 1>(a, plan, stream) : launch_b<2, false, 1>(a, plan, stream);
     if (p.W % 2 != 0) return plan.kg == 2 ? launch_b<1, true, 2>(a, plan, stream) : launch_b<1, true, 1>(a, plan, stream);
     return launch_b<1, false, 1>(a, plan, stream);

@@ -1,7 +1,7 @@
 """The bf16 3x3 kernel of strips (knobs stages = 1, row_loads = 2; by rule it stands in for the kernels that are reported)
 against the oracle, every output: strips of 4 to 8 rows, rows of one to four strips of an even and an odd number of pixels
-and rows cut into windows, both strides, one and two groups of waves, the last strip and the last tile partly outside, channels that end inside a tile, reductions
-of one to sixteen chunks, several tiles per workgroup.  Bounds as for every single operator."""
+and rows cut into windows, both strides, one, two and four groups of waves, the last strip and the last tile partly outside,
+channels that end inside a tile, reductions of one to twenty chunks, several tiles per workgroup.  Bounds as for every single operator."""
 import pytest
 
 import oracle
@@ -10,7 +10,7 @@ from _util import check, dev_inputs, to_host
 
 pytestmark = pytest.mark.gpu
 
-# (n, ic, h, w, oc), rows of a strip (groups: 1, for odd rows 1 and 2)
+# (n, ic, h, w, oc), rows of a strip (groups: 1, for odd rows 2, and 4)
 SHAPES = [
     ((2, 64, 9, 6, 70), 4), ((3, 160, 14, 14, 130), 4), ((1, 96, 13, 18, 40), 4), ((2, 128, 28, 28, 72), 4), ((1, 32, 5, 32, 33), 4), ((1, 512, 3, 8, 17), 4),
     ((70, 64, 3, 2, 16), 4), ((1, 32, 1, 1, 1), 4), ((3, 128, 7, 7, 130), 4), ((2, 64, 13, 13, 80), 4), ((1, 192, 17, 21, 64), 4), ((2, 64, 9, 31, 20), 4),
@@ -20,6 +20,8 @@ SHAPES = [
     ((130, 64, 8, 30, 16), 8), ((520, 64, 8, 8, 16), 8), ((260, 64, 8, 16, 16), 8), ((260, 64, 8, 15, 16), 8), ((520, 64, 8, 3, 16), 8),
     # windows: rows of 36 to 112 pixels
     ((1, 64, 5, 36, 16), 4), ((2, 96, 13, 56, 70), 4), ((1, 32, 9, 112, 20), 4), ((70, 64, 5, 36, 16), 5), ((70, 64, 16, 36, 16), 6), ((70, 64, 7, 40, 16), 7), ((70, 64, 8, 60, 16), 8),
+    # reductions that four groups split too, even and odd rows, windows
+    ((33, 256, 5, 14, 40), 4), ((2, 384, 9, 31, 33), 4), ((5, 128, 2, 5, 64), 4), ((1, 640, 6, 26, 97), 4), ((1, 128, 9, 112, 20), 4),
     # two and three tiles per workgroup, of one and of several channel tiles
     ((1100, 64, 7, 28, 16), 7), ((300, 32, 14, 14, 200), 7), ((700, 96, 8, 10, 130), 8),
 ]
@@ -52,12 +54,12 @@ def _check(tvg, cfg, b, kg, residual, bias, relu, stride=1):
     check(to_host(ys[0]), want, "bf16", (cfg, b, kg))
 
 
-@pytest.mark.parametrize("kg", [1, 2])
+@pytest.mark.parametrize("kg", [1, 2, 4])
 @pytest.mark.parametrize("tail", ["plain", "bias+residual"])
 @pytest.mark.parametrize("cfg,b", SHAPES, ids=lambda c: "x".join(map(str, c)) if isinstance(c, tuple) else str(c))
 def test_strips_every_instance(tvg, cfg, b, tail, kg):
-    if kg == 2 and (cfg[3] % 2 == 0 or cfg[1] % 64 != 0):
-        pytest.skip("one group: even rows, or an odd number of chunks")
+    if (kg == 2 and (cfg[3] % 2 == 0 or cfg[1] % 64 != 0)) or (kg == 4 and (b != 4 or cfg[1] % 128 != 0)):
+        pytest.skip("two groups: odd rows; four: strips of four rows; both: a multiple of their number of chunks")
     full = tail != "plain"
     _check(tvg, cfg, b, kg, full, full, full)
 
