@@ -724,6 +724,9 @@ bool plan_conv3x3_strips(const ConvProblem &p, const Patch3x3Plan &patch, Strips
             const float us = strips_us(p, g);
             if (best == 0.0f || us < best) best = us, *plan = g;
         }
+    // Two chunks in windows do not cover the set-up of a single round of tiles (64 -> 64 at 56x56 amid other layers, 2 to 8 images: 0.2
+    // to 0.8 us slower than the kernel behind; 32 images: 15.1 us against 16.4).
+    if (best > 0.0f && !named && p.sh == 1 && plan->windows > 1 && p.IC == 2 * kChunk && plan->tiles <= kComputeUnits) return false;
     // What the fits leave open goes to the kernels behind.  Of 7900 shapes this takes 4900, which run 1.32 (even rows), 1.27 (odd),
     // 1.39 (rows of more than 32 pixels) and 1.34 (stride 2) times as fast in the geometric mean.
     return best > 0.0f && (named || best * (p.W % 2 == 0 || p.sh == 2 ? 1.05f : 1.08f) < patch_us(p, patch));
