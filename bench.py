@@ -8,7 +8,7 @@ batch 64 with bf16 inputs/outputs, fp32 accumulate and the fused scale/shift + R
 12 launches of tvg_conv2d_fused through the C ABI, inputs already resident in HBM.
 Prints ONE JSON line.  ``value`` is the whole step's throughput in TFLOP/s (2*MACs of the
 direct method over the step time).  ``roofline`` describes ONE kernel, the one with the
-largest share of the step (conv3x3_strips_kernel: its four deepest layers are
+largest share of the step (conv3x3_strips_kernel: its layers are
 launched last and back to back, two HIP events per step bracket exactly them inside the timed
 region); ``layers`` lists all twelve.  ``ceilings`` holds what the GPU sustains in this very run
 (a plain copy, a register-resident matrix-instruction loop per dtype), so every fraction can be
@@ -232,11 +232,9 @@ def main():
     if args.only:
         keep = set(args.only.split(","))
         layers = [l for l in layers if l.sh.name in keep]
-    # The twelve layers are independent.  The deepest 3x3 layers, those of at least eight channel
-    # chunks (the largest share of the step), come last and back to back, so that two events per
-    # step bracket exactly their launches.  They are the layers whose plan names the pipelined 3x3
-    # kernel; at this batch conv3x3_strips_kernel stands in for it on all four.
-    DOM_KERNEL = 2          # TVG_KERNEL_3X3_PIPELINED
+    # The twelve layers are independent.  Those that run in the kernel of strips (the largest share
+    # of the step) come last and back to back, so that two events per step bracket exactly them.
+    DOM_KERNEL = 7          # TVG_KERNEL_3X3_STRIPS
     is_dom = lambda l: tvg.tvg_conv2d_get_plan(l.desc)[0] == DOM_KERNEL
 
     tuning = None

@@ -300,9 +300,7 @@ tvg_status tvg_plan_arena(const tvg_tensor_life *tensors, int32_t count, uint64_
  * cannot use makes the call fall back to the generic kernel, which is correct but slow: time
  * before you fix.  At most 1024 problems are remembered.
  * tvg_conv2d_get_plan: which kernel and tile shape a call with this descriptor would use now
- * (alignment of the pointers aside).  kernel, mt, nt are host pointers.  bf16 3x3 problems of 32 n
- * input channels may run in the kernel of strips instead, where that is the faster one by rule and
- * no knob is fixed: see tvg_conv2d_get_knobs.
+ * (alignment of the pointers aside).  kernel, mt, nt are host pointers.
  */
 typedef enum {
     TVG_KERNEL_GENERIC = 0,        /* implicit GEMM, any shape: three kernels, see tvg_conv2d_get_knobs */
@@ -311,7 +309,8 @@ typedef enum {
     TVG_KERNEL_STEM = 3,           /* bf16 7x7 or 3x3 stride 2, few input channels (mt 64|32; nt 256, few tiles 64|128) */
     TVG_KERNEL_1X1 = 4,            /* bf16 1x1                                             */
     TVG_KERNEL_F32_SMALL = 5,      /* fp32 1x1 / 3x3 / 7x7 stem of launch-bound problems (mt = nt = 32 or 16; stem 32 x 64; 1x1 also 32 x 64 and 32 x 128) */
-    TVG_KERNEL_1X1_DEEP = 6        /* bf16 1x1 stride 1, reductions of 128 n channels       */
+    TVG_KERNEL_1X1_DEEP = 6,       /* bf16 1x1 stride 1, reductions of 128 n channels       */
+    TVG_KERNEL_3X3_STRIPS = 7      /* bf16 3x3, strips of rows, reductions of 32 n channels */
 } tvg_kernel;
 tvg_status tvg_conv2d_set_tile(const tvg_conv_desc *desc, int32_t mt, int32_t nt);
 tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32_t *mt, int32_t *nt);
@@ -341,6 +340,7 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
  *               load per row and channel from the aligned address below the row, shifted into place
  *               bf16 1x1, stride 1, c a multiple of 32: 2 = 16-byte loads of pixels as they lie in
  *               memory (tiles 64x64, 64x128, 128x128), 1 or a tile alone = element loads
+ *               bf16 3x3 with stages = 1, no tile and no pitch: 2 = the kernel of strips (below)
  * tvg_conv2d_set_knobs: fix the knobs of this exact problem (every descriptor field but flags);
  * knobs == NULL or all zero forgets the problem.  Values outside the ranges above are
  * TVG_ERR_UNSUPPORTED.  A combination the problem's kernel cannot use (say, two stages that do
@@ -354,10 +354,11 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
  * bf16 3x3 and 1x1 problems with few tiles, whose waves split the reduction: get_plan reports TVG_KERNEL_3X3
  * or TVG_KERNEL_1X1 with mt = 16, get_knobs zeros, and fixing any knob selects the kernels above.  And for most fp32
  * 1x1 problems with 8 n channels (TVG_KERNEL_F32_SMALL or TVG_KERNEL_GENERIC, zeros).
- * The bf16 3x3 kernel of strips (c a multiple of 32; rows of more than 32 pixels: of 4 n) stands in by rule for the 3x3
- * kernel that get_plan and get_knobs report; fixing any of that kernel's knobs selects it.  stages = 1 with row_loads = 2,
- * no tile and no pitch, names the kernel of strips (split_k: 0, or 1, 2 or 4 groups of waves; 2 and 4 for stride 1, 2 for
- * rows of an odd number of pixels, 4 for a multiple of 128 channels), and is reported as such: TVG_KERNEL_3X3, 64 x 32 times the rows of a strip.
+ * TVG_KERNEL_3X3_STRIPS (c a multiple of 32; rows of more than 32 pixels: of 4 n) runs where the library's rule finds it the
+ * faster one.  get_knobs reports stages = 1, row_loads = 2 and in split_k its groups of waves that split the reduction, 1, 2
+ * or 4 (2 and 4 for stride 1, 2 for rows of an odd number of pixels, 4 for a multiple of 128 channels), and no tile and no
+ * pitch; the same values, or split_k = 0, name it.  Naming a tile or a pitch, stages = 2, or stages = 1 without row_loads,
+ * selects the two kernels above.
  */
 typedef struct {
     int32_t mt, nt, stages, split_k, lds_pitch, row_loads;

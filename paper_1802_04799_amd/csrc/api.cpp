@@ -318,12 +318,6 @@ tvg_status tvg_conv2d_set_knobs(const tvg_conv_desc *desc, const tvg_conv_knobs 
                                      knobs->lds_pitch, knobs->row_loads});
 }
 
-// The kernel of strips is reported where the knobs name it; by rule it stands in for the kernel that is reported.
-static bool named_strips(const ConvProblem &p, const Dispatch &d)
-{
-    return d.strips_shape && tvg::forced_knobs(p).row_loads == 2;
-}
-
 tvg_status tvg_conv2d_get_knobs(const tvg_conv_desc *desc, tvg_conv_knobs *knobs)
 {
     if (!knobs) return TVG_ERR_NULL;
@@ -334,7 +328,7 @@ tvg_status tvg_conv2d_get_knobs(const tvg_conv_desc *desc, tvg_conv_knobs *knobs
     tvg_conv_knobs k = {0, 0, 0, 0, 0, 0};
     if (d.rows_shape) {
         // no knobs: fixing one selects the 3x3 or 1x1 kernel behind it
-    } else if (named_strips(p, d)) {
+    } else if (d.strips_shape) {
         k.stages = 1;
         k.split_k = d.strips.kg;
         k.row_loads = 2;
@@ -390,8 +384,8 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
         *kernel = d.patch_shape ? TVG_KERNEL_3X3 : TVG_KERNEL_1X1;
         *mt = 16;
         *nt = 16 * d.rows.nj;
-    } else if (named_strips(p, d)) {
-        *kernel = TVG_KERNEL_3X3;
+    } else if (d.strips_shape) {
+        *kernel = TVG_KERNEL_3X3_STRIPS;
         *mt = 64;
         *nt = 32 * d.strips.b;
     } else if (d.patch_shape) {

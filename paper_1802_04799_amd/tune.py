@@ -62,7 +62,7 @@ def _time_us(call, iters: int, repeats: int) -> float:
 def space_for(desc, kernel: int) -> Dict[str, list]:
     """The values each knob can take for this problem's kernel family (0 = the library's rule is
     not a value of its own: every point of the space names all its knobs)."""
-    if kernel in (1, 2):                         # bf16 3x3: both kernels, all their knobs
+    if kernel in (1, 2, 7):                      # bf16 3x3: both tiled kernels, all their knobs
         s1 = desc.stride_w == 1
         odd_small = desc.w % 2 == 1 and desc.w <= 7 and s1
         return {"tile": TILES_3X3, "stages": [1, 2], "split_k": [1, 2] if s1 else [1],
@@ -136,7 +136,7 @@ def tune_conv2d(desc, x, w, scale, shift, y, bias=None, residual=None, workspace
             eff = _b.tvg_conv2d_get_knobs(desc)
             k2 = _b.tvg_conv2d_get_plan(desc)[0]
             # usable if the library really runs what the point names (no silent fall-back)
-            same_family = (k2 in (1, 2)) if kernel in (1, 2) else (k2 in (4, 6)) if kernel in (4, 6) else k2 == kernel
+            same_family = (k2 in (1, 2, 7)) if kernel in (1, 2, 7) else (k2 in (4, 6)) if kernel in (4, 6) else k2 == kernel
             named = all(want == 0 or want == got for want, got in zip(p, eff))
             if same_family and named:
                 us = measure()

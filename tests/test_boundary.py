@@ -204,6 +204,9 @@ def test_tile_table_sets_overrides_and_forgets():
     """tvg_conv2d_set_tile / tvg_conv2d_get_plan are host-only: the planners' choice, a fixed
     tile, its removal, and what is rejected."""
     c6 = desc(n=64, c=128, h=28, w=28, k=128, dtype=tvg.TVG_BF16, flags=tvg.TVG_RELU)
+    by_rule = tvg.tvg_conv2d_get_plan(c6)
+    assert by_rule[:2] == (7, 64)                                    # 3x3 in strips, 64 channels
+    assert tvg.tvg_conv2d_set_tile(c6, 64, 256) == 0
     assert tvg.tvg_conv2d_get_plan(c6) == (2, 64, 256)               # pipelined 3x3, 64 x 256
     assert tvg.tvg_conv2d_set_tile(c6, 64, 128) == 0
     plain = desc(n=64, c=128, h=28, w=28, k=128, dtype=tvg.TVG_BF16, flags=0)
@@ -213,7 +216,7 @@ def test_tile_table_sets_overrides_and_forgets():
     assert tvg.tvg_conv2d_set_tile(c6, 128, 64) == 0                 # replaces the entry
     assert tvg.tvg_conv2d_get_plan(c6)[1:] == (128, 64)
     assert tvg.tvg_conv2d_set_tile(c6, 0, 0) == 0
-    assert tvg.tvg_conv2d_get_plan(c6) == (2, 64, 256)
+    assert tvg.tvg_conv2d_get_plan(c6) == by_rule
     assert tvg.tvg_conv2d_set_tile(c6, 0, 0) == 0                    # forgetting twice is fine
     # 128 x 256 is the pipelined kernel's channel-split variant: it runs when named with its stages
     assert tvg.tvg_conv2d_set_knobs(c6, (128, 256, 2, 0, 0, 0)) == 0
@@ -299,6 +302,8 @@ def test_knob_table_host_side():
     """tvg_conv2d_set_knobs / tvg_conv2d_get_knobs (host only): what the library's rule picks, what
     a caller can fix, how the size query follows the reduction split, what is rejected."""
     c6 = desc(n=64, c=128, h=28, w=28, k=128, dtype=tvg.TVG_BF16)
+    assert tvg.tvg_conv2d_get_knobs(c6) == (0, 0, 1, 1, 0, 2)           # in strips, one group of waves
+    assert tvg.tvg_conv2d_set_knobs(c6, (0, 0, 2, 0, 0, 0)) == 0
     assert tvg.tvg_conv2d_get_knobs(c6) == (64, 256, 2, 1, 2, 0)        # pipelined, padded pitch
     assert tvg.tvg_conv2d_set_knobs(c6, (64, 128, 1, 0, 0, 0)) == 0
     assert tvg.tvg_conv2d_get_plan(c6) == (1, 64, 128)                 # the single-stage kernel
@@ -306,16 +311,21 @@ def test_knob_table_host_side():
     assert tvg.tvg_conv2d_set_tile(c6, 64, 64) == 0                    # the tile alone: stages stay
     assert tvg.tvg_conv2d_get_knobs(c6)[:3] == (64, 64, 1)
     assert tvg.tvg_conv2d_set_knobs(c6, None) == 0
-    assert tvg.tvg_conv2d_get_knobs(c6) == (64, 256, 2, 1, 2, 0)
-    # C12 at batch 64: odd 7-pixel rows, 200 tiles: by rule whole-row loads, one wave group, padded pitch
+    assert tvg.tvg_conv2d_get_knobs(c6) == (0, 0, 1, 1, 0, 2)
+    # C12 at batch 64 in the pipelined kernel: odd 7-pixel rows, 200 tiles: whole-row loads, one wave group, padded pitch
     c12 = desc(n=64, c=512, h=7, w=7, k=512, dtype=tvg.TVG_BF16)
+    assert tvg.tvg_conv2d_get_plan(c12)[0] == 7
+    assert tvg.tvg_conv2d_set_knobs(c12, (0, 0, 2, 0, 0, 0)) == 0
     assert tvg.tvg_conv2d_get_knobs(c12) == (64, 128, 2, 1, 2, 2)
     assert tvg.tvg_conv2d_set_knobs(c12, (0, 0, 2, 0, 0, 1)) == 0       # element loads: two wave groups
     assert tvg.tvg_conv2d_get_knobs(c12)[2:] == (2, 2, 2, 1)
     assert tvg.tvg_conv2d_set_knobs(c12, None) == 0
     # C9 at batch 64: a lone workgroup per CU keeps the padded pitch (86 KB of LDS), one group
     c9 = desc(n=64, c=256, h=14, w=14, k=256, dtype=tvg.TVG_BF16)
+    assert tvg.tvg_conv2d_get_plan(c9)[0] == 7
+    assert tvg.tvg_conv2d_set_knobs(c9, (0, 0, 2, 0, 0, 0)) == 0
     assert tvg.tvg_conv2d_get_knobs(c9) == (64, 256, 2, 1, 2, 0)
+    assert tvg.tvg_conv2d_set_knobs(c9, None) == 0
     # the generic kernel: the size query follows the split
     f = desc(n=1, c=508, h=7, w=7, k=512)
     auto = tvg.tvg_conv2d_workspace_size(f)
@@ -360,7 +370,11 @@ def test_knob_table_host_side():
     # the gather kernel and the specialised ones, as before
     (dict(n=1, c=60, h=56, w=56, k=64), (0, 64, 128)),
     (dict(n=1, c=508, h=7, w=7, k=512), (0, 128, 128)),
-    (dict(n=64, c=128, h=28, w=28, k=128, dtype=1), (2, 64, 256)),
+    (dict(n=64, c=64, h=56, w=56, k=64, dtype=1), (1, 64, 512)),
+    # 3x3 in strips: one group of waves, two, four, windows, a stride
+    (dict(n=64, c=128, h=28, w=28, k=128, dtype=1), (7, 64, 224)),
+    (dict(n=64, c=512, h=7, w=7, k=512, dtype=1), None), (dict(n=64, c=256, h=14, w=14, k=64, dtype=1), None),
+    (dict(n=24, c=192, h=56, w=56, k=64, dtype=1), None), (dict(n=64, c=256, h=14, w=14, k=512, stride_h=2, stride_w=2, dtype=1), None),
     (dict(n=64, c=128, h=28, w=28, k=256, r=1, s=1, pad_h=0, pad_w=0, dtype=1), None),
 ])
 def test_fixing_the_knobs_that_a_plan_reports_changes_nothing(kw, plan):
@@ -373,6 +387,8 @@ def test_fixing_the_knobs_that_a_plan_reports_changes_nothing(kw, plan):
     try:
         assert tvg.tvg_conv2d_set_knobs(d, before[1]) == 0
         assert state() == before
+        if before[0][0] == 7:                                           # the kernel itself, not one that it stands in for
+            assert before[1][2:3] + before[1][5:] == (1, 2) and before[1][3] in (1, 2, 4)
         if not any(before[1]):                                          # the gather kernel, when asked for
             assert tvg.tvg_conv2d_set_tile(d, 64, 128) == 0
             assert tvg.tvg_conv2d_get_plan(d) == (0, 64, 128) and tvg.tvg_conv2d_get_knobs(d)[2] == 2

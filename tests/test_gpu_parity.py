@@ -253,7 +253,12 @@ def test_bf16_3x3_patch_kernel_wide_tile(tvg, cfg):
 
 def test_bf16_3x3_wide_tile_is_the_rule_for_shallow_layers_that_fill_the_chip(tvg):
     def plan(n, ic, h, w, oc, stride=1):
-        return tvg.tvg_conv2d_get_plan(tvg.ConvDesc(n, ic, h, w, oc, 3, 3, stride, stride, 1, 1, tvg.TVG_BF16, 0))
+        # (row_loads = 1, which even rows do not have: the rule of the kernels behind the kernel of strips)
+        desc = tvg.ConvDesc(n, ic, h, w, oc, 3, 3, stride, stride, 1, 1, tvg.TVG_BF16, 0)
+        assert tvg.tvg_conv2d_set_knobs(desc, (0, 0, 0, 0, 0, 1)) == 0
+        got = tvg.tvg_conv2d_get_plan(desc)
+        tvg.tvg_conv2d_set_knobs(desc, None)
+        return got
     assert plan(64, 64, 56, 56, 64) == (1, 64, 512)        # C2 at batch 64: 392 tiles
     assert plan(32, 64, 56, 56, 64) == (1, 64, 256)        # batch 32: the wide tile would leave CUs idle
     assert plan(64, 128, 28, 28, 128) == (2, 64, 256)      # eight chunks: the pipelined kernel
@@ -921,7 +926,7 @@ def test_tuner_fixes_a_tile_and_results_stay_right(tvg, tmp_path):
     try:
         rep = tune.tune_conv2d(desc, d["x"], d["w"], d["scale"], d["shift"], y, iters=10, repeats=2,
                                min_gain=0.0, max_trials=12)
-        assert rep["kernel"] == "3x3" and len(rep["candidates"]) >= 3
+        assert rep["kernel"] == "3x3-strips" and len(rep["candidates"]) >= 3
         assert rep["tuned_us"] <= rep["default_us"]
         walk = rep["walk"]
         assert 3 <= walk["trials"] <= 12 and walk["space_points"] > 12 and not walk["exhaustive"]

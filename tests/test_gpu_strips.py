@@ -45,7 +45,7 @@ def _check(tvg, cfg, b, kg, residual, bias, relu, stride=1):
                                inp["residual"] if residual else None, stride=(stride, stride), pad=(1, 1), relu=relu)
     assert tvg.tvg_conv2d_set_knobs(desc, (0, 0, 1, kg, 0, 2)) == 0
     try:
-        assert tvg.tvg_conv2d_get_plan(desc) == (1, 64, 32 * b) and tvg.tvg_conv2d_get_knobs(desc) == (0, 0, 1, kg, 0, 2)
+        assert tvg.tvg_conv2d_get_plan(desc) == (7, 64, 32 * b) and tvg.tvg_conv2d_get_knobs(desc) == (0, 0, 1, kg, 0, 2)
         ys = [tvg.conv2d_fused(d["x"], d["w"], d["scale"], d["shift"], d["bias"] if bias else None, d["residual"] if residual else None,
                                stride=stride, pad=1, relu=relu, stream_out=hint) for hint in (False, True)]
     finally:
