@@ -310,7 +310,8 @@ typedef enum {
     TVG_KERNEL_1X1 = 4,            /* bf16 1x1                                             */
     TVG_KERNEL_F32_SMALL = 5,      /* fp32 1x1 / 3x3 / 7x7 stem of launch-bound problems (mt = nt = 32 or 16; stem 32 x 64; 1x1 also 32 x 64 and 32 x 128) */
     TVG_KERNEL_1X1_DEEP = 6,       /* bf16 1x1 stride 1, reductions of 128 n channels       */
-    TVG_KERNEL_3X3_STRIPS = 7      /* bf16 3x3, strips of rows, reductions of 32 n channels */
+    TVG_KERNEL_3X3_STRIPS = 7      /* bf16 3x3, strips of rows, reductions of 32 n channels (mt 64, four groups of waves
+                                    * 32; nt up to four strips of 4 to 8 rows of 8 pixels, stride 2: 4 pixels) */
 } tvg_kernel;
 tvg_status tvg_conv2d_set_tile(const tvg_conv_desc *desc, int32_t mt, int32_t nt);
 tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32_t *mt, int32_t *nt);

@@ -386,8 +386,8 @@ tvg_status tvg_conv2d_get_plan(const tvg_conv_desc *desc, int32_t *kernel, int32
         *nt = 16 * d.rows.nj;
     } else if (d.strips_shape) {
         *kernel = TVG_KERNEL_3X3_STRIPS;
-        *mt = 64;
-        *nt = 32 * d.strips.b;
+        *mt = d.strips.kg == 4 ? 32 : 64;
+        *nt = d.strips.sr * d.strips.t8 * d.strips.b * 8 / p.sh;
     } else if (d.patch_shape) {
         *kernel = d.patch.dbuf ? TVG_KERNEL_3X3_PIPELINED : TVG_KERNEL_3X3;
         *mt = d.patch.mt;

@@ -432,6 +432,23 @@ def test_bf16_kernel_for_few_tiles_takes_them_where_it_is_faster(n, c, h, w, k, 
     assert any(tvg.tvg_conv2d_get_knobs(d)) != few
 
 
+@pytest.mark.parametrize("cfg,groups,channels,strip_row", [
+    ((64, 128, 28, 28, 128, 1), 1, 64, 32), ((64, 512, 7, 7, 512, 1), 1, 64, 32), ((64, 512, 7, 7, 512, 1), 2, 64, 32), ((2, 256, 14, 14, 64, 1), 4, 32, 32),
+    ((8, 256, 14, 14, 512, 2), 1, 64, 16), ((1, 64, 4, 8, 64, 1), 1, 64, 8), ((3, 64, 9, 20, 70, 1), 1, 64, 24), ((2, 96, 13, 56, 70, 2), 1, 64, 16),
+])
+def test_the_kernel_of_strips_reports_its_tile(cfg, groups, channels, strip_row):
+    """Output channels and pixels of a workgroup: four groups of waves own half the channels, a stride halves the pixels
+    of a strip's row, and a tile of few strips has fewer than four.  (strip_row: one row of all its strips, of 4 to 8.)"""
+    n, c, h, w, k, stride = cfg
+    d = desc(n=n, c=c, h=h, w=w, k=k, stride_h=stride, stride_w=stride, dtype=1)
+    assert tvg.tvg_conv2d_set_knobs(d, (0, 0, 1, groups, 0, 2)) == 0
+    try:
+        kernel, mt, nt = tvg.tvg_conv2d_get_plan(d)
+        assert (kernel, mt) == (7, channels) and nt in [strip_row * rows for rows in range(4, 9)]
+    finally:
+        tvg.tvg_conv2d_set_knobs(d, None)
+
+
 @pytest.mark.parametrize("n,h,w,k,r,tile", [(1, 224, 224, 64, 7, (64, 64)), (9, 128, 112, 64, 7, (64, 64)), (10, 128, 104, 64, 7, (64, 256)),
                                             (1, 224, 224, 32, 3, (32, 128)), (20, 128, 104, 32, 3, (32, 256)), (8, 128, 128, 50, 3, (64, 64))])
 def test_stem_plan_reports_the_tile_that_runs(n, h, w, k, r, tile):

@@ -36,6 +36,15 @@ STRIDE2 = [
 ]
 
 
+def tile_pixels(cfg, b, stride):
+    """Up to four strips of b rows x 8 input pixels: side by side in a row, or in part of a long one, and rows of strips."""
+    n, _, h, w, _ = cfg
+    side = min(-(-w // 8), 4)
+    windows = 1 if w <= 32 else -(-(w - 8) // 24) if stride == 1 else -(-(-(-w // 8) - 1) // 3)
+    rows = min(4 // side, n * windows * -(-(-(-h // stride)) // b))
+    return rows * side * b * 8 // stride
+
+
 def _check(tvg, cfg, b, kg, residual, bias, relu, stride=1):
     n, ic, h, w, oc = cfg
     desc = tvg.ConvDesc(n, ic, h, w, oc, 3, 3, stride, stride, 1, 1, tvg.TVG_BF16, 0)
@@ -45,7 +54,7 @@ def _check(tvg, cfg, b, kg, residual, bias, relu, stride=1):
                                inp["residual"] if residual else None, stride=(stride, stride), pad=(1, 1), relu=relu)
     assert tvg.tvg_conv2d_set_knobs(desc, (0, 0, 1, kg, 0, 2)) == 0
     try:
-        assert tvg.tvg_conv2d_get_plan(desc) == (7, 64, 32 * b) and tvg.tvg_conv2d_get_knobs(desc) == (0, 0, 1, kg, 0, 2)
+        assert tvg.tvg_conv2d_get_plan(desc) == (7, 32 if kg == 4 else 64, tile_pixels(cfg, b, stride)) and tvg.tvg_conv2d_get_knobs(desc) == (0, 0, 1, kg, 0, 2)
         ys = [tvg.conv2d_fused(d["x"], d["w"], d["scale"], d["shift"], d["bias"] if bias else None, d["residual"] if residual else None,
                                stride=stride, pad=1, relu=relu, stream_out=hint) for hint in (False, True)]
     finally:
