@@ -33,6 +33,8 @@ TILES: List[Tuple[int, int]] = [(64, 256), (128, 128), (64, 128), (128, 64), (64
 # the pipelined 3x3 kernel also has 128 x 256 (its channel-split variant: two wave groups share a patch),
 # the single-stage one 64 x 512 (stride 1, rows of 8n pixels)
 TILES_3X3: List[Tuple[int, int]] = TILES + [(128, 256), (64, 512)]
+# in the place of a tile: the 3x3 kernel of strips, whose tile follows from the problem
+STRIPS: Tuple[int, int] = (0, 0)
 KNOBS = ("mt", "nt", "stages", "split_k", "lds_pitch", "row_loads")
 _chosen: Dict[str, Tuple[int, ...]] = {}
 
@@ -62,10 +64,13 @@ def _time_us(call, iters: int, repeats: int) -> float:
 def space_for(desc, kernel: int) -> Dict[str, list]:
     """The values each knob can take for this problem's kernel family (0 = the library's rule is
     not a value of its own: every point of the space names all its knobs)."""
-    if kernel in (1, 2, 7):                      # bf16 3x3: both tiled kernels, all their knobs
+    if kernel in (1, 2, 7):                      # bf16 3x3: both tiled kernels and the one of strips, all their knobs
         s1 = desc.stride_w == 1
         odd_small = desc.w % 2 == 1 and desc.w <= 7 and s1
-        return {"tile": TILES_3X3, "stages": [1, 2], "split_k": [1, 2] if s1 else [1],
+        strips = desc.c % 32 == 0 and (desc.w <= 32 or desc.w % 4 == 0)
+        split = [1, 2] if s1 else [1]
+        return {"tile": TILES_3X3 + ([STRIPS] if strips else []), "stages": [1, 2],
+                "split_k": split + ([4] if strips and s1 and desc.c % 128 == 0 else []),
                 "lds_pitch": [1, 2] if s1 else [0], "row_loads": [1, 2] if odd_small else [0]}
     if kernel in (4, 6):                         # bf16 1x1: its tiles, or the deep-reduction kernel
         deep = desc.stride_w == 1 and desc.c % 128 == 0 and (desc.h * desc.w) % 4 == 0
@@ -84,9 +89,11 @@ def _point(tile, stages, split_k, lds_pitch, row_loads) -> Tuple[int, ...]:
 
 def _normalise(p: Tuple[int, ...]) -> Tuple[int, ...]:
     """Knobs that only the pipelined 3x3 kernel has (it always names its split) are dropped from a
-    single-stage point, and the wide loads of the 1x1 kernel from a deep-reduction point, so that
-    equivalent points share one measurement."""
+    single-stage point, all but the split from a point of the kernel of strips, and the wide loads of the 1x1 kernel
+    from a deep-reduction point, so that equivalent points share one measurement."""
     mt, nt, stages, split_k, pitch, rows = p
+    if (mt, nt) == STRIPS and split_k and stages:
+        return (0, 0, 1, split_k, 0, 2)
     if stages == 1:
         return (mt, nt, 1, 0, 0, 0 if split_k else rows)
     if not split_k and not pitch:
@@ -198,7 +205,7 @@ def tune_conv2d(desc, x, w, scale, shift, y, bias=None, residual=None, workspace
     if best_p is not None and best_us < base * (1.0 - min_gain):
         _b.tvg_conv2d_set_knobs(desc, best_p)
         _chosen[report["key"]] = tuple(best_p)
-        report["chosen"] = list(best_p[:2])
+        report["chosen"] = list(_b.tvg_conv2d_get_plan(desc)[1:])
         report["chosen_knobs"] = list(best_p)
     else:
         _chosen.pop(report["key"], None)

@@ -449,6 +449,30 @@ def test_the_kernel_of_strips_reports_its_tile(cfg, groups, channels, strip_row)
         tvg.tvg_conv2d_set_knobs(d, None)
 
 
+@pytest.mark.parametrize("cfg,groups", [((64, 128, 28, 28, 128, 1), (1, 4)), ((64, 512, 7, 7, 512, 1), (1, 2, 4)), ((1, 256, 14, 14, 64, 1), (1, 4)),
+                                        ((64, 64, 56, 56, 64, 1), (1,)), ((96, 64, 27, 27, 128, 1), (1, 2)), ((96, 128, 28, 28, 256, 2), (1,))])
+def test_the_tuner_reaches_the_kernel_of_strips(cfg, groups, monkeypatch):
+    """Whatever the rule picks: each number of groups that the problem has is a point of its space, and is chosen where
+    it is the fastest (times are made up)."""
+    from paper_1802_04799_amd import tune
+    n, c, h, w, k, stride = cfg
+    d = desc(n=n, c=c, h=h, w=w, k=k, stride_h=stride, stride_w=stride, dtype=1)
+    for fastest in groups:
+        want = (0, 0, 1, fastest, 0, 2)
+        monkeypatch.setattr(tune, "_time_us", lambda *a: 5.0 if tvg.tvg_conv2d_get_knobs(d) == want else 10.0)
+        by_rule = tvg.tvg_conv2d_get_knobs(d)
+        try:
+            rep = tune.tune_conv2d(d, None, None, None, None, None, max_trials=1000)
+            assert rep["default_knobs"] == list(by_rule) and {f"0/0/1/{g}/0/2" for g in groups} <= set(rep["candidates"])
+            if by_rule == want:
+                assert rep["chosen"] is None
+            else:
+                assert rep["chosen_knobs"] == list(want) and rep["chosen"] == list(tvg.tvg_conv2d_get_plan(d)[1:])
+                assert tvg.tvg_conv2d_get_plan(d)[0] == 7
+        finally:
+            tvg.tvg_conv2d_set_knobs(d, None)
+
+
 @pytest.mark.parametrize("n,h,w,k,r,tile", [(1, 224, 224, 64, 7, (64, 64)), (9, 128, 112, 64, 7, (64, 64)), (10, 128, 104, 64, 7, (64, 256)),
                                             (1, 224, 224, 32, 3, (32, 128)), (20, 128, 104, 32, 3, (32, 256)), (8, 128, 128, 50, 3, (64, 64))])
 def test_stem_plan_reports_the_tile_that_runs(n, h, w, k, r, tile):
