@@ -8,7 +8,7 @@ batch 64 with bf16 inputs/outputs, fp32 accumulate and the fused scale/shift + R
 12 launches of tvg_conv2d_fused through the C ABI, inputs already resident in HBM.
 Prints ONE JSON line.  ``value`` is the whole step's throughput in TFLOP/s (2*MACs of the
 direct method over the step time).  ``roofline`` describes ONE kernel, the one with the
-largest share of the step (conv3x3_strips_kernel: its layers are
+largest share of the step (by the calibration pass and the library's plans: its layers are
 launched last and back to back, two HIP events per step bracket exactly them inside the timed
 region); ``layers`` lists all twelve.  ``ceilings`` holds what the GPU sustains in this very run
 (a plain copy, a register-resident matrix-instruction loop per dtype), so every fraction can be
@@ -232,11 +232,6 @@ def main():
     if args.only:
         keep = set(args.only.split(","))
         layers = [l for l in layers if l.sh.name in keep]
-    # The twelve layers are independent.  Those that run in the kernel of strips (the largest share
-    # of the step) come last and back to back, so that two events per step bracket exactly them.
-    DOM_KERNEL = 7          # TVG_KERNEL_3X3_STRIPS
-    is_dom = lambda l: tvg.tvg_conv2d_get_plan(l.desc)[0] == DOM_KERNEL
-
     tuning = None
     if args.tune:       # the measured per-shape knob search, outside the timed region
         from paper_1802_04799_amd import tune
@@ -244,9 +239,6 @@ def main():
                                         workspace=l.ws if l.ws_bytes else None), layer=l.sh.name)
                   for l in layers]
 
-    layers = [l for l in layers if not is_dom(l)] + [l for l in layers if is_dom(l)]
-    n_dom = sum(1 for l in layers if is_dom(l))
-    first_dom = len(layers) - n_dom
     step_flops = sum(l.sh.flops for l in layers)
     step_bytes = sum(l.bytes for l in layers)
 
@@ -271,6 +263,17 @@ def main():
     per_layer_ms = [sum(ev[k][i].elapsed_time(ev[k][i + 1]) for k in range(cal)) / cal
                     for i in range(len(layers))]
     del ev
+    # The twelve layers are independent.  Those of the kernel with the largest share of the step come
+    # last and back to back, so that two events per step bracket exactly them.
+    share = {}
+    for l, ms in zip(layers, per_layer_ms):
+        share[kernel_symbol(tvg, l.desc)] = share.get(kernel_symbol(tvg, l.desc), 0.0) + ms
+    dom_kernel = max(share, key=share.get)
+    is_dom = lambda l: kernel_symbol(tvg, l.desc) == dom_kernel
+    order = sorted(range(len(layers)), key=lambda i: is_dom(layers[i]))
+    layers, per_layer_ms = [layers[i] for i in order], [per_layer_ms[i] for i in order]
+    n_dom = sum(1 for l in layers if is_dom(l))
+    first_dom = len(layers) - n_dom
 
     K = args.steps
     d0 = [torch.cuda.Event(enable_timing=True) for _ in range(K)]
@@ -279,11 +282,10 @@ def main():
     t0 = time.perf_counter()
     for k in range(K):
         for i, l in enumerate(layers):
-            if i == first_dom and n_dom:
+            if i == first_dom:
                 d0[k].record()
             l.launch()
-        if n_dom:
-            d1[k].record()
+        d1[k].record()
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
     ms_per_step = wall * 1e3 / K
@@ -313,10 +315,10 @@ def main():
         dom_flops = sum(l.sh.flops for l in dom)
         dom_bytes = sum(l.bytes for l in dom)
         dom_tf = dom_flops / (dom_ms * 1e-3) / 1e12
-        roofline = {"bound": "mfma", "achieved": round(dom_tf, 2), "peak": PEAK_BF16_TFLOPS,
+        roofline = {"bound": "mfma" if dom_flops / dom_bytes > PEAK_BF16_TFLOPS * 1e3 / PEAK_HBM_GBS else "hbm", "achieved": round(dom_tf, 2), "peak": PEAK_BF16_TFLOPS,
                     "unit": "TFLOP/s", "frac": round(dom_tf / PEAK_BF16_TFLOPS, 4),
-                    "traffic": measured_traffic("conv3x3_strips_kernel"),
-                    "kernel": "conv3x3_strips_kernel",
+                    "traffic": measured_traffic(dom_kernel, [l.sh.name for l in dom]),
+                    "kernel": dom_kernel,
                     "frac_of_achievable_mfma": round(dom_tf / ach_bf16, 4),
                     "launches_per_step": n_dom,
                     "layers": [l.sh.name for l in dom],
@@ -326,7 +328,7 @@ def main():
                     "share_of_step_time": round(dom_ms / ms_per_step, 3),
                     "timing": "two HIP events per step around this kernel's back-to-back launches, "
                               "inside the timed region, on the launch stream; per-unit figures: "
-                              "2*IC*9 flops per output element, (|x|+|w|+|y|)*2 + 8*OC bytes per launch"}
+                              "2*IC*R*S flops per output element, (|x|+|w|+|y|)*2 + 8*OC bytes per launch"}
 
     r3 = [(l, ms) for l, ms in zip(layers, per_layer_ms) if l.sh.r == 3]
     out = {
@@ -544,13 +546,25 @@ def copy_probe(torch, args):
     print(json.dumps({"copy_probe_mib": args.copy_probe, "copies": args.steps}))
 
 
-def measured_traffic(kernel):
-    """HBM bytes per launch of `kernel` from the committed rocprofv3 counter summary
+def kernel_symbol(tvg, desc):
+    """The device kernel that the library runs this dense problem in, by its plan."""
+    kernel, mt, _ = tvg.tvg_conv2d_get_plan(desc)
+    if kernel in (1, 4) and mt == 16:
+        return "conv_rows_kernel"
+    if kernel == 4 and tvg.tvg_conv2d_get_knobs(desc)[5] == 2:
+        return "conv1x1_rows_kernel"
+    return {1: "conv3x3_patch_kernel", 2: "conv3x3_dbuf_kernel", 3: "conv_stem_s2_kernel", 4: "conv1x1_kernel",
+            6: "conv1x1_deep_kernel", 7: "conv3x3_strips_kernel"}.get(kernel, tvg.KERNEL_NAMES[kernel])
+
+
+def measured_traffic(kernel, layers):
+    """HBM bytes per launch of `kernel` on these layers from the committed rocprofv3 counter summary
     (profiles/hbm_traffic.json, written from two --pmc runs), or None when there is none."""
     path = os.path.join(ROOT, "profiles", "hbm_traffic.json")
     try:
         with open(path) as f:
-            return json.load(f).get(kernel, {}).get("bytes_per_launch")
+            entry = json.load(f).get(kernel, {})
+        return entry.get("bytes_per_launch") if sorted(entry.get("launches", [])) == sorted(layers) else None
     except (OSError, ValueError):
         return None
 

@@ -473,6 +473,21 @@ def test_the_tuner_reaches_the_kernel_of_strips(cfg, groups, monkeypatch):
             tvg.tvg_conv2d_set_knobs(d, None)
 
 
+def test_the_bench_line_names_the_kernel_that_a_plan_names():
+    """... and takes the profile's traffic only for the launches that were profiled."""
+    import bench
+    c6, c2 = desc(n=64, c=128, h=28, w=28, k=128, dtype=1), desc(n=64, c=64, h=56, w=56, k=64, dtype=1)
+    assert bench.kernel_symbol(tvg, c6) == "conv3x3_strips_kernel" and bench.kernel_symbol(tvg, c2) == "conv3x3_patch_kernel"
+    assert tvg.tvg_conv2d_set_knobs(c6, (0, 0, 2, 0, 0, 0)) == 0
+    try:
+        assert bench.kernel_symbol(tvg, c6) == "conv3x3_dbuf_kernel"
+    finally:
+        tvg.tvg_conv2d_set_knobs(c6, None)
+    assert bench.kernel_symbol(tvg, desc(n=1, c=128, h=28, w=28, k=128, dtype=1)) == "conv_rows_kernel"
+    assert bench.kernel_symbol(tvg, desc(n=64, c=128, h=28, w=28, k=512, r=1, s=1, pad_h=0, pad_w=0, dtype=1)) == "conv1x1_rows_kernel"
+    assert bench.measured_traffic("conv3x3_strips_kernel", ["C6"]) is None
+
+
 @pytest.mark.parametrize("n,h,w,k,r,tile", [(1, 224, 224, 64, 7, (64, 64)), (9, 128, 112, 64, 7, (64, 64)), (10, 128, 104, 64, 7, (64, 256)),
                                             (1, 224, 224, 32, 3, (32, 128)), (20, 128, 104, 32, 3, (32, 256)), (8, 128, 128, 50, 3, (64, 64))])
 def test_stem_plan_reports_the_tile_that_runs(n, h, w, k, r, tile):
