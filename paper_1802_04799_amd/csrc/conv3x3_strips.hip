@@ -70,11 +70,14 @@ struct StripsArgs {
 };
 
 // 16 bytes per lane from a buffer straight into LDS at `lds` + 16 lane.  In assembly because the compiler waits for all
-// loads in flight before any LDS read that follows its own form; whoever reads the bytes waits with wait_loads.
+// loads in flight before any LDS read that follows its own form; whoever reads the bytes waits with wait_loads.  (M0 is an
+// operand, so that the compiler knows what is in it.  Five wait states: an SGPR that a vector instruction wrote, a spilled
+// one read back, say, has to be that old when a memory instruction reads it, and the compiler keeps no distance to what is
+// inside.)
 __device__ __forceinline__ void load_to_lds(uint32_t lds, uint32_t offset, const uint4v &rsrc, uint32_t uniform_offset)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds), "v"(offset), "s"(rsrc), "s"(uniform_offset) : "memory");
+    asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "{m0}"(lds), "v"(offset), "s"(rsrc), "s"(uniform_offset) : "memory");
 }
 
 // The kernel's arguments read anew, and a value that looks new: what a tile's set-up and tail derive from them would
