@@ -121,6 +121,11 @@ template <class A> __device__ __forceinline__ int split_tile(A &a, int t, int *p
     return a.pixels_first ? outer : inner;
 }
 
+// Whether a workgroup may go on to further tiles.  Not with odd rows: store_row takes the parity of a row's start from goff,
+// which next_rows has overwritten for the next tile by then.  Nor where groups split the reduction: what they exchange lies over
+// the weights and rows of the next step.  Planning gives these a workgroup per tile, and launch refuses anything else.
+constexpr bool walks_tiles(bool odd_rows, int groups) { return !odd_rows && groups == 1; }
+
 // WM waves along the output channels, 16 each, in each of KG groups that split the reduction.
 template <int B, int ST, bool UNAL, int KG, int WM>
 __global__ __launch_bounds__(64 * WM * KG, 2) void conv3x3_strips_kernel(const StripsArgs a)
@@ -585,6 +590,7 @@ __global__ __launch_bounds__(64 * WM * KG, 2) void conv3x3_strips_kernel(const S
 template <int B, int ST, bool UNAL, int KG, int WM = 4>
 tvg_status launch(const StripsArgs &args, const StripsPlan &plan, hipStream_t stream)
 {
+    if (!walks_tiles(UNAL, KG) && plan.workgroups != plan.tiles) return TVG_ERR_LAUNCH;
     const auto kernel = conv3x3_strips_kernel<B, ST, UNAL, KG, WM>;
     static bool configured = false;                // opt in to > 64 KB of dynamic LDS once per instance
     if (!configured && plan.lds_bytes > 64 * 1024) {
@@ -643,7 +649,7 @@ bool set_geometry(const ConvProblem &p, int b, int kg, StripsPlan *g)
     if (g->lds_bytes > 160 * 1024) return false;
     g->ptiles = ((long)p.N * g->spi + g->sr - 1) / g->sr;
     g->tiles = g->ptiles * ((p.OC + 16 * waves - 1) / (16 * waves));
-    g->workgroups = kg == 1 && p.W % 2 == 0 ? std::min(g->tiles, 2L * kComputeUnits) : g->tiles;
+    g->workgroups = walks_tiles(p.W % 2 != 0, kg) ? std::min(g->tiles, 2L * kComputeUnits) : g->tiles;
     return true;
 }
 

@@ -24,6 +24,8 @@ SHAPES = [
     ((33, 256, 5, 14, 40), 4), ((2, 384, 9, 31, 33), 4), ((5, 128, 2, 5, 64), 4), ((1, 640, 6, 26, 97), 4), ((1, 128, 9, 112, 20), 4),
     # two and three tiles per workgroup, of one and of several channel tiles, pixel tiles first and (many images) channel tiles first
     ((1100, 64, 7, 28, 16), 7), ((300, 32, 14, 14, 200), 7), ((700, 96, 8, 10, 130), 8), ((260, 64, 7, 28, 130), 7),
+    # more tiles than workgroups that walk: odd rows and split reductions, which have a workgroup per tile
+    ((1100, 64, 7, 9, 16), 7), ((560, 128, 4, 28, 40), 4), ((560, 128, 4, 27, 40), 4),
 ]
 
 # ... under a stride of 2
@@ -32,7 +34,7 @@ STRIDE2 = [
     ((70, 64, 3, 2, 16), 4), ((1, 64, 9, 3, 33), 4), ((3, 128, 7, 7, 130), 4), ((2, 64, 13, 13, 80), 4), ((1, 192, 17, 21, 64), 4), ((2, 64, 9, 31, 20), 4), ((1, 64, 6, 32, 24), 4),
     ((1, 64, 5, 40, 16), 4), ((2, 96, 14, 56, 70), 4), ((1, 32, 9, 112, 20), 4), ((1, 64, 6, 36, 16), 4),
     ((260, 64, 9, 14, 16), 5), ((130, 64, 9, 21, 16), 5), ((70, 64, 9, 40, 16), 5), ((130, 64, 11, 26, 16), 6), ((520, 64, 11, 3, 16), 6),
-    ((520, 64, 13, 6, 16), 7), ((130, 64, 13, 28, 40), 7), ((260, 64, 13, 13, 16), 7), ((70, 64, 13, 40, 16), 7), ((300, 32, 28, 28, 100), 7), ((300, 64, 13, 13, 130), 7),
+    ((520, 64, 13, 6, 16), 7), ((130, 64, 13, 28, 40), 7), ((260, 64, 13, 13, 16), 7), ((70, 64, 13, 40, 16), 7), ((300, 32, 28, 28, 100), 7), ((300, 64, 13, 13, 130), 7), ((1100, 64, 13, 11, 16), 7),
 ]
 
 
