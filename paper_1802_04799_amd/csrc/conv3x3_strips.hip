@@ -55,7 +55,7 @@ struct StripsArgs {
     const float *scale, *shift, *bias;
     const bf16_t *residual;
     bf16_t *y;
-    int N, IC, H, W, OC, OH, OW, relu, nt;
+    int N, IC, H, W, OC, OH, OW, relu, nt, any;            // any: output rows start at any element
     int t8, spi, sr, rows;             // strips per row, strip rows per image and per tile, staged rows per tile
     int windows;                       // parts of a row (strip rows of their own) where it has more than four strips
     int dg, drow, dch;                 // 256 load tasks further: pieces, rows, channels
@@ -425,7 +425,7 @@ __global__ __launch_bounds__(64 * WM * KG, 2) void conv3x3_strips_kernel(const S
         const uint32_t y_at = mine ? 2u * (uint32_t)(((my_n * OC + oc) * OH + row0) * OW + col0) : kOutOfRange;
         const auto row_at = [&](int b) __attribute__((always_inline)) { return row0 + b < OH ? y_at + 2 * b * OW : kOutOfRange; };
         const auto kept = [&](int b) __attribute__((always_inline)) { return KG == 1 || b % KG == kg; };
-        const bool any = UNAL || (ST == 2 && OW % 2 != 0);            // output rows start at any element
+        const bool any = UNAL || f.any;
 
         uint4v res[B];
 #pragma unroll
@@ -546,7 +546,9 @@ __global__ __launch_bounds__(64 * WM * KG, 2) void conv3x3_strips_kernel(const S
                 if (!kept(b) || at >= kOutOfRange) continue;
                 const uint4v out = finish(b);
                 bf16_t *p = y + at / 2;
-                if (to >= PX) {
+                if (ST == 1 && !UNAL && from > 0) {                   // (a window's first strip: its last four)
+                    *reinterpret_cast<uint2e *>(p + 4) = uint2v{out[2], out[3]};
+                } else if (to >= PX) {
                     if constexpr (ST == 1) *reinterpret_cast<uint4e *>(p) = out;
                     else *reinterpret_cast<uint2e *>(p) = uint2v{out[0], out[1]};
                 } else {
@@ -743,8 +745,9 @@ bool plan_conv3x3_strips(const ConvProblem &p, const Patch3x3Plan &patch, Strips
 
 bool conv3x3_strips_pointers_ok(const ConvPointers &ptr)
 {
-    return (reinterpret_cast<uintptr_t>(ptr.x) | reinterpret_cast<uintptr_t>(ptr.w) | reinterpret_cast<uintptr_t>(ptr.y) |
-            reinterpret_cast<uintptr_t>(ptr.residual)) % 16 == 0;
+    // (x and w as for the kernels behind; y and the residual take accesses of the width that they allow)
+    return (reinterpret_cast<uintptr_t>(ptr.x) | reinterpret_cast<uintptr_t>(ptr.w)) % 16 == 0 &&
+           (reinterpret_cast<uintptr_t>(ptr.y) | reinterpret_cast<uintptr_t>(ptr.residual)) % 2 == 0;
 }
 
 tvg_status launch_conv3x3_strips(const ConvProblem &p, const StripsPlan &plan, const ConvPointers &ptr, hipStream_t stream)
@@ -757,6 +760,7 @@ tvg_status launch_conv3x3_strips(const ConvProblem &p, const StripsPlan &plan, c
     a.y = static_cast<bf16_t *>(ptr.y);
     a.N = p.N; a.IC = p.IC; a.H = p.H; a.W = p.W; a.OC = p.OC; a.OH = p.OH; a.OW = p.OW;
     a.relu = p.relu; a.nt = p.stream_out;
+    a.any = p.OW % 2 != 0 || (reinterpret_cast<uintptr_t>(ptr.y) | reinterpret_cast<uintptr_t>(ptr.residual)) % 4 != 0;
     a.t8 = plan.t8; a.spi = plan.spi; a.sr = plan.sr; a.rows = plan.rows; a.windows = plan.windows;
     const int threads = plan.kg == 4 ? 128 : 256;                              // of a group
     a.dg = threads % plan.t8;

@@ -82,26 +82,62 @@ def test_strips_every_instance_stride_2(tvg, cfg, b, tail):
     _check(tvg, cfg, b, 1, full, full, full, 2)
 
 
+def at(t, off):
+    """A copy of t that starts `off` elements into a buffer of zeros, and that buffer."""
+    import torch
+    buf = torch.zeros(t.numel() + 24, dtype=torch.bfloat16, device="cuda")
+    v = buf[off:off + t.numel()].view(t.shape)
+    v.copy_(t)
+    return v, buf
+
+
 @pytest.mark.parametrize("cfg", [(3, 128, 28, 28, 64), (5, 128, 7, 7, 128)], ids=lambda c: "x".join(map(str, c)))
-def test_strips_unaligned_pointers_get_the_kernel_behind(tvg, cfg):
-    """x, w, y or the residual off a 16-byte address: another kernel, the same result up to the order of the sums."""
+def test_strips_unaligned_pixels_get_the_kernel_behind(tvg, cfg):
+    """x off a 16-byte address: another kernel, the same result up to the order of the sums."""
     import torch
     n, ic, h, w, oc = cfg
     desc = tvg.ConvDesc(n, ic, h, w, oc, 3, 3, 1, 1, 1, 1, tvg.TVG_BF16, 0)
     inp = ti.make_inputs(ti.ConvShape("strips", n, ic, h, w, oc, 3, 3, 1, 1), 10500, "bf16", residual=True)
     d = dev_inputs(inp, "bf16")
     want = oracle.conv2d_fused(inp["x"], inp["w"], inp["scale"], inp["shift"], None, inp["residual"], stride=(1, 1), pad=(1, 1), relu=False)
-    def at(t, off):
-        v = torch.zeros(t.numel() + 8, dtype=torch.bfloat16, device="cuda")[off:off + t.numel()].view(t.shape)
-        v.copy_(t)
-        return v
     assert tvg.tvg_conv2d_set_knobs(desc, (0, 0, 1, 0, 0, 2)) == 0
     try:
-        for ox, oy, orr in ((0, 0, 0), (2, 0, 0), (0, 1, 0), (0, 0, 4)):
-            y = at(torch.zeros_like(d["residual"]), oy)
-            rc = tvg.tvg_conv2d_fused(desc, at(d["x"], ox), d["w"], d["scale"], d["shift"], None, at(d["residual"], orr), y, None, 0, None)
+        for ox in (0, 2):
+            y = torch.zeros_like(d["residual"])
+            rc = tvg.tvg_conv2d_fused(desc, at(d["x"], ox)[0], d["w"], d["scale"], d["shift"], None, d["residual"], y, None, 0, None)
             assert rc == 0, tvg.status_string(rc)
-            check(to_host(y), want, "bf16", (ox, oy, orr))
+            check(to_host(y), want, "bf16", ox)
+    finally:
+        tvg.tvg_conv2d_set_knobs(desc, None)
+
+
+# n, ic, h, w, oc, stride, groups: rows that end in 8, 4, 2 and an odd number of pixels, windows, both strides, split reductions
+ANY_ELEMENT = [(3, 128, 28, 28, 64, 1, 1), (2, 64, 9, 30, 20, 1, 1), (2, 64, 8, 16, 33, 1, 1), (5, 128, 7, 7, 128, 1, 2), (2, 96, 13, 56, 70, 1, 1), (1, 64, 9, 36, 20, 1, 1),
+               (2, 128, 14, 14, 40, 1, 4), (2, 64, 13, 15, 16, 1, 1), (2, 64, 28, 28, 64, 2, 1), (2, 64, 14, 14, 70, 2, 1), (3, 64, 13, 13, 20, 2, 1), (2, 64, 14, 56, 24, 2, 1)]
+
+
+@pytest.mark.parametrize("cfg", ANY_ELEMENT, ids=lambda c: "x".join(map(str, c)))
+def test_strips_outputs_at_any_element(tvg, cfg):
+    """y and the residual at any element: the bits of an aligned call, and nothing written outside y."""
+    import torch
+    n, ic, h, w, oc, stride, kg = cfg
+    desc = tvg.ConvDesc(n, ic, h, w, oc, 3, 3, stride, stride, 1, 1, tvg.TVG_BF16, 0)
+    d = dev_inputs(ti.make_inputs(ti.ConvShape("strips", n, ic, h, w, oc, 3, 3, stride, 1), 10550 + sum(cfg), "bf16", residual=True), "bf16")
+    assert tvg.tvg_conv2d_set_knobs(desc, (0, 0, 1, kg, 0, 2)) == 0
+    try:
+        assert tvg.tvg_conv2d_get_plan(desc)[0] == 7
+        want = None
+        for oy, orr in ((0, 0), (1, 0), (2, 0), (4, 0), (0, 1), (0, 2), (0, 4), (3, 5), (2, 6)):
+            y, buf = at(torch.full_like(d["residual"], float("nan")), oy)
+            rc = tvg.tvg_conv2d_fused(desc, d["x"], d["w"], d["scale"], d["shift"], None, at(d["residual"], orr)[0], y, None, 0, None)
+            assert rc == 0, tvg.status_string(rc)
+            want = y.clone() if want is None else want
+            assert torch.equal(y, want), (oy, orr)
+            assert not bool(buf[:oy].any()) and not bool(buf[oy + y.numel():].any()), (oy, orr)
+        # in place: y may be the residual
+        v, _ = at(d["residual"], 1)
+        assert tvg.tvg_conv2d_fused(desc, d["x"], d["w"], d["scale"], d["shift"], None, v, v, None, 0, None) == 0
+        assert torch.equal(v, want)
     finally:
         tvg.tvg_conv2d_set_knobs(desc, None)
 
