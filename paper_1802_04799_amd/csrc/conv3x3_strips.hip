@@ -71,13 +71,16 @@ struct StripsArgs {
 
 // 16 bytes per lane from a buffer straight into LDS at `lds` + 16 lane.  In assembly because the compiler waits for all
 // loads in flight before any LDS read that follows its own form; whoever reads the bytes waits with wait_loads.  (M0 is an
-// operand, so that the compiler knows what is in it.  Five wait states: an SGPR that a vector instruction wrote, a spilled
-// one read back, say, has to be that old when a memory instruction reads it, and the compiler keeps no distance to what is
-// inside.)
-__device__ __forceinline__ void load_to_lds(uint32_t lds, uint32_t offset, const uint4v &rsrc, uint32_t uniform_offset)
+// output, so that the compiler knows that it has changed.)  An SGPR that a vector instruction wrote has to be five wait states
+// old when a memory instruction reads it, and the compiler keeps no distance to what is inside.  FAR keeps it: for instances
+// that keep SGPRs in lanes of vector registers and read them back where they are wanted.  The others' operands come from scalar
+// instructions, which a test reads from the machine code, and five wait states are longer than an MFMA hides: 32 images
+// 128 -> 128 at 28x28 14.2 us instead of 13.9, ResNet-18 body at batch 32 313.8 us instead of 307.3.
+template <bool FAR> __device__ __forceinline__ void load_to_lds(uint32_t lds, uint32_t offset, const uint4v &rsrc, uint32_t uniform_offset)
 {
-    asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "{m0}"(lds), "v"(offset), "s"(rsrc), "s"(uniform_offset) : "memory");
+    uint32_t m0;
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop %5\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds"
+                 : "={m0}"(m0) : "s"(lds), "v"(offset), "s"(rsrc), "s"(uniform_offset), "n"(FAR ? 3 : 0) : "memory");
 }
 
 // The kernel's arguments read anew, and a value that looks new: what a tile's set-up and tail derive from them would
@@ -161,7 +164,7 @@ __global__ __launch_bounds__(64 * WM * KG, 2) void conv3x3_strips_kernel(const S
     const uint32_t lds_weights = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)weights;
     uint32_t woff;
     auto load_weights = [&](int k, uint32_t bytes, int c) __attribute__((always_inline)) {
-        load_to_lds(lds_weights + 1024 * k, woff, raw_buffer(a.w, bytes), c * (2 * kChunk * 9) + 64 * k);
+        load_to_lds<UNAL>(lds_weights + 1024 * k, woff, raw_buffer(a.w, bytes), c * (2 * kChunk * 9) + 64 * k);
     };
     // a lane's run: channels 8 quad .. + 7 of output channel l16, pieces 9 quad .. + 8
     int wrun[4];

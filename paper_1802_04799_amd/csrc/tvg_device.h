@@ -29,10 +29,12 @@ __device__ __forceinline__ int xcd_remap(int bid, int nb)
 
 // Requests the cache line at `offset` of a buffer, for the sake of the L2: four bytes per lane go to 256 bytes of LDS that
 // nothing reads.  The compiler does not count the load; its waits for loads of its own, which return in order, cover it.
-// (Five wait states before the load: a vector instruction may have written its SGPRs just before.)
+// (M0 is an output, so that the compiler knows that it has changed.  Five wait states before the load: a vector instruction
+// may have written its SGPRs just before.)
 __device__ __forceinline__ void touch_line(uint32_t lds, uint32_t offset, const uint4v &rsrc)
 {
-    asm volatile("s_nop 4\n\tbuffer_load_dword %1, %2, 0 offen lds" :: "{m0}"(lds), "v"(offset), "s"(rsrc) : "memory");
+    uint32_t m0;
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 3\n\tbuffer_load_dword %2, %3, 0 offen lds" : "={m0}"(m0) : "s"(lds), "v"(offset), "s"(rsrc) : "memory");
 }
 
 // Raw buffer descriptor of `bytes` at p.
