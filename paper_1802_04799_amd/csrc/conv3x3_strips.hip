@@ -55,7 +55,7 @@ struct StripsArgs {
     const float *scale, *shift, *bias;
     const bf16_t *residual;
     bf16_t *y;
-    int N, IC, H, W, OC, OH, OW, relu, nt, any;            // any: output rows start at any element
+    int N, IC, H, W, OC, OH, OW, relu, nt;
     int t8, spi, sr, rows;             // strips per row, strip rows per image and per tile, staged rows per tile
     int windows;                       // parts of a row (strip rows of their own) where it has more than four strips
     int dg, drow, dch;                 // 256 load tasks further: pieces, rows, channels
@@ -130,7 +130,9 @@ template <class A> __device__ __forceinline__ int split_tile(A &a, int t, int *p
 constexpr bool walks_tiles(bool odd_rows, int groups) { return !odd_rows && groups == 1; }
 
 // WM waves along the output channels, 16 each, in each of KG groups that split the reduction.
-template <int B, int ST, bool UNAL, int KG, int WM>
+// ANY: output rows start at any element, by their length or by the addresses of y and the residual.  (An instance of its own: a
+// branch for it makes the others' code a fifth longer, which costs 0.1 to 0.4 us where it is fetched anew between layers.)
+template <int B, int ST, bool UNAL, int KG, int WM, bool ANY>
 __global__ __launch_bounds__(64 * WM * KG, 2) void conv3x3_strips_kernel(const StripsArgs a)
 {
     constexpr int kIn = ST == 1 ? B + 2 : 2 * B + 1;      // input rows of a strip
@@ -428,13 +430,12 @@ __global__ __launch_bounds__(64 * WM * KG, 2) void conv3x3_strips_kernel(const S
         const uint32_t y_at = mine ? 2u * (uint32_t)(((my_n * OC + oc) * OH + row0) * OW + col0) : kOutOfRange;
         const auto row_at = [&](int b) __attribute__((always_inline)) { return row0 + b < OH ? y_at + 2 * b * OW : kOutOfRange; };
         const auto kept = [&](int b) __attribute__((always_inline)) { return KG == 1 || b % KG == kg; };
-        const bool any = UNAL || f.any;
 
         uint4v res[B];
 #pragma unroll
         for (int b = 0; b < B; ++b) res[b] = uint4v{0, 0, 0, 0};
         if (residual) {
-            if (any) {
+            if constexpr (ANY) {
 #pragma unroll
                 for (int b = 0; b < B; ++b) {
                     const uint32_t at = row_at(b);
@@ -542,7 +543,7 @@ __global__ __launch_bounds__(64 * WM * KG, 2) void conv3x3_strips_kernel(const S
             }
             return out;
         };
-        if (any) {
+        if constexpr (ANY) {
 #pragma unroll
             for (int b = 0; b < B; ++b) {
                 const uint32_t at = row_at(b);
@@ -592,11 +593,11 @@ __global__ __launch_bounds__(64 * WM * KG, 2) void conv3x3_strips_kernel(const S
     }
 }
 
-template <int B, int ST, bool UNAL, int KG, int WM = 4>
-tvg_status launch(const StripsArgs &args, const StripsPlan &plan, hipStream_t stream)
+template <int B, int ST, bool UNAL, int KG, int WM, bool ANY>
+tvg_status launch_instance(const StripsArgs &args, const StripsPlan &plan, hipStream_t stream)
 {
     if (!walks_tiles(UNAL, KG) && plan.workgroups != plan.tiles) return TVG_ERR_LAUNCH;
-    const auto kernel = conv3x3_strips_kernel<B, ST, UNAL, KG, WM>;
+    const auto kernel = conv3x3_strips_kernel<B, ST, UNAL, KG, WM, ANY>;
     static bool configured = false;                // opt in to > 64 KB of dynamic LDS once per instance
     if (!configured && plan.lds_bytes > 64 * 1024) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
@@ -605,6 +606,15 @@ tvg_status launch(const StripsArgs &args, const StripsPlan &plan, hipStream_t st
     }
     kernel<<<dim3((unsigned)plan.workgroups), dim3(64 * WM * KG), plan.lds_bytes, stream>>>(args);
     return hipGetLastError() == hipSuccess ? TVG_OK : TVG_ERR_LAUNCH;
+}
+
+template <int B, int ST, bool UNAL, int KG, int WM = 4>
+tvg_status launch(const StripsArgs &args, const StripsPlan &plan, hipStream_t stream)
+{
+    const bool any = args.OW % 2 != 0 || (reinterpret_cast<uintptr_t>(args.y) | reinterpret_cast<uintptr_t>(args.residual)) % 4 != 0;
+    if constexpr (!UNAL)
+        if (!any) return launch_instance<B, ST, UNAL, KG, WM, false>(args, plan, stream);
+    return launch_instance<B, ST, UNAL, KG, WM, true>(args, plan, stream);
 }
 
 template <int ST, bool UNAL, int KG>
@@ -763,7 +773,6 @@ tvg_status launch_conv3x3_strips(const ConvProblem &p, const StripsPlan &plan, c
     a.y = static_cast<bf16_t *>(ptr.y);
     a.N = p.N; a.IC = p.IC; a.H = p.H; a.W = p.W; a.OC = p.OC; a.OH = p.OH; a.OW = p.OW;
     a.relu = p.relu; a.nt = p.stream_out;
-    a.any = p.OW % 2 != 0 || (reinterpret_cast<uintptr_t>(ptr.y) | reinterpret_cast<uintptr_t>(ptr.residual)) % 4 != 0;
     a.t8 = plan.t8; a.spi = plan.spi; a.sr = plan.sr; a.rows = plan.rows; a.windows = plan.windows;
     const int threads = plan.kg == 4 ? 128 : 256;                              // of a group
     a.dg = threads % plan.t8;
