@@ -74,7 +74,8 @@ typedef enum { TVG_F32 = 0, TVG_BF16 = 1 } tvg_dtype;
  *                 HBM what it could have found there.  Off by default.  Kernels without
  *                 16-byte stores of bf16 (the generic kernel and the fp32 kernels, the bf16 kernel for
  *                 few tiles, whose outputs the caches hold anyway, the element-wise tail of
- *                 unaligned maps) ignore it; depthwise kernels take it in both dtypes. */
+ *                 unaligned maps, the 3x3 kernel of strips under a stride and on rows of more than
+ *                 32 pixels, whose parts of a line come from several workgroups) ignore it; depthwise kernels take it in both dtypes. */
 enum { TVG_RELU = 1u, TVG_STREAM_OUT = 2u };
 /* Only in the flags2 argument of tvg_conv2d_fused_dual: see there. */
 enum { TVG_CENTRE_TAP_ONLY = 4u };
