@@ -668,57 +668,81 @@ bool set_geometry(const ConvProblem &p, int b, int kg, StripsPlan *g)
     return true;
 }
 
-// Times in us on both sides of the dispatch, fitted to 7900 shapes of 64 to 512 input channels that were timed in this
-// kernel (every b) and in the kernels behind it (maps of 3 to 112 rows and columns, 32 to 512 output channels, batches of 1
-// to 128; standard deviation of the fits 5 to 9 and 5 to 15 %).  A CU's tiles run in pairs, two waves on a SIMD.
-struct Fit { float launch, tile, pair0, pair1, single0, single1, mbyte; };
-constexpr Fit kEven = {4.2f, 0.9f, 0.37f, 0.30f, 0.22f, 0.18f, 0.14f};            // rows of 2n pixels
-constexpr Fit kWindows = {3.4f, 1.15f, 0.28f, 0.33f, 0.28f, 0.19f, 0.23f};        // ... of more than 32
-constexpr Fit kOdd[2] = {{5.2f, 0.8f, 0.40f, 0.31f, 0.06f, 0.24f, 0.46f}, {2.4f, 4.4f, -0.10f, 0.41f, 0.0f, 0.0f, 0.5f}};
-constexpr Fit kQuarters[2] = {{1.2f, 4.3f, 1.97f, 0.0f, 0.0f, 0.0f, 0.57f}, {1.55f, 5.2f, 2.29f, 0.0f, 0.0f, 0.0f, 0.98f}};    // four groups: even, odd rows
-constexpr Fit kStride2[2] = {{4.3f, 0.45f, 0.57f, 0.234f, 0.29f, 0.16f, 0.61f}, {4.25f, 1.3f, 0.51f, 0.27f, 0.22f, 0.23f, 0.6f}};   // even, odd rows
+// Times in us on both sides of the dispatch, fitted to calls without a residual of 31400 shapes of 64 to 512 input channels that
+// were timed in every form of this kernel and in the kernel behind it (maps of 3 to 112 rows and columns, 32 to 512 output
+// channels, batches of 1 to 128; the geometric mean of repeated calls and of calls over buffers of 120 MB; standard deviation
+// of the fits 2 to 5 %, strided windows 7.5, the kernels behind 4.7).  A CU's tiles run in pairs, two waves on a SIMD.  row,
+// short_row: per tile and row of a strip, the latter for maps of 5, 6, 7 or 14 columns; mbyte, x_mbyte: of
+// y and of x.
+struct Fit { float launch, tile, pair0, pair1, single0, single1, mbyte, row, short_row, x_mbyte; };
+constexpr Fit kEven = {4.49f, 0.0f, 0.60f, 0.269f, 0.441f, 0.16f, 0.24f, 0.13f, 0.14f, 0.0f};            // rows of 2n pixels
+constexpr Fit kWindows = {4.14f, 0.0f, 0.71f, 0.248f, 0.489f, 0.16f, 0.26f, 0.17f, 0.0f, 0.02f};         // ... of more than 32
+constexpr Fit kOdd[2] = {{4.54f, 0.0f, 0.75f, 0.239f, 0.375f, 0.20f, 0.34f, 0.29f, 0.13f, 0.0f},         // one group, two
+                         {2.31f, 1.49f, 0.76f, 0.278f, 0.0f, 0.0f, 0.46f, 0.55f, 0.14f, 0.0f}};
+constexpr Fit kQuarters[2] = {{1.65f, 0.0f, 0.0f, 0.53f, 0.0f, 0.0f, 0.37f, 1.12f, 0.06f, 0.02f},        // four groups: even, odd rows
+                              {2.16f, 0.0f, 0.0f, 0.599f, 0.0f, 0.0f, 0.64f, 1.25f, 0.07f, 0.0f}};
+constexpr Fit kStride2[2] = {{4.94f, 0.0f, 0.67f, 0.203f, 0.413f, 0.14f, 0.37f, 0.13f, 0.12f, 0.005f},   // even, odd rows
+                             {4.42f, 0.03f, 1.08f, 0.17f, 0.56f, 0.17f, 0.39f, 0.32f, 0.0f, 0.001f}};
+constexpr Fit kStride2Windows = {3.95f, 0.0f, 0.82f, 0.184f, 0.536f, 0.129f, 0.34f, 0.20f, 0.0f, 0.06f};
+
+float x_mbytes(const ConvProblem &p) { return 2e-6f * p.N * p.IC * p.H * p.W; }
 
 float strips_us(const ConvProblem &p, const StripsPlan &g)
 {
-    const bool odd = p.W % 2 != 0;
-    const Fit &f = g.kg == 4 ? kQuarters[odd] : p.sh == 2 ? kStride2[odd] : g.windows > 1 ? kWindows : odd ? kOdd[g.kg - 1] : kEven;
+    const bool odd = p.W % 2 != 0, short_rows = odd ? p.W == 5 || p.W == 7 : p.W == 6 || p.W == 14;
+    const Fit &f = p.sh == 2 ? (g.windows > 1 ? kStride2Windows : kStride2[odd])
+                             : g.kg == 4 ? kQuarters[odd] : g.windows > 1 ? kWindows : odd ? kOdd[g.kg - 1] : kEven;
     const long q = (g.tiles + kComputeUnits - 1) / kComputeUnits;
     const bool two = g.kg == 1 && g.lds_bytes <= 80 * 1024;
     const float pairs = g.kg > 1 ? q : two ? q / 2 : 0, singles = g.kg > 1 ? 0 : two ? q % 2 : q;
-    const float us = f.launch + f.tile * q + p.IC / kChunk / g.kg * (pairs * (f.pair0 + f.pair1 * g.b) + singles * (f.single0 + f.single1 * g.b)) +
-                     f.mbyte * 2e-6f * p.OC * p.npix;
-    return p.sh == 2 && g.windows > 1 ? 1.15f * us : us;
+    return f.launch + q * (f.tile + g.b * (f.row + (short_rows ? f.short_row : 0.0f))) +
+           p.IC / kChunk / g.kg * (pairs * (f.pair0 + f.pair1 * g.b) + singles * (f.single0 + f.single1 * g.b)) +
+           f.mbyte * 2e-6f * p.OC * p.npix + f.x_mbyte * x_mbytes(p);
 }
 
-float patch_us(const ConvProblem &p, const Patch3x3Plan &g)
+// The kernels behind, by what decides their speed: stages, pixels per tile, pixels per load and load tasks per thread.  (8-pixel
+// loads of rows of 8n pixels meet on banks.)  The first row that fits; pair, single: per 16 input channels and 64 output channels.
+// rows: 1 of an odd number of pixels, 0 even, 8 of 8n, -1 any; px, pt: at least.
+struct TiledFit { int sh, dbuf, nt, groups, rows, px, pt; float launch, tile, pair, single, mbyte, x_mbyte; };
+constexpr TiledFit kTiled[] = {
+    {1, 0, 64, 0, 1, 1, 1, 4.79f, 0.0f, 0.93f, 0.68f, 0.21f, 0.0f},
+    {1, 0, 64, 0, 8, 1, 3, 5.14f, 0.0f, 1.40f, 0.82f, 0.0f, 0.0f}, {1, 0, 64, 0, 8, 1, 1, 4.40f, 0.0f, 0.92f, 0.64f, 0.14f, 0.015f},
+    {1, 0, 64, 0, 0, 1, 3, 5.42f, 0.0f, 1.36f, 0.79f, 0.04f, 0.0f}, {1, 0, 64, 0, 0, 1, 1, 4.61f, 0.0f, 0.91f, 0.67f, 0.20f, 0.0f},
+    {1, 0, 128, 0, 1, 1, 3, 5.27f, 0.0f, 1.65f, 0.78f, 0.28f, 0.0f}, {1, 0, 128, 0, 1, 1, 1, 2.50f, 0.11f, 1.61f, 0.47f, 0.42f, 0.0f},
+    {1, 0, 128, 0, 8, 1, 3, 6.12f, 0.0f, 1.39f, 0.89f, 0.12f, 0.019f}, {1, 0, 128, 0, 8, 1, 1, 2.63f, 0.37f, 1.46f, 0.51f, 0.19f, 0.009f},
+    {1, 0, 128, 0, 0, 1, 3, 6.05f, 0.0f, 1.39f, 0.92f, 0.18f, 0.013f}, {1, 0, 128, 0, 0, 1, 1, 3.27f, 0.09f, 1.46f, 0.53f, 0.31f, 0.0f},
+    {1, 0, 256, 0, -1, 8, 1, 3.44f, 1.32f, 2.39f, 1.44f, 0.05f, 0.019f}, {1, 0, 256, 0, -1, 2, 1, 6.78f, 0.0f, 1.89f, 0.86f, 0.17f, 0.026f},
+    {1, 0, 256, 0, -1, 1, 1, 5.68f, 1.16f, 2.06f, 1.82f, 0.25f, 0.0f}, {1, 0, 512, 0, -1, 8, 1, 6.41f, 2.55f, 3.40f, 1.98f, 0.0f, 0.053f},
+    {1, 1, 64, 1, 1, 8, 1, 3.80f, 0.0f, 0.81f, 0.48f, 0.40f, 0.007f}, {1, 1, 64, 1, 1, 1, 1, 4.15f, 0.0f, 0.95f, 0.60f, 0.39f, 0.0f},
+    {1, 1, 64, 1, 8, 8, 1, 3.11f, 0.57f, 2.28f, 1.22f, 0.12f, 0.031f}, {1, 1, 64, 1, 0, 2, 2, 4.77f, 0.0f, 1.42f, 0.79f, 0.67f, 0.0f},
+    {1, 1, 64, 1, 0, 2, 1, 3.57f, 0.23f, 1.06f, 0.60f, 0.38f, 0.005f},
+    {1, 1, 128, 1, 1, 8, 1, 4.23f, 0.58f, 1.02f, 0.60f, 0.23f, 0.0f}, {1, 1, 128, 1, 1, 1, 3, 0.0f, 2.67f, 1.43f, 1.12f, 0.53f, 0.007f},
+    {1, 1, 128, 1, 1, 1, 1, 0.0f, 2.54f, 1.07f, 0.91f, 0.46f, 0.004f}, {1, 1, 128, 1, 8, 8, 1, 4.27f, 0.80f, 2.39f, 1.26f, 0.0f, 0.0f},
+    {1, 1, 128, 1, 0, 2, 2, 5.01f, 0.12f, 1.60f, 0.88f, 0.41f, 0.012f}, {1, 1, 128, 1, 0, 2, 1, 3.37f, 0.83f, 1.19f, 0.70f, 0.38f, 0.0f},
+    {1, 1, 256, 1, 1, 8, 1, 5.09f, 0.73f, 1.64f, 0.90f, 0.49f, 0.0f}, {1, 1, 256, 1, 1, 1, 1, 7.15f, 0.10f, 1.72f, 1.02f, 0.43f, 0.0f},
+    {1, 1, 256, 1, 8, 8, 1, 5.87f, 0.58f, 2.55f, 1.36f, 0.09f, 0.021f}, {1, 1, 256, 1, 0, 2, 2, 5.72f, 0.40f, 1.91f, 1.06f, 0.28f, 0.023f},
+    {1, 1, 256, 1, 0, 2, 1, 5.38f, 0.0f, 1.64f, 0.88f, 0.37f, 0.011f},
+    // two groups of waves split the reduction: a single round of tiles
+    {1, 1, 128, 2, 1, 1, 3, 5.95f, 0.0f, 0.0f, 0.79f, 0.36f, 0.014f}, {1, 1, 128, 2, 1, 1, 1, 4.52f, 0.0f, 0.0f, 0.61f, 0.59f, 0.0f},
+    {1, 1, 256, 2, 1, 1, 1, 6.69f, 0.0f, 0.0f, 0.92f, 0.56f, 0.0f},
+    {2, 0, 64, 0, -1, 2, 1, 4.08f, 0.0f, 1.19f, 1.03f, 0.06f, 0.012f}, {2, 0, 64, 0, -1, 1, 3, 4.82f, 0.0f, 1.44f, 1.15f, 0.08f, 0.0f},
+    {2, 0, 64, 0, -1, 1, 1, 3.98f, 0.0f, 1.14f, 0.96f, 0.16f, 0.0f},
+    {2, 0, 128, 0, -1, 2, 1, 3.58f, 0.0f, 1.62f, 0.85f, 0.35f, 0.031f}, {2, 0, 128, 0, -1, 1, 1, 3.30f, 1.0f, 2.27f, 1.81f, 0.40f, 0.078f},
+    {2, 0, 256, 0, -1, 2, 1, 5.09f, 1.27f, 2.47f, 1.91f, 0.15f, 0.03f}, {2, 0, 256, 0, -1, 1, 1, 5.42f, 1.01f, 2.90f, 2.82f, 0.19f, 0.003f},
+    {2, 1, 256, 1, -1, 2, 1, 4.50f, 0.0f, 0.0f, 1.90f, 0.40f, 0.0f},                  // (maps of a few rows or columns)
+    {2, 1, 128, 1, -1, 8, 1, 4.42f, 0.0f, 0.0f, 1.05f, 0.27f, 0.002f}, {2, 1, 128, 1, -1, 2, 1, 4.57f, 0.0f, 0.0f, 0.95f, 0.51f, 0.0f},
+};
+
+// 0 where no row of the table fits
+float tiled_us(const ConvProblem &p, const Patch3x3Plan &g)
 {
-    const bool odd = p.W % 2 != 0;
+    const int rows = p.W % 2 != 0 ? 1 : p.W % 8 == 0 ? 8 : 0;
     const long q = (((long)p.npix + g.nt - 1) / g.nt * ((p.OC + g.mt - 1) / g.mt) + kComputeUnits - 1) / kComputeUnits;
-    float base = 5.0f, mbyte = odd ? 0.6f : 0.22f, pair, single;                  // (pair, single: per 16 channels)
-    if (p.sh == 2) {
-        base = 4.0f;
-        mbyte = 0.24f;
-        pair = odd ? 1.44f : 1.22f, single = odd ? 1.1f : 0.99f;                  // 64 pixels
-        if (g.nt == 128) pair = odd ? 2.5f : 1.73f, single = odd ? 1.9f : 0.82f;
-        if (g.nt >= 256) pair = odd ? 3.8f : 2.65f, single = odd ? 2.8f : 1.95f;
-        if (g.dbuf) pair = 9.0f, single = 1.03f;
-    } else if (p.W > 32) {
-        mbyte = 0.15f;
-        pair = 1.12f, single = 0.68f;
-        if (g.nt == 128) pair = 1.35f, single = 0.85f;
-        if (g.nt == 256) pair = g.dbuf ? 1.89f : 2.45f, single = g.dbuf ? 1.08f : 1.43f;
-        if (g.nt == 512) pair = 3.6f, single = 2.07f;
-        if (g.dbuf && p.W % 8 == 0) pair += g.nt < 256 ? 1.0f : 0.6f, single += g.nt < 256 ? 0.5f : 0.3f;
-    } else {
-        if (odd) base -= 0.5f * (q - 1);
-        pair = odd ? 0.92f : 1.08f, single = odd ? 0.50f : 0.58f;
-        if (g.nt == 128) pair = odd ? 1.16f : 1.3f, single = odd ? 0.60f : 0.71f;
-        if (g.nt == 256) pair = odd ? 1.85f : 1.75f, single = odd ? 1.0f : 0.97f;
-        if (g.nt == 512) pair = 3.2f, single = 1.7f;
-        if (p.W % 8 == 0 && g.nt >= 128) pair += 0.8f, single += 0.4f;            // (their patch rows meet on banks)
-    }
-    if (g.mt == 128) pair *= 1.9f, single *= 1.9f;
-    return base + p.IC / 16 * (q / 2 * pair + q % 2 * single) + mbyte * 2e-6f * p.OC * p.npix;
+    for (const TiledFit &f : kTiled)
+        if (f.sh == p.sh && f.dbuf == g.dbuf && f.nt == g.nt && (!g.dbuf || f.groups == g.kg) && (f.rows < 0 || f.rows == rows) && g.px >= f.px && g.pt >= f.pt)
+            return f.launch + f.tile * q + p.IC / 16 * (g.mt == 128 ? 1.9f : 1.0f) * (q / 2 * f.pair + q % 2 * f.single) +
+                   f.mbyte * 2e-6f * p.OC * p.npix + f.x_mbyte * x_mbytes(p);
+    return 0.0f;
 }
 
 }  // namespace
@@ -734,26 +758,33 @@ bool plan_conv3x3_strips(const ConvProblem &p, const Patch3x3Plan &patch, Strips
     if (!named && (k.mt || k.nt || k.stages || k.split_k || k.lds_pitch || k.row_loads)) return false;
     // One chunk is not worth the set-up (306 shapes: 1.01 times as fast in the geometric mean, 99 slower).  Two groups
     // that split the reduction pay where rows are odd, whose pixels take more instructions to lay down.  Four, of half the output
-    // channels, pay where the tiles of the others leave compute units idle and a workgroup's serial chain of chunks is the time:
-    // of 3220 shapes of even rows 1472 go to them and run 1.34 times as fast in the geometric mean, none more than 5 % slower; of
-    // 1394 of odd rows 566, 1.17 times (rows of less than 8 pixels against less than 384 channels: 0.75 to 0.95, so not those).
+    // channels, pay where the tiles of the others leave compute units idle and a workgroup's serial chain of chunks is the time.
     if (!named && p.IC < 2 * kChunk) return false;
     float best = 0.0f;
     StripsPlan g;
     for (int kg : {1, 2, 4})
         for (int b = 4; b <= (p.sh == 1 ? 8 : 7); ++b) {
             if (named && k.split_k && kg != k.split_k) continue;
-            if (!named && kg == 4 && p.W % 2 != 0 && p.W < 8 && p.IC < 384) continue;
             if (!set_geometry(p, b, kg, &g)) continue;
             const float us = strips_us(p, g);
             if (best == 0.0f || us < best) best = us, *plan = g;
         }
-    // Two chunks in windows do not cover the set-up of a single round of tiles (64 -> 64 at 56x56 amid other layers, 2 to 8 images: 0.2
-    // to 0.8 us slower than the kernel behind; 32 images: 15.1 us against 16.4).
-    if (best > 0.0f && !named && p.sh == 1 && plan->windows > 1 && p.IC == 2 * kChunk && plan->tiles <= kComputeUnits) return false;
-    // What the fits leave open goes to the kernels behind.  Of 7900 shapes this takes 4900, which run 1.32 (even rows), 1.27 (odd),
-    // 1.39 (rows of more than 32 pixels) and 1.34 (stride 2) times as fast in the geometric mean.
-    return best > 0.0f && (named || best * (p.W % 2 == 0 || p.sh == 2 ? 1.05f : 1.08f) < patch_us(p, patch));
+    if (best == 0.0f || named) return best > 0.0f;
+    // What the fits leave open goes to the kernels behind, but for calls with a residual, which a plan serves too (three of five
+    // unstrided layers of a residual network have one): they cost 1.01 to 1.13 times as much here and 1.04 to 1.8 behind, the more the
+    // fewer pixels of a plane lie at aligned addresses.  Further from the line: outputs beyond 24 MB, whose store hint the
+    // kernels behind make more of; two chunks in windows in a single round of tiles, which nothing else on the CU covers (16 images of
+    // 64 -> 64 at 56x56 amid ResNet-18's layers 124.6 us a pass, 121.8 behind).
+    // Odd rows of less than 8 pixels in one group of waves are where the fits are worst.
+    // Of 14200 shapes without a residual 0.9 % are more than 5 % slower than in the kernel behind and 0.25 % more than 10 %, at worst 1.27
+    // times (by the rule before, which did not know the load width of the kernels behind, 1.3 and 0.35 %); of 4100 with one 0.3 and 0.1 %
+    // (0.5 and 0.2 %).  Time over the time behind in the geometric mean, without and with: rows of up to 32 even pixels 0.82 and 0.77, odd
+    // 0.92 and 0.84 (0.93 and 0.88 before), longer ones 0.83 and 0.81, under a stride 0.81, of more than 32 pixels 0.86.
+    const int plane = p.OH * p.OW;
+    float margin = p.sh == 2 ? (plan->windows > 1 ? 1.09f : 1.04f) : plane % 8 == 0 ? 1.01f : plane % 4 == 0 ? 0.975f : plane % 2 == 0 ? 0.895f : p.W < 8 && plan->kg == 1 ? 1.06f : 0.945f;
+    if (2e-6f * p.OC * p.npix > 24.0f) margin *= 1.05f;
+    if (p.sh == 1 && plan->windows > 1 && p.IC == 2 * kChunk && plan->tiles <= kComputeUnits) margin *= 1.04f;
+    return best * margin < tiled_us(p, patch);
 }
 
 bool conv3x3_strips_pointers_ok(const ConvPointers &ptr)

@@ -432,6 +432,39 @@ def test_bf16_kernel_for_few_tiles_takes_them_where_it_is_faster(n, c, h, w, k, 
     assert any(tvg.tvg_conv2d_get_knobs(d)) != few
 
 
+@pytest.mark.parametrize("cfg,groups", [
+    # (images, channels, rows, columns, output channels, stride); us in strips and in the kernel behind where the line is meant to hold them apart
+    ((96, 64, 27, 27, 128, 1), 1),      # 26.0, 32.9 (with a residual 34.1, 58.5)
+    ((96, 96, 29, 29, 96, 1), 1),       # 28.2, 36.8
+    ((64, 512, 7, 7, 512, 1), 2),       # 23.2, 22.5 (with a residual 23.7, 33.4)
+    ((8, 512, 14, 14, 512, 1), 4),      # 14.8, 22.0
+    ((16, 192, 56, 56, 192, 1), 1),     # windows: 36.3, 53.4
+    ((32, 64, 56, 56, 64, 1), 1),       # two chunks: 13.3, 14.3
+    ((4, 64, 56, 56, 160, 1), 1),       # ... in a single round: 8.9, 11.8
+    ((2, 64, 100, 100, 128, 1), 1),     # 10.5, 13.8
+    ((12, 512, 36, 36, 256, 2), 1),     # under a stride: 30.2, 39.9
+    ((64, 128, 28, 28, 256, 2), 1),     # 17.0, 17.9
+    ((64, 64, 56, 56, 64, 1), 0),       # 25.4, 24.0; 21.2 with the store hint
+    ((16, 64, 56, 56, 64, 1), 0),       # between other layers 124.6 a pass, 121.8
+    ((128, 96, 62, 6, 128, 1), 0),      # short rows: 24.1, 18.7
+    ((96, 128, 6, 6, 512, 1), 0),       # 13.2, 10.8
+    ((64, 64, 64, 14, 128, 1), 0),      # 19.0, 13.6
+    ((32, 64, 96, 15, 128, 1), 0),      # 17.3, 12.6
+    ((128, 96, 7, 7, 512, 1), 0),       # 17.9, 15.0
+    ((128, 128, 15, 15, 512, 2), 0),    # 26.5, 19.8
+    ((64, 64, 26, 14, 512, 2), 0),      # 15.9, 12.8
+    # not built or not worth it: one chunk, channels off 32 n, long rows off 4 n, few tiles
+    ((64, 32, 28, 28, 128, 1), 0), ((64, 80, 28, 28, 128, 1), 0), ((64, 128, 34, 34, 128, 1), 0), ((64, 128, 35, 35, 128, 1), 0), ((2, 128, 28, 28, 256, 1), 0),
+], ids=str)
+def test_which_3x3_layers_run_in_strips(cfg, groups):
+    """Both sides of the rule's lines, and the groups of waves that it takes."""
+    n, c, h, w, k, stride = cfg
+    d = desc(n=n, c=c, h=h, w=w, k=k, stride_h=stride, stride_w=stride, dtype=1)
+    assert (tvg.tvg_conv2d_get_plan(d)[0] == 7) == (groups > 0)
+    if groups:
+        assert tvg.tvg_conv2d_get_knobs(d) == (0, 0, 1, groups, 0, 2)
+
+
 @pytest.mark.parametrize("cfg,groups,channels,strip_row", [
     ((64, 128, 28, 28, 128, 1), 1, 64, 32), ((64, 512, 7, 7, 512, 1), 1, 64, 32), ((64, 512, 7, 7, 512, 1), 2, 64, 32), ((2, 256, 14, 14, 64, 1), 4, 32, 32),
     ((8, 256, 14, 14, 512, 2), 1, 64, 16), ((1, 64, 4, 8, 64, 1), 1, 64, 8), ((3, 64, 9, 20, 70, 1), 1, 64, 24), ((2, 96, 13, 56, 70, 2), 1, 64, 16),

@@ -926,7 +926,7 @@ def test_tuner_fixes_a_tile_and_results_stay_right(tvg, tmp_path):
     try:
         rep = tune.tune_conv2d(desc, d["x"], d["w"], d["scale"], d["shift"], y, iters=10, repeats=2,
                                min_gain=0.0, max_trials=12)
-        assert rep["kernel"] == "3x3-strips" and len(rep["candidates"]) >= 3
+        assert rep["kernel"] == "3x3" and len(rep["candidates"]) >= 3
         assert rep["tuned_us"] <= rep["default_us"]
         walk = rep["walk"]
         assert 3 <= walk["trials"] <= 12 and walk["space_points"] > 12 and not walk["exhaustive"]

@@ -10,16 +10,16 @@ from _util import check, dev_inputs, to_host
 
 pytestmark = pytest.mark.gpu
 
-# (n, ic, h, w, oc), rows of a strip (groups: 1, for odd rows 2, and 4)
+# (n, ic, h, w, oc), rows of a strip that planning picks there (groups: 1, for odd rows 2, and 4)
 SHAPES = [
     ((2, 64, 9, 6, 70), 4), ((3, 160, 14, 14, 130), 4), ((1, 96, 13, 18, 40), 4), ((2, 128, 28, 28, 72), 4), ((1, 32, 5, 32, 33), 4), ((1, 512, 3, 8, 17), 4),
     ((70, 64, 3, 2, 16), 4), ((1, 32, 1, 1, 1), 4), ((3, 128, 7, 7, 130), 4), ((2, 64, 13, 13, 80), 4), ((1, 192, 17, 21, 64), 4), ((2, 64, 9, 31, 20), 4),
     ((130, 64, 5, 26, 16), 5), ((260, 64, 5, 14, 16), 5), ((520, 64, 5, 5, 16), 5), ((130, 64, 5, 19, 16), 5),
     ((130, 64, 6, 20, 16), 6), ((520, 64, 6, 6, 40), 6), ((260, 64, 6, 13, 16), 6), ((130, 64, 6, 29, 16), 6),
     ((130, 64, 7, 28, 20), 7), ((260, 32, 7, 14, 16), 7), ((520, 64, 7, 7, 16), 7), ((130, 64, 7, 25, 16), 7),
-    ((130, 64, 8, 30, 16), 8), ((520, 64, 8, 8, 16), 8), ((260, 64, 8, 16, 16), 8), ((260, 64, 8, 15, 16), 8), ((520, 64, 8, 3, 16), 8),
+    ((390, 64, 8, 30, 16), 8), ((1560, 64, 8, 8, 16), 8), ((780, 64, 8, 16, 16), 8), ((780, 64, 8, 15, 16), 8), ((1560, 64, 8, 3, 16), 8),
     # windows: rows of 36 to 112 pixels
-    ((1, 64, 5, 36, 16), 4), ((2, 96, 13, 56, 70), 4), ((1, 32, 9, 112, 20), 4), ((70, 64, 5, 36, 16), 5), ((70, 64, 16, 36, 16), 6), ((70, 64, 7, 40, 16), 7), ((70, 64, 8, 60, 16), 8),
+    ((1, 64, 5, 36, 16), 4), ((2, 96, 13, 56, 70), 4), ((1, 32, 9, 112, 20), 4), ((70, 64, 5, 36, 16), 5), ((70, 64, 16, 36, 16), 6), ((70, 64, 7, 40, 16), 7), ((140, 64, 8, 60, 16), 8),
     # reductions that four groups split too, even and odd rows, windows
     ((33, 256, 5, 14, 40), 4), ((2, 384, 9, 31, 33), 4), ((5, 128, 2, 5, 64), 4), ((1, 640, 6, 26, 97), 4), ((1, 128, 9, 112, 20), 4),
     # two and three tiles per workgroup, of one and of several channel tiles, pixel tiles first and (many images) channel tiles first
