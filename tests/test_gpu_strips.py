@@ -65,12 +65,14 @@ def _check(tvg, cfg, b, kg, residual, bias, relu, stride=1):
     check(to_host(ys[0]), want, "bf16", (cfg, b, kg))
 
 
-@pytest.mark.parametrize("kg", [1, 2, 4])
+# two groups: odd rows; four: strips of four rows; both: a multiple of their number of chunks
+GROUPED = [(cfg, b, kg) for kg in (1, 2, 4) for cfg, b in SHAPES
+           if not (kg == 2 and (cfg[3] % 2 == 0 or cfg[1] % 64 != 0)) and not (kg == 4 and (b != 4 or cfg[1] % 128 != 0))]
+
+
 @pytest.mark.parametrize("tail", ["plain", "bias+residual"])
-@pytest.mark.parametrize("cfg,b", SHAPES, ids=lambda c: "x".join(map(str, c)) if isinstance(c, tuple) else str(c))
-def test_strips_every_instance(tvg, cfg, b, tail, kg):
-    if (kg == 2 and (cfg[3] % 2 == 0 or cfg[1] % 64 != 0)) or (kg == 4 and (b != 4 or cfg[1] % 128 != 0)):
-        pytest.skip("two groups: odd rows; four: strips of four rows; both: a multiple of their number of chunks")
+@pytest.mark.parametrize("cfg,b,kg", GROUPED, ids=lambda c: "x".join(map(str, c)) if isinstance(c, tuple) else str(c))
+def test_strips_every_instance(tvg, cfg, b, kg, tail):
     full = tail != "plain"
     _check(tvg, cfg, b, kg, full, full, full)
 
@@ -150,6 +152,8 @@ def test_two_heads_have_the_bits_of_separate_calls_in_strips(tvg, cfg, centre):
     import torch
     n, ic, h, w, k1, k2, stride = cfg
     r2 = 1 if centre else 3
+    plan = lambda k, r: tvg.tvg_conv2d_get_plan(tvg.ConvDesc(n, ic, h, w, k, r, r, stride, stride, r // 2, r // 2, tvg.TVG_BF16, 0))
+    assert plan(k1, 3)[0] == 7 and plan(k2, r2)[0] == (4 if centre else 7)
     g = torch.Generator(device="cuda").manual_seed(10600 + sum(cfg))
     def rand(*shape):
         return torch.rand(shape, generator=g, device="cuda") * 2 - 1
@@ -170,22 +174,30 @@ def test_two_heads_have_the_bits_of_separate_calls_in_strips(tvg, cfg, centre):
     assert torch.equal(y1, want1) and torch.equal(y2, want2)
 
 
-def test_strips_infinity_stays_in_its_window(tvg):
-    """Pixels at the end of a row and of a strip, whose neighbours in LDS belong to other rows and images."""
+# rows, columns, stride, groups of waves
+@pytest.mark.parametrize("h,w,stride,kg", [(14, 14, 1, 1), (28, 28, 1, 1), (7, 7, 1, 1), (9, 18, 1, 1), (6, 56, 1, 1), (7, 7, 1, 2), (13, 13, 1, 2), (9, 31, 1, 2),
+                                           (14, 14, 1, 4), (7, 7, 1, 4), (9, 18, 1, 4), (6, 56, 1, 4), (14, 14, 2, 1), (28, 28, 2, 1), (7, 7, 2, 1), (9, 18, 2, 1),
+                                           (13, 31, 2, 1), (6, 56, 2, 1)])
+def test_strips_infinity_stays_in_its_window(tvg, h, w, stride, kg):
+    """Pixels at the end of a row and of a strip, whose neighbours in LDS belong to other rows and images, and the first channel
+    of every group's share of the reduction."""
     import torch
-    for h, w in ((14, 14), (28, 28), (7, 7), (9, 18), (6, 56)):
-        desc = tvg.ConvDesc(3, 64, h, w, 64, 3, 3, 1, 1, 1, 1, tvg.TVG_BF16, 0)
-        d = dev_inputs(ti.make_inputs(ti.ConvShape("strips", 3, 64, h, w, 64, 3, 3, 1, 1), 10700, "bf16"), "bf16")
-        assert tvg.tvg_conv2d_set_knobs(desc, (0, 0, 1, 1, 0, 2)) == 0
-        try:
-            call = lambda x: tvg.conv2d_fused(x, d["w"], d["scale"], d["shift"], stride=1, pad=1, relu=False)
-            clean = call(d["x"])
-            for row, col in ((3, w - 1), (4, 0), (h - 1, w - 1), (0, 0), (2, w // 2), (2, w // 2 - 1)):
-                x = d["x"].clone()
-                x[1, 5, row, col] = float("inf")
-                y = call(x)
-                hit = torch.zeros_like(y, dtype=torch.bool)
-                hit[1, :, max(row - 1, 0):row + 2, max(col - 1, 0):col + 2] = True
-                assert not bool(torch.isfinite(y[hit]).any()) and torch.equal(y[~hit], clean[~hit]), (h, w, row, col)
-        finally:
-            tvg.tvg_conv2d_set_knobs(desc, None)
+    desc = tvg.ConvDesc(3, 128, h, w, 64, 3, 3, stride, stride, 1, 1, tvg.TVG_BF16, 0)
+    d = dev_inputs(ti.make_inputs(ti.ConvShape("strips", 3, 128, h, w, 64, 3, 3, stride, 1), 10700, "bf16"), "bf16")
+    assert tvg.tvg_conv2d_set_knobs(desc, (0, 0, 1, kg, 0, 2)) == 0
+    try:
+        assert tvg.tvg_conv2d_get_plan(desc)[0] == 7 and tvg.tvg_conv2d_get_knobs(desc)[3] == kg
+        call = lambda x: tvg.conv2d_fused(x, d["w"], d["scale"], d["shift"], stride=stride, pad=1, relu=False)
+        clean = call(d["x"])
+        for i, (row, col) in enumerate(((3, w - 1), (4, 0), (h - 1, w - 1), (0, 0), (2, w // 2), (2, w // 2 - 1))):
+            x = d["x"].clone()
+            x[1, 32 * i % 128, row, col] = float("inf")
+            y = call(x)
+            hit = torch.zeros_like(y, dtype=torch.bool)
+            rows = [o for o in range(y.shape[2]) if abs(o * stride - row) <= 1]
+            cols = [o for o in range(y.shape[3]) if abs(o * stride - col) <= 1]
+            if rows and cols:
+                hit[1, :, rows[0]:rows[-1] + 1, cols[0]:cols[-1] + 1] = True
+            assert not bool(torch.isfinite(y[hit]).any()) and torch.equal(y[~hit], clean[~hit]), (row, col)
+    finally:
+        tvg.tvg_conv2d_set_knobs(desc, None)
