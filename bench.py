@@ -474,7 +474,8 @@ def main():
                 tvg, ti, torch, np, dev, to_dev, time_loop, iters=50, warmup=20, graph=False,
                 use_arena=False)["ms"]
         # the same body with every down-sampling block's first conv and projection shortcut as
-        # one two-head launch: 18 launches (FLOPs counted as for the 21-launch chain)
+        # one two-head call (the slower form where the kernel of strips takes a head): 18 calls
+        # (FLOPs counted as for the 21-launch chain)
         fused = bench_body(tvg, ti, torch, np, dev, to_dev, time_loop, iters=50, warmup=20,
                            use_arena=not args.no_arena, fuse_projection=True)
         out["resnet18_body"]["two_head_blocks"] = {k: fused[k] for k in

@@ -1,8 +1,10 @@
 // bf16 3x3 convolutions (pad 1, stride 1 or 2) at throughput size.
 //
-// Bound: the matrix pipe at the clock that its power leaves (1.9 GHz under this load, 2.4 without), with the set-up and
-// the tail of a tile around it.  The 64 x 256 tiles of the pipelined kernel read 1 KB of LDS per 32x32x16 MFMA, as much as
-// the LDS delivers, and spend a third of their loop on making channel words of NCHW rows.  Here:
+// Bound: no single unit.  At batch 64 the matrix pipes are busy 37 to 40 % of the time without a stride (128 -> 128 at 28x28, 256 ->
+// 256 at 14x14, 512 -> 512 at 7x7, at about 1.9 GHz) and 20 to 23 % under one, the LDS 13 to 22 %; the rest is the in-order stream of one or two
+// waves on a SIMD: a tile's set-up and tail around a loop of 2 to 16 chunks.  The 64 x 256 tiles of the pipelined kernel
+// read 1 KB of LDS per 32x32x16 MFMA, as much as the LDS delivers, and spend a third of their loop on making channel words
+// of NCHW rows.  Here:
 //   - A wave owns 16 output channels of four strips of B rows x 8 pixels (4 to 8 rows).  Strip and column pair are the pixel
 //     rows of an MFMA, so the operand of a strip's input row serves three output rows, and the chunk's weights of all nine
 //     taps stay in registers: 0.2 KB of LDS per 16x16x32 MFMA instead of 0.5.
@@ -19,13 +21,13 @@
 // With fewer still four groups of two waves do, on 32 output channels: twice the workgroups, a quarter of the chain of chunks.
 // Rows of more than 32 pixels are cut into windows of four strips that overlap by one.
 // Under a stride the two halves are what a filter's columns take anyway: two sums (ae, se), each pixel of them fed by every
-// other row, and the LDS is the bound: 0.76 KB per MFMA, 1.6 us per chunk and pair of workgroups against 1.0 of MFMAs.
-// us, warm, in the kernels behind and here, without and with a residual: 128 -> 128 at 28x28, batch 32 13.9 / 15.8 -> 13.6 /
-// 13.7, batch 128 38.6 / 43.3 -> 34.7 / 39.5 (850 TFLOP/s without); 256 -> 256 at 14x14, batch 128 36.3 / 40.4 -> 34.9 / 34.6; 512 ->
-// 512 at 7x7, batch 128 36.1 / 54.8 -> 36.5 / 37.7; 192 -> 192 at 56x56, batch 16 59.1 / 59.1 -> 41.0 / 45.6; stride 2, 256 -> 512 at
-// 14x14, batch 128 36.8 / 45.1 -> 32.4 / 33.4, 512 -> 512 at 28x28, batch 16 36.2 / 38.2 -> 28.1 / 29.6.  Four groups (behind
-// or two and one, cold -> four): 256 -> 256 at 14x14, batch 16 13.1 -> 10.7; 512 -> 512 at 14x14, batch 8 22.4 -> 15.9, at 7x7,
-// batch 32 20.5 -> 18.1.
+// other row, so that an operand serves half as many MFMAs: 0.76 KB of LDS per MFMA, and 7 to 10 instructions instead of 4 to 6.
+// us, warm, in the kernels behind and here, without and with a residual: 128 -> 128 at 28x28, batch 32 15.1 / 16.7 -> 13.9 /
+// 13.7, batch 128 39.6 / 44.4 -> 34.6 / 35.9 (850 TFLOP/s without); 256 -> 256 at 14x14, batch 128 37.4 / 41.7 -> 34.9 / 35.6; 512 ->
+// 512 at 7x7, batch 128 38.1 / 55.9 -> 37.0 / 38.6; 192 -> 192 at 56x56, batch 16 53.2 / 55.7 -> 37.0 / 39.8; stride 2, 256 -> 512 at
+// 14x14, batch 128 36.1 / 44.5 -> 30.7 / 32.7, 512 -> 512 at 28x28, batch 16 36.1 / 38.1 -> 28.3 / 28.6.  Four groups (behind,
+// one group, two, with buffers in turn -> four): 256 -> 256 at 14x14, batch 16 13.4, 13.9 -> 11.7; 512 -> 512 at 14x14, batch 8 23.7, 22.6 ->
+// 15.7, at 7x7, batch 32 20.8, 25.2, 21.1 -> 18.0.
 #include <algorithm>
 #include <type_traits>
 
@@ -113,7 +115,7 @@ template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_
 
 // Windows of a row of more than four strips: four strips each, which overlap by one, since the sums of a window's first
 // column (and without a stride those of its last) miss the column beside it.
-template <int ST> __device__ __forceinline__ int window_step() { return 24; }       // columns; (of the input)
+constexpr int kWindowStep = 24;                    // columns of the input
 
 // The channel tile of a tile, and in *pt its pixel tile.
 template <class A> __device__ __forceinline__ int split_tile(A &a, int t, int *pt)
@@ -204,7 +206,7 @@ __global__ __launch_bounds__(64 * WM * KG, 2) void conv3x3_strips_kernel(const S
             const int ih = rb * B * ST + rho - 1;
             goff[k] = kOutOfRange;
             if (ih >= 0 && ih < a.H && n < a.N)
-                goff[k] = 2u * (__umul24(__umul24(n, a.IC) + ch, HW) + __umul24(ih, a.W) + window * window_step<ST>() + g8 * 8);
+                goff[k] = 2u * (__umul24(__umul24(n, a.IC) + ch, HW) + __umul24(ih, a.W) + window * kWindowStep + g8 * 8);
             if (first) {
                 dst[k] = __umul24(ch, a.plane) + (ch >> 3) * kOctetGap + __umul24(s, a.strip_bytes) + __umul24(rho, a.row_bytes) + g8 * 8;
                 if constexpr (UNAL) dst[k] = dst[k] * 16 + g8;     // (t8 <= 16)
@@ -420,7 +422,7 @@ __global__ __launch_bounds__(64 * WM * KG, 2) void conv3x3_strips_kernel(const S
         const int my_s = divide(quad, f.by_t8, &my_g8);
         const int my_n = divide(pt * sr + my_s, f.by_spi, &my_rb);
         my_rb = divide(my_rb, f.by_windows, &window);
-        const int oc0 = (cb * kWaves + wm) * 16, oc = oc0 + l16, col0 = window * (window_step<ST>() / ST) + PX * my_g8;
+        const int oc0 = (cb * kWaves + wm) * 16, oc = oc0 + l16, col0 = window * (kWindowStep / ST) + PX * my_g8;
         const int rest = OW - col0, row0 = my_rb * B;                 // columns from the strip's first on, first row
         // pixels [from, to) of the strip's row: windows meet inside a strip without a stride, and at its end with one
         const int from = window > 0 && my_g8 == 0 ? (ST == 1 ? 4 : PX) : 0;

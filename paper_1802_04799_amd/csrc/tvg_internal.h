@@ -117,10 +117,10 @@ bool conv_rows_pointers_ok(const ConvPointers &ptr);
 tvg_status launch_conv_rows(const ConvProblem &p, const RowsPlan &plan, const ConvPointers &ptr, hipStream_t stream,
                             const DualHead *dual = nullptr, bool centre = false);
 
-// bf16 3x3 without a stride, rows of at most 32 pixels, at throughput size: a wave owns 16 channels of four strips of
-// b rows x 8 pixels, a group of four waves 64 channels of them.
+// bf16 3x3, stride 1 or 2, at throughput size: a wave owns 16 output channels of four strips of b output rows x 8 input
+// pixels.  One or two groups of four waves (64 channels), or four of two (32).
 struct StripsPlan {
-    int b, kg;                        // rows of a strip, groups that split the reduction (1 or 2)
+    int b, kg;                        // rows of a strip, groups that split the reduction (1, 2 or 4)
     int t8, windows, spi, sr, rows;   // strips per row or part of a row, such parts, strip rows per image and per tile, staged rows per tile
     int row_bytes, strip_bytes, half, plane, rows_bytes;
     long ptiles, tiles, workgroups;
